@@ -916,74 +916,182 @@ fa_fwd_pingpong_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
 }
 
 // ---------------------------------------------------------------------------------------
-// fp32 path (d = 64): plain fp32 FMA arithmetic with the same structure -- a query tile per
-// workgroup, K/V blocks staged in LDS, online softmax with exp2 and the scale folded in.
-// One thread owns one query row, so no cross-lane reductions are needed.
+// fp32 path (d = 64) on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: fp32 operands, products and sums).
+//
+// Bound by that instruction: 64 cycles for 4 KFLOP per SIMD, 157 TFLOP/s for the chip, against which the softmax of
+// a 32 x 32 score tile (64 MFMAs) is about a tenth.  Requests in fp32 are mostly small, so the tile is chosen to
+// put work on every SIMD: a workgroup owns 64 query rows in two slabs of 32, and the four waves of a slab split
+// the keys (wave `split` takes keys 32 split .. 32 split + 31 of every 128-key block) with a softmax state each;
+// the four states are merged through the LDS at the end, in a fixed order.  That quarters the serial chain of key
+// blocks and puts two waves on each SIMD, one's softmax under the other's MFMAs.
+//   S^T = K Q^T: step i contracts head-dim elements {i, 32 + i}, so a lane's operands are 32 consecutive floats of a
+//     row, four MFMAs to a 16-byte LDS read (rows padded to 272 bytes: 16 rows, 16 chunk positions).
+//   O^T += V^T P^T: score register r of a lane is key 8 (r / 4) + 4 half + r % 4, so the register itself is the B
+//     operand of the step that contracts this pair of keys; A is V read down a column (rows padded to 288 bytes: the
+//     two rows of a step lie in different halves of the banks).
+// B = 2, H = 8, N = 1000: 857 us with one thread per row and scalar FMAs, 42 us so (97 TFLOP/s).
 template <int D, int BC, bool CAUSAL>
-__global__ void __launch_bounds__(64) fa_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                                                        const float* __restrict__ v, float* __restrict__ o,
-                                                        float* __restrict__ lse, int N, int n_qtiles, int kv_group,
-                                                        float scale) {
-    constexpr int BR = 64;
-    __shared__ float lds_k[BC * D];
-    __shared__ float lds_v[BC * D];
+__global__ void __launch_bounds__(512, 2)
+fa_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+                  float* __restrict__ o, float* __restrict__ lse, int N, int n_qtiles, int total_wg, int kv_group,
+                  float scale) {
+    static_assert(D == 64 && BC == 32, "one 32-key score tile per wave and block, two 32-column output tiles");
+    constexpr int NT = 512, SLABS = 2, SPLITS = 4;
+    constexpr int BR = 32 * SLABS;    // query rows per workgroup
+    constexpr int BS = BC * SPLITS;   // keys per staged block
+    constexpr int KSTR = D + 4, VSTR = D + 8;  // LDS row strides (floats)
+    constexpr int CPT = BS * D / 4 / NT;       // 16-byte chunks per thread and tensor
+    __shared__ __attribute__((aligned(16))) float lds_k[2][BS * KSTR];
+    __shared__ __attribute__((aligned(16))) float lds_v[2][BS * VSTR];
+    __shared__ float lds_m[SPLITS][BR], lds_l[SPLITS][BR];
+
     const int tid = threadIdx.x;
-    const int bh = blockIdx.x / n_qtiles, qt = blockIdx.x % n_qtiles;
+    const int wave = tid >> 6, lane = tid & 63;
+    const int col = lane & 31, half = lane >> 5;
+    const int slab = wave & 1, split = wave >> 1;
+
+    const int id = xcd_contiguous(blockIdx.x, total_wg);
+    const int bh = id / n_qtiles;
+    const int qt = CAUSAL ? n_qtiles - 1 - id % n_qtiles : id % n_qtiles;  // causal: longest rows first
     const size_t head_off = (size_t)bh * N * D;
-    const size_t kv_off = (size_t)(bh / kv_group) * N * D;
-    const int qi = qt * BR + tid;
+    const size_t kv_off = (size_t)(bh / kv_group) * N * D;  // grouped-query: kv_group query heads per K/V head
+    const int q0 = qt * BR + slab * 32;                     // first row of this wave's slab
+    const int row = min(q0 + col, N - 1);                   // rows past N compute a copy of row N-1, never stored
+    const int limit = CAUSAL ? row : N - 1;                 // last visible key
     const float sc = scale * kLog2e;
 
-    float qr[D], acc[D];
+    const __amdgpu_buffer_rsrc_t k_rsrc = make_buffer(k + kv_off, (uint32_t)N * D * 4);
+    const __amdgpu_buffer_rsrc_t v_rsrc = make_buffer(v + kv_off, (uint32_t)N * D * 4);
+    i32x4 kpre[CPT], vpre[CPT];
+    auto load_block = [&](int t) {  // rows past N read as zero
 #pragma unroll
-    for (int c = 0; c < D; ++c) {
-        qr[c] = qi < N ? q[head_off + (size_t)qi * D + c] : 0.f;
-        acc[c] = 0.f;
-    }
+        for (int i = 0; i < CPT; ++i) {
+            kpre[i] = buffer_load_16B(k_rsrc, t * BS * D * 4 + (tid + i * NT) * 16);
+            vpre[i] = buffer_load_16B(v_rsrc, t * BS * D * 4 + (tid + i * NT) * 16);
+        }
+    };
+    auto store_block = [&](int st) {
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) {
+            const int c = tid + i * NT, r = c / (D / 4), cc = c % (D / 4);
+            *reinterpret_cast<i32x4*>(lds_k[st] + r * KSTR + cc * 4) = kpre[i];
+            *reinterpret_cast<i32x4*>(lds_v[st] + r * VSTR + cc * 4) = vpre[i];
+        }
+    };
+    load_block(0);
+
+    f32x4 qreg[D / 8];  // Q^T as the B operand: lane (row, half) holds elements 32 half .. 32 half + 31
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j)
+        qreg[j] = *reinterpret_cast<const f32x4*>(q + head_off + (size_t)row * D + half * (D / 2) + 4 * j);
+    f32x16 acc[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;
-    int last_q = min(qt * BR + BR, N) - 1;
-    int n_blocks = CAUSAL ? (last_q / BC + 1) : ((N + BC - 1) / BC);
+
+    const int last_q = min(qt * BR + BR, N) - 1;
+    const int n_blocks = CAUSAL ? last_q / BS + 1 : (N + BS - 1) / BS;
+    store_block(0);
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j) asm volatile("" : "+v"(qreg[j]));  // Q loads complete before the loop
+    __syncthreads();
+
     for (int t = 0; t < n_blocks; ++t) {
-        int key0 = t * BC;
+        const int st = t & 1;
+        const bool more = t + 1 < n_blocks;
+        if (more) load_block(t + 1);
+        const int key0 = t * BS + split * BC;  // this wave's keys
+        if (key0 < N && (!CAUSAL || key0 <= q0 + 31)) {
+            f32x16 s;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] = 0.f;
+            const float* krow = lds_k[st] + (split * BC + col) * KSTR + half * (D / 2);
+#pragma unroll
+            for (int j = 0; j < D / 8; ++j) {
+                const f32x4 a = *reinterpret_cast<const f32x4*>(krow + 4 * j);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], qreg[j][e], s, 0, 0, 0);
+            }
+            if (key0 + BC > N || (CAUSAL && key0 + BC - 1 > q0)) {
+                const int bound = limit - key0 - 4 * half;
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (8 * (r >> 2) + (r & 3) > bound) s[r] = -INFINITY;
+            }
+            float mx[4] = {s[0], s[1], s[2], s[3]};
+#pragma unroll
+            for (int r = 4; r < 16; ++r) mx[r & 3] = fmaxf(mx[r & 3], s[r]);
+            const float m_new = fmaxf(m_run, max_both_halves(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3]))));
+            const float mb = m_new == -INFINITY ? 0.f : m_new * sc;  // a row that sees none of these keys: P = 0
+            if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
+                const float corr = fast_exp2(__builtin_fmaf(m_run, sc, -mb));
+                m_run = m_new;
+                l_run *= corr;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    acc[0][r] *= corr;
+                    acc[1][r] *= corr;
+                }
+            }
+            float ps[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                s[r] = fast_exp2(__builtin_fmaf(s[r], sc, -mb));
+                ps[r & 3] += s[r];
+            }
+            l_run += (ps[0] + ps[1]) + (ps[2] + ps[3]);
+            const float* vrow = lds_v[st] + (split * BC + 4 * half) * VSTR + col;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float* p = vrow + (8 * (r >> 2) + (r & 3)) * VSTR;
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(p[0], s[r], acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(p[32], s[r], acc[1], 0, 0, 0);
+            }
+        }
+        if (more) store_block(st ^ 1);
         __syncthreads();
-        for (int e = tid; e < BC * D; e += 64) {
-            int key = key0 + e / D;
-            lds_k[e] = key < N ? k[kv_off + (size_t)key0 * D + e] : 0.f;
-            lds_v[e] = key < N ? v[kv_off + (size_t)key0 * D + e] : 0.f;
-        }
-        __syncthreads();
-        float s[BC];
-        float mx = -INFINITY;
-        int limit = CAUSAL ? min(qi, N - 1) : N - 1;
-#pragma unroll
-        for (int j = 0; j < BC; ++j) {
-            float a = 0.f;
-#pragma unroll
-            for (int c = 0; c < D; ++c) a = __builtin_fmaf(qr[c], lds_k[j * D + c], a);
-            s[j] = (key0 + j > limit) ? -INFINITY : a;
-            mx = fmaxf(mx, s[j]);
-        }
-        float m_new = fmaxf(m_run, mx);
-        if (m_new == -INFINITY) continue;  // row past N in a causal tail: nothing visible yet
-        float corr = fast_exp2((m_run - m_new) * sc);
-        m_run = m_new;
-        float mb = m_new * sc;
-        l_run *= corr;
-#pragma unroll
-        for (int c = 0; c < D; ++c) acc[c] *= corr;
-#pragma unroll
-        for (int j = 0; j < BC; ++j) {
-            float p = fast_exp2(__builtin_fmaf(s[j], sc, -mb));
-            l_run += p;
-#pragma unroll
-            for (int c = 0; c < D; ++c) acc[c] = __builtin_fmaf(p, lds_v[j * D + c], acc[c]);
-        }
     }
-    if (qi < N) {
-        float inv = 1.0f / l_run;
+
+    // ---- merge the four key splits of a row: with M the largest of their maxima and f = exp(m - M),
+    // L = M + log sum f l and O = sum f O / sum f l
+    const float l = sum_both_halves(l_run);
+    if (half == 0) {
+        lds_m[split][slab * 32 + col] = m_run;
+        lds_l[split][slab * 32 + col] = l;
+    }
+    __syncthreads();
+    float m_all = -INFINITY, l_all = 0.f;
 #pragma unroll
-        for (int c = 0; c < D; ++c) o[head_off + (size_t)qi * D + c] = acc[c] * inv;
-        lse[(size_t)bh * N + qi] = (m_run * sc + log2f(l_run)) * kLn2;
+    for (int w = 0; w < SPLITS; ++w) m_all = fmaxf(m_all, lds_m[w][slab * 32 + col]);
+#pragma unroll
+    for (int w = 0; w < SPLITS; ++w)
+        l_all += lds_l[w][slab * 32 + col] * fast_exp2((lds_m[w][slab * 32 + col] - m_all) * sc);
+    const float f = fast_exp2((m_run - m_all) * sc) / l_all;
+    // the K buffers are free: [split][row][d] partial outputs, already scaled
+    static_assert(sizeof(lds_k) >= SPLITS * BR * KSTR * sizeof(float), "partial outputs must fit");
+    float* part = &lds_k[0][0];
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 w = {acc[dt][4 * g] * f, acc[dt][4 * g + 1] * f, acc[dt][4 * g + 2] * f, acc[dt][4 * g + 3] * f};
+            *reinterpret_cast<f32x4*>(part + (split * BR + slab * 32 + col) * KSTR + dt * 32 + 8 * g + 4 * half) = w;
+        }
+    if (split == 0 && half == 0 && q0 + col < N) lse[(size_t)bh * N + q0 + col] = (m_all * sc + log2f(l_all)) * kLn2;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < BR * D / 4 / NT; ++i) {
+        const int c = tid + i * NT, r = c / (D / 4), cc = (c % (D / 4)) * 4;
+        if (qt * BR + r < N) {
+            f32x4 w = *reinterpret_cast<const f32x4*>(part + r * KSTR + cc);
+#pragma unroll
+            for (int sp = 1; sp < SPLITS; ++sp) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(part + (sp * BR + r) * KSTR + cc);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] += x[e];
+            }
+            *reinterpret_cast<f32x4*>(o + head_off + (size_t)(qt * BR + r) * D + cc) = w;
+        }
     }
 }
 
@@ -1140,17 +1248,17 @@ int launch_fwd_f32(const void* q, const void* k, const void* v, void* o, float* 
     int n_qtiles = (N + BR - 1) / BR;
     long total = (long)B * H * n_qtiles;
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
-    dim3 grid((unsigned)total), block(64);
+    dim3 grid((unsigned)total), block(512);
     auto qp = static_cast<const float*>(q);
     auto kp = static_cast<const float*>(k);
     auto vp = static_cast<const float*>(v);
     auto op = static_cast<float*>(o);
     if (causal)
         hipLaunchKernelGGL((fa_fwd_f32_kernel<64, 32, true>), grid, block, 0, stream, qp, kp, vp, op, lse, N, n_qtiles,
-                           H / H_kv, scale);
+                           (int)total, H / H_kv, scale);
     else
         hipLaunchKernelGGL((fa_fwd_f32_kernel<64, 32, false>), grid, block, 0, stream, qp, kp, vp, op, lse, N,
-                           n_qtiles, H / H_kv, scale);
+                           n_qtiles, (int)total, H / H_kv, scale);
     return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
 }
 

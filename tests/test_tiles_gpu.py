@@ -1,0 +1,33 @@
+"""The sizes at which a kernel's tiles, splits and dispatch rules change, against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import f64, max_abs
+from paper_2407_08608_amd import binding, inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("N", [31, 32, 33, 64, 65, 96, 97, 127, 128, 130, 255, 257, 513, 700])
+def test_fp32_tile_and_split_edges(N, causal):
+    # 64-row workgroups of two 32-row slabs; four waves of a slab split every 128-key block, so at 31..130 keys
+    # some splits see no key at all, or (causal) none that a given row may see
+    q = inputs.normal_tensor(300 + N, "q", (1, 6, N, 64), "f32")
+    k, v = (inputs.normal_tensor(300 + N, n, (1, 2, N, 64), "f32") for n in ("k", "v"))
+    o, lse = binding.fa_fwd_gqa(q.cuda(), k.cuda(), v.cuda(), 0.125, causal)
+    o_ref, l_ref = oracle.attention_fwd_gqa(f64(q), f64(k), f64(v), 0.125, causal)
+    assert max_abs(f64(o), o_ref) <= 2e-5 and max_abs(f64(lse), l_ref) <= 2e-5  # fp32 sums of at most 700 terms
+
+
+@pytest.mark.parametrize("causal", [False, True])
+def test_fp32_splits_merge_when_their_maxima_differ(causal):
+    # scores rise to 80 nats over the sequence: the splits of a row end with different maxima.  A raw score of up
+    # to 640 in sums of 64 terms carries about 8 roundings of 2^-24 * 640, times 1 / 8: 4e-5 relative in P, and
+    # |V| reaches 4.
+    q, k, v = inputs.rising_maximum_qkv(310, 1, 2, 600, 64, "f32")
+    o, lse = binding.fa_fwd(q.cuda(), k.cuda(), v.cuda(), 0.125, causal)
+    o_ref, l_ref = oracle.attention_fwd(f64(q), f64(k), f64(v), 0.125, causal)
+    assert max_abs(f64(o), o_ref) <= 2e-4 and max_abs(f64(lse), l_ref) <= 2e-4
