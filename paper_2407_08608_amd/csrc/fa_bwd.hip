@@ -2,8 +2,8 @@
 // Algorithm 3's recomputation of P from L and its D = rowsum(dO o O)).
 //
 //   preprocess : D = rowsum(dO o O) per query row (HBM-bound)
-//   dK/dV pass : one workgroup per block of 128 keys (wave w owns keys 32w..32w+31 and keeps
-//                dK_j, dV_j on chip); loop over tiles of 64 queries:
+//   dK/dV pass : one workgroup per block of 128 keys (64 at d = 256), dK_j, dV_j kept on chip; loop over
+//                tiles of 64 queries:
 //                S = Q_i K_j^T, dP = dO_i V_j^T, P = exp(S - L), dS = P o (dP - D),
 //                dV_j += P^T dO_i, dK_j += dS^T Q_i
 //   dQ pass    : one workgroup per tile of queries (dQ_i on chip), loop over key blocks:
@@ -30,7 +30,9 @@ namespace fa {
 
 // LDS row stride (elements) of tiles that are read both by rows and transposed: an odd multiple
 // of 16 bytes keeps the row reads conflict-free, and the offset from a multiple of 256 bytes
-// decides how much the four rows of a transposing read overlap in the banks.
+// decides how much the four rows of a transposing read overlap in the banks.  Measured LDS rates
+// per CU at d = 128: 304 B gives 211 / 123 B/clk (rows / transposed), 272 B gives 208 / 63, 320 B
+// gives 63 / 208.
 constexpr int bwd_row_stride(int d) { return d >= 128 ? d + 24 : d + 40; }
 
 // ---------------------------------------------------------------------------------------
@@ -60,7 +62,7 @@ fa_bwd_preprocess_kernel(const uint16_t* __restrict__ o, const uint16_t* __restr
 
 // ---------------------------------------------------------------------------------------
 template <typename Tag, int D, bool CAUSAL>
-__global__ void __launch_bounds__(256, D >= 128 ? 1 : 2)
+__global__ void __launch_bounds__(256, 2)
 fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
               const uint16_t* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ dvec,
               uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int N,
@@ -69,33 +71,16 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
     constexpr int BK = 128;        // keys per workgroup
     constexpr int BQ = 64;         // queries per loop iteration
     constexpr int NT = 256;
-    // Row stride of the Q and dO tiles: they are read both as rows (128-bit) and transposed.
-    // Measured LDS rates per CU at D = 128: 304 B gives 211 / 123 B/clk (rows / transposed), 272 B
-    // gives 208 / 63, 320 B gives 63 / 208.  (An unpadded XOR-swizzled layout that frees both
-    // reads of bank conflicts altogether was measured too: same speed, the kernel is bound by
-    // the instruction issue of its one wave per SIMD, not by the LDS.)
+    static_assert(D == 64, "two workgroups per CU; wider heads share scores (fa_bwd_dkdv_shared_kernel)");
     constexpr int RSTR = bwd_row_stride(D);
     constexpr int TILE_B = BQ * RSTR * 2;  // bytes per tile
     constexpr int KS = D / 16;
     // MFMA steps by which LDS operand reads lead their use (registers permitting)
-    constexpr int KP = D == 128 ? 4 : 2;
-    // The step loops below must be unrolled (register arrays are indexed by the step).  At d = 256
-    // with the causal mask the unrolled body passes the size at which "#pragma unroll" gives up
-    // silently; this file is compiled with that threshold raised (see build.py).
-    // S and dP contract over the whole head dimension; dK and dV are produced for a slice of DO
-    // columns per workgroup (the whole of it up to d = 128; at d = 256 two workgroups, blockIdx.y,
-    // take half each and both recompute S and dP -- the accumulators of all 256 columns, 256
-    // registers per lane on top of the K and V operands, do not fit the register file)
-    constexpr int DO = D > 128 ? 128 : D;
-    constexpr int DT = DO / 32;
+    constexpr int KP = 2;
+    constexpr int DT = D / 32;
     constexpr int CPR = D / 8;     // 16-byte chunks per row
     constexpr int QCH = BQ * CPR / NT;  // chunks per thread for a Q / dO tile
-    // With one wave per SIMD (more than 256 registers per lane) MFMA results land in the
-    // accumulation half of the register file unless told otherwise; the score tiles S and dP,
-    // which the exponentials read, are then produced by MfmaVgprAcc into ordinary registers.
-    constexpr bool VACC = D >= 128;
     using E = Elem<Tag>;
-    const int col0 = blockIdx.y * DO;  // first column of this workgroup's slice
 
     // tiles 0, 1: Q_i double-buffered; tiles 2, 3: dO_i (a fixed distance from the Q tile of the
     // same parity, so one address register serves both)
@@ -128,15 +113,6 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
         kreg[ks] = my_key < N ? *reinterpret_cast<const i32x4*>(kh + (size_t)my_key * D + ks * 16 + half * 8) : z;
         vreg[ks] = my_key < N ? *reinterpret_cast<const i32x4*>(vh + (size_t)my_key * D + ks * 16 + half * 8) : z;
     }
-    // The kernel needs more than 256 registers per lane, so part of them live in the accumulation
-    // half of the register file, which only MFMA can address directly.  K_j / V_j operands and the
-    // dK / dV accumulators are touched by MFMA alone and live there; the score tiles, which the
-    // exponentials read, are kept in ordinary registers (VACC below).
-    if constexpr (D >= 128) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(kreg[ks]), "+a"(vreg[ks]));
-    }
-
     f32x16 dkacc[DT], dvacc[DT];
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
@@ -169,24 +145,16 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
     // buffer resources and read as zero.
     const __amdgpu_buffer_rsrc_t q_rsrc = make_buffer(qh, (uint32_t)N * D * 2);
     const __amdgpu_buffer_rsrc_t do_rsrc = make_buffer(doh, (uint32_t)N * D * 2);
-    // At d = 256 the staging registers of a whole tile pair (64 per lane) would not fit beside the
-    // operands and accumulators: the tile travels in two halves, the first stored to LDS between
-    // the two GEMM pairs of the iteration, the second at its end.
-    constexpr int NG = QCH >= 8 ? 2 : 1;
-    constexpr int QG = QCH / NG;
-    i32x4 qpre[QG], dopre[QG];
+    i32x4 qpre[QCH], dopre[QCH];
     float lpre = 0.f;  // threads 0..63 carry L, 64..127 carry D
     int lrow = 0;
     // The next tile travels global -> registers (issued at the top of an iteration) -> LDS (at its
-    // end).  Spreading the loads and the LDS writes over the MFMA steps was measured and is no
-    // faster: the single wave of a SIMD is bound by its own instruction issue, not by where in
-    // the iteration an instruction sits.
-    auto load_group = [&](int it, int grp) {  // chunks grp * QG .. of the Q_i and dO_i tiles
+    // end).
+    auto load_tile = [&](int it) {
 #pragma unroll
-        for (int j = 0; j < QG; ++j) {
-            const int i = grp * QG + j;
-            qpre[j] = buffer_load_16B(q_rsrc, it * BQ * D * 2 + (tid + i * NT) * 16);
-            dopre[j] = buffer_load_16B(do_rsrc, it * BQ * D * 2 + (tid + i * NT) * 16);
+        for (int j = 0; j < QCH; ++j) {
+            qpre[j] = buffer_load_16B(q_rsrc, it * BQ * D * 2 + (tid + j * NT) * 16);
+            dopre[j] = buffer_load_16B(do_rsrc, it * BQ * D * 2 + (tid + j * NT) * 16);
         }
     };
     auto load_ld = [&](int it) {
@@ -197,10 +165,10 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
             lpre = (tid < BQ ? lh : dh)[min(lrow, N - 1)];
         }
     };
-    auto store_group = [&](int st, int grp) {
+    auto store_tile = [&](int st) {
 #pragma unroll
-        for (int j = 0; j < QG; ++j) {
-            int c = tid + (grp * QG + j) * NT;
+        for (int j = 0; j < QCH; ++j) {
+            int c = tid + j * NT;
             int row = c / CPR, cc = c % CPR;
             *reinterpret_cast<i32x4*>(lds_t[st] + row * RSTR + cc * 8) = qpre[j];
             *reinterpret_cast<i32x4*>(lds_t[2 + st] + row * RSTR + cc * 8) = dopre[j];
@@ -215,11 +183,8 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
 
     if (it0 < n_qtiles) {
         load_ld(it0);
-#pragma unroll
-        for (int grp = 0; grp < NG; ++grp) {
-            load_group(it0, grp);
-            store_group(0, grp);
-        }
+        load_tile(it0);
+        store_tile(0);
         store_ld(0);
     }
     __syncthreads();
@@ -229,7 +194,7 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
         const int q0 = it * BQ;
         const bool more = it + 1 < n_qtiles;
         if (more) {
-            load_group(it + 1, 0);
+            load_tile(it + 1);
             load_ld(it + 1);
         }
 
@@ -255,7 +220,7 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
             // sub-tile).  Transposing reads: lane takes 4 elements at tr_col of row 4 half + tr_row
             // (+ 8 for the second read, + 16 per slab), 32 elements further per d-tile.
             uint32_t q_rows = lds_address(lds_t[st]) + (col * RSTR + half * 8) * 2;
-            uint32_t q_tr = lds_address(lds_t[st]) + ((4 * half + tr_row) * RSTR + tr_col + col0) * 2;
+            uint32_t q_tr = lds_address(lds_t[st]) + ((4 * half + tr_row) * RSTR + tr_col) * 2;
             uint32_t l_rows = lds_address(lds_l[st]) + 16 * half;  // 4 consecutive rows from 4 * half
             uint32_t d_rows = lds_address(lds_d[st]) + 16 * half;
             asm volatile("" : "+v"(q_rows), "+v"(q_tr), "+v"(l_rows), "+v"(d_rows));
@@ -324,17 +289,8 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
                     // A wave issues in order and its second MFMA waits for the matrix pipe to take it:
                     // vector work placed after both MFMAs of a step runs in the shadow of the second
                     // one only.  Half of it goes between the two.
-                    if constexpr (VACC) {
-                        if (ks == 0) MfmaVgprAcc<Tag>::first(sacc[sub], a0, kreg[ks]);
-                        else MfmaVgprAcc<Tag>::run(sacc[sub], a0, kreg[ks]);
-                    } else {
-                        sacc[sub] = E::mma(a0, kreg[ks], ks == 0 ? zero : sacc[sub]);
-                    }
+                    sacc[sub] = E::mma(a0, kreg[ks], ks == 0 ? zero : sacc[sub]);
                     if (sub == 1) {
-                        // sub-tile 0's results were written by MFMAs the hazard checker cannot see
-                        if constexpr (VACC) {
-                            if (ks == 0) mfma_result_wait(sacc[0], pacc[0]);
-                        }
                         // the 8 register pairs of sub-tile 0 spread over the KS steps (pair c runs at
                         // step c KS / 8); the L group of a pair is fetched one step before the step
                         // that needs it first
@@ -347,8 +303,7 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
                             if ((c * KS) / 8 == ks) softmax_elem(0, c, 0);
                     }
                     __builtin_amdgcn_sched_barrier(0);
-                    if constexpr (VACC) MfmaVgprAcc<Tag>::run(pacc[sub], a1, vreg[ks]);
-                    else pacc[sub] = E::mma(a1, vreg[ks], pacc[sub]);
+                    pacc[sub] = E::mma(a1, vreg[ks], pacc[sub]);
                     if (sub == 0 && ks == KS - 1) fetch_l(0, 0);
                     if (sub == 1) {
 #pragma unroll
@@ -359,13 +314,6 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
                             }
                     }
                     __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-
-            if constexpr (NG == 2) {
-                if (more) {  // the other LDS buffers are free for the whole iteration
-                    store_group(st ^ 1, 0);
-                    load_group(it + 1, 1);
                 }
             }
 
@@ -395,9 +343,6 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
                     dvacc[dt] = E::mma(pa[sub][s2], b, dvacc[dt]);
                     constexpr int PP = 8 / (2 * DT);
                     if (sub == 0) {
-                        if constexpr (VACC) {
-                            if (u == 0) mfma_result_wait(sacc[1], pacc[1]);
-                        }
 #pragma unroll
                         for (int g = 1; g < 4; ++g)
                             if ((2 * g) / PP == u + 1) fetch_l(1, g);
@@ -420,7 +365,7 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
         body(mask_tag);
 
         if (more) {
-            store_group(st ^ 1, NG - 1);
+            store_tile(st ^ 1);
             store_ld(st ^ 1);
         }
         __syncthreads();
@@ -437,11 +382,370 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
         for (int r = 0; r < 16; ++r) {
             int key = key0 + wave * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
             if (key < N) {
-                size_t off = head_off + (size_t)key * D + col0 + dt * 32 + col;
+                size_t off = head_off + (size_t)key * D + dt * 32 + col;
                 dk[off] = (uint16_t)(E::pack2(dkacc[dt][r] * scale, 0.f) & 0xFFFF);
                 dv[off] = (uint16_t)(E::pack2(dvacc[dt][r], 0.f) & 0xFFFF);
             }
         }
+}
+
+// ---------------------------------------------------------------------------------------
+// dK/dV pass, head dimensions 128 and 256: four waves, one per SIMD, that share scores.
+//
+// Bound by the matrix pipes (64 MFMAs of 32 cycles per wave and iteration) if the LDS can feed them: an operand read
+// from the LDS serves as many MFMAs as the wave owns 32-key tiles, and the register file holds accumulators for one
+// tile of all 128 columns or for two tiles of 64.  So the waves divide the two halves of the work differently:
+//   S, dP   : by key tiles and 32-query sub-tiles -- wave (p, g) computes those of its K, V operands (resident: two
+//             key tiles at d = 128, one at d = 256) for sub-tile g;
+//   dK, dV  : by columns -- a wave accumulates two key tiles x 64 columns, from the P and dS of both sub-tiles.
+// P and dS, packed, are already the A operands of the second half (lane = key), so what the waves exchange is raw
+// registers, 1 KiB per 32 x 16 piece through the LDS, with one barrier per iteration.  At d = 128 a row operand and a
+// transposed operand serve two MFMAs each (48 LDS operand reads per wave and iteration instead of 96); at d = 256
+// the four waves cover all 256 columns from one computation of S and dP (no second workgroup that repeats it: 64
+// MFMAs instead of 96 per 32 keys).
+//
+// Within an iteration (64 queries; "own" = this wave's sub-tile):
+//   phase 1  S                               16 MFMAs
+//   phase 2  dP                              16 MFMAs  ||  P = exp2(S c - L), packed and sent
+//   phase 3  dV += own P dO                            ||  dS = P o (dP - D), packed and sent
+//   barrier; the other waves' pieces are requested
+//   phase 4  dK += own dS Q, then dV and dK of everything else
+// Every step ends in a full scheduling barrier so that the interleaving written here is what runs.
+// Measured (bf16, whole backward, one key tile x all columns per wave before): d = 256, B = 2, H = 8, N = 8192 4801 ->
+// 3873 us (this pass 3046 -> 2112, 1.04 PFLOP/s of executed MFMAs); d = 128, B = 4, H = 16, N = 4096 causal 1065 ->
+// 1029 us.  The chip's power, not a pipe, is what is left at these sizes: without the exponentials, the barrier or the
+// row reads the pass gains 1 to 4 %.  Tiles requested two iterations ahead instead of one: no gain.
+template <typename Tag, int D, bool CAUSAL>
+__global__ void __launch_bounds__(256, 1)
+fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                          const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
+                          const float* __restrict__ lse, const float* __restrict__ dvec, uint16_t* __restrict__ dk,
+                          uint16_t* __restrict__ dv, int N, int n_kblocks, int total_wg, int kv_group, float scale) {
+    [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
+    static_assert(D == 128 || D == 256, "d = 64 keeps two workgroups per CU (fa_bwd_dkdv_kernel)");
+    constexpr int NT = 256;
+    constexpr int BQ = 64;                    // queries per iteration, two sub-tiles
+    constexpr int KEYT = D == 128 ? 2 : 1;    // key tiles whose scores a wave computes
+    constexpr int NKT = 2 * KEYT;             // key tiles per workgroup
+    constexpr int BK = 32 * NKT;              // keys per workgroup
+    constexpr int KS = D / 16;                // MFMA steps along the head dimension
+    constexpr int RSTR = bwd_row_stride(D);
+    constexpr int TILE_B = BQ * RSTR * 2;     // bytes per Q or dO tile
+    constexpr int DO_DIST = 2 * TILE_B;
+    constexpr int CPR = D / 8;                // 16-byte chunks per row
+    constexpr int QCH = BQ * CPR / NT;        // chunks per thread of a tile
+    constexpr int KP = 4;                     // steps by which row operand reads lead their MFMAs
+    constexpr int PIECE = 1024;               // bytes of one exchanged operand: 32 keys x 16 queries
+    using E = Elem<Tag>;
+
+    // tiles 0, 1: Q_i double-buffered; tiles 2, 3: dO_i (a fixed distance from the Q tile of the same parity)
+    __shared__ __attribute__((aligned(16))) uint16_t lds_t[4][BQ * RSTR];
+    __shared__ __attribute__((aligned(16))) char lds_x[2][NKT * 4 * PIECE];  // P, dS: [key tile][sub-tile][slab]
+    __shared__ __attribute__((aligned(16))) float lds_l[2][BQ];
+    __shared__ __attribute__((aligned(16))) float lds_d[2][BQ];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int col = lane & 31, half = lane >> 5;
+    const int p = wave >> 1, g = wave & 1;
+
+    const int id = xcd_contiguous(blockIdx.x, total_wg);
+    const int bh = id / n_kblocks;
+    const int kb = id % n_kblocks;  // causal: key block 0 has the longest loop and comes first
+    const int key0 = kb * BK;
+    // this wave's accumulators: key tiles acc_tile(0), acc_tile(1), columns col0 .. col0 + 63; tile 0 is one whose
+    // scores it computes itself (at d = 128 both are)
+    auto acc_tile = [&](int j) { return KEYT == 2 ? 2 * p + j : p ^ j; };
+    const int col0 = 64 * (KEYT == 2 ? g : wave);
+
+    // bh counts key/value heads; the kv_group query heads that share this one are bh * kv_group + i
+    const size_t head_off = (size_t)bh * N * D;
+    float sc = scale * kLog2e;
+    asm volatile("" : "+v"(sc));  // in a vector register: an FMA with a scalar operand issues at a lower rate
+
+    // ---- K and V rows of the score tiles as B operands, in the accumulation half of the register file
+    i32x4 kreg[KEYT][KS], vreg[KEYT][KS];
+    int my_key[KEYT];
+#pragma unroll
+    for (int i = 0; i < KEYT; ++i) {
+        my_key[i] = key0 + (p * KEYT + i) * 32 + col;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const i32x4 z = {0, 0, 0, 0};
+            const size_t off = head_off + (size_t)my_key[i] * D + ks * 16 + half * 8;
+            kreg[i][ks] = my_key[i] < N ? *reinterpret_cast<const i32x4*>(k + off) : z;
+            vreg[i][ks] = my_key[i] < N ? *reinterpret_cast<const i32x4*>(v + off) : z;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < KEYT; ++i)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(kreg[i][ks]), "+a"(vreg[i][ks]));
+
+    f32x16 dkacc[2][2], dvacc[2][2];  // [key tile][32 columns]
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) dkacc[j][dt][r] = dvacc[j][dt][r] = 0.f;
+
+    const int n_qtiles = (N + BQ - 1) / BQ;
+    const int it0 = CAUSAL ? key0 / BQ : 0;  // first query tile that can see this key block
+    const int tr_row = (lane & 15) >> 2;
+    const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    // Masked query tiles come first: every tile when the key block is ragged (keys past N), else the tiles on the
+    // causal diagonal.  They get a loop of their own so that the main loop has a single straight-line body.
+    const int it_masked_end = key0 + BK > N ? n_qtiles : (CAUSAL ? min(n_qtiles, (key0 + BK - 1) / BQ + 1) : it0);
+
+    // Barrier for LDS traffic only: the next tile's global loads stay in flight.
+    auto lds_barrier = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // Every query head of the group adds into the same dK_j, dV_j.
+#pragma nounroll
+    for (int gi = 0; gi < kv_group; ++gi) {
+    const size_t qhead = (size_t)bh * kv_group + gi;
+    const float* lh = lse + qhead * N;
+    const float* dh = dvec + qhead * N;
+    // Rows past N lie outside the buffer resources and read as zero, so every iteration requests and stores a next
+    // tile: the one after the last is zeros that nothing reads.
+    const __amdgpu_buffer_rsrc_t q_rsrc = make_buffer(q + qhead * N * D, (uint32_t)N * D * 2);
+    const __amdgpu_buffer_rsrc_t do_rsrc = make_buffer(dout + qhead * N * D, (uint32_t)N * D * 2);
+
+    i32x4 qpre[QCH], dopre[QCH];
+    float lpre = 0.f;  // threads 0..63 carry L, 64..127 carry D
+    int lrow = 0;
+    auto load_chunk = [&](int it, int c) __attribute__((always_inline)) {  // chunk c of 2 QCH: Q then dO
+        const int off = it * BQ * D * 2 + (tid + (c % QCH) * NT) * 16;
+        if (c < QCH) qpre[c] = buffer_load_16B(q_rsrc, off);
+        else dopre[c - QCH] = buffer_load_16B(do_rsrc, off);
+    };
+    auto store_chunk = [&](int st, int c) __attribute__((always_inline)) {
+        const int e = tid + (c % QCH) * NT, row = e / CPR, cc = e % CPR;
+        *reinterpret_cast<i32x4*>(lds_t[c < QCH ? st : 2 + st] + row * RSTR + cc * 8) = c < QCH ? qpre[c % QCH] : dopre[c % QCH];
+    };
+    auto load_ld = [&](int it) __attribute__((always_inline)) {
+        if (tid < 2 * BQ) {  // the raw value only: arithmetic on it here would wait for the load on the spot
+            lrow = it * BQ + (tid & (BQ - 1));
+            lpre = (tid < BQ ? lh : dh)[min(lrow, N - 1)];
+        }
+    };
+    auto store_ld = [&](int st) __attribute__((always_inline)) {
+        // rows past N get L = +inf so that P = exp2(0 - inf) = 0, and D = 0.  D is kept negated: the dP
+        // accumulators start from -D_i, so dP - D comes out of the MFMAs
+        if (tid < BQ) lds_l[st][tid] = lrow < N ? lpre * kLog2e : INFINITY;
+        else if (tid < 2 * BQ) lds_d[st][tid - BQ] = lrow < N ? -lpre : 0.f;
+    };
+
+    if (it0 < n_qtiles) {
+        load_ld(it0);
+#pragma unroll
+        for (int c = 0; c < 2 * QCH; ++c) load_chunk(it0, c);
+#pragma unroll
+        for (int c = 0; c < 2 * QCH; ++c) store_chunk(0, c);
+        store_ld(0);
+    }
+    __syncthreads();
+
+    auto iteration = [&](int it, auto mask_tag) __attribute__((always_inline)) {
+        constexpr bool MASK = decltype(mask_tag)::value;
+        const int st = (it - it0) & 1;
+        const int q_first = it * BQ + 32 * g + 4 * half;  // query of score register 0
+
+        // One register per LDS base; every read below adds a compile-time offset.
+        uint32_t q_rows = lds_address(lds_t[st]) + ((32 * g + col) * RSTR + half * 8) * 2;
+        uint32_t tr_own = lds_address(lds_t[st]) + ((32 * g + 4 * half + tr_row) * RSTR + tr_col + col0) * 2;
+        uint32_t tr_oth = lds_address(lds_t[st]) + ((32 * (g ^ 1) + 4 * half + tr_row) * RSTR + tr_col + col0) * 2;
+        uint32_t l_rows = lds_address(lds_l[st]) + 128 * g + 16 * half;
+        uint32_t d_rows = lds_address(lds_d[st]) + 128 * g + 16 * half;
+        asm volatile("" : "+v"(q_rows), "+v"(tr_own), "+v"(tr_oth), "+v"(l_rows), "+v"(d_rows));
+
+        f32x16 sacc[KEYT], pacc[KEYT];
+        i32x4 pa[KEYT][2], dsa[KEYT][2];  // [key tile][16-query slab] of the own sub-tile, as A operands
+        f32x4 l4[4];
+
+        auto await = [&](f32x16 (&x)[KEYT]) __attribute__((always_inline)) {  // results the hazard checker cannot see
+            if constexpr (KEYT == 2) mfma_result_wait(x[0], x[1]);
+            else mfma_result_wait(x[0]);
+        };
+        auto row_read = [&](int u) __attribute__((always_inline)) {  // step u of phases 1 (Q) and 2 (dO)
+            return lds_load_16B(q_rows + (u < KS ? 0 : DO_DIST) + (u % KS) * 32);
+        };
+        auto tr_read = [&](uint32_t base, int tensor, int w) __attribute__((always_inline)) {  // w = (slab, 32 columns)
+            const uint32_t a = base + (tensor ? 0 : DO_DIST) + ((w >> 1) * 16 * RSTR + (w & 1) * 32) * 2;
+            const i32x2 lo = lds_read_tr16(a), hi = lds_read_tr16(a + 8 * RSTR * 2);
+            return i32x4{lo[0], lo[1], hi[0], hi[1]};
+        };
+        auto piece = [&](int tensor, int kt, int sub, int slab) __attribute__((always_inline)) {
+            return lds_address(lds_x[tensor]) + ((kt * 2 + sub) * 2 + slab) * PIECE + lane * 16;
+        };
+        auto send = [&](int tensor, int i, int slab, const i32x4& x) __attribute__((always_inline)) {
+            typedef i32x4 __attribute__((address_space(3))) * lds_vec_ptr;
+            *(lds_vec_ptr)(uintptr_t)piece(tensor, p * KEYT + i, g, slab) = x;
+        };
+
+        // ---- phases 1 and 2
+        i32x4 ring[KP], bdo[4];
+#pragma unroll
+        for (int u = 0; u < KP; ++u) ring[u] = row_read(u);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) l4[i] = lds_load_4f(l_rows + 32 * i);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {  // dP starts from -D: registers 4i .. 4i+3 are query rows 8i + 4 half ..
+            const f32x4 t = lds_load_4f(d_rows + 32 * i);
+#pragma unroll
+            for (int j = 0; j < KEYT; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) pacc[j][4 * i + r] = t[r];
+        }
+        load_ld(it + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        auto probability = [&](int n) __attribute__((always_inline)) {  // score n of 16 KEYT
+            const int i = n / 16, rr = n % 16;
+            float x = fast_exp2(__builtin_fmaf(sacc[i][rr], sc, -l4[rr >> 2][rr & 3]));
+            if constexpr (MASK) {
+                const int qi = q_first + 8 * (rr >> 2) + (rr & 3);
+                x = (my_key[i] >= N || (CAUSAL && my_key[i] > qi)) ? 0.f : x;
+            }
+            sacc[i][rr] = x;
+            if (rr & 1) pa[i][rr >> 3][(rr >> 1) & 3] = E::pack2(sacc[i][rr - 1], x);
+            if ((rr & 7) == 7) send(0, i, rr >> 3, pa[i][rr >> 3]);
+        };
+#pragma unroll
+        for (int u = 0; u < 2 * KS; ++u) {
+            const i32x4 a = ring[u % KP];
+            if (u + KP < 2 * KS) ring[u % KP] = row_read(u + KP);
+            else if (u + KP - 2 * KS < 4) bdo[u + KP - 2 * KS] = tr_read(tr_own, 0, u + KP - 2 * KS);
+            const int ks = u % KS;
+#pragma unroll
+            for (int i = 0; i < KEYT; ++i) {
+                if (u < KS) {
+                    if (ks == 0) MfmaVgprAcc<Tag>::first(sacc[i], a, kreg[i][ks]);
+                    else MfmaVgprAcc<Tag>::run(sacc[i], a, kreg[i][ks]);
+                } else {
+                    MfmaVgprAcc<Tag>::run(pacc[i], a, vreg[i][ks]);
+                    if (u == KS && i == KEYT - 1) await(sacc);
+                    // 16 KEYT scores over the 16 MFMAs of this phase, none before the wait above
+                    constexpr int M0 = KEYT - 1;
+                    const int m = ks * KEYT + i;
+#pragma unroll
+                    for (int n = 0; n < 16 * KEYT; ++n)
+                        if (m >= M0 && M0 + (n * (16 - M0)) / (16 * KEYT) == m) probability(n);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (u * 2 * QCH / (2 * KS) != (u + 1) * 2 * QCH / (2 * KS)) load_chunk(it + 1, u * 2 * QCH / (2 * KS));
+        }
+
+        // ---- phase 3: dV of the own piece beside dS
+        i32x4 bq[4];
+        auto gradient = [&](int n) __attribute__((always_inline)) {
+            const int i = n / 16, rr = n % 16;
+            pacc[i][rr] *= sacc[i][rr];
+            if (rr & 1) dsa[i][rr >> 3][(rr >> 1) & 3] = E::pack2(pacc[i][rr - 1], pacc[i][rr]);
+            if ((rr & 7) == 7) send(1, i, rr >> 3, dsa[i][rr >> 3]);
+        };
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+            for (int i = 0; i < KEYT; ++i) {
+                dvacc[i][w & 1] = E::mma(pa[i][w >> 1], bdo[w], dvacc[i][w & 1]);
+                if (w == 0 && i == 0) await(pacc);
+                if (i == 0) bq[w] = tr_read(tr_own, 1, w);
+#pragma unroll
+                for (int n = 0; n < 4; ++n) gradient((w * KEYT + i) * 4 + n);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+
+        lds_barrier();
+
+        // ---- phase 4
+        // the other waves' pieces: those of the other sub-tile and, at d = 256, the other key tile's of this one
+        i32x4 bo[4], pf[2][2], dsf[2][2], px[2], dsx[2];
+        if constexpr (KEYT == 1) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) px[s] = lds_load_16B(piece(0, acc_tile(1), g, s));
+#pragma unroll
+            for (int s = 0; s < 2; ++s) dsx[s] = lds_load_16B(piece(1, acc_tile(1), g, s));
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) pf[j][s] = lds_load_16B(piece(0, acc_tile(j), g ^ 1, s));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+            for (int i = 0; i < KEYT; ++i) {
+                dkacc[i][w & 1] = E::mma(dsa[i][w >> 1], bq[w], dkacc[i][w & 1]);
+                if (i == 0) bo[w] = tr_read(tr_oth, 0, w);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        if constexpr (KEYT == 1) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                dvacc[1][w & 1] = E::mma(px[w >> 1], bdo[w], dvacc[1][w & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                dkacc[1][w & 1] = E::mma(dsx[w >> 1], bq[w], dkacc[1][w & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                dvacc[j][w & 1] = E::mma(pf[j][w >> 1], bo[w], dvacc[j][w & 1]);
+                if (j == 0) bq[w] = tr_read(tr_oth, 1, w);
+                else if (w < 2) {
+#pragma unroll
+                    for (int jj = 0; jj < 2; ++jj) dsf[jj][w] = lds_load_16B(piece(1, acc_tile(jj), g ^ 1, w));
+                }
+#pragma unroll
+                for (int c = 0; c < QCH / 4; ++c)
+                    if (w * 2 + j < 4) store_chunk(st ^ 1, (w * 2 + j) * (QCH / 4) + c);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                dkacc[j][w & 1] = E::mma(dsf[j][w >> 1], bq[w], dkacc[j][w & 1]);
+#pragma unroll
+                for (int c = 0; c < QCH / 4; ++c)
+                    if (w * 2 + j < 4) store_chunk(st ^ 1, QCH + (w * 2 + j) * (QCH / 4) + c);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        store_ld(st ^ 1);
+        __syncthreads();
+    };
+    int it = it0;
+    for (; it < it_masked_end; ++it) iteration(it, std::true_type{});
+    for (; it < n_qtiles; ++it) iteration(it, std::false_type{});
+    }  // query heads of the group
+
+    // ---- epilogue: dK_j = scale * acc, dV_j = acc  (rows = keys 8g+4h+r of a tile, col = d)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int key = key0 + acc_tile(j) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+                if (key < N) {
+                    const size_t off = head_off + (size_t)key * D + col0 + dt * 32 + col;
+                    dk[off] = (uint16_t)(E::pack2(dkacc[j][dt][r] * scale, 0.f) & 0xFFFF);
+                    dv[off] = (uint16_t)(E::pack2(dvacc[j][dt][r], 0.f) & 0xFFFF);
+                }
+            }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -687,7 +991,8 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
     float* dvec = static_cast<float*>(workspace);
     auto u16 = [](const void* p) { return static_cast<const uint16_t*>(p); };
     // every size check comes before the first launch: a call that fails has enqueued nothing
-    const int n_kblocks = (N + 127) / 128;
+    constexpr int kKeys = D == 256 ? 64 : 128;  // keys per workgroup of the dK/dV pass
+    const int n_kblocks = (N + kKeys - 1) / kKeys;
     const long total = (long)B * H_kv * n_kblocks;
     constexpr int BC = 64, NW = D == 256 ? 4 : 8;  // d = 256: a wave needs the whole register file
     const int n_qtiles = (N + NW * 32 - 1) / (NW * 32);
@@ -700,15 +1005,13 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
                        u16(o), u16(dout), dvec, rows);
     if (hipGetLastError() != hipSuccess) return FA_ERR_LAUNCH;
 
-    const dim3 kv_grid((unsigned)total, D > 128 ? D / 128 : 1);  // y: 128-column slices of dK, dV
-    if (causal)
-        hipLaunchKernelGGL((fa_bwd_dkdv_kernel<Tag, D, true>), kv_grid, dim3(256), 0, stream, u16(q),
-                           u16(k), u16(v), u16(dout), lse, dvec, static_cast<uint16_t*>(dk),
-                           static_cast<uint16_t*>(dv), N, n_kblocks, (int)total, H / H_kv, scale);
-    else
-        hipLaunchKernelGGL((fa_bwd_dkdv_kernel<Tag, D, false>), kv_grid, dim3(256), 0, stream, u16(q),
-                           u16(k), u16(v), u16(dout), lse, dvec, static_cast<uint16_t*>(dk),
-                           static_cast<uint16_t*>(dv), N, n_kblocks, (int)total, H / H_kv, scale);
+    auto dkdv = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(256), 0, stream, u16(q), u16(k), u16(v), u16(dout), lse,
+                           dvec, static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv), N, n_kblocks, (int)total,
+                           H / H_kv, scale);
+    };
+    if constexpr (D == 64) causal ? dkdv(fa_bwd_dkdv_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_kernel<Tag, D, false>);
+    else causal ? dkdv(fa_bwd_dkdv_shared_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_shared_kernel<Tag, D, false>);
     if (hipGetLastError() != hipSuccess) return FA_ERR_LAUNCH;
 
     if (causal)

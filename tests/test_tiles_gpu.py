@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import oracle
-from helpers import f64, max_abs
+from helpers import f64, max_abs, rel_rmse
 from paper_2407_08608_amd import binding, inputs
 
 pytestmark = pytest.mark.gpu
@@ -31,3 +31,30 @@ def test_fp32_splits_merge_when_their_maxima_differ(causal):
     o, lse = binding.fa_fwd(q.cuda(), k.cuda(), v.cuda(), 0.125, causal)
     o_ref, l_ref = oracle.attention_fwd(f64(q), f64(k), f64(v), 0.125, causal)
     assert max_abs(f64(o), o_ref) <= 2e-4 and max_abs(f64(lse), l_ref) <= 2e-4
+
+
+REL_RMSE, REL_MAXABS = 1e-2, 5e-2  # 2^-9 (bf16) rounding of P, dS and the outputs in sums over the sequence
+
+
+def _check_backward(seed, B, H, H_kv, N, d, causal, dtype):
+    q, dout = (inputs.normal_tensor(seed, n, (B, H, N, d), dtype) for n in ("q", "do"))
+    k, v = (inputs.normal_tensor(seed, n, (B, H_kv, N, d), dtype) for n in ("k", "v"))
+    qg, kg, vg, dog = (t.cuda() for t in (q, k, v, dout))
+    o, lse = binding.fa_fwd_gqa(qg, kg, vg, d ** -0.5, causal)
+    got = binding.fa_bwd_gqa(qg, kg, vg, o, lse, dog, d ** -0.5, causal)
+    torch.cuda.synchronize()
+    ref = oracle.attention_bwd_gqa(f64(q), f64(k), f64(v), f64(dout), d ** -0.5, causal)
+    for name, t in zip(("dq", "dk", "dv"), got):
+        g, r = f64(t), ref[name]
+        assert np.isfinite(g).all(), name
+        assert rel_rmse(g, r) <= REL_RMSE and max_abs(g, r) <= REL_MAXABS * np.abs(r).max(), (name, rel_rmse(g, r))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,N", [(128, n) for n in (2, 33, 63, 65, 127, 128, 129, 191, 321)] +
+                         [(256, n) for n in (2, 31, 32, 63, 64, 65, 127, 129, 321)])
+def test_backward_shared_score_tiles(d, N, causal, dtype):
+    # key blocks of 128 (64 at d = 256) in 32-key tiles, query tiles of 64 in two sub-tiles whose P and dS the waves
+    # exchange; an odd and an even number of query tiles, and two query heads per K/V head walking the ring twice
+    _check_backward(500 + N, 1, 4, 2, N, d, causal, dtype)
