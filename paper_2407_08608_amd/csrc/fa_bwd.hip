@@ -1,13 +1,15 @@
 // Backward attention for gfx950, head dimensions 64, 128 and 256, bf16 / fp16 (paper section 2.1 chain rule,
 // Algorithm 3's recomputation of P from L and its D = rowsum(dO o O)).
 //
-//   preprocess : D = rowsum(dO o O) per query row (HBM-bound)
+//   dQ pass    : one workgroup per tile of queries (dQ_i on chip).  Its prologue computes D = rowsum(dO o O) of
+//                its rows and leaves it in the workspace; loop over key blocks:
+//                S^T = K_j Q_i^T, dP^T = V_j dO_i^T, P = exp(S - L), dS = P o (dP - D),
+//                dQ_i^T += K_j^T dS^T
 //   dK/dV pass : one workgroup per block of 128 keys (64 at d = 256), dK_j, dV_j kept on chip; loop over
-//                tiles of 64 queries:
-//                S = Q_i K_j^T, dP = dO_i V_j^T, P = exp(S - L), dS = P o (dP - D),
+//                tiles of 64 queries: S = Q_i K_j^T, dP = dO_i V_j^T, P, dS as above,
 //                dV_j += P^T dO_i, dK_j += dS^T Q_i
-//   dQ pass    : one workgroup per tile of queries (dQ_i on chip), loop over key blocks:
-//                S^T = K_j Q_i^T, dP^T = V_j dO_i^T, P, dS as above, dQ_i^T += K_j^T dS^T
+// (A launch of its own for D read dO once more: 2.7 us of a training step's 34 at B = 2, H = 8, N = 333, d = 64;
+// at sizes where the chip's power is the limit the two forms take the same time.)
 //
 // Algorithm 3 produces dQ inside the dK/dV loop and adds it to HBM with atomics.  Measured on
 // MI355X that accumulation (17 GB of fp32 atomic traffic at seqlen 16k) cost about 30 % of the
@@ -34,31 +36,6 @@ namespace fa {
 // per CU at d = 128: 304 B gives 211 / 123 B/clk (rows / transposed), 272 B gives 208 / 63, 320 B
 // gives 63 / 208.
 constexpr int bwd_row_stride(int d) { return d >= 128 ? d + 24 : d + 40; }
-
-// ---------------------------------------------------------------------------------------
-template <typename Tag, int D>
-__global__ void __launch_bounds__(256)
-fa_bwd_preprocess_kernel(const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout,
-                         float* __restrict__ dvec, long rows) {
-    constexpr int LPR = D / 8;  // lanes per row, 8 elements each
-    using E = Elem<Tag>;
-    const int lane16 = threadIdx.x & (LPR - 1);
-    long row = (long)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
-    float acc = 0.f;
-    if (row < rows) {
-        i32x4 a = *reinterpret_cast<const i32x4*>(o + row * D + lane16 * 8);
-        i32x4 b = *reinterpret_cast<const i32x4*>(dout + row * D + lane16 * 8);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            uint32_t ua = (uint32_t)a[t], ub = (uint32_t)b[t];
-            acc = __builtin_fmaf(E::to_float((uint16_t)(ua & 0xFFFF)), E::to_float((uint16_t)(ub & 0xFFFF)), acc);
-            acc = __builtin_fmaf(E::to_float((uint16_t)(ua >> 16)), E::to_float((uint16_t)(ub >> 16)), acc);
-        }
-    }
-#pragma unroll
-    for (int off = LPR / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-    if (row < rows && lane16 == 0) dvec[row] = acc;
-}
 
 // ---------------------------------------------------------------------------------------
 template <typename Tag, int D, bool CAUSAL>
@@ -753,8 +730,8 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
 template <typename Tag, int D, int BC, int NW, bool CAUSAL>
 __global__ void __launch_bounds__(NW * 64, NW == 8 ? 2 : 1)
 fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-                 const uint16_t* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ dvec,
-                 uint16_t* __restrict__ dq, int N, int n_qtiles, int total_wg, int kv_group, float scale) {
+                 const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
+                 float* __restrict__ dvec, uint16_t* __restrict__ dq, int N, int n_qtiles, int total_wg, int kv_group, float scale) {
     [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
     constexpr int NT = NW * 64;
     constexpr int BR = NW * 32;
@@ -797,7 +774,21 @@ fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         doreg[ks] = *reinterpret_cast<const i32x4*>(dout + head_off + (size_t)qrow * D + ks * 16 + half * 8);
     }
     const float l2 = lse[(size_t)bh * N + qrow] * kLog2e;
-    const float dq_row = dvec[(size_t)bh * N + qrow];
+    // D = rowsum(dO o O): the two lanes of a row hold its dO between them, so O is read in the same pieces.  The
+    // dK/dV pass, launched after this one, reads D from the workspace.
+    float dq_row = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const i32x4 x = *reinterpret_cast<const i32x4*>(o + head_off + (size_t)qrow * D + ks * 16 + half * 8);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint32_t ua = (uint32_t)x[t], ub = (uint32_t)doreg[ks][t];
+            dq_row = __builtin_fmaf(E::to_float((uint16_t)(ua & 0xFFFF)), E::to_float((uint16_t)(ub & 0xFFFF)), dq_row);
+            dq_row = __builtin_fmaf(E::to_float((uint16_t)(ua >> 16)), E::to_float((uint16_t)(ub >> 16)), dq_row);
+        }
+    }
+    dq_row = sum_both_halves(dq_row);
+    if (half == 0 && qi < N) dvec[(size_t)bh * N + qi] = dq_row;
     constexpr bool NEG_D_START = D == 64;
     f32x16 negd;
 #pragma unroll
@@ -987,7 +978,6 @@ template <typename Tag, int D>
 static int launch_bwd_t(const void* q, const void* k, const void* v, const void* o, const float* lse,
                         const void* dout, void* dq, void* dk, void* dv, void* workspace, int B, int H, int H_kv,
                         int N, float scale, int causal, hipStream_t stream) {
-    const long rows = (long)B * H * N;
     float* dvec = static_cast<float*>(workspace);
     auto u16 = [](const void* p) { return static_cast<const uint16_t*>(p); };
     // every size check comes before the first launch: a call that fails has enqueued nothing
@@ -999,10 +989,12 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
     const long total_q = (long)B * H * n_qtiles;
     if (total > 0x7fffffffL || total_q > 0x7fffffffL) return FA_ERR_SHAPE;
 
-    constexpr int kRowsPerWg = 256 / (D / 8);
-    hipLaunchKernelGGL((fa_bwd_preprocess_kernel<Tag, D>), dim3((unsigned)((rows + kRowsPerWg - 1) / kRowsPerWg)),
-                       dim3(256), 0, stream,
-                       u16(o), u16(dout), dvec, rows);
+    // the dQ pass first: it also writes D, which the dK/dV pass reads
+    auto dqp = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)total_q), dim3(NW * 64), 0, stream, u16(q), u16(k), u16(v), u16(o),
+                           u16(dout), lse, dvec, static_cast<uint16_t*>(dq), N, n_qtiles, (int)total_q, H / H_kv, scale);
+    };
+    causal ? dqp(fa_bwd_dq_kernel<Tag, D, BC, NW, true>) : dqp(fa_bwd_dq_kernel<Tag, D, BC, NW, false>);
     if (hipGetLastError() != hipSuccess) return FA_ERR_LAUNCH;
 
     auto dkdv = [&](auto kernel) {
@@ -1012,16 +1004,6 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
     };
     if constexpr (D == 64) causal ? dkdv(fa_bwd_dkdv_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_kernel<Tag, D, false>);
     else causal ? dkdv(fa_bwd_dkdv_shared_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_shared_kernel<Tag, D, false>);
-    if (hipGetLastError() != hipSuccess) return FA_ERR_LAUNCH;
-
-    if (causal)
-        hipLaunchKernelGGL((fa_bwd_dq_kernel<Tag, D, BC, NW, true>), dim3((unsigned)total_q), dim3(NW * 64), 0, stream,
-                           u16(q), u16(k), u16(v), u16(dout), lse, dvec, static_cast<uint16_t*>(dq), N, n_qtiles,
-                           (int)total_q, H / H_kv, scale);
-    else
-        hipLaunchKernelGGL((fa_bwd_dq_kernel<Tag, D, BC, NW, false>), dim3((unsigned)total_q), dim3(NW * 64), 0, stream,
-                           u16(q), u16(k), u16(v), u16(dout), lse, dvec, static_cast<uint16_t*>(dq), N, n_qtiles,
-                           (int)total_q, H / H_kv, scale);
     return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
 }
 
