@@ -726,6 +726,236 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
 }
 
 // ---------------------------------------------------------------------------------------
+// dK/dV pass for launches that leave the chip idle (few key/value heads, short sequences), d = 64 and 128.
+//
+// A workgroup owns 32 keys instead of 128 and its four waves split the queries -- of all query heads that share the
+// key/value head -- each with accumulators for all columns; the four partial sums meet in the LDS at the end, in a
+// fixed order.  Four times as many workgroups, each with a quarter of the serial chain.  What it costs is operand
+// traffic: a Q / dO tile is staged for one wave instead of four and an operand read serves one MFMA, which a chip
+// that is mostly idle has to spare.  A wave stages its own tiles (32 queries of Q and dO, straight from global memory
+// into two LDS stages that no other wave touches), so the loop has no barrier.
+// The tiles are unpadded; 16-byte chunk c of row r sits at c ^ swizzle(r), applied through the global address a lane
+// fetches: row reads (16 rows at one chunk) and transposing reads (4 rows x 4 chunks) both hit every bank once.
+// bf16, B = 1, H = 32 on 4 K/V heads, N = 2048, d = 128, causal (64 workgroups of 128 keys, the longest 256 iterations):
+// whole backward 476 -> 223 us.
+template <typename Tag, int D, bool CAUSAL>
+__global__ void __launch_bounds__(256, D == 64 ? 2 : 1)
+fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                       const uint16_t* __restrict__ dout, const float* __restrict__ lse,
+                       const float* __restrict__ dvec, uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int N,
+                       int n_heads, int kv_group, float scale) {
+    [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
+    static_assert(D == 64 || D == 128, "two stages of a wave's Q and dO tiles must fit a quarter of the LDS");
+    constexpr int NW = 4, BQ = 32, BK = 32;
+    constexpr int ROWB = D * 2, KS = D / 16, DT = D / 32;
+    constexpr int TILE_B = BQ * ROWB;           // one tensor's tile
+    constexpr int STAGE_B = 2 * TILE_B;         // Q then dO
+    constexpr int RPI = 1024 / ROWB;            // rows per staging instruction (1 KiB)
+    constexpr int NI = BQ / RPI;                // staging instructions per tile
+    constexpr int CPR = D / 8;                  // 16-byte chunks per row
+    constexpr int KP = 4;                       // steps by which operand reads lead their MFMAs
+    constexpr int PSTR = D + 4;                 // row stride of the partial sums (floats)
+    constexpr int STAGING_B = NW * 2 * STAGE_B, PARTIAL_B = NW * 2 * BK * PSTR * 4;
+    using E = Elem<Tag>;
+    __shared__ __attribute__((aligned(1024))) char lds[STAGING_B > PARTIAL_B ? STAGING_B : PARTIAL_B];
+    __shared__ __attribute__((aligned(16))) float lds_ld[NW][2 * BQ];  // L (log2 units), then -D, of a wave's tile
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int col = lane & 31, half = lane >> 5;
+    // key blocks of equal index one after the other over the heads: under a causal mask the longest come first, and
+    // with a multiple of 8 heads all blocks of a head stay on one XCD
+    const int bh = blockIdx.x % n_heads;
+    const int key0 = (blockIdx.x / n_heads) * BK;
+    const size_t head_off = (size_t)bh * N * D;
+    const int my_key = key0 + col;
+    float sc = scale * kLog2e;
+    asm volatile("" : "+v"(sc));
+
+    i32x4 kreg[KS], vreg[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const i32x4 z = {0, 0, 0, 0};
+        const size_t off = head_off + (size_t)my_key * D + ks * 16 + half * 8;
+        kreg[ks] = my_key < N ? *reinterpret_cast<const i32x4*>(k + off) : z;
+        vreg[ks] = my_key < N ? *reinterpret_cast<const i32x4*>(v + off) : z;
+    }
+    f32x16 dkacc[DT], dvacc[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dkacc[dt][r] = dvacc[dt][r] = 0.f;
+
+    auto swizzle = [](int r) { return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3); };
+    // staging: instruction i of a tile brings rows i RPI .. ; this lane's row within them and its chunk position
+    int src[4];  // byte offset within a tile for instructions 0..3 (the pattern repeats every 4)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = i * RPI + lane / CPR;
+        src[i] = r * ROWB + ((lane % CPR) ^ swizzle(r)) * 16;
+    }
+    static_assert(NI % 4 == 0 && 4 * RPI % 16 == 0, "swizzle(r) has period 16, the rows of four instructions");
+    const uint32_t stage0 = lds_address(lds) + wave * 2 * STAGE_B;
+    const int n_t = (N + BQ - 1) / BQ, t0 = CAUSAL ? key0 / BQ : 0;
+
+    float ldpre = 0.f;
+    int ldrow = 0;
+    auto request = [&](int gi, int t, int st) __attribute__((always_inline)) {  // tile t of query head gi of the group
+        const size_t qhead = (size_t)bh * kv_group + gi;
+        const BufferWords q_rsrc = make_buffer_words(q + qhead * N * D, (uint32_t)N * D * 2);
+        const BufferWords do_rsrc = make_buffer_words(dout + qhead * N * D, (uint32_t)N * D * 2);
+        const uint32_t to = stage0 + st * STAGE_B;
+        const int from = t * TILE_B;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            global_to_lds_16B(q_rsrc, to + i * 1024, from + src[i & 3] + (i >> 2) * 4096);
+            global_to_lds_16B(do_rsrc, to + TILE_B + i * 1024, from + src[i & 3] + (i >> 2) * 4096);
+        }
+        ldrow = t * BQ + col;  // lanes 0..31 carry L, 32..63 carry D
+        ldpre = (half ? dvec : lse)[qhead * N + min(ldrow, N - 1)];
+    };
+
+    // operand addresses within a stage
+    int row_ofs[KS], tr_ofs[DT][2];
+    const int tr_row = (lane & 15) >> 2, quad = lane & 3, blk = (lane >> 4) & 1;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) row_ofs[ks] = col * ROWB + (((2 * ks + half) ^ swizzle(col)) << 4);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int hi = 0; hi < 2; ++hi) {  // rows 4 half + tr_row (+ 8); + 16 per slab leaves the swizzle as it is
+            const int r = 4 * half + tr_row + 8 * hi;
+            tr_ofs[dt][hi] = r * ROWB + (((4 * dt + 2 * blk + (quad >> 1)) ^ swizzle(r)) << 4) + 8 * (quad & 1);
+        }
+
+    auto tile = [&](uint32_t base, int q0) __attribute__((always_inline)) {
+        f32x4 l4[4];
+        f32x16 sacc, pacc;
+        const uint32_t ld = lds_address(lds_ld[wave]) + 16 * half;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {  // register r of 16 is query row 8 (r / 4) + 4 half + r % 4
+            l4[i] = lds_load_4f(ld + 32 * i);
+            const f32x4 t = lds_load_4f(ld + 128 + 32 * i);  // dP starts from -D
+#pragma unroll
+            for (int r = 0; r < 4; ++r) pacc[4 * i + r] = t[r];
+        }
+        auto row_read = [&](int u) { return lds_load_16B(base + (u < KS ? 0 : TILE_B) + row_ofs[u % KS]); };
+        auto tr_read = [&](int u) {  // u = (tensor: dO then Q, slab, dt)
+            const uint32_t a = base + (u < 2 * DT ? TILE_B : 0) + ((u / DT) % 2) * 16 * ROWB;
+            const i32x2 lo = lds_read_tr16(a + tr_ofs[u % DT][0]), hi = lds_read_tr16(a + tr_ofs[u % DT][1]);
+            return i32x4{lo[0], lo[1], hi[0], hi[1]};
+        };
+        i32x4 ring[KP], tr[KP], pa[2], dsa[2];
+#pragma unroll
+        for (int u = 0; u < KP; ++u) ring[u] = row_read(u);
+        int first_visible = my_key - q0 - 4 * half;  // of the lane's query rows
+        asm volatile("" : "+v"(first_visible));
+        auto probability = [&](int rr) __attribute__((always_inline)) {
+            float x = fast_exp2(__builtin_fmaf(sacc[rr], sc, -l4[rr >> 2][rr & 3]));
+            // (only the tile on the diagonal needs it, but a second body for the others would cost more: the
+            // accumulators then change halves of the register file in every tile)
+            if (CAUSAL && 8 * (rr >> 2) + (rr & 3) < first_visible) x = 0.f;
+            sacc[rr] = x;
+            if (rr & 1) pa[rr >> 3][(rr >> 1) & 3] = E::pack2(sacc[rr - 1], x);
+        };
+        // S, then dP beside P
+#pragma unroll
+        for (int u = 0; u < 2 * KS; ++u) {
+            const i32x4 a = ring[u % KP];
+            if (u + KP < 2 * KS) ring[u % KP] = row_read(u + KP);
+            else tr[u + KP - 2 * KS] = tr_read(u + KP - 2 * KS);
+            if (u == 0) MfmaVgprAcc<Tag>::first(sacc, a, kreg[u]);
+            else if (u < KS) MfmaVgprAcc<Tag>::run(sacc, a, kreg[u]);
+            else MfmaVgprAcc<Tag>::run(pacc, a, vreg[u - KS]);
+            if (u == KS) mfma_result_wait(sacc);
+            if (u >= KS) {
+#pragma unroll
+                for (int n = 0; n < 16 / KS; ++n) probability((u - KS) * (16 / KS) + n);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // dV beside dS, then dK
+        constexpr int GE = 16 / (2 * DT);  // gradients per MFMA of the dV group
+#pragma unroll
+        for (int u = 0; u < 4 * DT; ++u) {
+            const i32x4 b = tr[u % KP];
+            if (u + KP < 4 * DT) tr[u % KP] = tr_read(u + KP);
+            if (u < 2 * DT) {
+                dvacc[u % DT] = E::mma(pa[u / DT], b, dvacc[u % DT]);
+                if (u == 0) mfma_result_wait(pacc);
+#pragma unroll
+                for (int n = 0; n < GE; ++n) {
+                    const int rr = u * GE + n;
+                    pacc[rr] *= sacc[rr];
+                    if (rr & 1) dsa[rr >> 3][(rr >> 1) & 3] = E::pack2(pacc[rr - 1], pacc[rr]);
+                }
+            } else {
+                dkacc[u % DT] = E::mma(dsa[(u - 2 * DT) / DT], b, dkacc[u % DT]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    // ---- this wave's tiles: numbers wave, wave + NW, ... of the group's tiles in order
+    int gi = 0, t = t0 + wave, st = 0;
+    auto settle = [&]() {  // carry a tile number past the last tile over to the next query head
+        while (t >= n_t && gi < kv_group) {
+            t -= n_t - t0;
+            ++gi;
+        }
+    };
+    settle();
+    if (gi < kv_group) request(gi, t, 0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(kreg[ks]), "+a"(vreg[ks]));
+    while (gi < kv_group) {
+        const int q0 = t * BQ;
+        // rows past N get L = +inf so that P = exp2(0 - inf) = 0, and D = 0.  (Keys past N need nothing: what their
+        // lanes compute goes to rows of dK and dV that are not stored.)
+        const float x = ldrow < N ? (half ? -ldpre : ldpre * kLog2e) : (half ? 0.f : INFINITY);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this tile has landed
+        lds_ld[wave][lane] = x;
+        t += NW;
+        settle();
+        if (gi < kv_group) request(gi, t, st ^ 1);
+        const uint32_t base = stage0 + st * STAGE_B;
+        tile(base, q0);
+        st ^= 1;
+    }
+
+    // ---- sum of the four waves' parts, wave 0 first
+    __syncthreads();
+    float* part = reinterpret_cast<float*>(lds);  // [wave][dK, dV][key][PSTR]
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            float* p = part + (wave * 2 * BK + 8 * (r >> 2) + 4 * half + (r & 3)) * PSTR + dt * 32 + col;
+            p[0] = dkacc[dt][r];
+            p[BK * PSTR] = dvacc[dt][r];
+        }
+    __syncthreads();
+#pragma nounroll
+    for (int i = 0; i < 2 * BK * CPR / 256; ++i) {
+        const int c = tid + i * 256, row = c / CPR, cc = (c % CPR) * 8;  // row: keys of dK, then of dV
+        const int key = key0 + row % BK;
+        f32x4 s[2];
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(part + (w * 2 * BK + row) * PSTR + cc + 4 * h);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[h][e] = w == 0 ? x[e] : s[h][e] + x[e];
+            }
+        const float f = row < BK ? scale : 1.0f;
+        const i32x4 w = {E::pack2(s[0][0] * f, s[0][1] * f), E::pack2(s[0][2] * f, s[0][3] * f),
+                         E::pack2(s[1][0] * f, s[1][1] * f), E::pack2(s[1][2] * f, s[1][3] * f)};
+        if (key < N) *reinterpret_cast<i32x4*>((row < BK ? dk : dv) + head_off + (size_t)key * D + cc) = w;
+    }
+}
+
+// ---------------------------------------------------------------------------------------
 // dQ pass: the forward kernel's structure with dO alongside Q and K^T in place of V^T.
 template <typename Tag, int D, int BC, int NW, bool CAUSAL>
 __global__ void __launch_bounds__(NW * 64, NW == 8 ? 2 : 1)
@@ -974,6 +1204,14 @@ size_t bwd_workspace_bytes(int B, int H, int N, int d) {
     return (rows * sizeof(float) + 15) & ~(size_t)15;  // D = rowsum(dO o O)
 }
 
+// Up to how many 128-key workgroups the dK/dV pass uses fa_bwd_dkdv_few_kernel instead: on fewer workgroups than CUs
+// the 32-key form's four-fold parallelism wins until its operand traffic costs as much.  Whole backward, B = 1, bf16,
+// us, 128-key / 32-key form:
+//   d = 128  no mask: 128 workgroups 74 / 69 (H = 16, N = 1024), 160 88 / 96 (H = 16, N = 1280)
+//            causal:  160 88 / 81, 192 75 / 73 (H = 24, N = 1024) and 465 / 401 (H = 3, N = 8192), 256 76 / 82 (H = 32)
+//   d = 64   no mask: 160 55 / 53, 192 46.2 / 45.0, 256 46.5 / 51;  causal: 256 47.5 / 44.6 (N = 1024), 83 / 73 (N = 2048)
+constexpr long few_key_blocks(int d, int causal) { return d == 64 ? (causal ? 256 : 192) : (causal ? 192 : 128); }
+
 template <typename Tag, int D>
 static int launch_bwd_t(const void* q, const void* k, const void* v, const void* o, const float* lse,
                         const void* dout, void* dq, void* dk, void* dv, void* workspace, int B, int H, int H_kv,
@@ -1002,6 +1240,18 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
                            dvec, static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv), N, n_kblocks, (int)total,
                            H / H_kv, scale);
     };
+    if constexpr (D <= 128) {
+        const long few = (long)B * H_kv * ((N + 31) / 32);
+        if (total <= few_key_blocks(D, causal) && few <= 0x7fffffffL) {
+            auto run = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3((unsigned)few), dim3(256), 0, stream, u16(q), u16(k), u16(v), u16(dout),
+                                   lse, dvec, static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv), N, B * H_kv,
+                                   H / H_kv, scale);
+            };
+            causal ? run(fa_bwd_dkdv_few_kernel<Tag, D, true>) : run(fa_bwd_dkdv_few_kernel<Tag, D, false>);
+            return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
+        }
+    }
     if constexpr (D == 64) causal ? dkdv(fa_bwd_dkdv_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_kernel<Tag, D, false>);
     else causal ? dkdv(fa_bwd_dkdv_shared_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_shared_kernel<Tag, D, false>);
     return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;

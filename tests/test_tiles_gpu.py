@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import oracle
-from helpers import f64, max_abs, rel_rmse
+from helpers import f64, max_abs, rmse
 from paper_2407_08608_amd import binding, inputs
 
 pytestmark = pytest.mark.gpu
@@ -47,7 +47,10 @@ def _check_backward(seed, B, H, H_kv, N, d, causal, dtype):
     for name, t in zip(("dq", "dk", "dv"), got):
         g, r = f64(t), ref[name]
         assert np.isfinite(g).all(), name
-        assert rel_rmse(g, r) <= REL_RMSE and max_abs(g, r) <= REL_MAXABS * np.abs(r).max(), (name, rel_rmse(g, r))
+        # the floors: with one visible key dS = P (dP - D) is exactly 0 and what is left are the roundings of two fp32
+        # sums of d products (2^-24 * sqrt(d) * |dO| |V| ~ 2e-6), times |K| * scale
+        ref_rms = float(np.sqrt(np.mean(r * r)))
+        assert rmse(g, r) <= REL_RMSE * ref_rms + 1e-5 and max_abs(g, r) <= REL_MAXABS * np.abs(r).max() + 1e-4, name
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
@@ -58,3 +61,21 @@ def test_backward_shared_score_tiles(d, N, causal, dtype):
     # key blocks of 128 (64 at d = 256) in 32-key tiles, query tiles of 64 in two sub-tiles whose P and dS the waves
     # exchange; an odd and an even number of query tiles, and two query heads per K/V head walking the ring twice
     _check_backward(500 + N, 1, 4, 2, N, d, causal, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("H,H_kv,N", [(1, 1, 1), (2, 2, 31), (2, 1, 33), (4, 1, 64), (3, 3, 97), (8, 2, 129), (1, 1, 130),
+                                      (4, 2, 333), (2, 2, 1025)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_backward_query_split_for_few_key_blocks(d, H, H_kv, N, causal, dtype):
+    # 32-key workgroups whose four waves take every fourth 32-query tile of the group's heads: fewer tiles than waves,
+    # ragged last tiles of queries and of keys, tile numbers that carry over to the next query head
+    _check_backward(700 + N + d, 1, H, H_kv, N, d, causal, dtype)
+
+
+@pytest.mark.parametrize("d,causal,most", [(64, False, 192), (64, True, 256), (128, False, 128), (128, True, 192)])
+def test_backward_on_both_sides_of_the_key_split_rule(d, causal, most):
+    # the most workgroups of 128 keys that the 32-key form takes over, and one more
+    for H in (most, most + 1):
+        _check_backward(800 + H, 1, H, H, 70, d, causal, "bf16")
