@@ -37,6 +37,38 @@ namespace fa {
 // gives 63 / 208.
 constexpr int bwd_row_stride(int d) { return d >= 128 ? d + 24 : d + 40; }
 
+// acc + the dot product of 8 packed 16-bit elements, in fp32
+template <typename Tag>
+static __device__ __forceinline__ float dot8(const i32x4& a, const i32x4& b, float acc) {
+    using E = Elem<Tag>;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const uint32_t ua = (uint32_t)a[t], ub = (uint32_t)b[t];
+        acc = __builtin_fmaf(E::to_float((uint16_t)(ua & 0xFFFF)), E::to_float((uint16_t)(ub & 0xFFFF)), acc);
+        acc = __builtin_fmaf(E::to_float((uint16_t)(ua >> 16)), E::to_float((uint16_t)(ub >> 16)), acc);
+    }
+    return acc;
+}
+
+// 8 consecutive outputs: the sum over NP partial results `stride` floats apart, first to last, times `factor`
+template <typename Tag, int NP>
+static __device__ __forceinline__ i32x4 sum_parts(const float* p, int stride, float factor) {
+    i32x4 out;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        f32x4 s = *reinterpret_cast<const f32x4*>(p + 4 * h);
+#pragma unroll
+        for (int w = 1; w < NP; ++w) {
+            const f32x4 x = *reinterpret_cast<const f32x4*>(p + w * stride + 4 * h);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] += x[e];
+        }
+        out[2 * h] = Elem<Tag>::pack2(s[0] * factor, s[1] * factor);
+        out[2 * h + 1] = Elem<Tag>::pack2(s[2] * factor, s[3] * factor);
+    }
+    return out;
+}
+
 // ---------------------------------------------------------------------------------------
 template <typename Tag, int D, bool CAUSAL>
 __global__ void __launch_bounds__(256, 2)
@@ -726,16 +758,72 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
 }
 
 // ---------------------------------------------------------------------------------------
+// A wave's private tiles of 32 rows of two tensors (first, second), staged straight from global memory into two LDS
+// stages that no other wave touches.  The tiles are unpadded; 16-byte chunk c of row r sits at c ^ swizzle(r),
+// applied through the global address a lane fetches: row reads (16 rows at one chunk) and transposing reads (4 rows x
+// 4 chunks) both hit every bank once.
+template <int D>
+struct WaveTiles {
+    static_assert(D == 64 || D == 128, "two stages of a wave's tiles must fit a quarter of the LDS");
+    static constexpr int ROWS = 32, ROWB = D * 2, KS = D / 16, DT = D / 32;
+    static constexpr int CPR = D / 8;             // 16-byte chunks per row
+    static constexpr int TILE_B = ROWS * ROWB;    // one tensor's tile
+    static constexpr int STAGE_B = 2 * TILE_B;    // first, second
+    static constexpr int RPI = 1024 / ROWB;       // rows per staging instruction (1 KiB)
+    static constexpr int NI = ROWS / RPI;         // staging instructions per tile
+    static_assert(NI % 4 == 0 && 4 * RPI % 16 == 0, "swizzle(r) has period 16, the rows of four instructions");
+    uint32_t stage0;
+    int src[4];             // byte offset within a tile for instructions 0..3 (the pattern repeats every 4)
+    int row_ofs[KS];        // row operands: lane (col, half) takes 8 elements from 16 ks + 8 half of row col
+    int tr_ofs[DT][2];      // transposed operands of rows 0..15; + 16 rows leaves the swizzle as it is
+
+    static __device__ __forceinline__ int swizzle(int r) {
+        return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+    }
+    __device__ __forceinline__ WaveTiles(uint32_t base, int lane) : stage0(base) {
+        const int col = lane & 31, half = lane >> 5, tr_row = (lane & 15) >> 2, quad = lane & 3, blk = (lane >> 4) & 1;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = i * RPI + lane / CPR;
+            src[i] = r * ROWB + ((lane % CPR) ^ swizzle(r)) * 16;
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) row_ofs[ks] = col * ROWB + (((2 * ks + half) ^ swizzle(col)) << 4);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int hi = 0; hi < 2; ++hi) {
+                const int r = 4 * half + tr_row + 8 * hi;
+                tr_ofs[dt][hi] = r * ROWB + (((4 * dt + 2 * blk + (quad >> 1)) ^ swizzle(r)) << 4) + 8 * (quad & 1);
+            }
+    }
+    // Instruction n of 2 NI that bring tile t of both heads into stage st (rows past a resource's end arrive as zeros).
+    // One per MFMA step: in a burst, the wave sits about 100 cycles in the issue of each, 64 bytes per clock being
+    // what a CU's vector memory path moves.
+    static constexpr int NREQ = 2 * NI;
+    static_assert(NREQ == 2 * KS, "one per MFMA step of the two score products");
+    __device__ __forceinline__ void request(const BufferWords& first, const BufferWords& second, int t, int st, int n) const {
+        const int i = n >> 1;
+        global_to_lds_16B(n & 1 ? second : first, stage0 + st * STAGE_B + (n & 1) * TILE_B + i * 1024,
+                          t * TILE_B + src[i & 3] + (i >> 2) * 4096);
+    }
+    // `base`: a stage's address, + TILE_B for the second tensor
+    __device__ __forceinline__ i32x4 row_read(uint32_t base, int ks) const { return lds_load_16B(base + row_ofs[ks]); }
+    __device__ __forceinline__ i32x4 tr_read(uint32_t base, int slab, int dt) const {
+        const uint32_t a = base + slab * 16 * ROWB;
+        const i32x2 lo = lds_read_tr16(a + tr_ofs[dt][0]), hi = lds_read_tr16(a + tr_ofs[dt][1]);
+        return i32x4{lo[0], lo[1], hi[0], hi[1]};
+    }
+};
+
+// ---------------------------------------------------------------------------------------
 // dK/dV pass for launches that leave the chip idle (few key/value heads, short sequences), d = 64 and 128.
 //
 // A workgroup owns 32 keys instead of 128 and its four waves split the queries -- of all query heads that share the
 // key/value head -- each with accumulators for all columns; the four partial sums meet in the LDS at the end, in a
 // fixed order.  Four times as many workgroups, each with a quarter of the serial chain.  What it costs is operand
 // traffic: a Q / dO tile is staged for one wave instead of four and an operand read serves one MFMA, which a chip
-// that is mostly idle has to spare.  A wave stages its own tiles (32 queries of Q and dO, straight from global memory
-// into two LDS stages that no other wave touches), so the loop has no barrier.
-// The tiles are unpadded; 16-byte chunk c of row r sits at c ^ swizzle(r), applied through the global address a lane
-// fetches: row reads (16 rows at one chunk) and transposing reads (4 rows x 4 chunks) both hit every bank once.
+// that is mostly idle has to spare.  A wave stages its own tiles (32 queries of Q and dO), so the loop has no barrier.
 // bf16, B = 1, H = 32 on 4 K/V heads, N = 2048, d = 128, causal (64 workgroups of 128 keys, the longest 256 iterations):
 // whole backward 476 -> 223 us.
 template <typename Tag, int D, bool CAUSAL>
@@ -745,17 +833,12 @@ fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
                        const float* __restrict__ dvec, uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int N,
                        int n_heads, int kv_group, float scale) {
     [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
-    static_assert(D == 64 || D == 128, "two stages of a wave's Q and dO tiles must fit a quarter of the LDS");
-    constexpr int NW = 4, BQ = 32, BK = 32;
-    constexpr int ROWB = D * 2, KS = D / 16, DT = D / 32;
-    constexpr int TILE_B = BQ * ROWB;           // one tensor's tile
-    constexpr int STAGE_B = 2 * TILE_B;         // Q then dO
-    constexpr int RPI = 1024 / ROWB;            // rows per staging instruction (1 KiB)
-    constexpr int NI = BQ / RPI;                // staging instructions per tile
-    constexpr int CPR = D / 8;                  // 16-byte chunks per row
+    using Tiles = WaveTiles<D>;
+    constexpr int NW = 4, BQ = Tiles::ROWS, BK = 32;
+    constexpr int KS = D / 16, DT = D / 32, CPR = D / 8;
     constexpr int KP = 4;                       // steps by which operand reads lead their MFMAs
     constexpr int PSTR = D + 4;                 // row stride of the partial sums (floats)
-    constexpr int STAGING_B = NW * 2 * STAGE_B, PARTIAL_B = NW * 2 * BK * PSTR * 4;
+    constexpr int STAGING_B = NW * 2 * Tiles::STAGE_B, PARTIAL_B = NW * 2 * BK * PSTR * 4;
     using E = Elem<Tag>;
     __shared__ __attribute__((aligned(1024))) char lds[STAGING_B > PARTIAL_B ? STAGING_B : PARTIAL_B];
     __shared__ __attribute__((aligned(16))) float lds_ld[NW][2 * BQ];  // L (log2 units), then -D, of a wave's tile
@@ -786,49 +869,23 @@ fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
 #pragma unroll
         for (int r = 0; r < 16; ++r) dkacc[dt][r] = dvacc[dt][r] = 0.f;
 
-    auto swizzle = [](int r) { return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3); };
-    // staging: instruction i of a tile brings rows i RPI .. ; this lane's row within them and its chunk position
-    int src[4];  // byte offset within a tile for instructions 0..3 (the pattern repeats every 4)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = i * RPI + lane / CPR;
-        src[i] = r * ROWB + ((lane % CPR) ^ swizzle(r)) * 16;
-    }
-    static_assert(NI % 4 == 0 && 4 * RPI % 16 == 0, "swizzle(r) has period 16, the rows of four instructions");
-    const uint32_t stage0 = lds_address(lds) + wave * 2 * STAGE_B;
+    const Tiles tiles(lds_address(lds) + wave * 2 * Tiles::STAGE_B, lane);  // Q, dO
     const int n_t = (N + BQ - 1) / BQ, t0 = CAUSAL ? key0 / BQ : 0;
 
     float ldpre = 0.f;
     int ldrow = 0;
-    auto request = [&](int gi, int t, int st) __attribute__((always_inline)) {  // tile t of query head gi of the group
-        const size_t qhead = (size_t)bh * kv_group + gi;
-        const BufferWords q_rsrc = make_buffer_words(q + qhead * N * D, (uint32_t)N * D * 2);
-        const BufferWords do_rsrc = make_buffer_words(dout + qhead * N * D, (uint32_t)N * D * 2);
-        const uint32_t to = stage0 + st * STAGE_B;
-        const int from = t * TILE_B;
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            global_to_lds_16B(q_rsrc, to + i * 1024, from + src[i & 3] + (i >> 2) * 4096);
-            global_to_lds_16B(do_rsrc, to + TILE_B + i * 1024, from + src[i & 3] + (i >> 2) * 4096);
-        }
+    BufferWords q_rsrc, do_rsrc;
+    auto aim = [&](int gi, int t) __attribute__((always_inline)) {  // the next requests: tile t of query head gi of the group
+        const size_t qhead = (size_t)bh * kv_group + min(gi, kv_group - 1);
+        const uint32_t bytes = gi < kv_group ? (uint32_t)N * D * 2 : 0;  // past the last tile: zeros that nothing reads
+        q_rsrc = make_buffer_words(q + qhead * N * D, bytes);
+        do_rsrc = make_buffer_words(dout + qhead * N * D, bytes);
         ldrow = t * BQ + col;  // lanes 0..31 carry L, 32..63 carry D
         ldpre = (half ? dvec : lse)[qhead * N + min(ldrow, N - 1)];
     };
 
-    // operand addresses within a stage
-    int row_ofs[KS], tr_ofs[DT][2];
-    const int tr_row = (lane & 15) >> 2, quad = lane & 3, blk = (lane >> 4) & 1;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) row_ofs[ks] = col * ROWB + (((2 * ks + half) ^ swizzle(col)) << 4);
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int hi = 0; hi < 2; ++hi) {  // rows 4 half + tr_row (+ 8); + 16 per slab leaves the swizzle as it is
-            const int r = 4 * half + tr_row + 8 * hi;
-            tr_ofs[dt][hi] = r * ROWB + (((4 * dt + 2 * blk + (quad >> 1)) ^ swizzle(r)) << 4) + 8 * (quad & 1);
-        }
-
-    auto tile = [&](uint32_t base, int q0) __attribute__((always_inline)) {
+    // one tile at `base`, while tile t_next of the heads aimed at is requested into stage st_next
+    auto tile = [&](uint32_t base, int q0, int t_next, int st_next) __attribute__((always_inline)) {
         f32x4 l4[4];
         f32x16 sacc, pacc;
         const uint32_t ld = lds_address(lds_ld[wave]) + 16 * half;
@@ -839,11 +896,9 @@ fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
 #pragma unroll
             for (int r = 0; r < 4; ++r) pacc[4 * i + r] = t[r];
         }
-        auto row_read = [&](int u) { return lds_load_16B(base + (u < KS ? 0 : TILE_B) + row_ofs[u % KS]); };
+        auto row_read = [&](int u) { return tiles.row_read(base + (u < KS ? 0 : Tiles::TILE_B), u % KS); };
         auto tr_read = [&](int u) {  // u = (tensor: dO then Q, slab, dt)
-            const uint32_t a = base + (u < 2 * DT ? TILE_B : 0) + ((u / DT) % 2) * 16 * ROWB;
-            const i32x2 lo = lds_read_tr16(a + tr_ofs[u % DT][0]), hi = lds_read_tr16(a + tr_ofs[u % DT][1]);
-            return i32x4{lo[0], lo[1], hi[0], hi[1]};
+            return tiles.tr_read(base + (u < 2 * DT ? Tiles::TILE_B : 0), (u / DT) % 2, u % DT);
         };
         i32x4 ring[KP], tr[KP], pa[2], dsa[2];
 #pragma unroll
@@ -864,6 +919,7 @@ fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
             const i32x4 a = ring[u % KP];
             if (u + KP < 2 * KS) ring[u % KP] = row_read(u + KP);
             else tr[u + KP - 2 * KS] = tr_read(u + KP - 2 * KS);
+            tiles.request(q_rsrc, do_rsrc, t_next, st_next, u);
             if (u == 0) MfmaVgprAcc<Tag>::first(sacc, a, kreg[u]);
             else if (u < KS) MfmaVgprAcc<Tag>::run(sacc, a, kreg[u]);
             else MfmaVgprAcc<Tag>::run(pacc, a, vreg[u - KS]);
@@ -905,7 +961,9 @@ fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
         }
     };
     settle();
-    if (gi < kv_group) request(gi, t, 0);
+    aim(gi, t);
+#pragma unroll
+    for (int n = 0; n < Tiles::NREQ; ++n) tiles.request(q_rsrc, do_rsrc, t, 0, n);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(kreg[ks]), "+a"(vreg[ks]));
     while (gi < kv_group) {
@@ -917,11 +975,11 @@ fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
         lds_ld[wave][lane] = x;
         t += NW;
         settle();
-        if (gi < kv_group) request(gi, t, st ^ 1);
-        const uint32_t base = stage0 + st * STAGE_B;
-        tile(base, q0);
+        aim(gi, t);
+        tile(tiles.stage0 + st * Tiles::STAGE_B, q0, t, st ^ 1);
         st ^= 1;
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the zeros of the last request: the LDS is about to be reused
 
     // ---- sum of the four waves' parts, wave 0 first
     __syncthreads();
@@ -939,18 +997,7 @@ fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
     for (int i = 0; i < 2 * BK * CPR / 256; ++i) {
         const int c = tid + i * 256, row = c / CPR, cc = (c % CPR) * 8;  // row: keys of dK, then of dV
         const int key = key0 + row % BK;
-        f32x4 s[2];
-#pragma unroll
-        for (int w = 0; w < NW; ++w)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const f32x4 x = *reinterpret_cast<const f32x4*>(part + (w * 2 * BK + row) * PSTR + cc + 4 * h);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) s[h][e] = w == 0 ? x[e] : s[h][e] + x[e];
-            }
-        const float f = row < BK ? scale : 1.0f;
-        const i32x4 w = {E::pack2(s[0][0] * f, s[0][1] * f), E::pack2(s[0][2] * f, s[0][3] * f),
-                         E::pack2(s[1][0] * f, s[1][1] * f), E::pack2(s[1][2] * f, s[1][3] * f)};
+        const i32x4 w = sum_parts<Tag, NW>(part + row * PSTR + cc, 2 * BK * PSTR, row < BK ? scale : 1.0f);
         if (key < N) *reinterpret_cast<i32x4*>((row < BK ? dk : dv) + head_off + (size_t)key * D + cc) = w;
     }
 }
@@ -958,7 +1005,7 @@ fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
 // ---------------------------------------------------------------------------------------
 // dQ pass: the forward kernel's structure with dO alongside Q and K^T in place of V^T.
 template <typename Tag, int D, int BC, int NW, bool CAUSAL>
-__global__ void __launch_bounds__(NW * 64, NW == 8 ? 2 : 1)
+__global__ void __launch_bounds__(NW * 64, D == 256 ? 1 : 2)
 fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                  const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
                  float* __restrict__ dvec, uint16_t* __restrict__ dq, int N, int n_qtiles, int total_wg, int kv_group, float scale) {
@@ -1009,13 +1056,7 @@ fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     float dq_row = 0.f;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-        const i32x4 x = *reinterpret_cast<const i32x4*>(o + head_off + (size_t)qrow * D + ks * 16 + half * 8);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const uint32_t ua = (uint32_t)x[t], ub = (uint32_t)doreg[ks][t];
-            dq_row = __builtin_fmaf(E::to_float((uint16_t)(ua & 0xFFFF)), E::to_float((uint16_t)(ub & 0xFFFF)), dq_row);
-            dq_row = __builtin_fmaf(E::to_float((uint16_t)(ua >> 16)), E::to_float((uint16_t)(ub >> 16)), dq_row);
-        }
+        dq_row = dot8<Tag>(*reinterpret_cast<const i32x4*>(o + head_off + (size_t)qrow * D + ks * 16 + half * 8), doreg[ks], dq_row);
     }
     dq_row = sum_both_halves(dq_row);
     if (half == 0 && qi < N) dvec[(size_t)bh * N + qi] = dq_row;
@@ -1060,7 +1101,7 @@ fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     // registers instead (Q_i, dO_i, touched by MFMA alone, go to the accumulation half), and the next
     // block's K and V travel in 16-byte chunks spread over the MFMA steps: as one burst, the 16 loads
     // of a wave keep it in its own issue for over a thousand cycles (see fa_fwd_d256_kernel).
-    constexpr bool ONE_WAVE = NW == 4;
+    constexpr bool ONE_WAVE = D == 256;
     constexpr int NSTEP = KS * KT;  // MFMA steps of either GEMM group; a staging chunk every CH_EVERY of them
     constexpr int CH_EVERY = ONE_WAVE ? NSTEP / CPT : 1;
     static_assert(!ONE_WAVE || (CPT * CH_EVERY == NSTEP && SL * DT == NSTEP), "chunks must spread evenly");
@@ -1191,10 +1232,149 @@ fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 
     // dQ_i = scale * acc.  Every LDS read of the loop was followed by a barrier, so the K and V
     // buffers are free: each wave takes 4 KiB of them to transpose its tile into whole 128-byte lines.
-    static_assert(NW <= 8 && sizeof(lds_k) >= 4 * 4096 && sizeof(lds_v) >= 4 * 4096, "patches must fit");
-    char* patch = (wave < 4 ? reinterpret_cast<char*>(&lds_k[0][0]) : reinterpret_cast<char*>(&lds_v[0][0])) +
-                  (wave & 3) * 4096;
+    static_assert(sizeof(lds_k) >= NW / 2 * 4096 && sizeof(lds_v) >= NW / 2 * 4096, "patches must fit");
+    char* patch = (wave < NW / 2 ? reinterpret_cast<char*>(&lds_k[0][0]) : reinterpret_cast<char*>(&lds_v[0][0])) +
+                  (wave % (NW / 2)) * 4096;
     store_rows_via_lds<Tag, DT>(acc, scale, patch, make_buffer(dq + head_off, (uint32_t)N * D * 2), wave_q0, lane);
+}
+
+// ---------------------------------------------------------------------------------------
+// dQ pass for launches that leave the chip idle, d = 64 and 128: the same division the other way round.  A workgroup
+// owns 32 queries and its four waves split the keys (tiles of 32, staged by the wave that works them), each with a dQ
+// accumulator; the four partial sums meet in the LDS at the end, in a fixed order.
+// bf16, B = 1, H = 4, N = 1024: whole backward 54 -> 27 us at d = 128, 33 -> 18 us at d = 64.
+template <typename Tag, int D, bool CAUSAL>
+__global__ void __launch_bounds__(256, D == 64 ? 2 : 1)
+fa_bwd_dq_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                     const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
+                     float* __restrict__ dvec, uint16_t* __restrict__ dq, int N, int n_heads, int kv_group, float scale) {
+    [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
+    using Tiles = WaveTiles<D>;
+    constexpr int NW = 4, BQ = 32, BK = Tiles::ROWS;
+    constexpr int KS = D / 16, DT = D / 32, CPR = D / 8;
+    constexpr int KP = 4;        // steps by which operand reads lead their MFMAs
+    constexpr int PSTR = D + 4;  // row stride of the partial sums (floats)
+    constexpr int STAGING_B = NW * 2 * Tiles::STAGE_B, PARTIAL_B = NW * BQ * PSTR * 4;
+    using E = Elem<Tag>;
+    __shared__ __attribute__((aligned(1024))) char lds[STAGING_B > PARTIAL_B ? STAGING_B : PARTIAL_B];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int col = lane & 31, half = lane >> 5;
+    // tiles of equal index one after the other over the heads (all of a head on one XCD when their number is a
+    // multiple of 8); causal: the longest rows first
+    const int bh = blockIdx.x % n_heads;
+    const int n_t = (N + BK - 1) / BK;
+    const int qt = CAUSAL ? n_t - 1 - blockIdx.x / n_heads : blockIdx.x / n_heads;
+    const int q0 = qt * BQ;
+    const int row = min(q0 + col, N - 1);  // rows past N compute a copy of row N-1, never stored
+    const int limit = CAUSAL ? row : N - 1;  // last visible key
+    const size_t head_off = (size_t)bh * N * D;
+    const size_t kv_off = (size_t)(bh / kv_group) * N * D;
+    float sc = scale * kLog2e;
+    asm volatile("" : "+v"(sc));
+    const BufferWords k_rsrc = make_buffer_words(k + kv_off, (uint32_t)N * D * 2);
+    const BufferWords v_rsrc = make_buffer_words(v + kv_off, (uint32_t)N * D * 2);
+    const Tiles tiles(lds_address(lds) + wave * 2 * Tiles::STAGE_B, lane);  // K, V
+
+    const int n_tiles = CAUSAL ? qt + 1 : n_t;
+#pragma unroll
+    for (int n = 0; n < Tiles::NREQ; ++n) tiles.request(k_rsrc, v_rsrc, wave, 0, n);
+
+    i32x4 qreg[KS], doreg[KS];
+    float d_row = 0.f;  // D = rowsum(dO o O)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const size_t off = head_off + (size_t)row * D + ks * 16 + half * 8;
+        qreg[ks] = *reinterpret_cast<const i32x4*>(q + off);
+        doreg[ks] = *reinterpret_cast<const i32x4*>(dout + off);
+        d_row = dot8<Tag>(*reinterpret_cast<const i32x4*>(o + off), doreg[ks], d_row);
+    }
+    d_row = sum_both_halves(d_row);
+    if (wave == 0 && half == 0 && q0 + col < N) dvec[(size_t)bh * N + q0 + col] = d_row;
+    const float l2 = lse[(size_t)bh * N + row] * kLog2e;
+    f32x16 acc[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[dt][r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(qreg[ks]), "+a"(doreg[ks]));
+
+    int st = 0;
+    for (int t = wave; t < n_tiles; t += NW, st ^= 1) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this tile has landed
+        const uint32_t base = tiles.stage0 + st * Tiles::STAGE_B;
+        auto row_read = [&](int u) { return tiles.row_read(base + (u < KS ? 0 : Tiles::TILE_B), u % KS); };
+        f32x16 sacc, pacc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) pacc[r] = -d_row;  // dP - D comes out of the MFMAs
+        i32x4 ring[KP], tr[KP], dsb[2];
+#pragma unroll
+        for (int u = 0; u < KP; ++u) ring[u] = row_read(u);
+        __builtin_amdgcn_sched_barrier(0);
+        int bound = limit - t * BK - 4 * half;  // key 8 (r / 4) + r % 4 of the lane's half is visible up to here
+        asm volatile("" : "+v"(bound));
+        // S^T, then dP^T beside P
+#pragma unroll
+        for (int u = 0; u < 2 * KS; ++u) {
+            const i32x4 a = ring[u % KP];
+            if (u + KP < 2 * KS) ring[u % KP] = row_read(u + KP);
+            else tr[u + KP - 2 * KS] = tiles.tr_read(base, (u + KP - 2 * KS) / DT, (u + KP - 2 * KS) % DT);
+            // past this workgroup's last tile these bring rows (or zeros) that nothing reads
+            tiles.request(k_rsrc, v_rsrc, t + NW, st ^ 1, u);
+            if (u == 0) MfmaVgprAcc<Tag>::first(sacc, a, qreg[u]);
+            else if (u < KS) MfmaVgprAcc<Tag>::run(sacc, a, qreg[u]);
+            else MfmaVgprAcc<Tag>::run(pacc, a, doreg[u - KS]);
+            if (u == KS) mfma_result_wait(sacc);
+            if (u >= KS) {
+#pragma unroll
+                for (int n = 0; n < 16 / KS; ++n) {
+                    const int r = (u - KS) * (16 / KS) + n;
+                    sacc[r] = fast_exp2(__builtin_fmaf(sacc[r], sc, -l2));
+                    // keys past N (K = 0, but their P may be anything) and keys after the query
+                    if (8 * (r >> 2) + (r & 3) > bound) sacc[r] = 0.f;
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        mfma_result_wait(pacc);
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int r = 8 * s2 + 2 * e;
+                dsb[s2][e] = E::pack2(sacc[r] * pacc[r], sacc[r + 1] * pacc[r + 1]);
+            }
+        // dQ^T += K^T dS^T
+#pragma unroll
+        for (int u = 0; u < 2 * DT; ++u) {
+            const i32x4 a = tr[u % KP];
+            if (u + KP < 2 * DT) tr[u % KP] = tiles.tr_read(base, (u + KP) / DT, (u + KP) % DT);
+            acc[u % DT] = E::mma(a, dsb[u / DT], acc[u % DT]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last request: the LDS is about to be reused
+
+    // ---- sum of the four waves' parts, wave 0 first
+    __syncthreads();
+    float* part = reinterpret_cast<float*>(lds);  // [wave][query][PSTR]
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 w = {acc[dt][4 * g], acc[dt][4 * g + 1], acc[dt][4 * g + 2], acc[dt][4 * g + 3]};
+            *reinterpret_cast<f32x4*>(part + (wave * BQ + col) * PSTR + dt * 32 + 8 * g + 4 * half) = w;
+        }
+    __syncthreads();
+#pragma nounroll
+    for (int c = tid; c < BQ * CPR; c += 256) {
+        const int r = c / CPR, cc = (c % CPR) * 8;
+        const i32x4 w = sum_parts<Tag, NW>(part + r * PSTR + cc, BQ * PSTR, scale);
+        if (q0 + r < N) *reinterpret_cast<i32x4*>(dq + head_off + (size_t)(q0 + r) * D + cc) = w;
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1211,6 +1391,13 @@ size_t bwd_workspace_bytes(int B, int H, int N, int d) {
 //            causal:  160 88 / 81, 192 75 / 73 (H = 24, N = 1024) and 465 / 401 (H = 3, N = 8192), 256 76 / 82 (H = 32)
 //   d = 64   no mask: 160 55 / 53, 192 46.2 / 45.0, 256 46.5 / 51;  causal: 256 47.5 / 44.6 (N = 1024), 83 / 73 (N = 2048)
 constexpr long few_key_blocks(int d, int causal) { return d == 64 ? (causal ? 256 : 192) : (causal ? 192 : 128); }
+
+// Up to how many 256-query workgroups the dQ pass uses fa_bwd_dq_few_kernel instead.  Whole backward, B = 1, bf16, us,
+// 256-query / 32-query form:
+//   d = 128  no mask: 64 workgroups 69 / 55 (H = 16, N = 1024), 96 466 / 404 (H = 3, N = 8192), 128 81 / 90 (H = 32)
+//            causal:  64 61 / 40, 128 75.7 / 73.5 (N = 1024) and 131 / 114 (N = 2048), 192 152 / 161 (H = 24, N = 2048)
+//   d = 64   no mask: 64 39 / 28, 96 279 / 238, 128 46.5 / 49.7;  causal: 192 101 / 95, 256 141 / 146 (H = 32 on 4)
+constexpr long few_query_tiles(int d, int causal) { return causal ? (d == 64 ? 192 : 128) : 96; }
 
 template <typename Tag, int D>
 static int launch_bwd_t(const void* q, const void* k, const void* v, const void* o, const float* lse,
@@ -1232,7 +1419,19 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
         hipLaunchKernelGGL(kernel, dim3((unsigned)total_q), dim3(NW * 64), 0, stream, u16(q), u16(k), u16(v), u16(o),
                            u16(dout), lse, dvec, static_cast<uint16_t*>(dq), N, n_qtiles, (int)total_q, H / H_kv, scale);
     };
-    causal ? dqp(fa_bwd_dq_kernel<Tag, D, BC, NW, true>) : dqp(fa_bwd_dq_kernel<Tag, D, BC, NW, false>);
+    bool dq_done = false;
+    if constexpr (D <= 128) {
+        const long few = (long)B * H * ((N + 31) / 32);
+        if (total_q <= few_query_tiles(D, causal) && few <= 0x7fffffffL) {
+            auto run = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3((unsigned)few), dim3(256), 0, stream, u16(q), u16(k), u16(v), u16(o),
+                                   u16(dout), lse, dvec, static_cast<uint16_t*>(dq), N, B * H, H / H_kv, scale);
+            };
+            causal ? run(fa_bwd_dq_few_kernel<Tag, D, true>) : run(fa_bwd_dq_few_kernel<Tag, D, false>);
+            dq_done = true;
+        }
+    }
+    if (!dq_done) causal ? dqp(fa_bwd_dq_kernel<Tag, D, BC, NW, true>) : dqp(fa_bwd_dq_kernel<Tag, D, BC, NW, false>);
     if (hipGetLastError() != hipSuccess) return FA_ERR_LAUNCH;
 
     auto dkdv = [&](auto kernel) {

@@ -79,3 +79,26 @@ def test_backward_on_both_sides_of_the_key_split_rule(d, causal, most):
     # the most workgroups of 128 keys that the 32-key form takes over, and one more
     for H in (most, most + 1):
         _check_backward(800 + H, 1, H, H, 70, d, causal, "bf16")
+
+
+@pytest.mark.parametrize("d,causal,most", [(64, False, 96), (64, True, 192), (128, False, 96), (128, True, 128)])
+def test_backward_on_both_sides_of_the_query_split_rule(d, causal, most):
+    # the most workgroups of 256 queries that the 32-query form takes over, and one more; N = 70: three 32-key tiles
+    # for four waves
+    for H in (most, most + 1):
+        _check_backward(900 + H, 1, H, H, 70, d, causal, "f16")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_backward_with_a_very_low_logsumexp(d):
+    # scores near -140 (-200 in log2 units) everywhere: exp2 of a padding key's zero score against such an L overflows, and
+    # must not reach dQ through the zero rows past N (N = 70 leaves 26 of them)
+    q, k, v = (inputs.normal_tensor(950, n, (1, 2, 70, d), "f32") for n in ("q", "k", "v"))
+    q, k = q * 0.1 + 10.0, k * 0.1 - 14.0 / d ** 0.5
+    q, k, v = (t.to(torch.bfloat16) for t in (q, k, v))
+    dout = inputs.normal_tensor(951, "do", (1, 2, 70, d), "bf16")
+    for causal in (False, True):
+        o, lse = binding.fa_fwd(q.cuda(), k.cuda(), v.cuda(), d ** -0.5, causal)
+        assert float(lse.max()) < -100.0
+        got = binding.fa_bwd(q.cuda(), k.cuda(), v.cuda(), o, lse, dout.cuda(), d ** -0.5, causal)
+        assert all(torch.isfinite(t).all() for t in got)
