@@ -102,10 +102,9 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
     const int wave = tid >> 6, lane = tid & 63;
     const int col = lane & 31, half = lane >> 5;
 
-    int id = xcd_contiguous(blockIdx.x, total_wg);
-    const int bh = id / n_kblocks;
-    const int kb = id % n_kblocks;  // causal: key block 0 has the longest loop and comes first
-    const int key0 = kb * BK;
+    const WorkItem item = work_item<CAUSAL>(blockIdx.x, total_wg, n_kblocks);  // key block 0 has the longest loop
+    const int bh = item.head;
+    const int key0 = item.tile * BK;
 
     // bh counts key/value heads; the kv_group query heads that share this one are bh * kv_group + g
     const size_t head_off = (size_t)bh * N * D;
@@ -458,10 +457,11 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
     const int col = lane & 31, half = lane >> 5;
     const int p = wave >> 1, g = wave & 1;
 
-    const int id = xcd_contiguous(blockIdx.x, total_wg);
-    const int bh = id / n_kblocks;
-    const int kb = id % n_kblocks;  // causal: key block 0 has the longest loop and comes first
-    const int key0 = kb * BK;
+    // Longest first over all heads (work_item), B = 4, H = 16, N = 4096 causal, with the dQ pass in the same order:
+    // whole backward 1016 -> 924 us at d = 128, 578 -> 494 us at d = 64; B = 8, N = 2048: 624 -> 547, 333 -> 273 us.
+    const WorkItem item = work_item<CAUSAL>(blockIdx.x, total_wg, n_kblocks);  // key block 0 has the longest loop
+    const int bh = item.head;
+    const int key0 = item.tile * BK;
     // this wave's accumulators: key tiles acc_tile(0), acc_tile(1), columns col0 .. col0 + 63; tile 0 is one whose
     // scores it computes itself (at d = 128 both are)
     auto acc_tile = [&](int j) { return KEYT == 2 ? 2 * p + j : p ^ j; };
@@ -1030,10 +1030,9 @@ fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const int wave = tid >> 6, lane = tid & 63;
     const int col = lane & 31, half = lane >> 5;
 
-    int id = xcd_contiguous(blockIdx.x, total_wg);
-    const int bh = id / n_qtiles;
-    int qt = id % n_qtiles;
-    if (CAUSAL) qt = n_qtiles - 1 - qt;  // longest rows first
+    const WorkItem item = work_item<CAUSAL>(blockIdx.x, total_wg, n_qtiles);
+    const int bh = item.head;
+    const int qt = CAUSAL ? n_qtiles - 1 - item.tile : item.tile;  // the last rows see the most keys
 
     const size_t head_off = (size_t)bh * N * D;
     const size_t kv_off = (size_t)(bh / kv_group) * N * D;  // grouped-query: kv_group query heads per K/V head
@@ -1388,15 +1387,15 @@ size_t bwd_workspace_bytes(int B, int H, int N, int d) {
 // the 32-key form's four-fold parallelism wins until its operand traffic costs as much.  Whole backward, B = 1, bf16,
 // us, 128-key / 32-key form:
 //   d = 128  no mask: 128 workgroups 74 / 69 (H = 16, N = 1024), 160 88 / 96 (H = 16, N = 1280)
-//            causal:  160 88 / 81, 192 75 / 73 (H = 24, N = 1024) and 465 / 401 (H = 3, N = 8192), 256 76 / 82 (H = 32)
-//   d = 64   no mask: 160 55 / 53, 192 46.2 / 45.0, 256 46.5 / 51;  causal: 256 47.5 / 44.6 (N = 1024), 83 / 73 (N = 2048)
-constexpr long few_key_blocks(int d, int causal) { return d == 64 ? (causal ? 256 : 192) : (causal ? 192 : 128); }
+//            causal:  192 75 / 71 (H = 24, N = 1024) and 459 / 395 (H = 3, N = 8192), 256 76 / 81 (H = 32, N = 1024)
+//   d = 64   no mask: 160 55 / 53, 192 46.2 / 45.0, 256 46.5 / 51;  causal: 256 47 / 44 (N = 1024), 384 86 / 84 (N = 2048)
+constexpr long few_key_blocks(int d, int causal) { return d == 64 ? (causal ? 384 : 192) : (causal ? 192 : 128); }
 
 // Up to how many 256-query workgroups the dQ pass uses fa_bwd_dq_few_kernel instead.  Whole backward, B = 1, bf16, us,
 // 256-query / 32-query form:
 //   d = 128  no mask: 64 workgroups 69 / 55 (H = 16, N = 1024), 96 466 / 404 (H = 3, N = 8192), 128 81 / 90 (H = 32)
-//            causal:  64 61 / 40, 128 75.7 / 73.5 (N = 1024) and 131 / 114 (N = 2048), 192 152 / 161 (H = 24, N = 2048)
-//   d = 64   no mask: 64 39 / 28, 96 279 / 238, 128 46.5 / 49.7;  causal: 192 101 / 95, 256 141 / 146 (H = 32 on 4)
+//            causal:  64 74 / 54, 128 76 / 74 (N = 1024) and 130 / 112 (N = 2048), 192 134 / 141 (H = 24, N = 2048)
+//   d = 64   no mask: 64 39 / 28, 96 279 / 238, 128 46.5 / 49.7;  causal: 192 86 / 80 (N = 2048), 256 141 / 146 (H = 32 on 4)
 constexpr long few_query_tiles(int d, int causal) { return causal ? (d == 64 ? 192 : 128) : 96; }
 
 template <typename Tag, int D>

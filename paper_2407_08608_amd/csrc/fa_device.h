@@ -237,6 +237,25 @@ static __device__ __forceinline__ int xcd_contiguous(int id, int total) {
     return (id % kXcd) * (total / kXcd) + id / kXcd;
 }
 
+// (head, tile) of a workgroup.  Without a mask all tiles of a head cost the same and consecutive ids of an XCD take
+// the tiles of one head (above).  Under a causal mask tile 0 is the longest by convention, and workgroups are dealt in
+// order of length over all heads: the hardware hands the next one to the first CU that is free, so the last to start
+// are the shortest and the CUs finish together.  (Head after head, long tiles of the last heads start when nothing is
+// left to fill the other CUs with.)  With a multiple of 8 heads every head still stays on one XCD.
+struct WorkItem {
+    int head, tile;
+};
+template <bool CAUSAL>
+static __device__ __forceinline__ WorkItem work_item(int block, int total, int n_tiles) {
+    if constexpr (CAUSAL) {
+        const int n_heads = total / n_tiles;
+        return {block % n_heads, block / n_heads};
+    } else {
+        const int id = xcd_contiguous(block, total);
+        return {id / n_tiles, id % n_tiles};
+    }
+}
+
 // Measurement builds (-DFA_CLOCK_SPAN): how many shader-clock cycles a launch took on one CU.  A kernel
 // declares a ClockSpan as its first statement; workgroups that run on the chosen CU record the earliest
 // entry stamp and the latest exit stamp (the shader clock is only comparable within a CU).  The CU is that

@@ -74,7 +74,7 @@ def test_backward_query_split_for_few_key_blocks(d, H, H_kv, N, causal, dtype):
     _check_backward(700 + N + d, 1, H, H_kv, N, d, causal, dtype)
 
 
-@pytest.mark.parametrize("d,causal,most", [(64, False, 192), (64, True, 256), (128, False, 128), (128, True, 192)])
+@pytest.mark.parametrize("d,causal,most", [(64, False, 192), (64, True, 384), (128, False, 128), (128, True, 192)])
 def test_backward_on_both_sides_of_the_key_split_rule(d, causal, most):
     # the most workgroups of 128 keys that the 32-key form takes over, and one more
     for H in (most, most + 1):
