@@ -1398,6 +1398,16 @@ constexpr long few_key_blocks(int d, int causal) { return d == 64 ? (causal ? 38
 //   d = 64   no mask: 64 39 / 28, 96 279 / 238, 128 46.5 / 49.7;  causal: 192 86 / 80 (N = 2048), 256 141 / 146 (H = 32 on 4)
 constexpr long few_query_tiles(int d, int causal) { return causal ? (d == 64 ? 192 : 128) : 96; }
 
+// Up to which length the dQ pass takes 128-query workgroups of four waves with 32-key blocks, two or three to a CU,
+// instead of 256-query ones of eight with 64-key blocks: finer tiles waste less on the diagonal and on ragged ends, and
+// the start and end of one workgroup run under the loop of another; over long sequences staging every block twice as
+// often costs more.  Whole backward, bf16, H = 16, us, 256 / 128 queries:
+//   d = 64   no mask: N = 512 160 / 151, 1300 368 / 347, 2048 485 / 487;  causal: 512 128 / 121, 1300 223 / 200,
+//            2048 282 / 274, 3001 437 / 423, 4096 503 / 501
+//   d = 128  no mask: 512 356 / 340, 1300 710 / 690, 2048 931 / 950;  causal: 512 289 / 267, 1300 455 / 427,
+//            2048 575 / 570, 3001 845 / 863
+constexpr int short_rows(int d, int causal) { return d == 64 && causal ? 3072 : 1536; }
+
 template <typename Tag, int D>
 static int launch_bwd_t(const void* q, const void* k, const void* v, const void* o, const float* lse,
                         const void* dout, void* dq, void* dk, void* dv, void* workspace, int B, int H, int H_kv,
@@ -1414,9 +1424,10 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
     if (total > 0x7fffffffL || total_q > 0x7fffffffL) return FA_ERR_SHAPE;
 
     // the dQ pass first: it also writes D, which the dK/dV pass reads
-    auto dqp = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)total_q), dim3(NW * 64), 0, stream, u16(q), u16(k), u16(v), u16(o),
-                           u16(dout), lse, dvec, static_cast<uint16_t*>(dq), N, n_qtiles, (int)total_q, H / H_kv, scale);
+    auto dqp = [&](auto kernel, int rows) {  // `rows`: queries, and threads / 2, of a workgroup
+        const int tiles = (N + rows - 1) / rows, items = B * H * tiles;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)items), dim3(rows * 2), 0, stream, u16(q), u16(k), u16(v), u16(o),
+                           u16(dout), lse, dvec, static_cast<uint16_t*>(dq), N, tiles, items, H / H_kv, scale);
     };
     bool dq_done = false;
     if constexpr (D <= 128) {
@@ -1428,9 +1439,13 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
             };
             causal ? run(fa_bwd_dq_few_kernel<Tag, D, true>) : run(fa_bwd_dq_few_kernel<Tag, D, false>);
             dq_done = true;
+        } else if (N <= short_rows(D, causal) && (long)B * H * ((N + 127) / 128) <= 0x7fffffffL) {
+            causal ? dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, true>, 128) : dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, false>, 128);
+            dq_done = true;
         }
     }
-    if (!dq_done) causal ? dqp(fa_bwd_dq_kernel<Tag, D, BC, NW, true>) : dqp(fa_bwd_dq_kernel<Tag, D, BC, NW, false>);
+    if (!dq_done)
+        causal ? dqp(fa_bwd_dq_kernel<Tag, D, BC, NW, true>, NW * 32) : dqp(fa_bwd_dq_kernel<Tag, D, BC, NW, false>, NW * 32);
     if (hipGetLastError() != hipSuccess) return FA_ERR_LAUNCH;
 
     auto dkdv = [&](auto kernel) {

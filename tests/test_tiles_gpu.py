@@ -102,3 +102,25 @@ def test_backward_with_a_very_low_logsumexp(d):
         assert float(lse.max()) < -100.0
         got = binding.fa_bwd(q.cuda(), k.cuda(), v.cuda(), o, lse, dout.cuda(), d ** -0.5, causal)
         assert all(torch.isfinite(t).all() for t in got)
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,N", [(64, 127), (64, 129), (64, 290), (128, 33), (128, 128), (128, 130), (128, 260)])
+def test_backward_four_wave_query_tiles(d, N, causal):
+    # enough heads that neither pass takes its few-workgroup form: 128-query tiles with 32-key blocks, ragged in both
+    _check_backward(960 + N, 2, 200, 100, N, d, causal, "bf16")
+
+
+@pytest.mark.parametrize("d,causal,N", [(64, True, 3072), (64, True, 3073), (128, False, 1536), (128, False, 1537)])
+def test_backward_query_tile_rule_edges(d, causal, N):
+    # on both sides of the length up to which the 128-query tiles are used, with more tiles than the few-workgroup form
+    # takes (one head's gradients are held against the oracle; the heads share K and V)
+    H = 24
+    q, dout = (inputs.normal_tensor(990, n, (1, H, N, d), "bf16") for n in ("q", "do"))
+    k, v = (inputs.normal_tensor(990, n, (1, 1, N, d), "bf16") for n in ("k", "v"))
+    qg, kg, vg, dog = (t.cuda() for t in (q, k, v, dout))
+    o, lse = binding.fa_fwd_gqa(qg, kg, vg, d ** -0.5, causal)
+    dq = binding.fa_bwd_gqa(qg, kg, vg, o, lse, dog, d ** -0.5, causal)[0]
+    ref = oracle.attention_bwd_gqa(f64(q[:, 5:6]), f64(k), f64(v), f64(dout[:, 5:6]), d ** -0.5, causal)["dq"]
+    g = f64(dq[:, 5:6])
+    assert rmse(g, ref) <= REL_RMSE * float(np.sqrt(np.mean(ref * ref)))
