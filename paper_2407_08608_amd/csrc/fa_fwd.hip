@@ -59,7 +59,7 @@ template <typename Tag, int D, int BC, int NW, int RQ, int PD, bool CAUSAL>
 __global__ void __launch_bounds__(NW * 64, (D == 64 && NW == 8) ? 4 : (RQ == 1 && D <= 128) ? 2 : 1)
 fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     const uint16_t* __restrict__ v, uint16_t* __restrict__ o, float* __restrict__ lse,
-                    int N, int n_qtiles, int total_wg, int kv_group, float scale) {
+                    int N, int n_qtiles, int total_wg, int paired, int kv_group, float scale) {
     [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
     constexpr int NT = NW * 64;
     constexpr int BR = NW * 32 * RQ;
@@ -79,14 +79,8 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     const int wave = tid >> 6, lane = tid & 63;
     const int col = lane & 31, half = lane >> 5;
 
-    // Work items.  Non-causal: one query tile.  Causal: query tiles i and n_qtiles-1-i of a head,
-    // one after the other, so that every item covers the same number of key blocks (with an odd
-    // tile count the middle tile is an item of its own).
-    int id = xcd_contiguous(blockIdx.x, total_wg);
-    const int n_items = CAUSAL ? (n_qtiles + 1) / 2 : n_qtiles;
-    const int bh = id / n_items;
-    const int item = id % n_items;
-    const int n_pass = (CAUSAL && n_qtiles - 1 - item != item) ? 2 : 1;
+    const TileRun run = query_tiles<CAUSAL>(blockIdx.x, total_wg, n_qtiles, paired);
+    const int bh = run.head;
 
     const size_t head_off = (size_t)bh * N * D;
     const size_t kv_off = (size_t)(bh / kv_group) * N * D;  // grouped-query: kv_group query heads per K/V head
@@ -99,9 +93,9 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     asm volatile("" : "+v"(sc_v));
 
 #pragma nounroll
-    for (int pass = 0; pass < n_pass; ++pass) {
-    // the longer tile first; every LDS read of the previous pass was followed by a barrier
-    const int qt = CAUSAL ? (pass == 0 ? n_qtiles - 1 - item : item) : item;
+    for (int pass = 0; pass < run.n_pass; ++pass) {
+    // every LDS read of the previous pass was followed by a barrier
+    const int qt = pass == 0 ? run.tile : n_qtiles - 1 - run.tile;
     const int wave_q0 = qt * BR + wave * (32 * RQ);
 
     // Q_i^T as the B operand, resident in registers for the whole loop
@@ -277,7 +271,7 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                                     lane);
         if (qi < N && half == 0) lse[(size_t)bh * N + qi] = (m_run + log2f(l)) * kLn2;
     }
-    if (pass + 1 < n_pass) __syncthreads();  // the next pass's first tile overwrites the patches
+    if (pass + 1 < run.n_pass) __syncthreads();  // the next pass's first tile overwrites the patches
     }  // passes of a causal pair
 }
 
@@ -304,7 +298,7 @@ template <typename Tag, bool CAUSAL>
 __global__ void __launch_bounds__(256, 1)
 fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                    uint16_t* __restrict__ o, float* __restrict__ lse, int N, int n_qtiles, int total_wg,
-                   int kv_group, float scale) {
+                   int paired, int kv_group, float scale) {
     [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
     constexpr int D = 256, BC = 64, NT = 256, BR = 128;
     constexpr int KSTR = D + 8;   // +16 B per row: 128-bit row reads hit distinct banks
@@ -320,12 +314,8 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
     const int wave = tid >> 6, lane = tid & 63;
     const int col = lane & 31, half = lane >> 5;
 
-    // work items as in fa_fwd_16bit_kernel: causal tiles i and n_qtiles-1-i form one item
-    int id = xcd_contiguous(blockIdx.x, total_wg);
-    const int n_items = CAUSAL ? (n_qtiles + 1) / 2 : n_qtiles;
-    const int bh = id / n_items;
-    const int item = id % n_items;
-    const int n_pass = (CAUSAL && n_qtiles - 1 - item != item) ? 2 : 1;
+    const TileRun run = query_tiles<CAUSAL>(blockIdx.x, total_wg, n_qtiles, paired);
+    const int bh = run.head;
 
     const size_t head_off = (size_t)bh * N * D;
     const size_t kv_off = (size_t)(bh / kv_group) * N * D;
@@ -337,8 +327,8 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
     const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
 
 #pragma nounroll
-    for (int pass = 0; pass < n_pass; ++pass) {
-    const int qt = CAUSAL ? (pass == 0 ? n_qtiles - 1 - item : item) : item;  // the longer tile first
+    for (int pass = 0; pass < run.n_pass; ++pass) {
+    const int qt = pass == 0 ? run.tile : n_qtiles - 1 - run.tile;
     const int wave_q0 = qt * BR + wave * 32;
     const int limit = CAUSAL ? min(wave_q0 + col, N - 1) : N - 1;  // last key this lane's query sees
 
@@ -551,7 +541,7 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
         store_rows_via_lds<Tag, DT>(oacc, 1.0f / l, patch, make_buffer(o + head_off, (uint32_t)N * D * 2), wave_q0, lane);
         if (qi < N && half == 0) lse[(size_t)bh * N + qi] = (m_run * sc + log2f(l)) * kLn2;
     }
-    if (pass + 1 < n_pass) __syncthreads();  // the next pass's first tile overwrites the patches
+    if (pass + 1 < run.n_pass) __syncthreads();  // the next pass's first tile overwrites the patches
     }  // passes of a causal pair
 }
 
@@ -588,7 +578,7 @@ template <typename Tag, int BC, int P, bool CAUSAL>
 __global__ void __launch_bounds__(512, 2)
 fa_fwd_pingpong_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                        const uint16_t* __restrict__ v, uint16_t* __restrict__ o, float* __restrict__ lse,
-                       int N, int n_qtiles, int total_wg, int kv_group, float scale) {
+                       int N, int n_qtiles, int total_wg, int paired, int kv_group, float scale) {
     [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
     constexpr int D = 128;
     constexpr int BR = 256;
@@ -615,15 +605,8 @@ fa_fwd_pingpong_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
     const int group = wave >> 2;
     const int slab = (wave & 3) * 2 + group;
 
-    // Work items.  Non-causal: one query tile.  Causal: query tiles i and n_qtiles-1-i of a head,
-    // one after the other -- every item then covers the same number of key blocks, so the grid
-    // has no long and short workgroups and no tail of stragglers (with an odd tile count the
-    // middle tile is an item of its own).
-    int id = xcd_contiguous(blockIdx.x, total_wg);
-    const int n_items = CAUSAL ? (n_qtiles + 1) / 2 : n_qtiles;
-    const int bh = id / n_items;
-    const int item = id % n_items;
-    const int n_pass = (CAUSAL && n_qtiles - 1 - item != item) ? 2 : 1;
+    const TileRun run = query_tiles<CAUSAL>(blockIdx.x, total_wg, n_qtiles, paired);
+    const int bh = run.head;
 
     const size_t head_off = (size_t)bh * N * D;
     const uint16_t* qh = q + head_off;
@@ -838,8 +821,8 @@ fa_fwd_pingpong_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
     const std::false_type no{};
 
 #pragma nounroll
-    for (int pass = 0; pass < n_pass; ++pass) {
-    const int qt = CAUSAL ? (pass == 0 ? n_qtiles - 1 - item : item) : item;  // the longer tile first
+    for (int pass = 0; pass < run.n_pass; ++pass) {
+    const int qt = pass == 0 ? run.tile : n_qtiles - 1 - run.tile;
     wave_q0 = qt * BR + slab * 32;
     {
         int row = min(wave_q0 + col, N - 1);  // rows past N compute a copy of row N-1, never stored
@@ -950,9 +933,8 @@ fa_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, cons
     const int col = lane & 31, half = lane >> 5;
     const int slab = wave & 1, split = wave >> 1;
 
-    const int id = xcd_contiguous(blockIdx.x, total_wg);
-    const int bh = id / n_qtiles;
-    const int qt = CAUSAL ? n_qtiles - 1 - id % n_qtiles : id % n_qtiles;  // causal: longest rows first
+    const TileRun run = query_tiles<CAUSAL>(blockIdx.x, total_wg, n_qtiles, 0);
+    const int bh = run.head, qt = run.tile;
     const size_t head_off = (size_t)bh * N * D;
     const size_t kv_off = (size_t)(bh / kv_group) * N * D;  // grouped-query: kv_group query heads per K/V head
     const int q0 = qt * BR + slab * 32;                     // first row of this wave's slab
@@ -1101,7 +1083,9 @@ static int launch_16bit(const void* q, const void* k, const void* v, void* o, fl
                         float scale, int causal, hipStream_t stream) {
     constexpr int BR = NW * 32 * RQ;
     int n_qtiles = (N + BR - 1) / BR;
-    long total = (long)B * H * (causal ? (n_qtiles + 1) / 2 : n_qtiles);  // causal: tiles are paired up
+    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, D == 64 ? 0 : NW == 4 ? 512 : 256,
+                                                    NW == 4 && n_qtiles <= 8 ? 11 : 9);
+    long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
     dim3 grid((unsigned)total), block(NW * 64);
     auto qp = static_cast<const uint16_t*>(q);
@@ -1110,10 +1094,10 @@ static int launch_16bit(const void* q, const void* k, const void* v, void* o, fl
     auto op = static_cast<uint16_t*>(o);
     if (causal)
         hipLaunchKernelGGL((fa_fwd_16bit_kernel<Tag, D, BC, NW, RQ, PD, true>), grid, block, 0, stream, qp, kp, vp,
-                           op, lse, N, n_qtiles, (int)total, H / H_kv, scale);
+                           op, lse, N, n_qtiles, (int)total, paired, H / H_kv, scale);
     else
         hipLaunchKernelGGL((fa_fwd_16bit_kernel<Tag, D, BC, NW, RQ, PD, false>), grid, block, 0, stream, qp, kp, vp,
-                           op, lse, N, n_qtiles, (int)total, H / H_kv, scale);
+                           op, lse, N, n_qtiles, (int)total, paired, H / H_kv, scale);
     return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
 }
 
@@ -1122,7 +1106,8 @@ static int launch_pingpong(const void* q, const void* k, const void* v, void* o,
                            float scale, int causal, hipStream_t stream) {
     constexpr int BR = 256, BC = 64, P = 4;
     int n_qtiles = (N + BR - 1) / BR;
-    long total = (long)B * H * (causal ? (n_qtiles + 1) / 2 : n_qtiles);  // causal: tiles are paired up
+    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, 256);
+    long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
     dim3 grid((unsigned)total), block(512);
     auto qp = static_cast<const uint16_t*>(q);
@@ -1131,10 +1116,10 @@ static int launch_pingpong(const void* q, const void* k, const void* v, void* o,
     auto op = static_cast<uint16_t*>(o);
     if (causal)
         hipLaunchKernelGGL((fa_fwd_pingpong_kernel<Tag, BC, P, true>), grid, block, 0, stream, qp, kp, vp, op, lse, N,
-                           n_qtiles, (int)total, H / H_kv, scale);
+                           n_qtiles, (int)total, paired, H / H_kv, scale);
     else
         hipLaunchKernelGGL((fa_fwd_pingpong_kernel<Tag, BC, P, false>), grid, block, 0, stream, qp, kp, vp, op, lse, N,
-                           n_qtiles, (int)total, H / H_kv, scale);
+                           n_qtiles, (int)total, paired, H / H_kv, scale);
     return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
 }
 
@@ -1143,7 +1128,8 @@ static int launch_d256(const void* q, const void* k, const void* v, void* o, flo
                        float scale, int causal, hipStream_t stream) {
     constexpr int BR = 128;
     int n_qtiles = (N + BR - 1) / BR;
-    long total = (long)B * H * (causal ? (n_qtiles + 1) / 2 : n_qtiles);  // causal: tiles are paired up
+    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, 256);
+    long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
     dim3 grid((unsigned)total), block(256);
     auto qp = static_cast<const uint16_t*>(q);
@@ -1152,16 +1138,15 @@ static int launch_d256(const void* q, const void* k, const void* v, void* o, flo
     auto op = static_cast<uint16_t*>(o);
     if (causal)
         hipLaunchKernelGGL((fa_fwd_d256_kernel<Tag, true>), grid, block, 0, stream, qp, kp, vp, op, lse, N, n_qtiles,
-                           (int)total, H / H_kv, scale);
+                           (int)total, paired, H / H_kv, scale);
     else
         hipLaunchKernelGGL((fa_fwd_d256_kernel<Tag, false>), grid, block, 0, stream, qp, kp, vp, op, lse, N, n_qtiles,
-                           (int)total, H / H_kv, scale);
+                           (int)total, paired, H / H_kv, scale);
     return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
 }
 
 // Kernel choice (measured on MI355X at the 16k-token benchmark shapes):
-//   d = 128: the eight-wave ping-pong kernel for long sequences (causal tiles are paired into
-//     items of equal length there, so its coarser tiles cost no balance); shorter problems keep
+//   d = 128: the eight-wave ping-pong kernel for long sequences; shorter problems keep
 //     128-row workgroups of four waves, which fill the chip better and waste less of a tile on
 //     the diagonal.  The two cross between 640 and 768 keys without a mask and near 1400 with one
 //     (measured at 16k and 64k tokens per launch).

@@ -62,7 +62,7 @@ __global__ void __launch_bounds__(NW * 64, D <= 128 ? 2 : 1)
 fa_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ k, const uint8_t* __restrict__ v,
                   const float* __restrict__ q_scale, const float* __restrict__ k_scale,
                   const float* __restrict__ v_scale, uint16_t* __restrict__ o, float* __restrict__ lse, int N,
-                  int n_qtiles, int total_wg, int n_sblocks, int kv_group, float scale) {
+                  int n_qtiles, int total_wg, int paired, int n_sblocks, int kv_group, float scale) {
     [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
     constexpr int NT = NW * 64;
     constexpr int BR = NW * 32;
@@ -85,14 +85,8 @@ fa_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ k, 
     const int wave = tid >> 6, lane = tid & 63;
     const int col = lane & 31, half = lane >> 5;
 
-    // Work items.  Non-causal: one query tile.  Causal: query tiles i and n_qtiles-1-i of a head,
-    // one after the other, so that every item covers the same number of key blocks (with an odd
-    // tile count the middle tile is an item of its own).
-    int id = xcd_contiguous(blockIdx.x, total_wg);
-    const int n_items = CAUSAL ? (n_qtiles + 1) / 2 : n_qtiles;
-    const int bh = id / n_items;
-    const int item = id % n_items;
-    const int n_pass = (CAUSAL && n_qtiles - 1 - item != item) ? 2 : 1;
+    const TileRun run = query_tiles<CAUSAL>(blockIdx.x, total_wg, n_qtiles, paired);
+    const int bh = run.head;
 
     const size_t head_off = (size_t)bh * N * D;
     const uint8_t* qh = q + head_off;
@@ -100,9 +94,9 @@ fa_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ k, 
     const uint8_t* kh = k + (size_t)kv_bh * N * D;
     const uint8_t* vh = v + (size_t)kv_bh * N * D;
 #pragma nounroll
-    for (int pass = 0; pass < n_pass; ++pass) {
-    // the longer tile first; every LDS read of the previous pass was followed by a barrier
-    const int qt = CAUSAL ? (pass == 0 ? n_qtiles - 1 - item : item) : item;
+    for (int pass = 0; pass < run.n_pass; ++pass) {
+    // every LDS read of the previous pass was followed by a barrier
+    const int qt = pass == 0 ? run.tile : n_qtiles - 1 - run.tile;
     const int wave_q0 = qt * BR + wave * 32;
 
     float sq = 1.0f;
@@ -342,7 +336,7 @@ __global__ void __launch_bounds__(512, 1)
 fa_fwd_fp8_async_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ k, const uint8_t* __restrict__ v,
                          const float* __restrict__ q_scale, const float* __restrict__ k_scale,
                          const float* __restrict__ v_scale, uint16_t* __restrict__ o, float* __restrict__ lse, int N,
-                         int n_qtiles, int total_wg, int n_sblocks, int kv_group, float scale) {
+                         int n_qtiles, int total_wg, int paired, int n_sblocks, int kv_group, float scale) {
     [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
     constexpr int NW = 8, BR = NW * 32;
     constexpr int NS = 2;            // LDS stages per tensor
@@ -363,12 +357,8 @@ fa_fwd_fp8_async_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int col = lane & 31, half = lane >> 5;
 
-    // work items as in fa_fwd_fp8_kernel: causal tiles i and n_qtiles-1-i form one item
-    int id = xcd_contiguous(blockIdx.x, total_wg);
-    const int n_items = CAUSAL ? (n_qtiles + 1) / 2 : n_qtiles;
-    const int bh = id / n_items;
-    const int item = id % n_items;
-    const int n_pass = (CAUSAL && n_qtiles - 1 - item != item) ? 2 : 1;
+    const TileRun run = query_tiles<CAUSAL>(blockIdx.x, total_wg, n_qtiles, paired);
+    const int bh = run.head;
 
     const size_t head_off = (size_t)bh * N * D;
     const uint8_t* qh = q + head_off;
@@ -418,8 +408,8 @@ fa_fwd_fp8_async_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict
         vofs[dt] = (8 * half + tr_row) * ROWB + (((2 * dt + blk) ^ v_swz(tr_row)) << 4) + 8 * (lane & 1);
 
 #pragma nounroll
-    for (int pass = 0; pass < n_pass; ++pass) {
-    const int qt = CAUSAL ? (pass == 0 ? n_qtiles - 1 - item : item) : item;  // the longer tile first
+    for (int pass = 0; pass < run.n_pass; ++pass) {
+    const int qt = pass == 0 ? run.tile : n_qtiles - 1 - run.tile;
     const int wave_q0 = qt * BR + wave * 32;
 
     float sq = 1.0f;
@@ -587,7 +577,8 @@ static int launch_fp8(const void* q8, const void* k8, const void* v8, const floa
     constexpr int BR = NW * 32;
     int n_qtiles = (N + BR - 1) / BR;
     int n_sblocks = (N + 127) / 128;
-    long total = (long)B * H * (causal ? (n_qtiles + 1) / 2 : n_qtiles);  // causal: tiles are paired up
+    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, D == 64 ? 0 : NW == 4 ? 512 : 256);
+    long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
     dim3 grid((unsigned)total), block(NW * 64);
     auto qp = static_cast<const uint8_t*>(q8);
@@ -597,7 +588,7 @@ static int launch_fp8(const void* q8, const void* k8, const void* v8, const floa
     const bool scaled = qs != nullptr;
 #define FA_LAUNCH_FP8(C, S)                                                                                       \
     hipLaunchKernelGGL((fa_fwd_fp8_kernel<D, BC, NW, C, S>), grid, block, 0, stream, qp, kp, vp, qs, ks, vs, op, \
-                       lse, N, n_qtiles, (int)total, n_sblocks, H / H_kv, scale)
+                       lse, N, n_qtiles, (int)total, paired, n_sblocks, H / H_kv, scale)
     if (causal) {
         if (scaled) FA_LAUNCH_FP8(true, true); else FA_LAUNCH_FP8(true, false);
     } else {
@@ -614,7 +605,8 @@ static int launch_fp8_async(const void* q8, const void* k8, const void* v8, cons
     constexpr int BR = 256;
     int n_qtiles = (N + BR - 1) / BR;
     int n_sblocks = (N + 127) / 128;
-    long total = (long)B * H * (causal ? (n_qtiles + 1) / 2 : n_qtiles);  // causal: tiles are paired up
+    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, D == 128 ? 256 : 0);
+    long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
     dim3 grid((unsigned)total), block(512);
     auto qp = static_cast<const uint8_t*>(q8);
@@ -624,7 +616,7 @@ static int launch_fp8_async(const void* q8, const void* k8, const void* v8, cons
     const bool scaled = qs != nullptr;
 #define FA_LAUNCH_FP8_D256(C, S)                                                                                  \
     hipLaunchKernelGGL((fa_fwd_fp8_async_kernel<D, BC, C, S>), grid, block, 0, stream, qp, kp, vp, qs, ks, vs, op, lse, N, \
-                       n_qtiles, (int)total, n_sblocks, H / H_kv, scale)
+                       n_qtiles, (int)total, paired, n_sblocks, H / H_kv, scale)
     if (causal) {
         if (scaled) FA_LAUNCH_FP8_D256(true, true); else FA_LAUNCH_FP8_D256(true, false);
     } else {

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import oracle
-from helpers import f64, max_abs, rmse
+from helpers import check_fp8_against_model_oracle, f64, max_abs, rmse
 from paper_2407_08608_amd import binding, inputs
 
 pytestmark = pytest.mark.gpu
@@ -124,3 +124,29 @@ def test_backward_query_tile_rule_edges(d, causal, N):
     ref = oracle.attention_bwd_gqa(f64(q[:, 5:6]), f64(k), f64(v), f64(dout[:, 5:6]), d ** -0.5, causal)["dq"]
     g = f64(dq[:, 5:6])
     assert rmse(g, ref) <= REL_RMSE * float(np.sqrt(np.mean(ref * ref)))
+
+
+@pytest.mark.parametrize("heads,N,d", [(64, 1500, 128), (128, 1500, 128), (512, 100, 128), (384, 200, 128), (100, 300, 128),
+                                       (7, 1409, 128), (256, 129, 256), (300, 300, 256), (5, 700, 256), (9, 1300, 64),
+                                       (11, 200, 64)])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_causal_forward_paired_and_single_tiles(heads, N, d, fp8):
+    # head counts on both sides of the rule that pairs causal query tiles, with odd and even tile counts; every row of
+    # the first, a middle and the last head against the oracle
+    pick = sorted({0, heads // 2, heads - 1})
+    q = inputs.normal_tensor(1000 + N, "q", (1, heads, N, d), "bf16")
+    k, v = (inputs.normal_tensor(1000 + N, n, (1, 1, N, d), "bf16") for n in ("k", "v"))
+    if fp8:
+        dev = [binding.fa_fp8_quant_hadamard(t.cuda()) for t in (q, k, v)]
+        o, lse = binding.fa_fwd_fp8_gqa(*(p[0] for p in dev), *(p[1] for p in dev), d ** -0.5, True)
+        codes = [[a.cpu().numpy() for a in p] for p in dev]
+        for h in pick:
+            (qc, qs), kc, vc = codes[0], codes[1], codes[2]
+            check_fp8_against_model_oracle(o[:, h:h + 1], lse[:, h:h + 1], (qc[:, h:h + 1], kc[0], vc[0]),
+                                           (qs[:, h:h + 1], kc[1], vc[1]), d ** -0.5, True, kv_heads=1)
+        return
+    o, lse = binding.fa_fwd_gqa(q.cuda(), k.cuda(), v.cuda(), d ** -0.5, True)
+    for h in pick:
+        o_ref, l_ref = oracle.attention_fwd(f64(q[:, h:h + 1]), f64(k), f64(v), d ** -0.5, True)
+        assert max_abs(f64(o[:, h:h + 1]), o_ref) <= 2e-2 and rmse(f64(o[:, h:h + 1]), o_ref) <= 3e-3
+        assert max_abs(f64(lse[:, h:h + 1]), l_ref) <= 2e-3
