@@ -1005,7 +1005,7 @@ fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
 // ---------------------------------------------------------------------------------------
 // dQ pass: the forward kernel's structure with dO alongside Q and K^T in place of V^T.
 template <typename Tag, int D, int BC, int NW, bool CAUSAL>
-__global__ void __launch_bounds__(NW * 64, D == 256 ? 1 : 2)
+__global__ void __launch_bounds__(NW * 64, 2)
 fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                  const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
                  float* __restrict__ dvec, uint16_t* __restrict__ dq, int N, int n_qtiles, int total_wg, int kv_group, float scale) {
@@ -1094,21 +1094,8 @@ fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     };
     load_tile(0);
     store_tile(0);
-    // One wave per SIMD (d = 256): the kernel may use more than 256 registers per lane, MFMA results
-    // then land in the accumulation half of the register file, and the score tiles would pay a copy per
-    // element on their way to the exponentials.  They are produced by MfmaVgprAcc into ordinary
-    // registers instead (Q_i, dO_i, touched by MFMA alone, go to the accumulation half), and the next
-    // block's K and V travel in 16-byte chunks spread over the MFMA steps: as one burst, the 16 loads
-    // of a wave keep it in its own issue for over a thousand cycles (see fa_fwd_d256_kernel).
-    constexpr bool ONE_WAVE = D == 256;
-    constexpr int NSTEP = KS * KT;  // MFMA steps of either GEMM group; a staging chunk every CH_EVERY of them
-    constexpr int CH_EVERY = ONE_WAVE ? NSTEP / CPT : 1;
-    static_assert(!ONE_WAVE || (CPT * CH_EVERY == NSTEP && SL * DT == NSTEP), "chunks must spread evenly");
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {  // loads done before the loop
-        if constexpr (ONE_WAVE) asm volatile("" : "+a"(qreg[ks]), "+a"(doreg[ks]));
-        else asm volatile("" : "+v"(qreg[ks]), "+v"(doreg[ks]));
-    }
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qreg[ks]), "+v"(doreg[ks]));  // loads done before the loop
     __syncthreads();
 
     const int tr_row = (lane & 15) >> 2;
@@ -1118,11 +1105,9 @@ fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         const int st = t & 1;
         const int key0 = t * BC;
         const bool more = (t + 1 < n_blocks);
-        // a wave whose queries all precede this block has nothing to add (causal).  With one wave per SIMD every
-        // wave works every block (a fully masked one adds zeros): the branch around the interleaved staging
-        // costs that instantiation a hundred registers.
-        const bool wave_active = !CAUSAL || ONE_WAVE || key0 <= wave_q0 + 31;
-        if (more && !(ONE_WAVE && wave_active)) load_tile(key0 + BC);
+        // a wave whose queries all precede this block has nothing to add (causal)
+        const bool wave_active = !CAUSAL || key0 <= wave_q0 + 31;
+        if (more) load_tile(key0 + BC);
 
         if (wave_active) {
             // ---- S^T = K_j Q_i^T and dP^T = V_j dO_i^T
@@ -1135,33 +1120,11 @@ fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 for (int kt = 0; kt < KT; ++kt) {
                     i32x4 ak = *reinterpret_cast<const i32x4*>(lds_k[st] + kbase + kt * 32 * RSTR + ks * 16);
                     i32x4 av = *reinterpret_cast<const i32x4*>(lds_v[st] + vbase + kt * 32 * VSTR + ks * 16);
-                    if constexpr (ONE_WAVE) {
-                        if (ks == 0) {
-                            MfmaVgprAcc<Tag>::first(sacc[kt], ak, qreg[ks]);
-                            MfmaVgprAcc<Tag>::first(pacc[kt], av, doreg[ks]);
-                        } else {
-                            MfmaVgprAcc<Tag>::run(sacc[kt], ak, qreg[ks]);
-                            MfmaVgprAcc<Tag>::run(pacc[kt], av, doreg[ks]);
-                        }
-                        const int u = ks * KT + kt;
-                        if (more && u % CH_EVERY == 0) {
-                            const int i = u / CH_EVERY;
-                            kpre[i] = buffer_load_16B(k_rsrc, (key0 + BC) * D * 2 + (tid + i * NT) * 16);
-                            vpre[i] = buffer_load_16B(v_rsrc, (key0 + BC) * D * 2 + (tid + i * NT) * 16);
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    } else {
-                        sacc[kt] = E::mma(ak, qreg[ks], ks == 0 ? zero : sacc[kt]);
-                        // where registers allow, dP starts from -D (a lane owns one query, so D is one value per
-                        // lane, kept as a 16-register constant): dP - D comes out of the MFMAs
-                        pacc[kt] = E::mma(av, doreg[ks], ks == 0 ? (NEG_D_START ? negd : zero) : pacc[kt]);
-                    }
+                    sacc[kt] = E::mma(ak, qreg[ks], ks == 0 ? zero : sacc[kt]);
+                    // where registers allow, dP starts from -D (a lane owns one query, so D is one value per
+                    // lane, kept as a 16-register constant): dP - D comes out of the MFMAs
+                    pacc[kt] = E::mma(av, doreg[ks], ks == 0 ? (NEG_D_START ? negd : zero) : pacc[kt]);
                 }
-            if constexpr (ONE_WAVE) {  // results of MFMAs the hazard checker cannot see
-                static_assert(!ONE_WAVE || KT == 2, "two score tiles per GEMM");
-                mfma_result_wait(sacc[0], sacc[1]);
-                mfma_result_wait(pacc[0], pacc[1]);
-            }
 
             // ---- P = exp(S - L), dS = P o (dP - D), packed as the B operand of the dQ product
             // keys past N, and keys after the query when causal, get S = -inf (P = 0): one uniform branch per
@@ -1213,19 +1176,10 @@ fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     i32x2 hi = lds_read_tr16(p0 + 8 * RSTR);
                     i32x4 a = {lo[0], lo[1], hi[0], hi[1]};
                     acc[dt] = E::mma(a, dsb[sl], acc[dt]);
-                    if constexpr (ONE_WAVE) {
-                        const int u = sl * DT + dt;
-                        if (more && u % CH_EVERY == 0) {  // the chunks loaded beside the first GEMM group go to the other buffers
-                            const int c = tid + (u / CH_EVERY) * NT;
-                            *reinterpret_cast<i32x4*>(lds_k[st ^ 1] + (c / CPR) * RSTR + (c % CPR) * 8) = kpre[u / CH_EVERY];
-                            *reinterpret_cast<i32x4*>(lds_v[st ^ 1] + (c / CPR) * VSTR + (c % CPR) * 8) = vpre[u / CH_EVERY];
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
                 }
         }
 
-        if (more && !(ONE_WAVE && wave_active)) store_tile(st ^ 1);
+        if (more) store_tile(st ^ 1);
         __syncthreads();
     }
 
@@ -1235,6 +1189,166 @@ fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     char* patch = (wave < NW / 2 ? reinterpret_cast<char*>(&lds_k[0][0]) : reinterpret_cast<char*>(&lds_v[0][0])) +
                   (wave % (NW / 2)) * 4096;
     store_rows_via_lds<Tag, DT>(acc, scale, patch, make_buffer(dq + head_off, (uint32_t)N * D * 2), wave_q0, lane);
+}
+
+// ---------------------------------------------------------------------------------------
+// dQ pass at head dimension 256: four waves, one per SIMD (the 128-register accumulator and the Q, dO operands fill the
+// register file), so only the wave's own instruction stream can keep its matrix pipe busy.  Per 64-key block:
+//   S^T   32 MFMAs  ||  dP accumulators set to -D, the first of the next block's global loads
+//   dP^T  32 MFMAs  ||  P = exp2(S c - L), the rest of the loads
+//   dQ^T  32 MFMAs  ||  dS of the second key tile, the next block's LDS writes
+// LDS operand reads lead their MFMAs by KP steps, across the phases (read in the step that used them, they cost the
+// wave the LDS latency 96 times per block).  S and dP are produced by MfmaVgprAcc into ordinary registers, Q, dO and
+// dQ live in the accumulation half; every step ends in a full scheduling barrier, so the order written here is what runs.
+// bf16, whole backward, us, before / so: B = 2, H = 8, N = 8192 3858 / 3452 (this pass 1834 / ~1410, 1.17 PFLOP/s of
+// executed MFMAs), causal 2020 / 1809; B = 8, H = 8, N = 2048 causal 650 / 579.
+template <typename Tag, bool CAUSAL>
+__global__ void __launch_bounds__(256, 1)
+fa_bwd_dq_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                      const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
+                      float* __restrict__ dvec, uint16_t* __restrict__ dq, int N, int n_qtiles, int total_wg,
+                      int kv_group, float scale) {
+    [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
+    constexpr int D = 256, BC = 64, NT = 256, BR = 128;
+    constexpr int KSTR = bwd_row_stride(D);  // K tile: row reads and transposed reads
+    constexpr int VSTR = D + 8;              // V tile: row reads only
+    constexpr int KS = D / 16, DT = D / 32, CPR = D / 8;
+    constexpr int NCH = BC * CPR / NT;       // 16-byte chunks per thread and tensor
+    constexpr int KP = 4;
+    using E = Elem<Tag>;
+    __shared__ __attribute__((aligned(16))) uint16_t lds_k[2][BC * KSTR];
+    __shared__ __attribute__((aligned(16))) uint16_t lds_v[2][BC * VSTR];
+
+    const int tid = threadIdx.x;
+    const int wave = tid >> 6, lane = tid & 63;
+    const int col = lane & 31, half = lane >> 5;
+    const WorkItem item = work_item<CAUSAL>(blockIdx.x, total_wg, n_qtiles);
+    const int bh = item.head;
+    const int qt = CAUSAL ? n_qtiles - 1 - item.tile : item.tile;  // the last rows see the most keys
+
+    const size_t head_off = (size_t)bh * N * D;
+    const size_t kv_off = (size_t)(bh / kv_group) * N * D;  // grouped-query: kv_group query heads per K/V head
+    const int wave_q0 = qt * BR + wave * 32;
+    const int qi = wave_q0 + col;
+    const int qrow = min(qi, N - 1);  // rows past N compute a copy of row N-1, never stored
+    const int limit = CAUSAL ? qrow : N - 1;  // last visible key
+    float sc = scale * kLog2e;
+    asm volatile("" : "+v"(sc));  // in a vector register: an FMA with a scalar operand issues at a lower rate
+
+    const __amdgpu_buffer_rsrc_t k_rsrc = make_buffer(k + kv_off, (uint32_t)N * D * 2);
+    const __amdgpu_buffer_rsrc_t v_rsrc = make_buffer(v + kv_off, (uint32_t)N * D * 2);
+    i32x4 pre[2 * NCH];  // the next block's K chunks, then its V chunks; blocks past the end read as zero
+    auto load_chunk = [&](int t, int c) __attribute__((always_inline)) {
+        pre[c] = buffer_load_16B(c < NCH ? k_rsrc : v_rsrc, t * BC * D * 2 + (tid + (c % NCH) * NT) * 16);
+    };
+    auto store_chunk = [&](int st, int c) __attribute__((always_inline)) {
+        const int e = tid + (c % NCH) * NT, row = e / CPR, cc = e % CPR;
+        if (c < NCH) *reinterpret_cast<i32x4*>(lds_k[st] + row * KSTR + cc * 8) = pre[c];
+        else *reinterpret_cast<i32x4*>(lds_v[st] + row * VSTR + cc * 8) = pre[c];
+    };
+#pragma unroll
+    for (int c = 0; c < 2 * NCH; ++c) load_chunk(0, c);
+
+    i32x4 qreg[KS], doreg[KS];
+    float d_row = 0.f;  // D = rowsum(dO o O)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const size_t off = head_off + (size_t)qrow * D + ks * 16 + half * 8;
+        qreg[ks] = *reinterpret_cast<const i32x4*>(q + off);
+        doreg[ks] = *reinterpret_cast<const i32x4*>(dout + off);
+        d_row = dot8<Tag>(*reinterpret_cast<const i32x4*>(o + off), doreg[ks], d_row);
+    }
+    d_row = sum_both_halves(d_row);
+    if (half == 0 && qi < N) dvec[(size_t)bh * N + qi] = d_row;
+    const float l2 = lse[(size_t)bh * N + qrow] * kLog2e;
+    f32x16 acc[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[dt][r] = 0.f;
+#pragma unroll
+    for (int c = 0; c < 2 * NCH; ++c) store_chunk(0, c);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(qreg[ks]), "+a"(doreg[ks]));
+    __syncthreads();
+
+    const int tr_row = (lane & 15) >> 2;
+    const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+
+    auto block = [&](int t, auto mask_tag) __attribute__((always_inline)) {
+        constexpr bool MASK = decltype(mask_tag)::value;
+        const int st = t & 1;
+        uint32_t k_rows = lds_address(lds_k[st]) + (col * KSTR + half * 8) * 2;
+        uint32_t v_rows = lds_address(lds_v[st]) + (col * VSTR + half * 8) * 2;
+        uint32_t k_tr = lds_address(lds_k[st]) + ((4 * half + tr_row) * KSTR + tr_col) * 2;
+        int bound = limit - t * BC - 4 * half;  // last visible key of the lane's half of a tile
+        asm volatile("" : "+v"(k_rows), "+v"(v_rows), "+v"(k_tr), "+v"(bound));
+        // step u of the two score products: (tensor, 16 columns, 32-key tile), the two tiles' chains alternating
+        auto row_read = [&](int u) __attribute__((always_inline)) {
+            const int ks = (u % (2 * KS)) / 2, kt = u & 1;
+            return u < 2 * KS ? lds_load_16B(k_rows + (kt * 32 * KSTR + ks * 16) * 2)
+                              : lds_load_16B(v_rows + (kt * 32 * VSTR + ks * 16) * 2);
+        };
+        auto tr_read = [&](int w) __attribute__((always_inline)) {  // step w of the dQ product: (16 keys, 32 columns)
+            const uint32_t a = k_tr + ((w / DT) * 16 * KSTR + (w % DT) * 32) * 2;
+            const i32x2 lo = lds_read_tr16(a), hi = lds_read_tr16(a + 8 * KSTR * 2);
+            return i32x4{lo[0], lo[1], hi[0], hi[1]};
+        };
+        f32x16 sacc[2], pacc[2];
+        i32x4 ring[KP], tr[KP], dsb[4];
+#pragma unroll
+        for (int u = 0; u < KP; ++u) ring[u] = row_read(u);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 4 * KS; ++u) {
+            const int ks = (u % (2 * KS)) / 2, kt = u & 1;
+            const i32x4 a = ring[u % KP];
+            if (u + KP < 4 * KS) ring[u % KP] = row_read(u + KP);
+            else tr[u + KP - 4 * KS] = tr_read(u + KP - 4 * KS);
+            if (u < 2) MfmaVgprAcc<Tag>::first(sacc[kt], a, qreg[ks]);
+            else if (u < 2 * KS) MfmaVgprAcc<Tag>::run(sacc[kt], a, qreg[ks]);
+            else MfmaVgprAcc<Tag>::run(pacc[kt], a, doreg[ks]);
+            if (u < 16) pacc[0][u] = pacc[1][u] = -d_row;  // dP - D comes out of the MFMAs
+            if (u == 2 * KS) mfma_result_wait(sacc[0], sacc[1]);
+            if (u >= 2 * KS) {
+                const int n = u - 2 * KS, i = n >> 4, r = n & 15;
+                float x = fast_exp2(__builtin_fmaf(sacc[i][r], sc, -l2));
+                if constexpr (MASK) x = i * 32 + 8 * (r >> 2) + (r & 3) > bound ? 0.f : x;
+                sacc[i][r] = x;
+            }
+            if (u % (2 * KS / NCH) == 0) load_chunk(t + 1, u / (2 * KS / NCH));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        mfma_result_wait(pacc[0], pacc[1]);
+        auto gradient = [&](int i, int r) __attribute__((always_inline)) {  // a pair of scores becomes a register of dS
+            dsb[2 * i + (r >> 3)][(r >> 1) & 3] = E::pack2(sacc[i][r] * pacc[i][r], sacc[i][r + 1] * pacc[i][r + 1]);
+        };
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) gradient(0, r);
+#pragma unroll
+        for (int w = 0; w < 4 * DT; ++w) {
+            const i32x4 a = tr[w % KP];
+            if (w + KP < 4 * DT) tr[w % KP] = tr_read(w + KP);
+            acc[w % DT] = E::mma(a, dsb[w / DT], acc[w % DT]);
+            if (w < 16 && !(w & 1)) gradient(1, w);
+            if (w % (4 * DT / (2 * NCH)) == 0) store_chunk(st ^ 1, w / (4 * DT / (2 * NCH)));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+    };
+    const int last_q = min(qt * BR + BR, N) - 1;
+    const int n_blocks = CAUSAL ? last_q / BC + 1 : (N + BC - 1) / BC;
+    // blocks that need no mask: all their keys exist and (causal) precede every row of the workgroup
+    const int n_plain = min(n_blocks, CAUSAL ? min(qt * BR + 1, N) / BC : N / BC);
+    int t = 0;
+    for (; t < n_plain; ++t) block(t, std::false_type{});
+    for (; t < n_blocks; ++t) block(t, std::true_type{});
+
+    // dQ_i = scale * acc, transposed into whole 128-byte lines through the K buffers (every read of them is behind the
+    // last barrier; what the last block stored there nobody reads)
+    static_assert(sizeof(lds_k) >= 4 * 4096, "patches must fit");
+    store_rows_via_lds<Tag, DT>(acc, scale, reinterpret_cast<char*>(&lds_k[0][0]) + wave * 4096,
+                                make_buffer(dq + head_off, (uint32_t)N * D * 2), wave_q0, lane);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1418,9 +1532,8 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
     constexpr int kKeys = D == 256 ? 64 : 128;  // keys per workgroup of the dK/dV pass
     const int n_kblocks = (N + kKeys - 1) / kKeys;
     const long total = (long)B * H_kv * n_kblocks;
-    constexpr int BC = 64, NW = D == 256 ? 4 : 8;  // d = 256: a wave needs the whole register file
-    const int n_qtiles = (N + NW * 32 - 1) / (NW * 32);
-    const long total_q = (long)B * H * n_qtiles;
+    constexpr int kRows = D == 256 ? 128 : 256;  // queries per workgroup of the dQ pass (d = 256: a wave needs a SIMD to itself)
+    const long total_q = (long)B * H * ((N + kRows - 1) / kRows);
     if (total > 0x7fffffffL || total_q > 0x7fffffffL) return FA_ERR_SHAPE;
 
     // the dQ pass first: it also writes D, which the dK/dV pass reads
@@ -1444,8 +1557,11 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
             dq_done = true;
         }
     }
-    if (!dq_done)
-        causal ? dqp(fa_bwd_dq_kernel<Tag, D, BC, NW, true>, NW * 32) : dqp(fa_bwd_dq_kernel<Tag, D, BC, NW, false>, NW * 32);
+    if constexpr (D == 256) {
+        causal ? dqp(fa_bwd_dq_d256_kernel<Tag, true>, 128) : dqp(fa_bwd_dq_d256_kernel<Tag, false>, 128);
+    } else {
+        if (!dq_done) causal ? dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, true>, 256) : dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, false>, 256);
+    }
     if (hipGetLastError() != hipSuccess) return FA_ERR_LAUNCH;
 
     auto dkdv = [&](auto kernel) {
