@@ -69,6 +69,23 @@ static __device__ __forceinline__ i32x4 sum_parts(const float* p, int stride, fl
     return out;
 }
 
+// D = rowsum(dO o O) in a launch of its own, for the one that runs both passes at once (fa_bwd_few_kernel); otherwise
+// the dQ pass computes it.
+template <typename Tag, int D>
+__global__ void __launch_bounds__(256)
+fa_bwd_rowsum_kernel(const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout, float* __restrict__ dvec, long rows) {
+    constexpr int LPR = D / 8;  // lanes per row, 8 elements each
+    const int part = threadIdx.x & (LPR - 1);
+    const long row = (long)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
+    float acc = 0.f;
+    if (row < rows)
+        acc = dot8<Tag>(*reinterpret_cast<const i32x4*>(o + row * D + part * 8),
+                        *reinterpret_cast<const i32x4*>(dout + row * D + part * 8), 0.f);
+#pragma unroll
+    for (int off = LPR / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    if (row < rows && part == 0) dvec[row] = acc;
+}
+
 // ---------------------------------------------------------------------------------------
 template <typename Tag, int D, bool CAUSAL>
 __global__ void __launch_bounds__(256, 2)
@@ -816,6 +833,12 @@ struct WaveTiles {
     }
 };
 
+// LDS of the kernels below: two stages of four waves' tiles, reused for the partial sums at the end
+constexpr int few_lds_bytes(int d) {
+    const int staging = 4 * 2 * 2 * 32 * d * 2, partial = 4 * 2 * 32 * (d + 4) * 4;
+    return staging > partial ? staging : partial;
+}
+
 // ---------------------------------------------------------------------------------------
 // dK/dV pass for launches that leave the chip idle (few key/value heads, short sequences), d = 64 and 128.
 //
@@ -827,29 +850,26 @@ struct WaveTiles {
 // bf16, B = 1, H = 32 on 4 K/V heads, N = 2048, d = 128, causal (64 workgroups of 128 keys, the longest 256 iterations):
 // whole backward 476 -> 223 us.
 template <typename Tag, int D, bool CAUSAL>
-__global__ void __launch_bounds__(256, D == 64 ? 2 : 1)
-fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-                       const uint16_t* __restrict__ dout, const float* __restrict__ lse,
-                       const float* __restrict__ dvec, uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int N,
-                       int n_heads, int kv_group, float scale) {
-    [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
+static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                                                const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
+                                                const float* __restrict__ lse, const float* __restrict__ dvec,
+                                                uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int N, int n_heads,
+                                                int kv_group, float scale, char* lds, float* lds_ld_all) {
     using Tiles = WaveTiles<D>;
     constexpr int NW = 4, BQ = Tiles::ROWS, BK = 32;
     constexpr int KS = D / 16, DT = D / 32, CPR = D / 8;
     constexpr int KP = 4;                       // steps by which operand reads lead their MFMAs
     constexpr int PSTR = D + 4;                 // row stride of the partial sums (floats)
-    constexpr int STAGING_B = NW * 2 * Tiles::STAGE_B, PARTIAL_B = NW * 2 * BK * PSTR * 4;
+    static_assert(few_lds_bytes(D) >= NW * 2 * BK * PSTR * 4, "partial sums must fit");
     using E = Elem<Tag>;
-    __shared__ __attribute__((aligned(1024))) char lds[STAGING_B > PARTIAL_B ? STAGING_B : PARTIAL_B];
-    __shared__ __attribute__((aligned(16))) float lds_ld[NW][2 * BQ];  // L (log2 units), then -D, of a wave's tile
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int col = lane & 31, half = lane >> 5;
     // key blocks of equal index one after the other over the heads: under a causal mask the longest come first, and
     // with a multiple of 8 heads all blocks of a head stay on one XCD
-    const int bh = blockIdx.x % n_heads;
-    const int key0 = (blockIdx.x / n_heads) * BK;
+    const int bh = block % n_heads;
+    const int key0 = (block / n_heads) * BK;
     const size_t head_off = (size_t)bh * N * D;
     const int my_key = key0 + col;
     float sc = scale * kLog2e;
@@ -869,6 +889,7 @@ fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
 #pragma unroll
         for (int r = 0; r < 16; ++r) dkacc[dt][r] = dvacc[dt][r] = 0.f;
 
+    float* lds_ld = lds_ld_all + wave * 2 * BQ;  // L (log2 units), then -D, of the wave's tile
     const Tiles tiles(lds_address(lds) + wave * 2 * Tiles::STAGE_B, lane);  // Q, dO
     const int n_t = (N + BQ - 1) / BQ, t0 = CAUSAL ? key0 / BQ : 0;
 
@@ -888,7 +909,7 @@ fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
     auto tile = [&](uint32_t base, int q0, int t_next, int st_next) __attribute__((always_inline)) {
         f32x4 l4[4];
         f32x16 sacc, pacc;
-        const uint32_t ld = lds_address(lds_ld[wave]) + 16 * half;
+        const uint32_t ld = lds_address(lds_ld) + 16 * half;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {  // register r of 16 is query row 8 (r / 4) + 4 half + r % 4
             l4[i] = lds_load_4f(ld + 32 * i);
@@ -972,7 +993,7 @@ fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
         // lanes compute goes to rows of dK and dV that are not stored.)
         const float x = ldrow < N ? (half ? -ldpre : ldpre * kLog2e) : (half ? 0.f : INFINITY);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this tile has landed
-        lds_ld[wave][lane] = x;
+        lds_ld[lane] = x;
         t += NW;
         settle();
         aim(gi, t);
@@ -1000,6 +1021,170 @@ fa_bwd_dkdv_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
         const i32x4 w = sum_parts<Tag, NW>(part + row * PSTR + cc, 2 * BK * PSTR, row < BK ? scale : 1.0f);
         if (key < N) *reinterpret_cast<i32x4*>((row < BK ? dk : dv) + head_off + (size_t)key * D + cc) = w;
     }
+}
+
+// The dQ pass for such launches: the same division the other way round.  A workgroup
+// owns 32 queries and its four waves split the keys (tiles of 32, staged by the wave that works them), each with a dQ
+// accumulator; the four partial sums meet in the LDS at the end, in a fixed order.
+// bf16, B = 1, H = 4, N = 1024: whole backward 54 -> 27 us at d = 128, 33 -> 18 us at d = 64.
+template <typename Tag, int D, bool CAUSAL>
+static __device__ __forceinline__ void dq_few(int block, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                                              const uint16_t* __restrict__ v, const uint16_t* __restrict__ o,
+                                              const uint16_t* __restrict__ dout, const float* __restrict__ lse,
+                                              float* __restrict__ dvec, bool d_ready, uint16_t* __restrict__ dq, int N,
+                                              int n_heads, int kv_group, float scale, char* lds) {
+    using Tiles = WaveTiles<D>;
+    constexpr int NW = 4, BQ = 32, BK = Tiles::ROWS;
+    constexpr int KS = D / 16, DT = D / 32, CPR = D / 8;
+    constexpr int KP = 4;        // steps by which operand reads lead their MFMAs
+    constexpr int PSTR = D + 4;  // row stride of the partial sums (floats)
+    using E = Elem<Tag>;
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int col = lane & 31, half = lane >> 5;
+    // tiles of equal index one after the other over the heads (all of a head on one XCD when their number is a
+    // multiple of 8); causal: the longest rows first
+    const int bh = block % n_heads;
+    const int n_t = (N + BK - 1) / BK;
+    const int qt = CAUSAL ? n_t - 1 - block / n_heads : block / n_heads;
+    const int q0 = qt * BQ;
+    const int row = min(q0 + col, N - 1);  // rows past N compute a copy of row N-1, never stored
+    const int limit = CAUSAL ? row : N - 1;  // last visible key
+    const size_t head_off = (size_t)bh * N * D;
+    const size_t kv_off = (size_t)(bh / kv_group) * N * D;
+    float sc = scale * kLog2e;
+    asm volatile("" : "+v"(sc));
+    const BufferWords k_rsrc = make_buffer_words(k + kv_off, (uint32_t)N * D * 2);
+    const BufferWords v_rsrc = make_buffer_words(v + kv_off, (uint32_t)N * D * 2);
+    const Tiles tiles(lds_address(lds) + wave * 2 * Tiles::STAGE_B, lane);  // K, V
+
+    const int n_tiles = CAUSAL ? qt + 1 : n_t;
+#pragma unroll
+    for (int n = 0; n < Tiles::NREQ; ++n) tiles.request(k_rsrc, v_rsrc, wave, 0, n);
+
+    i32x4 qreg[KS], doreg[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const size_t off = head_off + (size_t)row * D + ks * 16 + half * 8;
+        qreg[ks] = *reinterpret_cast<const i32x4*>(q + off);
+        doreg[ks] = *reinterpret_cast<const i32x4*>(dout + off);
+    }
+    float d_row = 0.f;  // D = rowsum(dO o O)
+    if (d_ready) {
+        d_row = dvec[(size_t)bh * N + row];
+    } else {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            d_row = dot8<Tag>(*reinterpret_cast<const i32x4*>(o + head_off + (size_t)row * D + ks * 16 + half * 8), doreg[ks], d_row);
+        d_row = sum_both_halves(d_row);
+        if (wave == 0 && half == 0 && q0 + col < N) dvec[(size_t)bh * N + q0 + col] = d_row;
+    }
+    const float l2 = lse[(size_t)bh * N + row] * kLog2e;
+    f32x16 acc[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[dt][r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(qreg[ks]), "+a"(doreg[ks]));
+
+    int st = 0;
+    for (int t = wave; t < n_tiles; t += NW, st ^= 1) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this tile has landed
+        const uint32_t base = tiles.stage0 + st * Tiles::STAGE_B;
+        auto row_read = [&](int u) { return tiles.row_read(base + (u < KS ? 0 : Tiles::TILE_B), u % KS); };
+        f32x16 sacc, pacc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) pacc[r] = -d_row;  // dP - D comes out of the MFMAs
+        i32x4 ring[KP], tr[KP], dsb[2];
+#pragma unroll
+        for (int u = 0; u < KP; ++u) ring[u] = row_read(u);
+        __builtin_amdgcn_sched_barrier(0);
+        int bound = limit - t * BK - 4 * half;  // key 8 (r / 4) + r % 4 of the lane's half is visible up to here
+        asm volatile("" : "+v"(bound));
+        // S^T, then dP^T beside P
+#pragma unroll
+        for (int u = 0; u < 2 * KS; ++u) {
+            const i32x4 a = ring[u % KP];
+            if (u + KP < 2 * KS) ring[u % KP] = row_read(u + KP);
+            else tr[u + KP - 2 * KS] = tiles.tr_read(base, (u + KP - 2 * KS) / DT, (u + KP - 2 * KS) % DT);
+            // past this workgroup's last tile these bring rows (or zeros) that nothing reads
+            tiles.request(k_rsrc, v_rsrc, t + NW, st ^ 1, u);
+            if (u == 0) MfmaVgprAcc<Tag>::first(sacc, a, qreg[u]);
+            else if (u < KS) MfmaVgprAcc<Tag>::run(sacc, a, qreg[u]);
+            else MfmaVgprAcc<Tag>::run(pacc, a, doreg[u - KS]);
+            if (u == KS) mfma_result_wait(sacc);
+            if (u >= KS) {
+#pragma unroll
+                for (int n = 0; n < 16 / KS; ++n) {
+                    const int r = (u - KS) * (16 / KS) + n;
+                    sacc[r] = fast_exp2(__builtin_fmaf(sacc[r], sc, -l2));
+                    // keys past N (K = 0, but their P may be anything) and keys after the query
+                    if (8 * (r >> 2) + (r & 3) > bound) sacc[r] = 0.f;
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        mfma_result_wait(pacc);
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int r = 8 * s2 + 2 * e;
+                dsb[s2][e] = E::pack2(sacc[r] * pacc[r], sacc[r + 1] * pacc[r + 1]);
+            }
+        // dQ^T += K^T dS^T
+#pragma unroll
+        for (int u = 0; u < 2 * DT; ++u) {
+            const i32x4 a = tr[u % KP];
+            if (u + KP < 2 * DT) tr[u % KP] = tiles.tr_read(base, (u + KP) / DT, (u + KP) % DT);
+            acc[u % DT] = E::mma(a, dsb[u / DT], acc[u % DT]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last request: the LDS is about to be reused
+
+    // ---- sum of the four waves' parts, wave 0 first
+    __syncthreads();
+    float* part = reinterpret_cast<float*>(lds);  // [wave][query][PSTR]
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 w = {acc[dt][4 * g], acc[dt][4 * g + 1], acc[dt][4 * g + 2], acc[dt][4 * g + 3]};
+            *reinterpret_cast<f32x4*>(part + (wave * BQ + col) * PSTR + dt * 32 + 8 * g + 4 * half) = w;
+        }
+    __syncthreads();
+#pragma nounroll
+    for (int c = tid; c < BQ * CPR; c += 256) {
+        const int r = c / CPR, cc = (c % CPR) * 8;
+        const i32x4 w = sum_parts<Tag, NW>(part + r * PSTR + cc, BQ * PSTR, scale);
+        if (q0 + r < N) *reinterpret_cast<i32x4*>(dq + head_off + (size_t)(q0 + r) * D + cc) = w;
+    }
+}
+
+// One launch for either pass or for both: workgroups 0 .. n_dkdv - 1 take 32 keys each, the rest 32 queries each.
+// With both in one launch (`d_ready`: D is in the workspace already) the dQ work fills the CUs that the shorter key
+// blocks of a causal dK/dV pass leave idle.
+// bf16 causal, whole backward, us, two launches / one and the row sums: d = 128 H = 4, N = 1024 27 / 17, H = 16 on 4,
+// N = 2048 126 / 97, H = 32 on 4, N = 2048 217 / 195; d = 64 H = 16, N = 1024 22.5 / 18.9.  Where neither pass leaves
+// CUs idle the two take the same time.
+template <typename Tag, int D, bool CAUSAL>
+__global__ void __launch_bounds__(256, D == 64 ? 2 : 1)
+fa_bwd_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                  const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
+                  float* __restrict__ dvec, int d_ready, uint16_t* __restrict__ dq, uint16_t* __restrict__ dk,
+                  uint16_t* __restrict__ dv, int N, int n_dkdv, int n_heads, int kv_group, float scale) {
+    [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
+    __shared__ __attribute__((aligned(1024))) char lds[few_lds_bytes(D)];
+    __shared__ __attribute__((aligned(16))) float lds_ld[4 * 64];
+    const int block = blockIdx.x;
+    if (block < n_dkdv)
+        dkdv_few<Tag, D, CAUSAL>(block, q, k, v, dout, lse, dvec, dk, dv, N, n_heads / kv_group, kv_group, scale, lds, lds_ld);
+    else
+        dq_few<Tag, D, CAUSAL>(block - n_dkdv, q, k, v, o, dout, lse, dvec, d_ready, dq, N, n_heads, kv_group, scale, lds);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1352,152 +1537,13 @@ fa_bwd_dq_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
 }
 
 // ---------------------------------------------------------------------------------------
-// dQ pass for launches that leave the chip idle, d = 64 and 128: the same division the other way round.  A workgroup
-// owns 32 queries and its four waves split the keys (tiles of 32, staged by the wave that works them), each with a dQ
-// accumulator; the four partial sums meet in the LDS at the end, in a fixed order.
-// bf16, B = 1, H = 4, N = 1024: whole backward 54 -> 27 us at d = 128, 33 -> 18 us at d = 64.
-template <typename Tag, int D, bool CAUSAL>
-__global__ void __launch_bounds__(256, D == 64 ? 2 : 1)
-fa_bwd_dq_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-                     const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
-                     float* __restrict__ dvec, uint16_t* __restrict__ dq, int N, int n_heads, int kv_group, float scale) {
-    [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
-    using Tiles = WaveTiles<D>;
-    constexpr int NW = 4, BQ = 32, BK = Tiles::ROWS;
-    constexpr int KS = D / 16, DT = D / 32, CPR = D / 8;
-    constexpr int KP = 4;        // steps by which operand reads lead their MFMAs
-    constexpr int PSTR = D + 4;  // row stride of the partial sums (floats)
-    constexpr int STAGING_B = NW * 2 * Tiles::STAGE_B, PARTIAL_B = NW * BQ * PSTR * 4;
-    using E = Elem<Tag>;
-    __shared__ __attribute__((aligned(1024))) char lds[STAGING_B > PARTIAL_B ? STAGING_B : PARTIAL_B];
-
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int col = lane & 31, half = lane >> 5;
-    // tiles of equal index one after the other over the heads (all of a head on one XCD when their number is a
-    // multiple of 8); causal: the longest rows first
-    const int bh = blockIdx.x % n_heads;
-    const int n_t = (N + BK - 1) / BK;
-    const int qt = CAUSAL ? n_t - 1 - blockIdx.x / n_heads : blockIdx.x / n_heads;
-    const int q0 = qt * BQ;
-    const int row = min(q0 + col, N - 1);  // rows past N compute a copy of row N-1, never stored
-    const int limit = CAUSAL ? row : N - 1;  // last visible key
-    const size_t head_off = (size_t)bh * N * D;
-    const size_t kv_off = (size_t)(bh / kv_group) * N * D;
-    float sc = scale * kLog2e;
-    asm volatile("" : "+v"(sc));
-    const BufferWords k_rsrc = make_buffer_words(k + kv_off, (uint32_t)N * D * 2);
-    const BufferWords v_rsrc = make_buffer_words(v + kv_off, (uint32_t)N * D * 2);
-    const Tiles tiles(lds_address(lds) + wave * 2 * Tiles::STAGE_B, lane);  // K, V
-
-    const int n_tiles = CAUSAL ? qt + 1 : n_t;
-#pragma unroll
-    for (int n = 0; n < Tiles::NREQ; ++n) tiles.request(k_rsrc, v_rsrc, wave, 0, n);
-
-    i32x4 qreg[KS], doreg[KS];
-    float d_row = 0.f;  // D = rowsum(dO o O)
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        const size_t off = head_off + (size_t)row * D + ks * 16 + half * 8;
-        qreg[ks] = *reinterpret_cast<const i32x4*>(q + off);
-        doreg[ks] = *reinterpret_cast<const i32x4*>(dout + off);
-        d_row = dot8<Tag>(*reinterpret_cast<const i32x4*>(o + off), doreg[ks], d_row);
-    }
-    d_row = sum_both_halves(d_row);
-    if (wave == 0 && half == 0 && q0 + col < N) dvec[(size_t)bh * N + q0 + col] = d_row;
-    const float l2 = lse[(size_t)bh * N + row] * kLog2e;
-    f32x16 acc[DT];
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[dt][r] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(qreg[ks]), "+a"(doreg[ks]));
-
-    int st = 0;
-    for (int t = wave; t < n_tiles; t += NW, st ^= 1) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this tile has landed
-        const uint32_t base = tiles.stage0 + st * Tiles::STAGE_B;
-        auto row_read = [&](int u) { return tiles.row_read(base + (u < KS ? 0 : Tiles::TILE_B), u % KS); };
-        f32x16 sacc, pacc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) pacc[r] = -d_row;  // dP - D comes out of the MFMAs
-        i32x4 ring[KP], tr[KP], dsb[2];
-#pragma unroll
-        for (int u = 0; u < KP; ++u) ring[u] = row_read(u);
-        __builtin_amdgcn_sched_barrier(0);
-        int bound = limit - t * BK - 4 * half;  // key 8 (r / 4) + r % 4 of the lane's half is visible up to here
-        asm volatile("" : "+v"(bound));
-        // S^T, then dP^T beside P
-#pragma unroll
-        for (int u = 0; u < 2 * KS; ++u) {
-            const i32x4 a = ring[u % KP];
-            if (u + KP < 2 * KS) ring[u % KP] = row_read(u + KP);
-            else tr[u + KP - 2 * KS] = tiles.tr_read(base, (u + KP - 2 * KS) / DT, (u + KP - 2 * KS) % DT);
-            // past this workgroup's last tile these bring rows (or zeros) that nothing reads
-            tiles.request(k_rsrc, v_rsrc, t + NW, st ^ 1, u);
-            if (u == 0) MfmaVgprAcc<Tag>::first(sacc, a, qreg[u]);
-            else if (u < KS) MfmaVgprAcc<Tag>::run(sacc, a, qreg[u]);
-            else MfmaVgprAcc<Tag>::run(pacc, a, doreg[u - KS]);
-            if (u == KS) mfma_result_wait(sacc);
-            if (u >= KS) {
-#pragma unroll
-                for (int n = 0; n < 16 / KS; ++n) {
-                    const int r = (u - KS) * (16 / KS) + n;
-                    sacc[r] = fast_exp2(__builtin_fmaf(sacc[r], sc, -l2));
-                    // keys past N (K = 0, but their P may be anything) and keys after the query
-                    if (8 * (r >> 2) + (r & 3) > bound) sacc[r] = 0.f;
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        mfma_result_wait(pacc);
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int r = 8 * s2 + 2 * e;
-                dsb[s2][e] = E::pack2(sacc[r] * pacc[r], sacc[r + 1] * pacc[r + 1]);
-            }
-        // dQ^T += K^T dS^T
-#pragma unroll
-        for (int u = 0; u < 2 * DT; ++u) {
-            const i32x4 a = tr[u % KP];
-            if (u + KP < 2 * DT) tr[u % KP] = tiles.tr_read(base, (u + KP) / DT, (u + KP) % DT);
-            acc[u % DT] = E::mma(a, dsb[u / DT], acc[u % DT]);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last request: the LDS is about to be reused
-
-    // ---- sum of the four waves' parts, wave 0 first
-    __syncthreads();
-    float* part = reinterpret_cast<float*>(lds);  // [wave][query][PSTR]
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const f32x4 w = {acc[dt][4 * g], acc[dt][4 * g + 1], acc[dt][4 * g + 2], acc[dt][4 * g + 3]};
-            *reinterpret_cast<f32x4*>(part + (wave * BQ + col) * PSTR + dt * 32 + 8 * g + 4 * half) = w;
-        }
-    __syncthreads();
-#pragma nounroll
-    for (int c = tid; c < BQ * CPR; c += 256) {
-        const int r = c / CPR, cc = (c % CPR) * 8;
-        const i32x4 w = sum_parts<Tag, NW>(part + r * PSTR + cc, BQ * PSTR, scale);
-        if (q0 + r < N) *reinterpret_cast<i32x4*>(dq + head_off + (size_t)(q0 + r) * D + cc) = w;
-    }
-}
-
-// ---------------------------------------------------------------------------------------
 size_t bwd_workspace_bytes(int B, int H, int N, int d) {
     (void)d;
     size_t rows = (size_t)B * H * N;
     return (rows * sizeof(float) + 15) & ~(size_t)15;  // D = rowsum(dO o O)
 }
 
-// Up to how many 128-key workgroups the dK/dV pass uses fa_bwd_dkdv_few_kernel instead: on fewer workgroups than CUs
+// Up to how many 128-key workgroups the dK/dV pass uses the 32-key form instead: on fewer workgroups than CUs
 // the 32-key form's four-fold parallelism wins until its operand traffic costs as much.  Whole backward, B = 1, bf16,
 // us, 128-key / 32-key form:
 //   d = 128  no mask: 128 workgroups 74 / 69 (H = 16, N = 1024), 160 88 / 96 (H = 16, N = 1280)
@@ -1505,12 +1551,19 @@ size_t bwd_workspace_bytes(int B, int H, int N, int d) {
 //   d = 64   no mask: 160 55 / 53, 192 46.2 / 45.0, 256 46.5 / 51;  causal: 256 47 / 44 (N = 1024), 384 86 / 84 (N = 2048)
 constexpr long few_key_blocks(int d, int causal) { return d == 64 ? (causal ? 384 : 192) : (causal ? 192 : 128); }
 
-// Up to how many 256-query workgroups the dQ pass uses fa_bwd_dq_few_kernel instead.  Whole backward, B = 1, bf16, us,
+// Up to how many 256-query workgroups the dQ pass uses the 32-query form instead.  Whole backward, B = 1, bf16, us,
 // 256-query / 32-query form:
 //   d = 128  no mask: 64 workgroups 69 / 55 (H = 16, N = 1024), 96 466 / 404 (H = 3, N = 8192), 128 81 / 90 (H = 32)
 //            causal:  64 74 / 54, 128 76 / 74 (N = 1024) and 130 / 112 (N = 2048), 192 134 / 141 (H = 24, N = 2048)
 //   d = 64   no mask: 64 39 / 28, 96 279 / 238, 128 46.5 / 49.7;  causal: 192 86 / 80 (N = 2048), 256 141 / 146 (H = 32 on 4)
-constexpr long few_query_tiles(int d, int causal) { return causal ? (d == 64 ? 192 : 128) : 96; }
+// With few key blocks (shared key/value heads) the dK/dV pass takes its 32-key form, and a dQ pass in the same launch
+// (fa_bwd_few_kernel) is worth more: 256, where the eight-wave form in a launch of its own / this one measured
+//   d = 128  causal:  64 key blocks 217 / 195 (H = 32 on 4, N = 2048), 128 164 / 190 (on 8);  no mask: 64 249 / 308
+//   d = 64   causal: 128 103 / 90 (H = 32 on 8, N = 2048);  no mask: 64 153 / 151 (on 4), 32 66 / 60 (H = 32 on 2, N = 512)
+constexpr long few_query_tiles(int d, int causal, long key_blocks) {
+    if (key_blocks <= (d == 64 ? (causal ? 128 : 64) : (causal ? 64 : 0))) return 256;
+    return causal ? (d == 64 ? 192 : 128) : 96;
+}
 
 // Up to which length the dQ pass takes 128-query workgroups of four waves with 32-key blocks, two or three to a CU,
 // instead of 256-query ones of eight with 64-key blocks: finer tiles waste less on the diagonal and on ragged ends, and
@@ -1536,31 +1589,48 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
     const long total_q = (long)B * H * ((N + kRows - 1) / kRows);
     if (total > 0x7fffffffL || total_q > 0x7fffffffL) return FA_ERR_SHAPE;
 
-    // the dQ pass first: it also writes D, which the dK/dV pass reads
+    // Two launches, the dQ pass first: it also writes D, which the dK/dV pass reads.  Or, with both passes in their
+    // few-workgroup forms, D and then both in one launch.
     auto dqp = [&](auto kernel, int rows) {  // `rows`: queries, and threads / 2, of a workgroup
         const int tiles = (N + rows - 1) / rows, items = B * H * tiles;
         hipLaunchKernelGGL(kernel, dim3((unsigned)items), dim3(rows * 2), 0, stream, u16(q), u16(k), u16(v), u16(o),
                            u16(dout), lse, dvec, static_cast<uint16_t*>(dq), N, tiles, items, H / H_kv, scale);
     };
-    bool dq_done = false;
+    // workgroups of 32 queries / of 32 keys, when a pass is to use them
+    long dq_few = 0, dkdv_few = 0;
     if constexpr (D <= 128) {
-        const long few = (long)B * H * ((N + 31) / 32);
-        if (total_q <= few_query_tiles(D, causal) && few <= 0x7fffffffL) {
+        if (total_q <= few_query_tiles(D, causal, total)) dq_few = (long)B * H * ((N + 31) / 32);
+        if (total <= few_key_blocks(D, causal)) dkdv_few = (long)B * H_kv * ((N + 31) / 32);
+    }
+    auto few = [&](long n_dkdv, long n_dq, int d_ready) {
+        if constexpr (D <= 128) {
             auto run = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, dim3((unsigned)few), dim3(256), 0, stream, u16(q), u16(k), u16(v), u16(o),
-                                   u16(dout), lse, dvec, static_cast<uint16_t*>(dq), N, B * H, H / H_kv, scale);
+                hipLaunchKernelGGL(kernel, dim3((unsigned)(n_dkdv + n_dq)), dim3(256), 0, stream, u16(q), u16(k), u16(v),
+                                   u16(o), u16(dout), lse, dvec, d_ready, static_cast<uint16_t*>(dq),
+                                   static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv), N, (int)n_dkdv, B * H, H / H_kv, scale);
             };
-            causal ? run(fa_bwd_dq_few_kernel<Tag, D, true>) : run(fa_bwd_dq_few_kernel<Tag, D, false>);
-            dq_done = true;
-        } else if (N <= short_rows(D, causal) && (long)B * H * ((N + 127) / 128) <= 0x7fffffffL) {
-            causal ? dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, true>, 128) : dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, false>, 128);
-            dq_done = true;
+            causal ? run(fa_bwd_few_kernel<Tag, D, true>) : run(fa_bwd_few_kernel<Tag, D, false>);
+        }
+    };
+    if constexpr (D <= 128) {
+        if (dq_few && dkdv_few) {
+            const long rows = (long)B * H * N;
+            constexpr int kRowsPerWg = 256 / (D / 8);
+            hipLaunchKernelGGL((fa_bwd_rowsum_kernel<Tag, D>), dim3((unsigned)((rows + kRowsPerWg - 1) / kRowsPerWg)), dim3(256),
+                               0, stream, u16(o), u16(dout), dvec, rows);
+            if (hipGetLastError() != hipSuccess) return FA_ERR_LAUNCH;
+            few(dkdv_few, dq_few, 1);
+            return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
         }
     }
     if constexpr (D == 256) {
         causal ? dqp(fa_bwd_dq_d256_kernel<Tag, true>, 128) : dqp(fa_bwd_dq_d256_kernel<Tag, false>, 128);
+    } else if (dq_few) {
+        few(0, dq_few, 0);
+    } else if (N <= short_rows(D, causal)) {
+        causal ? dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, true>, 128) : dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, false>, 128);
     } else {
-        if (!dq_done) causal ? dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, true>, 256) : dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, false>, 256);
+        causal ? dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, true>, 256) : dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, false>, 256);
     }
     if (hipGetLastError() != hipSuccess) return FA_ERR_LAUNCH;
 
@@ -1569,19 +1639,8 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
                            dvec, static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv), N, n_kblocks, (int)total,
                            H / H_kv, scale);
     };
-    if constexpr (D <= 128) {
-        const long few = (long)B * H_kv * ((N + 31) / 32);
-        if (total <= few_key_blocks(D, causal) && few <= 0x7fffffffL) {
-            auto run = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, dim3((unsigned)few), dim3(256), 0, stream, u16(q), u16(k), u16(v), u16(dout),
-                                   lse, dvec, static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv), N, B * H_kv,
-                                   H / H_kv, scale);
-            };
-            causal ? run(fa_bwd_dkdv_few_kernel<Tag, D, true>) : run(fa_bwd_dkdv_few_kernel<Tag, D, false>);
-            return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
-        }
-    }
-    if constexpr (D == 64) causal ? dkdv(fa_bwd_dkdv_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_kernel<Tag, D, false>);
+    if (dkdv_few) few(dkdv_few, 0, 1);
+    else if constexpr (D == 64) causal ? dkdv(fa_bwd_dkdv_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_kernel<Tag, D, false>);
     else causal ? dkdv(fa_bwd_dkdv_shared_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_shared_kernel<Tag, D, false>);
     return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
 }

@@ -150,3 +150,11 @@ def test_causal_forward_paired_and_single_tiles(heads, N, d, fp8):
         o_ref, l_ref = oracle.attention_fwd(f64(q[:, h:h + 1]), f64(k), f64(v), d ** -0.5, True)
         assert max_abs(f64(o[:, h:h + 1]), o_ref) <= 2e-2 and rmse(f64(o[:, h:h + 1]), o_ref) <= 3e-3
         assert max_abs(f64(lse[:, h:h + 1]), l_ref) <= 2e-3
+
+
+@pytest.mark.parametrize("d,causal,H,H_kv", [(64, True, 256, 128), (64, True, 258, 129), (64, False, 256, 64),
+                                             (128, True, 256, 64), (128, True, 260, 65), (128, False, 96, 32)])
+def test_backward_both_passes_in_one_launch(d, causal, H, H_kv):
+    # shared heads on both sides of the rule that lets the dQ work join the 32-key dK/dV launch (N = 70: one 128-key
+    # block and one 256-query tile per head)
+    _check_backward(1100 + H, 1, H, H_kv, 70, d, causal, "bf16")
