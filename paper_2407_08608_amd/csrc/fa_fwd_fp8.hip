@@ -628,13 +628,18 @@ static int launch_fp8_async(const void* q8, const void* k8, const void* v8, cons
 
 enum class FwdFp8 { kTile4, kTile8, kNone };
 static FwdFp8 choose_fp8(int d, int N, int causal) {
-    // Short problems keep the 128-row tile of four waves (more workgroups, less waste on the diagonal); the
-    // crossovers were measured on block-scaled inputs at 16k tokens per launch (TFLOPs/s, four waves /
-    // eight: d = 128 causal 1280 keys 1119 / 961, 1536 keys 1220 / 1233; no mask 768 keys 1189 / 1186;
-    // d = 64 causal 8192 keys 1152 / 1141, no mask 512 keys 909 / 960).  d = 256 has no four-wave tile.
+    // Short problems keep the 128-row tile of four waves (more workgroups, less waste on the diagonal, and without a
+    // mask none on the second half of a 256-row tile when the number of 128-row tiles is odd).  Block-scaled inputs,
+    // about 16k tokens, H = 16, us, four waves / eight:
+    //   d = 64   causal:  N = 2048 70 / 76, 8192 235 / 246, 16384 455 / 475
+    //            no mask: 512 36 / 34, 800 59 / 64, 1024 63 / 59, 1150 71 / 78, 1300 87 / 94, 1700 100 / 96
+    //   d = 128  causal:  1300 80 / 89, 1410 85 / 89, 1600 89 / 97, 1700 93 / 89, 2048 104 / 97
+    //            no mask: 800 90 / 101, 1024 97 / 93, 1150 108 / 121, 1300 131 / 141, 1700 152 / 147
+    // d = 256 has no four-wave tile.
+    const bool odd = !causal && odd_row_tiles(N);
     switch (d) {
-        case 64: return (causal || N < 512) ? FwdFp8::kTile4 : FwdFp8::kTile8;
-        case 128: return N <= (causal ? 1280 : 704) ? FwdFp8::kTile4 : FwdFp8::kTile8;
+        case 64: return causal || N < 512 || (odd && N <= 1408) ? FwdFp8::kTile4 : FwdFp8::kTile8;
+        case 128: return N <= (causal ? 1664 : 704) || (odd && N <= 1408) ? FwdFp8::kTile4 : FwdFp8::kTile8;
         case 256: return FwdFp8::kTile8;
         default: return FwdFp8::kNone;
     }

@@ -9,6 +9,9 @@
 
 namespace fa {
 
+// Whether N rows make an odd number of 128-row tiles.
+inline bool odd_row_tiles(int N) { return ((N + 127) / 128) & 1; }
+
 // Whether a causal forward launch pairs its query tiles (query_tiles in fa_device.h): when the pairs fill whole rounds
 // of the chip, or nearly.  `slots`: workgroups of that kernel that the chip holds at once, 0 for kernels that never
 // pair; `slack` / 8: how much of the last round may be empty once there is more than one.  Measured causal, bf16 unless

@@ -128,7 +128,7 @@ def test_backward_query_tile_rule_edges(d, causal, N):
 
 @pytest.mark.parametrize("heads,N,d", [(64, 1500, 128), (128, 1500, 128), (512, 100, 128), (384, 200, 128), (100, 300, 128),
                                        (7, 1409, 128), (256, 129, 256), (300, 300, 256), (5, 700, 256), (9, 1300, 64),
-                                       (11, 200, 64)])
+                                       (11, 200, 64), (3, 2048, 64), (3, 2049, 64), (3, 1664, 128), (3, 1665, 128)])
 @pytest.mark.parametrize("fp8", [False, True])
 def test_causal_forward_paired_and_single_tiles(heads, N, d, fp8):
     # head counts on both sides of the rule that pairs causal query tiles, with odd and even tile counts; every row of
@@ -158,3 +158,19 @@ def test_backward_both_passes_in_one_launch(d, causal, H, H_kv):
     # shared heads on both sides of the rule that lets the dQ work join the 32-key dK/dV launch (N = 70: one 128-key
     # block and one 256-query tile per head)
     _check_backward(1100 + H, 1, H, H_kv, 70, d, causal, "bf16")
+
+
+@pytest.mark.parametrize("d,N", [(64, 641), (64, 769), (64, 768), (64, 1408), (64, 1409), (128, 897), (128, 1152), (128, 1153)])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_forward_tile_rule_edges(d, N, fp8):
+    # odd and even numbers of 128-row tiles, where the unmasked forward changes between 128- and 256-row workgroups
+    q, k, v = inputs.qkv(1200 + N, 1, 2, N, d, "bf16")
+    if fp8:
+        dev = [binding.fa_fp8_quant_hadamard(t.cuda()) for t in (q, k, v)]
+        o, lse = binding.fa_fwd_fp8(*(p[0] for p in dev), *(p[1] for p in dev), d ** -0.5, False)
+        codes = [[a.cpu().numpy() for a in p] for p in dev]
+        check_fp8_against_model_oracle(o, lse, [c[0] for c in codes], [c[1] for c in codes], d ** -0.5, False)
+        return
+    o, lse = binding.fa_fwd(q.cuda(), k.cuda(), v.cuda(), d ** -0.5, False)
+    o_ref, l_ref = oracle.attention_fwd(f64(q), f64(k), f64(v), d ** -0.5, False)
+    assert max_abs(f64(o), o_ref) <= 2e-2 and rmse(f64(o), o_ref) <= 3e-3 and max_abs(f64(lse), l_ref) <= 2e-3
