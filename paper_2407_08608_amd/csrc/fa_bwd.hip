@@ -69,6 +69,37 @@ static __device__ __forceinline__ i32x4 sum_parts(const float* p, int stride, fl
     return out;
 }
 
+// Stores a 32-key x 64-column fp32 accumulator pair (MFMA result layout with keys as rows: lane (col, half), register r
+// of tile dt is key 8 (r / 4) + 4 half + r % 4, column 32 dt + col) as 16-bit elements times `factor`.  Straight from
+// that layout a store instruction moves two bytes per lane, 128 of them per wave for dK and dV; instead neighbouring
+// lanes trade halves (an even lane keeps the even key of a pair, its neighbour the odd one), the tile goes through
+// `patch` (4 KiB of LDS private to the wave) as 4-byte words and leaves as whole 128-byte lines.  Rows past the end of
+// `rsrc` are dropped by the hardware.  bf16, whole backward, us, two-byte stores / so:
+// d = 128 causal B = 64, H = 16, N = 256 228 / 215, B = 32, N = 512 269 / 258, B = 4, N = 4096 952 / 946; d = 256 B = 32, N = 512 630 / 604.
+template <typename Tag, int ROWB>
+static __device__ __forceinline__ void store_keys_via_lds(const f32x16 (&acc)[2], float factor, char* patch,
+                                                          __amdgpu_buffer_rsrc_t rsrc, int key0, int col_byte, int lane) {
+    using E = Elem<Tag>;
+    const int col = lane & 31, half = lane >> 5, odd = lane & 1;
+    const uint32_t sel = odd ? 0x03020706u : 0x05040100u;  // odd key: (neighbour's high, own high); even: (own low, neighbour's low)
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+            const uint32_t w = (uint32_t)E::pack2(acc[dt][r] * factor, acc[dt][r + 1] * factor);
+            const uint32_t v = (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0xB1, 0xF, 0xF, true);  // lane ^ 1
+            const int key = 8 * (r >> 2) + 4 * half + (r & 3) + odd;
+            *reinterpret_cast<uint32_t*>(patch + key * 128 + ((dt * 64 + (col >> 1) * 4) ^ ((key & 4) << 3))) =
+                __builtin_amdgcn_perm(v, w, sel);
+        }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int key = 8 * i + (lane >> 3), pos = (lane & 7) * 16;
+        const i32x4 x = *reinterpret_cast<const i32x4*>(patch + key * 128 + (pos ^ ((key & 4) << 3)));
+        __builtin_amdgcn_raw_buffer_store_b128(x, rsrc, (key0 + key) * ROWB + col_byte + pos, 0, 0);
+    }
+}
+
 // D = rowsum(dO o O) in a launch of its own, for the one that runs both passes at once (fa_bwd_few_kernel); otherwise
 // the dQ pass computes it.
 template <typename Tag, int D>
@@ -400,18 +431,11 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
     for (; it < n_qtiles; ++it) iteration(it, std::false_type{});
     }  // query heads of the group
 
-    // ---- epilogue: dK_j = scale * acc, dV_j = acc  (rows = keys 8g+4h+r of this wave, col = d)
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            int key = key0 + wave * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-            if (key < N) {
-                size_t off = head_off + (size_t)key * D + dt * 32 + col;
-                dk[off] = (uint16_t)(E::pack2(dkacc[dt][r] * scale, 0.f) & 0xFFFF);
-                dv[off] = (uint16_t)(E::pack2(dvacc[dt][r], 0.f) & 0xFFFF);
-            }
-        }
+    // ---- epilogue: dK_j = scale * acc, dV_j = acc, through the tile buffers (every read of them is behind a barrier)
+    char* patch = reinterpret_cast<char*>(&lds_t[0][0]) + wave * 4096;
+    static_assert(sizeof(lds_t) >= 4 * 4096, "patches must fit");
+    store_keys_via_lds<Tag, D * 2>(dkacc, scale, patch, make_buffer(dk + head_off, (uint32_t)N * D * 2), key0 + wave * 32, 0, lane);
+    store_keys_via_lds<Tag, D * 2>(dvacc, 1.0f, patch, make_buffer(dv + head_off, (uint32_t)N * D * 2), key0 + wave * 32, 0, lane);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -758,20 +782,16 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
     for (; it < n_qtiles; ++it) iteration(it, std::false_type{});
     }  // query heads of the group
 
-    // ---- epilogue: dK_j = scale * acc, dV_j = acc  (rows = keys 8g+4h+r of a tile, col = d)
+    // ---- epilogue: dK_j = scale * acc, dV_j = acc, through the exchange buffers (every read of them is behind the last barrier)
+    char* patch = &lds_x[0][0] + wave * 4096;
+    static_assert(sizeof(lds_x) >= 4 * 4096, "patches must fit");
+    const __amdgpu_buffer_rsrc_t dk_rsrc = make_buffer(dk + head_off, (uint32_t)N * D * 2);
+    const __amdgpu_buffer_rsrc_t dv_rsrc = make_buffer(dv + head_off, (uint32_t)N * D * 2);
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int key = key0 + acc_tile(j) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                if (key < N) {
-                    const size_t off = head_off + (size_t)key * D + col0 + dt * 32 + col;
-                    dk[off] = (uint16_t)(E::pack2(dkacc[j][dt][r] * scale, 0.f) & 0xFFFF);
-                    dv[off] = (uint16_t)(E::pack2(dvacc[j][dt][r], 0.f) & 0xFFFF);
-                }
-            }
+    for (int j = 0; j < 2; ++j) {
+        store_keys_via_lds<Tag, D * 2>(dkacc[j], scale, patch, dk_rsrc, key0 + acc_tile(j) * 32, col0 * 2, lane);
+        store_keys_via_lds<Tag, D * 2>(dvacc[j], 1.0f, patch, dv_rsrc, key0 + acc_tile(j) * 32, col0 * 2, lane);
+    }
 }
 
 // ---------------------------------------------------------------------------------------
