@@ -22,8 +22,9 @@
  *   - The return value is an fa_status.  Every argument and size check precedes the first
  *     launch: on any status other than FA_OK and FA_ERR_LAUNCH nothing has been enqueued.
  *     FA_ERR_LAUNCH means the HIP runtime refused a launch; calls made of several kernels
- *     (fa_bwd*: two, fa_fp8_quant_hadamard with per_tensor = 1: four) stop at the refused
- *     one, and the outputs are then undefined.  fa_status_string() names a status.
+ *     (fa_bwd*: two, or three with dq == q or dq == dout; fa_fp8_quant_hadamard with
+ *     per_tensor = 1: four) stop at the refused one, and the outputs are then undefined.
+ *     fa_status_string() names a status.
  *   - Supported head dimensions: d in {64, 128, 256}.  N >= 1 (any N; rows past N are
  *     never read or written).  B, H >= 1.  scale finite and > 0.  causal in {0, 1};
  *     causal means key j is visible to query i iff j <= i (N_q == N_k).

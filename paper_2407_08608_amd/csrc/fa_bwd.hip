@@ -100,8 +100,8 @@ static __device__ __forceinline__ void store_keys_via_lds(const f32x16 (&acc)[2]
     }
 }
 
-// D = rowsum(dO o O) in a launch of its own, for the one that runs both passes at once (fa_bwd_few_kernel); otherwise
-// the dQ pass computes it.
+// D = rowsum(dO o O) in a launch of its own, where the dK/dV pass cannot wait for the dQ pass to compute it: both passes
+// in one launch (fa_bwd_few_kernel), or dQ written over an input of the dK/dV pass.
 template <typename Tag, int D>
 __global__ void __launch_bounds__(256)
 fa_bwd_rowsum_kernel(const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout, float* __restrict__ dvec, long rows) {
@@ -1632,37 +1632,52 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
             causal ? run(fa_bwd_few_kernel<Tag, D, true>) : run(fa_bwd_few_kernel<Tag, D, false>);
         }
     };
-    if constexpr (D <= 128) {
-        if (dq_few && dkdv_few) {
-            const long rows = (long)B * H * N;
-            constexpr int kRowsPerWg = 256 / (D / 8);
-            hipLaunchKernelGGL((fa_bwd_rowsum_kernel<Tag, D>), dim3((unsigned)((rows + kRowsPerWg - 1) / kRowsPerWg)), dim3(256),
-                               0, stream, u16(o), u16(dout), dvec, rows);
-            if (hipGetLastError() != hipSuccess) return FA_ERR_LAUNCH;
-            few(dkdv_few, dq_few, 1);
-            return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
+    auto row_sums = [&]() {
+        const long rows = (long)B * H * N;
+        constexpr int kRowsPerWg = 256 / (D / 8);
+        hipLaunchKernelGGL((fa_bwd_rowsum_kernel<Tag, D>), dim3((unsigned)((rows + kRowsPerWg - 1) / kRowsPerWg)), dim3(256), 0,
+                           stream, u16(o), u16(dout), dvec, rows);
+        return hipGetLastError() == hipSuccess;
+    };
+    auto dq_pass = [&]() {
+        if constexpr (D == 256) {
+            causal ? dqp(fa_bwd_dq_d256_kernel<Tag, true>, 128) : dqp(fa_bwd_dq_d256_kernel<Tag, false>, 128);
+        } else if (dq_few) {
+            few(0, dq_few, 0);
+        } else if (N <= short_rows(D, causal)) {
+            causal ? dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, true>, 128) : dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, false>, 128);
+        } else {
+            causal ? dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, true>, 256) : dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, false>, 256);
         }
-    }
-    if constexpr (D == 256) {
-        causal ? dqp(fa_bwd_dq_d256_kernel<Tag, true>, 128) : dqp(fa_bwd_dq_d256_kernel<Tag, false>, 128);
-    } else if (dq_few) {
-        few(0, dq_few, 0);
-    } else if (N <= short_rows(D, causal)) {
-        causal ? dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, true>, 128) : dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, false>, 128);
-    } else {
-        causal ? dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, true>, 256) : dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, false>, 256);
-    }
-    if (hipGetLastError() != hipSuccess) return FA_ERR_LAUNCH;
-
+        return hipGetLastError() == hipSuccess;
+    };
     auto dkdv = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(256), 0, stream, u16(q), u16(k), u16(v), u16(dout), lse,
                            dvec, static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv), N, n_kblocks, (int)total,
                            H / H_kv, scale);
     };
-    if (dkdv_few) few(dkdv_few, 0, 1);
-    else if constexpr (D == 64) causal ? dkdv(fa_bwd_dkdv_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_kernel<Tag, D, false>);
-    else causal ? dkdv(fa_bwd_dkdv_shared_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_shared_kernel<Tag, D, false>);
-    return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
+    auto dkdv_pass = [&]() {
+        if (dkdv_few) few(dkdv_few, 0, 1);
+        else if constexpr (D == 64) causal ? dkdv(fa_bwd_dkdv_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_kernel<Tag, D, false>);
+        else causal ? dkdv(fa_bwd_dkdv_shared_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_shared_kernel<Tag, D, false>);
+        return hipGetLastError() == hipSuccess;
+    };
+
+    bool ok;
+    if (dq == q || dq == dout) {
+        // dQ written over Q or dO: a workgroup of the dQ pass reads these at its own rows before it writes them, but
+        // the dK/dV pass reads all of them and has to come first
+        ok = row_sums() && dkdv_pass() && dq_pass();
+    } else if (dq_few && dkdv_few) {
+        ok = row_sums();
+        if (ok) {
+            few(dkdv_few, dq_few, 1);
+            ok = hipGetLastError() == hipSuccess;
+        }
+    } else {
+        ok = dq_pass() && dkdv_pass();
+    }
+    return ok ? FA_OK : FA_ERR_LAUNCH;
 }
 
 int launch_bwd(const void* q, const void* k, const void* v, const void* o, const float* lse, const void* dout,

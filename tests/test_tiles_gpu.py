@@ -174,3 +174,18 @@ def test_forward_tile_rule_edges(d, N, fp8):
     o, lse = binding.fa_fwd(q.cuda(), k.cuda(), v.cuda(), d ** -0.5, False)
     o_ref, l_ref = oracle.attention_fwd(f64(q), f64(k), f64(v), d ** -0.5, False)
     assert max_abs(f64(o), o_ref) <= 2e-2 and rmse(f64(o), o_ref) <= 3e-3 and max_abs(f64(lse), l_ref) <= 2e-3
+
+
+@pytest.mark.parametrize("over", ["q", "dout"])
+@pytest.mark.parametrize("d,H,N,causal", [(64, 2, 100, True), (128, 2, 300, False), (128, 200, 140, True), (256, 4, 200, True),
+                                          (64, 200, 140, False)])
+def test_backward_writes_dq_over_an_input(d, H, N, causal, over):
+    # the calls that reuse Q's or dO's memory for dQ: every form of the two passes, against separate buffers (D is summed
+    # in another order there: at most a rounding of the outputs apart)
+    q, k, v, dout = (inputs.normal_tensor(1300 + N, n, (1, H, N, d), "bf16").cuda() for n in ("q", "k", "v", "do"))
+    o, lse = binding.fa_fwd(q, k, v, d ** -0.5, causal)
+    ref = binding.fa_bwd(q, k, v, o, lse, dout, d ** -0.5, causal)
+    t = {"q": q.clone(), "dout": dout.clone()}
+    got = binding.fa_bwd(t["q"], k, v, o, lse, t["dout"], d ** -0.5, causal, dq=t[over])
+    for a, b in zip(got, ref):
+        assert rmse(f64(a), f64(b)) <= 2.0 ** -9 * float(np.sqrt(np.mean(f64(b) ** 2)))
