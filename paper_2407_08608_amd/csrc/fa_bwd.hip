@@ -869,11 +869,11 @@ constexpr int few_lds_bytes(int d) {
 // that is mostly idle has to spare.  A wave stages its own tiles (32 queries of Q and dO), so the loop has no barrier.
 // bf16, B = 1, H = 32 on 4 K/V heads, N = 2048, d = 128, causal (64 workgroups of 128 keys, the longest 256 iterations):
 // whole backward 476 -> 223 us.
-template <typename Tag, int D, bool CAUSAL>
+template <typename Tag, int D, bool CAUSAL, bool D_READY>
 static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
-                                                const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
-                                                const float* __restrict__ lse, const float* __restrict__ dvec,
-                                                uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int N, int n_heads,
+                                                const uint16_t* __restrict__ v, const uint16_t* __restrict__ o,
+                                                const uint16_t* __restrict__ dout, const float* __restrict__ lse,
+                                                const float* __restrict__ dvec, uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int N, int n_heads,
                                                 int kv_group, float scale, char* lds, float* lds_ld_all) {
     using Tiles = WaveTiles<D>;
     constexpr int NW = 4, BQ = Tiles::ROWS, BK = 32;
@@ -915,6 +915,7 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
 
     float ldpre = 0.f;
     int ldrow = 0;
+    i32x4 opre[KS], dopre[KS];  // without D in the workspace: the lane's half of a row of O and of dO
     BufferWords q_rsrc, do_rsrc;
     auto aim = [&](int gi, int t) __attribute__((always_inline)) {  // the next requests: tile t of query head gi of the group
         const size_t qhead = (size_t)bh * kv_group + min(gi, kv_group - 1);
@@ -922,7 +923,17 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
         q_rsrc = make_buffer_words(q + qhead * N * D, bytes);
         do_rsrc = make_buffer_words(dout + qhead * N * D, bytes);
         ldrow = t * BQ + col;  // lanes 0..31 carry L, 32..63 carry D
-        ldpre = (half ? dvec : lse)[qhead * N + min(ldrow, N - 1)];
+        const size_t row = qhead * N + min(ldrow, N - 1);
+        if constexpr (D_READY) {
+            ldpre = (half ? dvec : lse)[row];
+        } else {
+            ldpre = lse[row];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                opre[ks] = *reinterpret_cast<const i32x4*>(o + row * D + ks * 16 + half * 8);
+                dopre[ks] = *reinterpret_cast<const i32x4*>(dout + row * D + ks * 16 + half * 8);
+            }
+        }
     };
 
     // one tile at `base`, while tile t_next of the heads aimed at is requested into stage st_next
@@ -1011,7 +1022,14 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
         const int q0 = t * BQ;
         // rows past N get L = +inf so that P = exp2(0 - inf) = 0, and D = 0.  (Keys past N need nothing: what their
         // lanes compute goes to rows of dK and dV that are not stored.)
-        const float x = ldrow < N ? (half ? -ldpre : ldpre * kLog2e) : (half ? 0.f : INFINITY);
+        float d_row = ldpre;
+        if constexpr (!D_READY) {
+            d_row = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) d_row = dot8<Tag>(opre[ks], dopre[ks], d_row);
+            d_row = sum_both_halves(d_row);
+        }
+        const float x = ldrow < N ? (half ? -d_row : ldpre * kLog2e) : (half ? 0.f : INFINITY);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this tile has landed
         lds_ld[lane] = x;
         t += NW;
@@ -1047,11 +1065,11 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
 // owns 32 queries and its four waves split the keys (tiles of 32, staged by the wave that works them), each with a dQ
 // accumulator; the four partial sums meet in the LDS at the end, in a fixed order.
 // bf16, B = 1, H = 4, N = 1024: whole backward 54 -> 27 us at d = 128, 33 -> 18 us at d = 64.
-template <typename Tag, int D, bool CAUSAL>
+template <typename Tag, int D, bool CAUSAL, bool D_READY>
 static __device__ __forceinline__ void dq_few(int block, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                               const uint16_t* __restrict__ v, const uint16_t* __restrict__ o,
                                               const uint16_t* __restrict__ dout, const float* __restrict__ lse,
-                                              float* __restrict__ dvec, bool d_ready, uint16_t* __restrict__ dq, int N,
+                                              float* __restrict__ dvec, uint16_t* __restrict__ dq, int N,
                                               int n_heads, int kv_group, float scale, char* lds) {
     using Tiles = WaveTiles<D>;
     constexpr int NW = 4, BQ = 32, BK = Tiles::ROWS;
@@ -1091,7 +1109,7 @@ static __device__ __forceinline__ void dq_few(int block, const uint16_t* __restr
         doreg[ks] = *reinterpret_cast<const i32x4*>(dout + off);
     }
     float d_row = 0.f;  // D = rowsum(dO o O)
-    if (d_ready) {
+    if constexpr (D_READY) {
         d_row = dvec[(size_t)bh * N + row];
     } else {
 #pragma unroll
@@ -1186,25 +1204,26 @@ static __device__ __forceinline__ void dq_few(int block, const uint16_t* __restr
 }
 
 // One launch for either pass or for both: workgroups 0 .. n_dkdv - 1 take 32 keys each, the rest 32 queries each.
-// With both in one launch (`d_ready`: D is in the workspace already) the dQ work fills the CUs that the shorter key
-// blocks of a causal dK/dV pass leave idle.
+// With both in one launch the dQ work fills the CUs that the shorter key blocks of a causal dK/dV pass leave idle.
+// D_READY: D is in the workspace already; otherwise both kinds compute it for the rows they work on (the dK/dV kind
+// once per tile: own_row_sums).
 // bf16 causal, whole backward, us, two launches / one and the row sums: d = 128 H = 4, N = 1024 27 / 17, H = 16 on 4,
 // N = 2048 126 / 97, H = 32 on 4, N = 2048 217 / 195; d = 64 H = 16, N = 1024 22.5 / 18.9.  Where neither pass leaves
 // CUs idle the two take the same time.
-template <typename Tag, int D, bool CAUSAL>
+template <typename Tag, int D, bool CAUSAL, bool D_READY>
 __global__ void __launch_bounds__(256, D == 64 ? 2 : 1)
 fa_bwd_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                   const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
-                  float* __restrict__ dvec, int d_ready, uint16_t* __restrict__ dq, uint16_t* __restrict__ dk,
+                  float* __restrict__ dvec, uint16_t* __restrict__ dq, uint16_t* __restrict__ dk,
                   uint16_t* __restrict__ dv, int N, int n_dkdv, int n_heads, int kv_group, float scale) {
     [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
     __shared__ __attribute__((aligned(1024))) char lds[few_lds_bytes(D)];
     __shared__ __attribute__((aligned(16))) float lds_ld[4 * 64];
     const int block = blockIdx.x;
     if (block < n_dkdv)
-        dkdv_few<Tag, D, CAUSAL>(block, q, k, v, dout, lse, dvec, dk, dv, N, n_heads / kv_group, kv_group, scale, lds, lds_ld);
+        dkdv_few<Tag, D, CAUSAL, D_READY>(block, q, k, v, o, dout, lse, dvec, dk, dv, N, n_heads / kv_group, kv_group, scale, lds, lds_ld);
     else
-        dq_few<Tag, D, CAUSAL>(block - n_dkdv, q, k, v, o, dout, lse, dvec, d_ready, dq, N, n_heads, kv_group, scale, lds);
+        dq_few<Tag, D, CAUSAL, D_READY>(block - n_dkdv, q, k, v, o, dout, lse, dvec, dq, N, n_heads, kv_group, scale, lds);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1585,6 +1604,12 @@ constexpr long few_query_tiles(int d, int causal, long key_blocks) {
     return causal ? (d == 64 ? 192 : 128) : 96;
 }
 
+// Whether the one launch that runs both passes computes D for itself: cheaper than a launch for it (2.7 us and the gap
+// behind it) while a wave of a key block has few tiles, each of which then reads its rows of O and dO once more.  Whole
+// backward, bf16, us, with / without a launch for D: d = 64 N = 60 15.1 / 12.1, 512 15.6 / 12.4 (12.1 is the host's time),
+// 1024 15.2 / 16.6; d = 128 N = 128 15.8 / 12.4, 333 17.3 / 21.8 (no mask).
+inline bool own_row_sums(int d, int N, int kv_group) { return (long)((N + 31) / 32) * kv_group <= (d == 64 ? 16 : 8); }
+
 // Up to which length the dQ pass takes 128-query workgroups of four waves with 32-key blocks, two or three to a CU,
 // instead of 256-query ones of eight with 64-key blocks: finer tiles waste less on the diagonal and on ragged ends, and
 // the start and end of one workgroup run under the loop of another; over long sequences staging every block twice as
@@ -1622,14 +1647,15 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
         if (total_q <= few_query_tiles(D, causal, total)) dq_few = (long)B * H * ((N + 31) / 32);
         if (total <= few_key_blocks(D, causal)) dkdv_few = (long)B * H_kv * ((N + 31) / 32);
     }
-    auto few = [&](long n_dkdv, long n_dq, int d_ready) {
+    auto few = [&](long n_dkdv, long n_dq, bool d_ready) {
         if constexpr (D <= 128) {
             auto run = [&](auto kernel) {
                 hipLaunchKernelGGL(kernel, dim3((unsigned)(n_dkdv + n_dq)), dim3(256), 0, stream, u16(q), u16(k), u16(v),
-                                   u16(o), u16(dout), lse, dvec, d_ready, static_cast<uint16_t*>(dq),
+                                   u16(o), u16(dout), lse, dvec, static_cast<uint16_t*>(dq),
                                    static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv), N, (int)n_dkdv, B * H, H / H_kv, scale);
             };
-            causal ? run(fa_bwd_few_kernel<Tag, D, true>) : run(fa_bwd_few_kernel<Tag, D, false>);
+            if (d_ready) causal ? run(fa_bwd_few_kernel<Tag, D, true, true>) : run(fa_bwd_few_kernel<Tag, D, false, true>);
+            else causal ? run(fa_bwd_few_kernel<Tag, D, true, false>) : run(fa_bwd_few_kernel<Tag, D, false, false>);
         }
     };
     auto row_sums = [&]() {
@@ -1643,7 +1669,7 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
         if constexpr (D == 256) {
             causal ? dqp(fa_bwd_dq_d256_kernel<Tag, true>, 128) : dqp(fa_bwd_dq_d256_kernel<Tag, false>, 128);
         } else if (dq_few) {
-            few(0, dq_few, 0);
+            few(0, dq_few, false);
         } else if (N <= short_rows(D, causal)) {
             causal ? dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, true>, 128) : dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, false>, 128);
         } else {
@@ -1657,7 +1683,7 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
                            H / H_kv, scale);
     };
     auto dkdv_pass = [&]() {
-        if (dkdv_few) few(dkdv_few, 0, 1);
+        if (dkdv_few) few(dkdv_few, 0, true);
         else if constexpr (D == 64) causal ? dkdv(fa_bwd_dkdv_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_kernel<Tag, D, false>);
         else causal ? dkdv(fa_bwd_dkdv_shared_kernel<Tag, D, true>) : dkdv(fa_bwd_dkdv_shared_kernel<Tag, D, false>);
         return hipGetLastError() == hipSuccess;
@@ -1669,9 +1695,10 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
         // the dK/dV pass reads all of them and has to come first
         ok = row_sums() && dkdv_pass() && dq_pass();
     } else if (dq_few && dkdv_few) {
-        ok = row_sums();
+        const bool own = own_row_sums(D, N, H / H_kv);
+        ok = own || row_sums();
         if (ok) {
-            few(dkdv_few, dq_few, 1);
+            few(dkdv_few, dq_few, !own);
             ok = hipGetLastError() == hipSuccess;
         }
     } else {

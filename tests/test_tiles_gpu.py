@@ -189,3 +189,11 @@ def test_backward_writes_dq_over_an_input(d, H, N, causal, over):
     got = binding.fa_bwd(t["q"], k, v, o, lse, t["dout"], d ** -0.5, causal, dq=t[over])
     for a, b in zip(got, ref):
         assert rmse(f64(a), f64(b)) <= 2.0 ** -9 * float(np.sqrt(np.mean(f64(b) ** 2)))
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,N,H,H_kv", [(64, 512, 2, 2), (64, 513, 2, 2), (64, 128, 8, 2), (64, 129, 8, 2), (128, 256, 2, 2),
+                                        (128, 257, 2, 2), (128, 100, 4, 2), (128, 3, 2, 1)])
+def test_backward_row_sums_inside_the_one_launch(d, N, H, H_kv, causal):
+    # on both sides of the number of tiles up to which the one launch computes D for itself, ragged and not
+    _check_backward(1400 + N, 1, H, H_kv, N, d, causal, "bf16")
