@@ -679,7 +679,8 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
                     if (ks == 0) MfmaVgprAcc<Tag>::first(sacc[i], a, kreg[i][ks]);
                     else MfmaVgprAcc<Tag>::run(sacc[i], a, kreg[i][ks]);
                 } else {
-                    MfmaVgprAcc<Tag>::run(pacc[i], a, vreg[i][ks]);
+                    if (ks == 0) MfmaVgprAcc<Tag>::start(pacc[i], a, vreg[i][ks]);
+                    else MfmaVgprAcc<Tag>::run(pacc[i], a, vreg[i][ks]);
                     if (u == KS && i == KEYT - 1) await(sacc);
                     // 16 KEYT scores over the 16 MFMAs of this phase, none before the wait above
                     constexpr int M0 = KEYT - 1;
@@ -974,6 +975,7 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
             tiles.request(q_rsrc, do_rsrc, t_next, st_next, u);
             if (u == 0) MfmaVgprAcc<Tag>::first(sacc, a, kreg[u]);
             else if (u < KS) MfmaVgprAcc<Tag>::run(sacc, a, kreg[u]);
+            else if (u == KS) MfmaVgprAcc<Tag>::start(pacc, a, vreg[u - KS]);
             else MfmaVgprAcc<Tag>::run(pacc, a, vreg[u - KS]);
             if (u == KS) mfma_result_wait(sacc);
             if (u >= KS) {
@@ -1151,6 +1153,7 @@ static __device__ __forceinline__ void dq_few(int block, const uint16_t* __restr
             tiles.request(k_rsrc, v_rsrc, t + NW, st ^ 1, u);
             if (u == 0) MfmaVgprAcc<Tag>::first(sacc, a, qreg[u]);
             else if (u < KS) MfmaVgprAcc<Tag>::run(sacc, a, qreg[u]);
+            else if (u == KS) MfmaVgprAcc<Tag>::start(pacc, a, doreg[u - KS]);
             else MfmaVgprAcc<Tag>::run(pacc, a, doreg[u - KS]);
             if (u == KS) mfma_result_wait(sacc);
             if (u >= KS) {
@@ -1531,6 +1534,7 @@ fa_bwd_dq_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
             else tr[u + KP - 4 * KS] = tr_read(u + KP - 4 * KS);
             if (u < 2) MfmaVgprAcc<Tag>::first(sacc[kt], a, qreg[ks]);
             else if (u < 2 * KS) MfmaVgprAcc<Tag>::run(sacc[kt], a, qreg[ks]);
+            else if (ks == 0) MfmaVgprAcc<Tag>::start(pacc[kt], a, doreg[ks]);
             else MfmaVgprAcc<Tag>::run(pacc[kt], a, doreg[ks]);
             if (u < 16) pacc[0][u] = pacc[1][u] = -d_row;  // dP - D comes out of the MFMAs
             if (u == 2 * KS) mfma_result_wait(sacc[0], sacc[1]);

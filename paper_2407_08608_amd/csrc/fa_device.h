@@ -73,12 +73,17 @@ template <> struct Elem<f16_tag> {
 // softmax reads would pay one copy per element.  Here the accumulator is forced into ordinary
 // registers and the B operand (touched by MFMA alone) is taken from the accumulation half.
 // The compiler's hazard checker cannot see inside: a VALU read of the accumulator must be
-// separated from the MFMA that wrote it by mfma_result_wait().
+// separated from the MFMA that wrote it by mfma_result_wait(), and the first MFMA onto an accumulator
+// that was filled with values has to be start(), which keeps the two wait states an MFMA needs behind
+// a VALU write of its operands (the compiler may put the copy that fills it directly in front).
 template <typename Tag> struct MfmaVgprAcc;
 #define FA_DEFINE_MFMA_VGPR_ACC(TAG, OPCODE)                                                          \
     template <> struct MfmaVgprAcc<TAG> {                                                             \
         static __device__ __forceinline__ void run(f32x16& acc, const i32x4& a, const i32x4& b) {     \
             asm volatile(OPCODE " %0, %1, %2, %0" : "+v"(acc) : "v"(a), "a"(b));                      \
+        }                                                                                             \
+        static __device__ __forceinline__ void start(f32x16& acc, const i32x4& a, const i32x4& b) {   \
+            asm volatile("s_nop 1\n\t" OPCODE " %0, %1, %2, %0" : "+v"(acc) : "v"(a), "a"(b));        \
         }                                                                                             \
         static __device__ __forceinline__ void first(f32x16& acc, const i32x4& a, const i32x4& b) {   \
             asm volatile(OPCODE " %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "a"(b));                      \

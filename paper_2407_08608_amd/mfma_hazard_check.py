@@ -1,4 +1,4 @@
-"""Static check of compiled gfx950 assembly: results of hand-written MFMAs are not touched too early.
+"""Static check of compiled gfx950 assembly: hand-written MFMAs and their neighbours keep their distance.
 
 Some kernels issue `v_mfma_*` through inline assembly so that the accumulator lands in ordinary
 registers.  The compiler's hazard recogniser does not look inside inline assembly, so nothing
@@ -15,6 +15,11 @@ instruction that names a register of that range, and any MFMA that takes it as a
 before `need` wait states have passed.  A following MFMA that accumulates into exactly the same
 range is the hardware-interlocked case and is allowed.
 
+The same holds ahead of such an MFMA: an ordinary vector instruction that writes one of its A, B or
+accumulator registers (again, a copy the register allocator makes is enough) must be two wait states away
+from it, the distance the compiler keeps in front of MFMAs of its own.  Those writes are followed over
+branches in the same way.
+
 The 8-pass 32x32x16 MFMA needs 11 wait states before a VALU read of its result and the 16-pass
 32x32x64 e4m3 MFMA 19; the compiler leaves 12 (20) or more in the code it schedules itself, and those
 are the defaults here.
@@ -22,17 +27,31 @@ are the defaults here.
 import re
 import sys
 
-_REG_RANGE = re.compile(r"\bv\[(\d+):(\d+)\]")
-_REG_ONE = re.compile(r"\bv(\d+)\b")
+_REG_RANGE = re.compile(r"\b([va])\[(\d+):(\d+)\]")
+_REG_ONE = re.compile(r"\b([va])(\d+)\b")
+VALU_WRITE_STATES = 2  # between a vector instruction's write of a register and an MFMA that reads it
+
+
+def _registers(text):
+    """Vector registers named in `text`: ("v", n) and, of the accumulation half, ("a", n)."""
+    out = set()
+    for m in _REG_RANGE.finditer(text):
+        out.update((m.group(1), n) for n in range(int(m.group(2)), int(m.group(3)) + 1))
+    for m in _REG_ONE.finditer(text):
+        out.add((m.group(1), int(m.group(2))))
+    return out
 
 
 def _vgprs(text):
-    out = set()
-    for m in _REG_RANGE.finditer(text):
-        out.update(range(int(m.group(1)), int(m.group(2)) + 1))
-    for m in _REG_ONE.finditer(text):
-        out.add(int(m.group(1)))
-    return out
+    return {r for r in _registers(text) if r[0] == "v"}
+
+
+def _valu_writes(op, args):
+    """Registers that a vector instruction other than an MFMA writes (empty for anything else)."""
+    if not op.startswith("v_") or op.startswith("v_mfma"):
+        return set()
+    operands = args.split(",")
+    return _registers(",".join(operands[:2]) if "swap" in op else operands[0])  # swaps write both operands
 
 
 def _parse(raw):
@@ -45,10 +64,11 @@ def _parse(raw):
     return text, op, args, (int(args.strip()) + 1 if op == "s_nop" else 1)
 
 
-def _walk(lines, labels, func, start, pending, track_new, need, need_16_pass, horizon, problems, depth):
+def _walk(lines, labels, func, start, pending, written, track_new, need, need_16_pass, horizon, problems, depth):
     """Walks `lines` (of one function) from index `start` in listing order.  `pending` holds [registers,
-    wait states so far, wait states required] of hand-written MFMAs whose results are not yet safe.  With
-    track_new the walk covers the function and registers every hand-written MFMA it meets; without, it
+    wait states so far, wait states required] of hand-written MFMAs whose results are not yet safe, `written`
+    [registers, wait states so far] of vector instructions whose results an MFMA may not read yet.  With
+    track_new the walk covers the function and registers every such instruction it meets; without, it
     only follows the entries it was given until they are safe.  A branch taken with entries still pending
     is followed to its target with a copy of them (the listing order alone would miss the reader at a loop
     head behind a back-edge, or behind a forward branch that skips the wait)."""
@@ -75,6 +95,9 @@ def _walk(lines, labels, func, start, pending, track_new, need, need_16_pass, ho
                     problems.append((func, ln, text, waited))
                 if regs & src_c and regs != src_c and waited < req:
                     problems.append((func, ln, text, waited))
+            if in_asm:
+                read = _registers(",".join(parts[1:]))
+                problems.extend((func, ln, text, waited) for regs, waited in written if regs & read)
             pending = [[regs, waited + states, req] for regs, waited, req in pending]
             if track_new and in_asm and dst:
                 pending = [p for p in pending if p[0] != dst]
@@ -87,13 +110,18 @@ def _walk(lines, labels, func, start, pending, track_new, need, need_16_pass, ho
             pending = [[regs, waited + states, req] for regs, waited, req in pending]
             if op.startswith("s_cbranch") or op == "s_branch":
                 unsafe = [list(p) for p in pending if p[1] < p[2]]
+                recent = [[regs, waited + states] for regs, waited in written if waited + states < VALU_WRITE_STATES]
                 target = labels.get(args.strip())
-                if unsafe and target is not None and depth < 4:
-                    _walk(lines, labels, func, target, unsafe, False, need, need_16_pass, horizon, problems, depth + 1)
+                if (unsafe or recent) and target is not None and depth < 4:
+                    _walk(lines, labels, func, target, unsafe, recent, False, need, need_16_pass, horizon, problems,
+                          depth + 1)
                 if op == "s_branch" and not track_new:
                     return  # an unconditional branch: the followed entries continue at the target only
         pending = [p for p in pending if p[1] < horizon]
-        if not track_new and all(p[1] >= p[2] for p in pending):
+        written = [[regs, waited + states] for regs, waited in written if waited + states < VALU_WRITE_STATES]
+        if track_new and _valu_writes(op, args):
+            written.append([_valu_writes(op, args), 0])
+        if not track_new and not written and all(p[1] >= p[2] for p in pending):
             return
 
 
@@ -115,7 +143,7 @@ def check(asm_text, need=12, need_16_pass=20, horizon=64):
             labels[lab.group(1)] = len(lines)
         lines.append((len(lines) + 1, raw))
     for name, lines, labels in funcs:
-        _walk(lines, labels, name, 0, [], True, need, need_16_pass, horizon, problems, 0)
+        _walk(lines, labels, name, 0, [], [], True, need, need_16_pass, horizon, problems, 0)
     return sorted(set(problems), key=problems.index)
 
 
@@ -123,7 +151,7 @@ def main(argv):
     bad = 0
     for path in argv[1:]:
         for func, ln, text, waited in check(open(path).read()):
-            print(f"{path}: {func} +{ln}: `{text}` only {waited} wait states after the MFMA that writes its registers")
+            print(f"{path}: {func} +{ln}: `{text}` only {waited} wait states after the write of its registers")
             bad += 1
     return 1 if bad else 0
 

@@ -148,6 +148,28 @@ def test_mfma_hazard_checker_finds_planted_early_access():
     assert hz.check("_Z6kernelv:\n\tv_mfma_f32_32x32x16_bf16 v[16:31], v[0:3], v[4:7], 0\n" + read) == []
 
 
+def test_mfma_hazard_checker_finds_planted_late_operand_writes():
+    # a vector instruction's write of an operand register must be two wait states ahead of a hand-written MFMA
+    from paper_2407_08608_amd import mfma_hazard_check as hz
+    kernel = "_Z6kernelv:\n"
+    mfma = "\t;;#ASMSTART\n\tv_mfma_f32_32x32x16_bf16 v[16:31], v[0:3], a[0:3], v[16:31]\n\t;;#ASMEND\n\ts_nop 12\n"
+    load = "\ts_waitcnt lgkmcnt(4)\n"
+    for write in ("v_mov_b64_e32 v[16:17], v[50:51]", "v_add_f32_e32 v3, v50, v51", "v_accvgpr_write_b32 a1, v50",
+                  "v_permlane32_swap_b32_e32 v50, v2"):
+        w = "\t" + write + "\n"
+        assert len(hz.check(kernel + w + mfma)) == 1 and len(hz.check(kernel + w + load + mfma)) == 1, write
+        assert hz.check(kernel + w + load + load + mfma) == [] and hz.check(kernel + w + "\ts_nop 1\n" + mfma) == []
+    # registers that the MFMA does not read, memory instructions (the hardware's counters cover those), a compare
+    for other in ("v_mov_b32_e32 v40, v16", "ds_read_b128 v[0:3], v60", "v_cmp_gt_f32_e32 vcc, v16, v17"):
+        assert hz.check(kernel + "\t" + other + "\n" + mfma) == [], other
+    # the write at a loop's end and the MFMA at its head, apart by the branch alone
+    loop = kernel + ".LBB0_1:\n" + mfma + "\tv_mov_b32_e32 v16, v50\n"
+    assert len(hz.check(loop + "\ts_cbranch_scc1 .LBB0_1\n")) == 1
+    assert hz.check(loop + "\ts_nop 0\n\ts_cbranch_scc1 .LBB0_1\n") == []
+    # the compiler's own MFMAs are its business
+    assert hz.check(kernel + "\tv_mov_b32_e32 v0, v50\n\tv_mfma_f32_32x32x16_bf16 v[16:31], v[0:3], v[4:7], 0\n") == []
+
+
 def test_bench_refuses_more_than_one_gpu_with_a_message():
     # the build measures one GPU; the benchmark says so instead of printing a line for several
     import subprocess
