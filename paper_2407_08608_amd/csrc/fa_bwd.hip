@@ -101,7 +101,8 @@ static __device__ __forceinline__ void store_keys_via_lds(const f32x16 (&acc)[2]
 }
 
 // D = rowsum(dO o O) in a launch of its own, where the dK/dV pass cannot wait for the dQ pass to compute it: both passes
-// in one launch (fa_bwd_few_kernel), or dQ written over an input of the dK/dV pass.
+// in one launch (fa_bwd_few_kernel), or dQ written over an input of the dK/dV pass; and where a gradient is written over
+// O, so that no later launch reads O.
 template <typename Tag, int D>
 __global__ void __launch_bounds__(256)
 fa_bwd_rowsum_kernel(const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout, float* __restrict__ dvec, long rows) {
@@ -1278,14 +1279,18 @@ fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     }
     const float l2 = lse[(size_t)bh * N + qrow] * kLog2e;
     // D = rowsum(dO o O): the two lanes of a row hold its dO between them, so O is read in the same pieces.  The
-    // dK/dV pass, launched after this one, reads D from the workspace.
+    // dK/dV pass, launched after this one, reads D from the workspace.  o == nullptr: D is there already.
     float dq_row = 0.f;
+    if (o) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        dq_row = dot8<Tag>(*reinterpret_cast<const i32x4*>(o + head_off + (size_t)qrow * D + ks * 16 + half * 8), doreg[ks], dq_row);
+        for (int ks = 0; ks < KS; ++ks) {
+            dq_row = dot8<Tag>(*reinterpret_cast<const i32x4*>(o + head_off + (size_t)qrow * D + ks * 16 + half * 8), doreg[ks], dq_row);
+        }
+        dq_row = sum_both_halves(dq_row);
+        if (half == 0 && qi < N) dvec[(size_t)bh * N + qi] = dq_row;
+    } else {
+        dq_row = dvec[(size_t)bh * N + qrow];
     }
-    dq_row = sum_both_halves(dq_row);
-    if (half == 0 && qi < N) dvec[(size_t)bh * N + qi] = dq_row;
     constexpr bool NEG_D_START = D == 64;
     f32x16 negd;
 #pragma unroll
@@ -1477,16 +1482,22 @@ fa_bwd_dq_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
     for (int c = 0; c < 2 * NCH; ++c) load_chunk(0, c);
 
     i32x4 qreg[KS], doreg[KS];
-    float d_row = 0.f;  // D = rowsum(dO o O)
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         const size_t off = head_off + (size_t)qrow * D + ks * 16 + half * 8;
         qreg[ks] = *reinterpret_cast<const i32x4*>(q + off);
         doreg[ks] = *reinterpret_cast<const i32x4*>(dout + off);
-        d_row = dot8<Tag>(*reinterpret_cast<const i32x4*>(o + off), doreg[ks], d_row);
     }
-    d_row = sum_both_halves(d_row);
-    if (half == 0 && qi < N) dvec[(size_t)bh * N + qi] = d_row;
+    float d_row = 0.f;  // D = rowsum(dO o O), or (o == nullptr) from the workspace
+    if (o) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            d_row = dot8<Tag>(*reinterpret_cast<const i32x4*>(o + head_off + (size_t)qrow * D + ks * 16 + half * 8), doreg[ks], d_row);
+        d_row = sum_both_halves(d_row);
+        if (half == 0 && qi < N) dvec[(size_t)bh * N + qi] = d_row;
+    } else {
+        d_row = dvec[(size_t)bh * N + qrow];
+    }
     const float l2 = lse[(size_t)bh * N + qrow] * kLog2e;
     f32x16 acc[DT];
 #pragma unroll
@@ -1624,6 +1635,12 @@ inline bool own_row_sums(int d, int N, int kv_group) { return (long)((N + 31) / 
 //            2048 575 / 570, 3001 845 / 863
 constexpr int short_rows(int d, int causal) { return d == 64 && causal ? 3072 : 1536; }
 
+// Whether two runs of bytes share memory.
+inline bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + b_bytes && y < x + a_bytes;
+}
+
 template <typename Tag, int D>
 static int launch_bwd_t(const void* q, const void* k, const void* v, const void* o, const float* lse,
                         const void* dout, void* dq, void* dk, void* dv, void* workspace, int B, int H, int H_kv,
@@ -1640,10 +1657,11 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
 
     // Two launches, the dQ pass first: it also writes D, which the dK/dV pass reads.  Or, with both passes in their
     // few-workgroup forms, D and then both in one launch.
-    auto dqp = [&](auto kernel, int rows) {  // `rows`: queries, and threads / 2, of a workgroup
+    auto dqp = [&](auto kernel, int rows, bool d_ready) {  // `rows`: queries, and threads / 2, of a workgroup
         const int tiles = (N + rows - 1) / rows, items = B * H * tiles;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)items), dim3(rows * 2), 0, stream, u16(q), u16(k), u16(v), u16(o),
-                           u16(dout), lse, dvec, static_cast<uint16_t*>(dq), N, tiles, items, H / H_kv, scale);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)items), dim3(rows * 2), 0, stream, u16(q), u16(k), u16(v),
+                           d_ready ? nullptr : u16(o), u16(dout), lse, dvec, static_cast<uint16_t*>(dq), N, tiles, items,
+                           H / H_kv, scale);
     };
     // workgroups of 32 queries / of 32 keys, when a pass is to use them
     long dq_few = 0, dkdv_few = 0;
@@ -1669,15 +1687,15 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
                            stream, u16(o), u16(dout), dvec, rows);
         return hipGetLastError() == hipSuccess;
     };
-    auto dq_pass = [&]() {
+    auto dq_pass = [&](bool d_ready) {
         if constexpr (D == 256) {
-            causal ? dqp(fa_bwd_dq_d256_kernel<Tag, true>, 128) : dqp(fa_bwd_dq_d256_kernel<Tag, false>, 128);
+            causal ? dqp(fa_bwd_dq_d256_kernel<Tag, true>, 128, d_ready) : dqp(fa_bwd_dq_d256_kernel<Tag, false>, 128, d_ready);
         } else if (dq_few) {
-            few(0, dq_few, false);
+            few(0, dq_few, d_ready);
         } else if (N <= short_rows(D, causal)) {
-            causal ? dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, true>, 128) : dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, false>, 128);
+            causal ? dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, true>, 128, d_ready) : dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, false>, 128, d_ready);
         } else {
-            causal ? dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, true>, 256) : dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, false>, 256);
+            causal ? dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, true>, 256, d_ready) : dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, false>, 256, d_ready);
         }
         return hipGetLastError() == hipSuccess;
     };
@@ -1693,20 +1711,23 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
         return hipGetLastError() == hipSuccess;
     };
 
+    // A gradient may be written over O, wholly or in part: D is then computed in full before anything is written
+    const size_t q_bytes = (size_t)B * H * N * D * 2, kv_bytes = (size_t)B * H_kv * N * D * 2;
+    const bool over_o = overlap(dq, q_bytes, o, q_bytes) || overlap(dk, kv_bytes, o, q_bytes) || overlap(dv, kv_bytes, o, q_bytes);
     bool ok;
     if (dq == q || dq == dout) {
         // dQ written over Q or dO: a workgroup of the dQ pass reads these at its own rows before it writes them, but
         // the dK/dV pass reads all of them and has to come first
-        ok = row_sums() && dkdv_pass() && dq_pass();
+        ok = row_sums() && dkdv_pass() && dq_pass(false);
     } else if (dq_few && dkdv_few) {
-        const bool own = own_row_sums(D, N, H / H_kv);
+        const bool own = !over_o && own_row_sums(D, N, H / H_kv);
         ok = own || row_sums();
         if (ok) {
             few(dkdv_few, dq_few, !own);
             ok = hipGetLastError() == hipSuccess;
         }
     } else {
-        ok = dq_pass() && dkdv_pass();
+        ok = (!over_o || row_sums()) && dq_pass(over_o) && dkdv_pass();
     }
     return ok ? FA_OK : FA_ERR_LAUNCH;
 }

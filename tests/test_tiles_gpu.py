@@ -191,6 +191,40 @@ def test_backward_writes_dq_over_an_input(d, H, N, causal, over):
         assert rmse(f64(a), f64(b)) <= 2.0 ** -9 * float(np.sqrt(np.mean(f64(b) ** 2)))
 
 
+# (d, H, N, causal) for every form of the two passes: one launch that computes D for itself, one launch behind the row
+# sums, 32-query / 32-key workgroups of one pass only, 128- and 256-query tiles, the shared-score dK/dV pass
+_FORMS = [(64, 2, 333, False), (64, 2, 1000, True), (128, 2, 100, True), (128, 2, 300, False), (64, 300, 70, True), (128, 110, 70, False),
+          (64, 400, 140, False), (128, 200, 140, True), (128, 100, 140, True), (128, 12, 3001, True), (256, 4, 200, True), (256, 40, 300, False)]
+
+
+@pytest.mark.parametrize("over", ["dq", "dk", "dv", "dq one head on", "dk one head on"])
+@pytest.mark.parametrize("d,H,N,causal", _FORMS)
+def test_backward_writes_a_gradient_over_the_output(d, H, N, causal, over):
+    # O is not needed once D is known, so a caller may hand its memory to a gradient, also shifted against O by a head:
+    # against separate buffers (D may be summed in another order: at most a rounding of the outputs apart)
+    q, k, v, dout = (inputs.normal_tensor(1500 + N, n, (1, H, N, d), "bf16").cuda() for n in ("q", "k", "v", "do"))
+    o, lse = binding.fa_fwd(q, k, v, d ** -0.5, causal)
+    ref = binding.fa_bwd(q, k, v, o, lse, dout, d ** -0.5, causal)
+    pool = torch.empty((1, H + 1, N, d), device="cuda", dtype=torch.bfloat16)
+    pool[:, :H] = o
+    out = {over.split()[0]: pool[:, 1:] if "head" in over else pool[:, :H]}
+    got = binding.fa_bwd(q, k, v, pool[:, :H], lse, dout, d ** -0.5, causal, **out)
+    for a, b in zip(got, ref):
+        assert rmse(f64(a), f64(b)) <= 2.0 ** -9 * float(np.sqrt(np.mean(f64(b) ** 2)))
+
+
+@pytest.mark.parametrize("H,H_kv,N", [(4, 2, 100), (8, 2, 700), (260, 65, 140)])
+def test_backward_writes_shared_head_gradients_inside_the_output(H, H_kv, N):
+    # dK and dV of shared heads are smaller than O: both fit into it, dV behind dK
+    q, dout = (inputs.normal_tensor(1550 + N, n, (1, H, N, 64), "f16").cuda() for n in ("q", "do"))
+    k, v = (inputs.normal_tensor(1550 + N, n, (1, H_kv, N, 64), "f16").cuda() for n in ("k", "v"))
+    o, lse = binding.fa_fwd_gqa(q, k, v, 0.125, True)
+    ref = binding.fa_bwd_gqa(q, k, v, o, lse, dout, 0.125, True)
+    got = binding.fa_bwd_gqa(q, k, v, o, lse, dout, 0.125, True, dk=o[:, :H_kv], dv=o[:, H_kv:2 * H_kv])
+    for a, b in zip(got, ref):
+        assert rmse(f64(a), f64(b)) <= 2.0 ** -12 * float(np.sqrt(np.mean(f64(b) ** 2)))
+
+
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d,N,H,H_kv", [(64, 512, 2, 2), (64, 513, 2, 2), (64, 128, 8, 2), (64, 129, 8, 2), (128, 256, 2, 2),
                                         (128, 257, 2, 2), (128, 100, 4, 2), (128, 3, 2, 1)])
