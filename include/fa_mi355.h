@@ -122,7 +122,9 @@ int fa_fp8_quant_hadamard(const void* x, int in_dtype, void* x8, float* scales,
  *   dq, dk, dv       : [B,H,N,d] of `dtype`                                   (device, written)
  *   workspace        : device scratch of at least fa_bwd_workspace_bytes(...) bytes (it holds D),
  *                      16-byte aligned, owned by the caller, contents undefined on return.
- * Memory of inputs may be reused for outputs as follows: dq, dk and dv may overlap o, in any way.
+ * Memory of inputs may be reused for outputs as follows: dq, dk and dv may overlap o, in any way; dq
+ * may be q or dout, and dk, dv over o at the same time.  Any other overlap of an output with an input
+ * or with another output gives undefined gradients.
  * dtype FA_BF16 or FA_F16 (others: FA_ERR_UNSUPPORTED; fa_bwd_workspace_bytes then returns 0);
  * d = 64, 128 or 256.  Nothing is accumulated
  * with atomics: results are bit-for-bit repeatable.

@@ -1715,10 +1715,10 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
     const size_t q_bytes = (size_t)B * H * N * D * 2, kv_bytes = (size_t)B * H_kv * N * D * 2;
     const bool over_o = overlap(dq, q_bytes, o, q_bytes) || overlap(dk, kv_bytes, o, q_bytes) || overlap(dv, kv_bytes, o, q_bytes);
     bool ok;
-    if (dq == q || dq == dout) {
+    if (overlap(dq, q_bytes, q, q_bytes) || overlap(dq, q_bytes, dout, q_bytes)) {
         // dQ written over Q or dO: a workgroup of the dQ pass reads these at its own rows before it writes them, but
-        // the dK/dV pass reads all of them and has to come first
-        ok = row_sums() && dkdv_pass() && dq_pass(false);
+        // the dK/dV pass reads all of them and has to come first.  (dK or dV may be over O then: D is not computed again.)
+        ok = row_sums() && dkdv_pass() && dq_pass(true);
     } else if (dq_few && dkdv_few) {
         const bool own = !over_o && own_row_sums(D, N, H / H_kv);
         ok = own || row_sums();

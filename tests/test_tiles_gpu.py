@@ -213,6 +213,18 @@ def test_backward_writes_a_gradient_over_the_output(d, H, N, causal, over):
         assert rmse(f64(a), f64(b)) <= 2.0 ** -9 * float(np.sqrt(np.mean(f64(b) ** 2)))
 
 
+@pytest.mark.parametrize("dq_over", ["q", "dout"])
+@pytest.mark.parametrize("d,H,N,causal", _FORMS)
+def test_backward_writes_dq_over_an_input_and_dv_over_the_output(d, H, N, causal, dq_over):
+    # dV replaces O before dQ, which goes over an input of the dK/dV pass, is computed
+    q, k, v, dout = (inputs.normal_tensor(1520 + N, n, (1, H, N, d), "bf16").cuda() for n in ("q", "k", "v", "do"))
+    o, lse = binding.fa_fwd(q, k, v, d ** -0.5, causal)
+    ref = binding.fa_bwd(q, k, v, o, lse, dout, d ** -0.5, causal)
+    got = binding.fa_bwd(q, k, v, o, lse, dout, d ** -0.5, causal, dq=q if dq_over == "q" else dout, dv=o)
+    for a, b in zip(got, ref):
+        assert rmse(f64(a), f64(b)) <= 2.0 ** -9 * float(np.sqrt(np.mean(f64(b) ** 2)))
+
+
 @pytest.mark.parametrize("H,H_kv,N", [(4, 2, 100), (8, 2, 700), (260, 65, 140)])
 def test_backward_writes_shared_head_gradients_inside_the_output(H, H_kv, N):
     # dK and dV of shared heads are smaller than O: both fit into it, dV behind dK
