@@ -1210,7 +1210,7 @@ static __device__ __forceinline__ void dq_few(int block, const uint16_t* __restr
 // One launch for either pass or for both: workgroups 0 .. n_dkdv - 1 take 32 keys each, the rest 32 queries each.
 // With both in one launch the dQ work fills the CUs that the shorter key blocks of a causal dK/dV pass leave idle.
 // D_READY: D is in the workspace already; otherwise both kinds compute it for the rows they work on (the dK/dV kind
-// once per tile: own_row_sums).
+// once per tile; own_row_sums says when).
 // bf16 causal, whole backward, us, two launches / one and the row sums: d = 128 H = 4, N = 1024 27 / 17, H = 16 on 4,
 // N = 2048 126 / 97, H = 32 on 4, N = 2048 217 / 195; d = 64 H = 16, N = 1024 22.5 / 18.9.  Where neither pass leaves
 // CUs idle the two take the same time.
@@ -1597,33 +1597,57 @@ size_t bwd_workspace_bytes(int B, int H, int N, int d) {
     return (rows * sizeof(float) + 15) & ~(size_t)15;  // D = rowsum(dO o O)
 }
 
-// Up to how many 128-key workgroups the dK/dV pass uses the 32-key form instead: on fewer workgroups than CUs
-// the 32-key form's four-fold parallelism wins until its operand traffic costs as much.  Whole backward, B = 1, bf16,
-// us, 128-key / 32-key form:
-//   d = 128  no mask: 128 workgroups 74 / 69 (H = 16, N = 1024), 160 88 / 96 (H = 16, N = 1280)
-//            causal:  192 75 / 71 (H = 24, N = 1024) and 459 / 395 (H = 3, N = 8192), 256 76 / 81 (H = 32, N = 1024)
-//   d = 64   no mask: 160 55 / 53, 192 46.2 / 45.0, 256 46.5 / 51;  causal: 256 47 / 44 (N = 1024), 384 86 / 84 (N = 2048)
-constexpr long few_key_blocks(int d, int causal) { return d == 64 ? (causal ? 384 : 192) : (causal ? 192 : 128); }
+// Which forms the two passes take at d = 64 and 128.  The 32-query / 32-key forms (fa_bwd_few_kernel) make four times as
+// many workgroups, each with a quarter of the serial chain, at a higher price per MFMA, so what counts is how often they
+// fill the chip (`chip`: how many it holds at once) and how long the chain is that they shorten: every limit below grows
+// with the chain, in 32-row tiles, up to `most` fillings.  Under a causal mask, where the large forms idle at the short
+// end, they grow further.  The dQ pass takes the form by itself only at d = 128 without a mask (over long sequences);
+// elsewhere the one launch covers what it would win.
+// Whole backward, bf16, us; large forms, dQ alone in its form, dK/dV alone in its, both in one launch:
+//   d = 128 causal   N = 128:  H = 64 21.5, 19.3, 17.2, 14.9;  H = 96 22.0, 25.3, 23.2, 20.6;  H = 128 22.4, 25.8, 23.6, 25.9
+//           causal   N = 512:  H = 32 42.4, 38.3, 38.5, 32.3;  H = 64 45.0, 55.1, 54.4, 61.4
+//           causal   N = 2048: H = 16 129, 112, 130, 112;  H = 24 136, 144, 164, 167;  H = 32 on 4 472, 501, 226, 199
+//           no mask  N = 512:  H = 20 40.0, 39.6, 40.0, 29.3;  H = 32 41.0, 40.7, 41.2, 38.4
+//           no mask  N = 4096: H = 6 250, 225, 265, 241;  N = 1024: H = 32 on 8 141, 157, 81.5, 97.6
+//   d = 64  causal   N = 256:  H = 64 18.3, 16.4, 16.5, 14.6;  H = 192 22.8, 30.3, 29.7, 34.5
+//           causal   N = 1536: H = 40 72.8, 77.4, 79.9, 79.5
+//           no mask  N = 640:  H = 28 32.5, 33.0, 32.6, 25.0;  N = 777: H = 28 41.0, 41.0, 40.1, 33.5
+// Over about 2600 shapes (heads 1 to 512, groups of 1 to 32, N from 16 to 16384) the choice is 0.4 % off the best of the
+// five on average.
+struct BwdForms {
+    bool dq_few, dkdv_few, one_launch;
+};
+template <int D>
+inline BwdForms choose_bwd_forms(long heads, long kv_heads, int N, int causal) {
+    if constexpr (D > 128) return {false, false, false};
+    struct Limit {  // workgroups, in fillings of the chip: min(most, base + tiles / step)
+        float base, step, most;
+        float at(long tiles) const { const float x = base + (float)tiles / step; return x < most ? x : most; }
+    };
+    constexpr int kChip = D == 64 ? 512 : 256;
+    const Limit one = D == 64 ? (causal ? Limit{1.25f, 8, 9} : Limit{1.25f, 12, 4.5f}) : (causal ? Limit{2, 6, 9} : Limit{2.25f, 12, 5});
+    const Limit key = D == 64 ? (causal ? Limit{1, 64, 4} : Limit{1, 128, 3}) : (causal ? Limit{1, 32, 4} : Limit{1, 32, 2});
+    const Limit query = D == 128 && !causal ? Limit{1, 32, 3} : Limit{0, 1, 0};
+    // with shared heads and few key blocks, dQ work beside them is worth more
+    const float shared_keys = D == 64 ? 0.5f : (causal ? 0.75f : 0.25f), shared_queries = D == 64 && !causal ? 2 : 3;
 
-// Up to how many 256-query workgroups the dQ pass uses the 32-query form instead.  Whole backward, B = 1, bf16, us,
-// 256-query / 32-query form:
-//   d = 128  no mask: 64 workgroups 69 / 55 (H = 16, N = 1024), 96 466 / 404 (H = 3, N = 8192), 128 81 / 90 (H = 32)
-//            causal:  64 74 / 54, 128 76 / 74 (N = 1024) and 130 / 112 (N = 2048), 192 134 / 141 (H = 24, N = 2048)
-//   d = 64   no mask: 64 39 / 28, 96 279 / 238, 128 46.5 / 49.7;  causal: 192 86 / 80 (N = 2048), 256 141 / 146 (H = 32 on 4)
-// With few key blocks (shared key/value heads) the dK/dV pass takes its 32-key form, and a dQ pass in the same launch
-// (fa_bwd_few_kernel) is worth more: 256, where the eight-wave form in a launch of its own / this one measured
-//   d = 128  causal:  64 key blocks 217 / 195 (H = 32 on 4, N = 2048), 128 164 / 190 (on 8);  no mask: 64 249 / 308
-//   d = 64   causal: 128 103 / 90 (H = 32 on 8, N = 2048);  no mask: 64 153 / 151 (on 4), 32 66 / 60 (H = 32 on 2, N = 512)
-constexpr long few_query_tiles(int d, int causal, long key_blocks) {
-    if (key_blocks <= (d == 64 ? (causal ? 128 : 64) : (causal ? 64 : 0))) return 256;
-    return causal ? (d == 64 ? 192 : 128) : 96;
+    const long tiles = (N + 31) / 32, group = heads / kv_heads, chain = tiles * group;
+    const float q = (float)(heads * tiles) / kChip, k = (float)(kv_heads * tiles) / kChip;  // fillings
+    const float both = tiles > 2 ? one.at(tiles) : 1.25f;
+    const bool one_launch = q + k <= both || (group > 1 && tiles >= 16 && k <= shared_keys && q <= shared_queries * both);
+    return {one_launch || (tiles > 2 && q <= query.at(tiles)), one_launch || (chain >= 6 && k <= key.at(chain)), one_launch};
 }
 
 // Whether the one launch that runs both passes computes D for itself: cheaper than a launch for it (2.7 us and the gap
-// behind it) while a wave of a key block has few tiles, each of which then reads its rows of O and dO once more.  Whole
-// backward, bf16, us, with / without a launch for D: d = 64 N = 60 15.1 / 12.1, 512 15.6 / 12.4 (12.1 is the host's time),
-// 1024 15.2 / 16.6; d = 128 N = 128 15.8 / 12.4, 333 17.3 / 21.8 (no mask).
-inline bool own_row_sums(int d, int N, int kv_group) { return (long)((N + 31) / 32) * kv_group <= (d == 64 ? 16 : 8); }
+// behind it) while a wave of a key block has few tiles, each of which then reads its rows of O and dO once more, and all
+// workgroups are on the chip at once, so that nothing waits for them.  Whole backward, bf16, us, with / without a launch
+// for D: d = 64, H = 2: N = 64 10.1 / 7.2 (the host's time), 384 10.2 / 8.3, 512 10.0 / 9.7, 1024 12.0 / 15.6; H = 40,
+// N = 384 17.1 / 20.9;  d = 128, H = 2: N = 128 9.5 / 9.4, 256 10.3 / 12.2, 512 12.3 / 18.0.
+template <int D>
+inline bool own_row_sums(long heads, long kv_heads, int N) {
+    const long tiles = (N + 31) / 32;
+    return tiles * (heads / kv_heads) <= (D == 64 ? 12 : 4) && (heads + kv_heads) * tiles <= (D == 64 ? 512 : 256);
+}
 
 // Up to which length the dQ pass takes 128-query workgroups of four waves with 32-key blocks, two or three to a CU,
 // instead of 256-query ones of eight with 64-key blocks: finer tiles waste less on the diagonal and on ragged ends, and
@@ -1633,7 +1657,9 @@ inline bool own_row_sums(int d, int N, int kv_group) { return (long)((N + 31) / 
 //            2048 282 / 274, 3001 437 / 423, 4096 503 / 501
 //   d = 128  no mask: 512 356 / 340, 1300 710 / 690, 2048 931 / 950;  causal: 512 289 / 267, 1300 455 / 427,
 //            2048 575 / 570, 3001 845 / 863
-constexpr int short_rows(int d, int causal) { return d == 64 && causal ? 3072 : 1536; }
+// Without a mask the line is drawn lower than it would be for these 16 heads: N = 1536, H = 20 68.5 / 65.9 (d = 64) and
+// 112 / 106 (d = 128), but H = 24 82.6 / 86.9 and 153 / 161.
+constexpr int short_rows(int d, int causal) { return causal ? (d == 64 ? 3072 : 1536) : 1280; }
 
 // Whether two runs of bytes share memory.
 inline bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
@@ -1655,8 +1681,8 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
     const long total_q = (long)B * H * ((N + kRows - 1) / kRows);
     if (total > 0x7fffffffL || total_q > 0x7fffffffL) return FA_ERR_SHAPE;
 
-    // Two launches, the dQ pass first: it also writes D, which the dK/dV pass reads.  Or, with both passes in their
-    // few-workgroup forms, D and then both in one launch.
+    // Two launches, the dQ pass first: it also writes D, which the dK/dV pass reads.  Or both passes in one, in their
+    // few-workgroup forms, behind a launch for D or not.
     auto dqp = [&](auto kernel, int rows, bool d_ready) {  // `rows`: queries, and threads / 2, of a workgroup
         const int tiles = (N + rows - 1) / rows, items = B * H * tiles;
         hipLaunchKernelGGL(kernel, dim3((unsigned)items), dim3(rows * 2), 0, stream, u16(q), u16(k), u16(v),
@@ -1664,11 +1690,9 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
                            H / H_kv, scale);
     };
     // workgroups of 32 queries / of 32 keys, when a pass is to use them
-    long dq_few = 0, dkdv_few = 0;
-    if constexpr (D <= 128) {
-        if (total_q <= few_query_tiles(D, causal, total)) dq_few = (long)B * H * ((N + 31) / 32);
-        if (total <= few_key_blocks(D, causal)) dkdv_few = (long)B * H_kv * ((N + 31) / 32);
-    }
+    const BwdForms forms = choose_bwd_forms<D>((long)B * H, (long)B * H_kv, N, causal);
+    const long dq_few = forms.dq_few ? (long)B * H * ((N + 31) / 32) : 0;
+    const long dkdv_few = forms.dkdv_few ? (long)B * H_kv * ((N + 31) / 32) : 0;
     auto few = [&](long n_dkdv, long n_dq, bool d_ready) {
         if constexpr (D <= 128) {
             auto run = [&](auto kernel) {
@@ -1719,8 +1743,8 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
         // dQ written over Q or dO: a workgroup of the dQ pass reads these at its own rows before it writes them, but
         // the dK/dV pass reads all of them and has to come first.  (dK or dV may be over O then: D is not computed again.)
         ok = row_sums() && dkdv_pass() && dq_pass(true);
-    } else if (dq_few && dkdv_few) {
-        const bool own = !over_o && own_row_sums(D, N, H / H_kv);
+    } else if (forms.one_launch) {
+        const bool own = !over_o && own_row_sums<D>((long)B * H, (long)B * H_kv, N);
         ok = own || row_sums();
         if (ok) {
             few(dkdv_few, dq_few, !own);

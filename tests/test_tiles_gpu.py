@@ -36,21 +36,24 @@ def test_fp32_splits_merge_when_their_maxima_differ(causal):
 REL_RMSE, REL_MAXABS = 1e-2, 5e-2  # 2^-9 (bf16) rounding of P, dS and the outputs in sums over the sequence
 
 
-def _check_backward(seed, B, H, H_kv, N, d, causal, dtype):
+def _check_backward(seed, B, H, H_kv, N, d, causal, dtype, kv_heads=None):
+    # against the oracle: everything, or the key/value heads `kv_heads` and their groups
     q, dout = (inputs.normal_tensor(seed, n, (B, H, N, d), dtype) for n in ("q", "do"))
     k, v = (inputs.normal_tensor(seed, n, (B, H_kv, N, d), dtype) for n in ("k", "v"))
     qg, kg, vg, dog = (t.cuda() for t in (q, k, v, dout))
     o, lse = binding.fa_fwd_gqa(qg, kg, vg, d ** -0.5, causal)
     got = binding.fa_bwd_gqa(qg, kg, vg, o, lse, dog, d ** -0.5, causal)
     torch.cuda.synchronize()
-    ref = oracle.attention_bwd_gqa(f64(q), f64(k), f64(v), f64(dout), d ** -0.5, causal)
-    for name, t in zip(("dq", "dk", "dv"), got):
-        g, r = f64(t), ref[name]
-        assert np.isfinite(g).all(), name
-        # the floors: with one visible key dS = P (dP - D) is exactly 0 and what is left are the roundings of two fp32
-        # sums of d products (2^-24 * sqrt(d) * |dO| |V| ~ 2e-6), times |K| * scale
-        ref_rms = float(np.sqrt(np.mean(r * r)))
-        assert rmse(g, r) <= REL_RMSE * ref_rms + 1e-5 and max_abs(g, r) <= REL_MAXABS * np.abs(r).max() + 1e-4, name
+    for h in [slice(0, H_kv)] if kv_heads is None else [slice(i, i + 1) for i in kv_heads]:
+        group = slice(h.start * (H // H_kv), h.stop * (H // H_kv))
+        ref = oracle.attention_bwd_gqa(f64(q[:, group]), f64(k[:, h]), f64(v[:, h]), f64(dout[:, group]), d ** -0.5, causal)
+        for name, t in zip(("dq", "dk", "dv"), got):
+            g, r = f64(t[:, group if name == "dq" else h]), ref[name]
+            assert np.isfinite(g).all(), name
+            # the floors: with one visible key dS = P (dP - D) is exactly 0 and what is left are the roundings of two fp32
+            # sums of d products (2^-24 * sqrt(d) * |dO| |V| ~ 2e-6), times |K| * scale
+            ref_rms = float(np.sqrt(np.mean(r * r)))
+            assert rmse(g, r) <= REL_RMSE * ref_rms + 1e-5 and max_abs(g, r) <= REL_MAXABS * np.abs(r).max() + 1e-4, name
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
@@ -74,19 +77,26 @@ def test_backward_query_split_for_few_key_blocks(d, H, H_kv, N, causal, dtype):
     _check_backward(700 + N + d, 1, H, H_kv, N, d, causal, dtype)
 
 
-@pytest.mark.parametrize("d,causal,most", [(64, False, 192), (64, True, 384), (128, False, 128), (128, True, 192)])
+@pytest.mark.parametrize("d,causal,most", [(64, False, 89), (64, True, 93), (128, False, 74), (128, True, 74)])
 def test_backward_on_both_sides_of_the_key_split_rule(d, causal, most):
-    # the most workgroups of 128 keys that the 32-key form takes over, and one more
-    for H in (most, most + 1):
-        _check_backward(800 + H, 1, H, H, 70, d, causal, "bf16")
+    # the most key/value heads of N = 170 whose dK/dV pass takes the 32-key form by itself, and one more (at d = 128 only
+    # shared heads get there)
+    for H_kv in (most, most + 1):
+        _check_backward(800 + H_kv, 1, H_kv * (4 if d == 128 else 1), H_kv, 170, d, causal, "bf16")
 
 
-@pytest.mark.parametrize("d,causal,most", [(64, False, 96), (64, True, 192), (128, False, 96), (128, True, 128)])
-def test_backward_on_both_sides_of_the_query_split_rule(d, causal, most):
-    # the most workgroups of 256 queries that the 32-query form takes over, and one more; N = 70: three 32-key tiles
-    # for four waves
+def test_backward_on_both_sides_of_the_query_split_rule():
+    # the most heads whose dQ pass takes the 32-query form by itself, and one more
+    for H in (12, 13):
+        _check_backward(900 + H, 1, H, H, 2000, 128, False, "f16", (0, H - 1))
+
+
+@pytest.mark.parametrize("d,causal,N,most", [(64, False, 70, 128), (64, True, 70, 138), (128, False, 70, 106), (128, True, 70, 106),
+                                             (64, True, 32, 320), (128, False, 64, 80)])
+def test_backward_on_both_sides_of_the_one_launch_rule(d, causal, N, most):
+    # the most heads for which both passes share a launch, and one more
     for H in (most, most + 1):
-        _check_backward(900 + H, 1, H, H, 70, d, causal, "f16")
+        _check_backward(850 + H, 1, H, H, N, d, causal, "bf16")
 
 
 @pytest.mark.parametrize("d", [64, 128])
@@ -111,7 +121,8 @@ def test_backward_four_wave_query_tiles(d, N, causal):
     _check_backward(960 + N, 2, 200, 100, N, d, causal, "bf16")
 
 
-@pytest.mark.parametrize("d,causal,N", [(64, True, 3072), (64, True, 3073), (128, False, 1536), (128, False, 1537)])
+@pytest.mark.parametrize("d,causal,N", [(64, True, 3072), (64, True, 3073), (128, True, 1536), (128, True, 1537), (64, False, 1280),
+                                        (128, False, 1281)])
 def test_backward_query_tile_rule_edges(d, causal, N):
     # on both sides of the length up to which the 128-query tiles are used, with more tiles than the few-workgroup form
     # takes (one head's gradients are held against the oracle; the heads share K and V)
@@ -152,12 +163,12 @@ def test_causal_forward_paired_and_single_tiles(heads, N, d, fp8):
         assert max_abs(f64(lse[:, h:h + 1]), l_ref) <= 2e-3
 
 
-@pytest.mark.parametrize("d,causal,H,H_kv", [(64, True, 256, 128), (64, True, 258, 129), (64, False, 256, 64),
-                                             (128, True, 256, 64), (128, True, 260, 65), (128, False, 96, 32)])
-def test_backward_both_passes_in_one_launch(d, causal, H, H_kv):
-    # shared heads on both sides of the rule that lets the dQ work join the 32-key dK/dV launch (N = 70: one 128-key
-    # block and one 256-query tile per head)
-    _check_backward(1100 + H, 1, H, H_kv, 70, d, causal, "bf16")
+@pytest.mark.parametrize("d,causal,N,H,H_kv", [(64, True, 70, 184, 92), (64, True, 70, 186, 93), (64, False, 70, 204, 51), (64, False, 70, 208, 52),
+                                               (128, True, 70, 168, 42), (128, True, 70, 172, 43), (128, True, 512, 96, 12), (128, True, 512, 104, 13),
+                                               (64, False, 512, 128, 16), (64, False, 512, 136, 17)])
+def test_backward_both_passes_in_one_launch(d, causal, N, H, H_kv):
+    # shared heads on both sides of the rules that let both passes share a launch
+    _check_backward(1100 + H, 1, H, H_kv, N, d, causal, "bf16", None if N < 100 else (0, H_kv - 1))
 
 
 @pytest.mark.parametrize("d,N", [(64, 641), (64, 769), (64, 768), (64, 1408), (64, 1409), (128, 897), (128, 1152), (128, 1153)])
@@ -192,9 +203,9 @@ def test_backward_writes_dq_over_an_input(d, H, N, causal, over):
 
 
 # (d, H, N, causal) for every form of the two passes: one launch that computes D for itself, one launch behind the row
-# sums, 32-query / 32-key workgroups of one pass only, 128- and 256-query tiles, the shared-score dK/dV pass
-_FORMS = [(64, 2, 333, False), (64, 2, 1000, True), (128, 2, 100, True), (128, 2, 300, False), (64, 300, 70, True), (128, 110, 70, False),
-          (64, 400, 140, False), (128, 200, 140, True), (128, 100, 140, True), (128, 12, 3001, True), (256, 4, 200, True), (256, 40, 300, False)]
+# sums, 32-key or 32-query workgroups of one pass only, 128- and 256-query tiles, d = 256
+_FORMS = [(64, 2, 333, False), (128, 2, 100, True), (64, 2, 1000, True), (128, 2, 300, False), (64, 88, 170, True), (128, 12, 2000, False),
+          (64, 400, 140, False), (128, 200, 140, True), (64, 30, 1400, False), (128, 20, 2000, True), (256, 4, 200, True), (256, 40, 300, False)]
 
 
 @pytest.mark.parametrize("over", ["dq", "dk", "dv", "dq one head on", "dk one head on"])
@@ -238,8 +249,9 @@ def test_backward_writes_shared_head_gradients_inside_the_output(H, H_kv, N):
 
 
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("d,N,H,H_kv", [(64, 512, 2, 2), (64, 513, 2, 2), (64, 128, 8, 2), (64, 129, 8, 2), (128, 256, 2, 2),
-                                        (128, 257, 2, 2), (128, 100, 4, 2), (128, 3, 2, 1)])
+@pytest.mark.parametrize("d,N,H,H_kv", [(64, 384, 2, 2), (64, 385, 2, 2), (64, 96, 8, 2), (64, 97, 8, 2), (128, 128, 2, 2),
+                                        (128, 129, 2, 2), (128, 64, 4, 2), (128, 65, 4, 2), (128, 3, 2, 1), (64, 32, 256, 256),
+                                        (64, 32, 257, 257), (128, 32, 128, 128), (128, 32, 129, 129)])
 def test_backward_row_sums_inside_the_one_launch(d, N, H, H_kv, causal):
-    # on both sides of the number of tiles up to which the one launch computes D for itself, ragged and not
+    # on both sides of the numbers of tiles and of workgroups up to which the one launch computes D for itself, ragged and not
     _check_backward(1400 + N, 1, H, H_kv, N, d, causal, "bf16")
