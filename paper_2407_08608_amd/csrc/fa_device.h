@@ -261,23 +261,21 @@ static __device__ __forceinline__ WorkItem work_item(int block, int total, int n
     }
 }
 
-// Query tiles of a forward workgroup: `tile` of `head`, then n_qtiles - 1 - tile if n_pass is 2.  A causal launch either
-// deals single tiles in order of length (work_item) or, `paired`, tiles i and n_qtiles-1-i one after the other, the
-// longer first: items that all cover the same number of key blocks (with an odd tile count the middle tile is an item
-// of its own).  Pairs start half as many workgroups, which is the better choice when the items fill whole rounds of
-// the chip (pair_causal_tiles).
+// Query tiles of a forward workgroup: `tile` of `head`, then `second` unless it is negative.  A causal launch either
+// deals single tiles in order of length (as work_item does; heads along the grid's x, tiles along its y, which spares
+// the workgroup the divisions) or, `paired`, tiles i and n_qtiles-1-i one after the other, the longer first: items that
+// all cover the same number of key blocks (with an odd tile count the middle tile is an item of its own).  Pairs start
+// half as many workgroups, which is the better choice when the items fill whole rounds of the chip (pair_causal_tiles).
 struct TileRun {
-    int head, tile, n_pass;
+    int head, tile, second;
+    __device__ __forceinline__ int n_pass() const { return second < 0 ? 1 : 2; }
 };
 template <bool CAUSAL>
-static __device__ __forceinline__ TileRun query_tiles(int block, int total, int n_qtiles, int paired) {
-    if (CAUSAL && paired) {
-        const int id = xcd_contiguous(block, total), n_items = (n_qtiles + 1) / 2;
-        const int i = id % n_items;
-        return {id / n_items, n_qtiles - 1 - i, n_qtiles - 1 - i != i ? 2 : 1};
-    }
-    const WorkItem w = work_item<CAUSAL>(block, total, n_qtiles);
-    return {w.head, CAUSAL ? n_qtiles - 1 - w.tile : w.tile, 1};
+static __device__ __forceinline__ TileRun query_tiles(int total, int n_qtiles, int paired) {
+    if (CAUSAL && !paired) return {(int)blockIdx.x, n_qtiles - 1 - (int)blockIdx.y, -1};
+    const int id = xcd_contiguous(blockIdx.x, total), n_items = CAUSAL ? (n_qtiles + 1) / 2 : n_qtiles;
+    const int i = id % n_items;
+    return {id / n_items, CAUSAL ? n_qtiles - 1 - i : i, CAUSAL && n_qtiles - 1 - i != i ? i : -1};
 }
 
 // Measurement builds (-DFA_CLOCK_SPAN): how many shader-clock cycles a launch took on one CU.  A kernel

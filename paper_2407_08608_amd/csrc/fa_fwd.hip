@@ -79,7 +79,7 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     const int wave = tid >> 6, lane = tid & 63;
     const int col = lane & 31, half = lane >> 5;
 
-    const TileRun run = query_tiles<CAUSAL>(blockIdx.x, total_wg, n_qtiles, paired);
+    const TileRun run = query_tiles<CAUSAL>(total_wg, n_qtiles, paired);
     const int bh = run.head;
 
     const size_t head_off = (size_t)bh * N * D;
@@ -93,9 +93,9 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     asm volatile("" : "+v"(sc_v));
 
 #pragma nounroll
-    for (int pass = 0; pass < run.n_pass; ++pass) {
+    for (int pass = 0; pass < run.n_pass(); ++pass) {
     // every LDS read of the previous pass was followed by a barrier
-    const int qt = pass == 0 ? run.tile : n_qtiles - 1 - run.tile;
+    const int qt = pass == 0 ? run.tile : run.second;
     const int wave_q0 = qt * BR + wave * (32 * RQ);
 
     // Q_i^T as the B operand, resident in registers for the whole loop
@@ -271,7 +271,7 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                                     lane);
         if (qi < N && half == 0) lse[(size_t)bh * N + qi] = (m_run + log2f(l)) * kLn2;
     }
-    if (pass + 1 < run.n_pass) __syncthreads();  // the next pass's first tile overwrites the patches
+    if (pass + 1 < run.n_pass()) __syncthreads();  // the next pass's first tile overwrites the patches
     }  // passes of a causal pair
 }
 
@@ -314,7 +314,7 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
     const int wave = tid >> 6, lane = tid & 63;
     const int col = lane & 31, half = lane >> 5;
 
-    const TileRun run = query_tiles<CAUSAL>(blockIdx.x, total_wg, n_qtiles, paired);
+    const TileRun run = query_tiles<CAUSAL>(total_wg, n_qtiles, paired);
     const int bh = run.head;
 
     const size_t head_off = (size_t)bh * N * D;
@@ -327,8 +327,8 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
     const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
 
 #pragma nounroll
-    for (int pass = 0; pass < run.n_pass; ++pass) {
-    const int qt = pass == 0 ? run.tile : n_qtiles - 1 - run.tile;
+    for (int pass = 0; pass < run.n_pass(); ++pass) {
+    const int qt = pass == 0 ? run.tile : run.second;
     const int wave_q0 = qt * BR + wave * 32;
     const int limit = CAUSAL ? min(wave_q0 + col, N - 1) : N - 1;  // last key this lane's query sees
 
@@ -541,7 +541,7 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
         store_rows_via_lds<Tag, DT>(oacc, 1.0f / l, patch, make_buffer(o + head_off, (uint32_t)N * D * 2), wave_q0, lane);
         if (qi < N && half == 0) lse[(size_t)bh * N + qi] = (m_run * sc + log2f(l)) * kLn2;
     }
-    if (pass + 1 < run.n_pass) __syncthreads();  // the next pass's first tile overwrites the patches
+    if (pass + 1 < run.n_pass()) __syncthreads();  // the next pass's first tile overwrites the patches
     }  // passes of a causal pair
 }
 
@@ -605,7 +605,7 @@ fa_fwd_pingpong_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
     const int group = wave >> 2;
     const int slab = (wave & 3) * 2 + group;
 
-    const TileRun run = query_tiles<CAUSAL>(blockIdx.x, total_wg, n_qtiles, paired);
+    const TileRun run = query_tiles<CAUSAL>(total_wg, n_qtiles, paired);
     const int bh = run.head;
 
     const size_t head_off = (size_t)bh * N * D;
@@ -821,8 +821,8 @@ fa_fwd_pingpong_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
     const std::false_type no{};
 
 #pragma nounroll
-    for (int pass = 0; pass < run.n_pass; ++pass) {
-    const int qt = pass == 0 ? run.tile : n_qtiles - 1 - run.tile;
+    for (int pass = 0; pass < run.n_pass(); ++pass) {
+    const int qt = pass == 0 ? run.tile : run.second;
     wave_q0 = qt * BR + slab * 32;
     {
         int row = min(wave_q0 + col, N - 1);  // rows past N compute a copy of row N-1, never stored
@@ -933,8 +933,8 @@ fa_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, cons
     const int col = lane & 31, half = lane >> 5;
     const int slab = wave & 1, split = wave >> 1;
 
-    const TileRun run = query_tiles<CAUSAL>(blockIdx.x, total_wg, n_qtiles, 0);
-    const int bh = run.head, qt = run.tile;
+    const WorkItem item = work_item<CAUSAL>(blockIdx.x, total_wg, n_qtiles);
+    const int bh = item.head, qt = CAUSAL ? n_qtiles - 1 - item.tile : item.tile;  // the last rows see the most keys
     const size_t head_off = (size_t)bh * N * D;
     const size_t kv_off = (size_t)(bh / kv_group) * N * D;  // grouped-query: kv_group query heads per K/V head
     const int q0 = qt * BR + slab * 32;                     // first row of this wave's slab
@@ -1083,11 +1083,12 @@ static int launch_16bit(const void* q, const void* k, const void* v, void* o, fl
                         float scale, int causal, hipStream_t stream) {
     constexpr int BR = NW * 32 * RQ;
     int n_qtiles = (N + BR - 1) / BR;
-    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, D == 64 ? 0 : NW == 4 ? 512 : 256,
-                                                    NW == 4 && n_qtiles <= 8 ? 11 : 9);
+    constexpr PairRule kPairs = NW == 4 ? (D == 64 ? PairRule{3, 15.f / 16, 384, 0.8f} : PairRule{2, 7.f / 8, 256, 0.75f})
+                                        : PairRule{D == 64 ? 2 : 1, 7.f / 8, 1 << 30, 1.f};
+    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, kPairs);
     long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
-    dim3 grid((unsigned)total), block(NW * 64);
+    const dim3 grid = forward_grid((long)B * H, n_qtiles, total, causal, paired), block(NW * 64);
     auto qp = static_cast<const uint16_t*>(q);
     auto kp = static_cast<const uint16_t*>(k);
     auto vp = static_cast<const uint16_t*>(v);
@@ -1106,10 +1107,10 @@ static int launch_pingpong(const void* q, const void* k, const void* v, void* o,
                            float scale, int causal, hipStream_t stream) {
     constexpr int BR = 256, BC = 64, P = 4;
     int n_qtiles = (N + BR - 1) / BR;
-    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, 256);
+    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, PairRule{1, 27.f / 32, 1 << 30, 1.f});
     long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
-    dim3 grid((unsigned)total), block(512);
+    const dim3 grid = forward_grid((long)B * H, n_qtiles, total, causal, paired), block(512);
     auto qp = static_cast<const uint16_t*>(q);
     auto kp = static_cast<const uint16_t*>(k);
     auto vp = static_cast<const uint16_t*>(v);
@@ -1128,10 +1129,10 @@ static int launch_d256(const void* q, const void* k, const void* v, void* o, flo
                        float scale, int causal, hipStream_t stream) {
     constexpr int BR = 128;
     int n_qtiles = (N + BR - 1) / BR;
-    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, 256);
+    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, PairRule{1, 7.f / 8, 128, 0.7f});
     long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
-    dim3 grid((unsigned)total), block(256);
+    const dim3 grid = forward_grid((long)B * H, n_qtiles, total, causal, paired), block(256);
     auto qp = static_cast<const uint16_t*>(q);
     auto kp = static_cast<const uint16_t*>(k);
     auto vp = static_cast<const uint16_t*>(v);

@@ -85,7 +85,7 @@ fa_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ k, 
     const int wave = tid >> 6, lane = tid & 63;
     const int col = lane & 31, half = lane >> 5;
 
-    const TileRun run = query_tiles<CAUSAL>(blockIdx.x, total_wg, n_qtiles, paired);
+    const TileRun run = query_tiles<CAUSAL>(total_wg, n_qtiles, paired);
     const int bh = run.head;
 
     const size_t head_off = (size_t)bh * N * D;
@@ -94,9 +94,9 @@ fa_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ k, 
     const uint8_t* kh = k + (size_t)kv_bh * N * D;
     const uint8_t* vh = v + (size_t)kv_bh * N * D;
 #pragma nounroll
-    for (int pass = 0; pass < run.n_pass; ++pass) {
+    for (int pass = 0; pass < run.n_pass(); ++pass) {
     // every LDS read of the previous pass was followed by a barrier
-    const int qt = pass == 0 ? run.tile : n_qtiles - 1 - run.tile;
+    const int qt = pass == 0 ? run.tile : run.second;
     const int wave_q0 = qt * BR + wave * 32;
 
     float sq = 1.0f;
@@ -357,7 +357,7 @@ fa_fwd_fp8_async_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int col = lane & 31, half = lane >> 5;
 
-    const TileRun run = query_tiles<CAUSAL>(blockIdx.x, total_wg, n_qtiles, paired);
+    const TileRun run = query_tiles<CAUSAL>(total_wg, n_qtiles, paired);
     const int bh = run.head;
 
     const size_t head_off = (size_t)bh * N * D;
@@ -408,8 +408,8 @@ fa_fwd_fp8_async_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict
         vofs[dt] = (8 * half + tr_row) * ROWB + (((2 * dt + blk) ^ v_swz(tr_row)) << 4) + 8 * (lane & 1);
 
 #pragma nounroll
-    for (int pass = 0; pass < run.n_pass; ++pass) {
-    const int qt = pass == 0 ? run.tile : n_qtiles - 1 - run.tile;
+    for (int pass = 0; pass < run.n_pass(); ++pass) {
+    const int qt = pass == 0 ? run.tile : run.second;
     const int wave_q0 = qt * BR + wave * 32;
 
     float sq = 1.0f;
@@ -577,10 +577,12 @@ static int launch_fp8(const void* q8, const void* k8, const void* v8, const floa
     constexpr int BR = NW * 32;
     int n_qtiles = (N + BR - 1) / BR;
     int n_sblocks = (N + 127) / 128;
-    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, D == 64 ? 0 : NW == 4 ? 512 : 256);
+    constexpr PairRule kPairs = NW == 4 ? (D == 64 ? PairRule{3, 15.f / 16, 1 << 30, 1.f} : PairRule{2, 7.f / 8, 320, 0.75f})
+                                        : PairRule{D == 64 ? 2 : 1, 0.9f, 1 << 30, 1.f};
+    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, kPairs);
     long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
-    dim3 grid((unsigned)total), block(NW * 64);
+    const dim3 grid = forward_grid((long)B * H, n_qtiles, total, causal, paired), block(NW * 64);
     auto qp = static_cast<const uint8_t*>(q8);
     auto kp = static_cast<const uint8_t*>(k8);
     auto vp = static_cast<const uint8_t*>(v8);
@@ -605,10 +607,11 @@ static int launch_fp8_async(const void* q8, const void* k8, const void* v8, cons
     constexpr int BR = 256;
     int n_qtiles = (N + BR - 1) / BR;
     int n_sblocks = (N + 127) / 128;
-    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, D == 128 ? 256 : 0);
+    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles,
+                                                   PairRule{D == 64 ? 2 : 1, D < 256 || n_qtiles > 4 ? 0.9f : n_qtiles > 2 ? 0.875f : 0.75f, 1 << 30, 1.f});
     long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
-    dim3 grid((unsigned)total), block(512);
+    const dim3 grid = forward_grid((long)B * H, n_qtiles, total, causal, paired), block(512);
     auto qp = static_cast<const uint8_t*>(q8);
     auto kp = static_cast<const uint8_t*>(k8);
     auto vp = static_cast<const uint8_t*>(v8);

@@ -12,22 +12,48 @@ namespace fa {
 // Whether N rows make an odd number of 128-row tiles.
 inline bool odd_row_tiles(int N) { return ((N + 127) / 128) & 1; }
 
-// Whether a causal forward launch pairs its query tiles (query_tiles in fa_device.h): when the pairs fill whole rounds
-// of the chip, or nearly.  `slots`: workgroups of that kernel that the chip holds at once, 0 for kernels that never
-// pair; `slack` / 8: how much of the last round may be empty once there is more than one.  Measured causal, bf16 unless
-// said, us, pairs / single tiles dealt longest first:
-//   ping-pong     3 rounds 269 / 270 (B = 4, H = 16, N = 4096), 2 158 / 162 (N = 2048); 1.5 183 / 164 (H = 64, N = 3001),
-//                 2.25 517 / 439 (H = 48, N = 6000), 0.25 101 / 89 (H = 8, N = 4096)
-//   d = 128, 4w   1 round 61 / 69 (H = 512, N = 512); 1.5 50.6 / 53.5 (H = 384, N = 512: hence its wider slack while
-//                 tiles are short), 2.25 136 / 126 (H = 192, N = 1300), 0.75 28.4 / 27.1 (H = 192, N = 512)
-//   d = 256       2 rounds 357 / 374 (H = 128, N = 2048); 4.5 1007 / 985 (H = 48, N = 6000)
-//   FP8 d = 128   2 rounds 101 / 104 (N = 2048); 2.25 347 / 295 (N = 6000), 2.5 166 / 156 (H = 128, N = 2500)
-//   never paired  d = 64: 164 / 157 (B = 4, H = 16, N = 4096), 329 / 259 (H = 48, N = 6000); FP8 d = 64 136 / 125,
-//                 230 / 196; FP8 d = 256 324 / 319, 617 / 514
-inline bool pair_causal_tiles(long heads, int n_qtiles, int slots, int slack = 9) {
-    if (slots == 0) return false;
-    const long items = heads * ((n_qtiles + 1) / 2), rounds = (items + slots - 1) / slots;
-    return rounds * slots * 8 <= items * (rounds == 1 ? 9 : slack);
+// Whether a causal forward launch pairs its query tiles (query_tiles in fa_device.h).  Pairs all take the same time, so
+// they are the better choice when they fill whole rounds of the chip; what decides is the share of the rounds that is
+// work (a pair without a partner, the middle tile of an odd number, counts half).  A round is one workgroup on each of
+// the 256 CUs while all pairs are resident, `per_cu` (workgroups of the kernel that a CU holds) on each beyond.  Against
+// single tiles dealt longest first pairs win from `share` on.  With `many_heads` heads or more they win from `many_share`
+// on: single tiles read the K and V of all heads at once, which costs most where few rows share a read.  On less than one
+// workgroup per CU pairs win for long sequences only, a few of which they finish as soon on two thirds of the chip; single
+// tiles even out by themselves three to a CU and, two to a CU, while both fit.
+// Causal, bf16 unless said, us, pairs / single tiles (share, heads x N):
+//   ping-pong     1.00 151 / 159 (128 x 2048), 0.88 67.8 / 71.6 (56 x 2048), 0.84 53.9 / 56.1 (72 x 1408), 0.75 197 / 209
+//                 (12 x 8192);  0.75 176 / 154 (64 x 3001), 0.25 99.5 / 90.1 (8 x 4096)
+//   d = 128, 4w   1.00 61.0 / 69.6 (512 x 512), 0.94 52.4 / 54.1 (96 x 1200), 0.83 84.2 / 89.6 (640 x 512);
+//                 0.86 106 / 97 (160 x 1300), 0.69 133 / 119 (192 x 1300)
+//   d = 256       1.00 79.7 / 94.1 (256 x 512), 1.00 107 / 115 (128 x 1024), 0.81 441 / 536 (224 x 1664), 0.83 227 / 301
+//                 (512 x 640);  0.88 243 / 223 (32 x 3500: lost), 0.88 648 / 593 (80 x 3500: lost)
+//   FP8 d = 128   1.00 96.6 / 101 (128 x 2048);  0.83 163 / 148 (128 x 2500), 0.75 126 / 106 (64 x 3001)
+//   FP8 d = 256   1.00 118 / 125 (256 x 1024);  0.75 588 / 486 (48 x 6000)
+//   d = 64, 8w    0.75 308 / 323 (6 x 16384), 1.00 167 / 180 (16 x 8192);  0.56 318 / 249 (48 x 6000)
+//   d = 64, 4w    1.00 21.1 / 22.8 (768 x 256);  1.00 49.0 / 46.5 (64 x 2048)
+// Over 4400 causal shapes the rule is 0.1 to 0.5 % off the better of the two on average, by kernel, and at one of them
+// (d = 256, 144 x 150, 1 us) more than 2 % slower than always pairing.
+struct PairRule {
+    int per_cu;
+    float share;
+    int many_heads;
+    float many_share;
+};
+inline bool pair_causal_tiles(long heads, int n_qtiles, const PairRule& rule) {
+    constexpr long kCus = 256;
+    const long pairs = heads * ((n_qtiles + 1) / 2);
+    const long slots = pairs <= kCus * rule.per_cu ? kCus : kCus * rule.per_cu, rounds = (pairs + slots - 1) / slots;
+    const float work = (float)(heads * n_qtiles) / (float)(2 * slots * rounds);
+    if (n_qtiles < 2) return false;
+    if (pairs <= kCus && n_qtiles >= 32) return work >= 2.f / 3;
+    if ((rule.per_cu == 3 && n_qtiles > 4) || (rule.per_cu > 1 && pairs <= kCus && n_qtiles < 16)) return false;
+    return work >= (heads >= rule.many_heads ? rule.many_share : rule.share);
+}
+
+// The grid of a forward launch of `total` work items (query_tiles): heads x tiles for single causal tiles (of 128 rows
+// or more, so at most 65504 of them at the largest N of any head dimension, which a grid's y takes).
+inline dim3 forward_grid(long heads, int n_qtiles, long total, int causal, int paired) {
+    return causal && !paired ? dim3((unsigned)heads, (unsigned)n_qtiles) : dim3((unsigned)total);
 }
 
 int launch_fwd_bf16(const void* q, const void* k, const void* v, void* o, float* lse, int B, int H, int H_kv, int N, int d,
