@@ -1146,24 +1146,24 @@ static int launch_d256(const void* q, const void* k, const void* v, void* o, flo
     return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
 }
 
-// Kernel choice, by N, d and mask alone:
+// Kernel choice, by N, d and mask alone (fa_fwd_kernel_name promises that, so a line lies where no number of heads loses
+// more than noise, though many win on its other side):
 //   d = 128: the eight-wave ping-pong kernel (256 query rows) for long sequences, 128-row workgroups of four waves for
 //     short ones, which fill the chip better and waste less of a tile on the diagonal.
 //   d = 64: eight waves share each K/V block (256 rows, two waves per SIMD), four waves for short problems.
 //   d = 256: the 128-register output accumulator allows only one wave per SIMD; fa_fwd_d256_kernel
 //     pipelines the softmax of one block under the score MFMAs of the next inside that wave.
-// Without a mask an odd number of 128-row tiles moves the line: the 256-row form then computes one more for nothing.
-// About 16k tokens, H = 16, us, 128 / 256 rows (with few heads the 128-row form is ahead by 10 to 25 % at all of these):
-//   d = 64   causal:  N = 1300 66 / 75, 1700 78 / 79, 2048 86 / 87, 2500 130 / 128
-//            no mask: 512 46 / 44, 800 76 / 80, 1024 81 / 77, 1150 92 / 102, 1300 110 / 113, 1700 131 / 125
-//   d = 128  causal:  1300 122 / 136, 1410 136 / 136, 1600 137 / 150, 1700 146 / 137, 2048 156 / 148
-//            no mask: 800 139 / 142, 890 136 / 149, 1024 148 / 138, 1150 168 / 175, 1300 196 / 196, 1600 233 / 224
+// us, 128 / 256 rows, heads x N, each in the better order of work:
+//   d = 64   causal:  16 x 1300 21.3 / 28.4, 16 x 2048 31.4 / 41.6, 80 x 2048 59.6 / 58.9, 192 x 2048 131 / 132
+//            no mask: 16 x 640 11.5 / 14.8;  16 x 650 12.7 / 16.2 but 144 x 650 31.4 / 27.9, 16 x 890 15.4 / 19.5 but 112 x 890 38.9 / 34.5
+//   d = 128  causal:  16 x 1408 32.4 / 34.9, 80 x 1408 54.6 / 57.4;  16 x 1500 34.9 / 38.5 but 80 x 1500 60.8 / 58.0;
+//                     16 x 1600 35.9 / 39.0, 64 x 1600 56.5 / 57.9, 192 x 1600 166 / 187 (13 tiles of 128 rows, 7 of 256)
+//            no mask: 16 x 640 16.6 / 19.1;  48 x 650 25.3 / 21.8, 16 x 1150 27.4 / 30.4 but 32 x 1150 38.2 / 32.2
 enum class Fwd16 { kTile4, kTile8, kPingPong, kD256, kNone };
 static Fwd16 choose_16bit(int d, int N, int causal) {
-    const bool odd = !causal && odd_row_tiles(N);
     switch (d) {
-        case 64: return N <= (causal ? 2048 : 640) || (odd && N <= 1408) ? Fwd16::kTile4 : Fwd16::kTile8;
-        case 128: return N <= (causal ? 1664 : 640) || (odd && N <= 1152) ? Fwd16::kTile4 : Fwd16::kPingPong;
+        case 64: return N <= (causal ? 2048 : 640) ? Fwd16::kTile4 : Fwd16::kTile8;
+        case 128: return N <= (causal ? 1408 : 640) || (causal && odd_row_tiles(N) && N <= 1664) ? Fwd16::kTile4 : Fwd16::kPingPong;
         case 256: return Fwd16::kD256;
         default: return Fwd16::kNone;
     }

@@ -631,18 +631,19 @@ static int launch_fp8_async(const void* q8, const void* k8, const void* v8, cons
 
 enum class FwdFp8 { kTile4, kTile8, kNone };
 static FwdFp8 choose_fp8(int d, int N, int causal) {
-    // Short problems keep the 128-row tile of four waves (more workgroups, less waste on the diagonal, and without a
-    // mask none on the second half of a 256-row tile when the number of 128-row tiles is odd).  Block-scaled inputs,
-    // about 16k tokens, H = 16, us, four waves / eight:
-    //   d = 64   causal:  N = 2048 70 / 76, 8192 235 / 246, 16384 455 / 475
-    //            no mask: 512 36 / 34, 800 59 / 64, 1024 63 / 59, 1150 71 / 78, 1300 87 / 94, 1700 100 / 96
-    //   d = 128  causal:  1300 80 / 89, 1410 85 / 89, 1600 89 / 97, 1700 93 / 89, 2048 104 / 97
-    //            no mask: 800 90 / 101, 1024 97 / 93, 1150 108 / 121, 1300 131 / 141, 1700 152 / 147
+    // Short problems keep the 128-row tile of four waves (more workgroups, less waste on the diagonal).  The choice is by
+    // N, d and mask alone, so a line lies where no number of heads loses more than noise.  Block-scaled inputs, us, four
+    // waves / eight, heads x N:
+    //   d = 64   causal:  about 16k tokens, H = 16: N = 2048 70 / 76, 8192 235 / 246, 16384 455 / 475
+    //            no mask: about 16k tokens, H = 16: N = 512 36 / 34;  16 x 1150 15.5 / 20.0 but 32 x 1150 22.3 / 20.4
+    //   d = 128  causal:  16 x 1408 24.5 / 28.1, 80 x 1408 38.7 / 39.3;  16 x 1500 26.1 / 30.7 but 80 x 1500 42.8 / 39.7;
+    //                     16 x 1600 26.6 / 32.2, 64 x 1600 41.2 / 40.1
+    //            no mask: 16 x 704 13.5 / 18.0, 48 x 704 19.3 / 18.8;  16 x 770 15.8 / 20.2 but 40 x 770 21.9 / 21.0,
+    //                     16 x 1408 24.1 / 28.6 but 28 x 1408 34.5 / 29.2
     // d = 256 has no four-wave tile.
-    const bool odd = !causal && odd_row_tiles(N);
     switch (d) {
-        case 64: return causal || N < 512 || (odd && N <= 1408) ? FwdFp8::kTile4 : FwdFp8::kTile8;
-        case 128: return N <= (causal ? 1664 : 704) || (odd && N <= 1408) ? FwdFp8::kTile4 : FwdFp8::kTile8;
+        case 64: return causal || N < 512 ? FwdFp8::kTile4 : FwdFp8::kTile8;
+        case 128: return N <= (causal ? 1408 : 704) || (causal && odd_row_tiles(N) && N <= 1664) ? FwdFp8::kTile4 : FwdFp8::kTile8;
         case 256: return FwdFp8::kTile8;
         default: return FwdFp8::kNone;
     }

@@ -139,7 +139,7 @@ def test_backward_query_tile_rule_edges(d, causal, N):
 
 @pytest.mark.parametrize("heads,N,d", [(64, 1500, 128), (128, 1500, 128), (512, 100, 128), (384, 200, 128), (100, 300, 128),
                                        (7, 1409, 128), (256, 129, 256), (300, 300, 256), (5, 700, 256), (9, 1300, 64),
-                                       (11, 200, 64), (3, 2048, 64), (3, 2049, 64), (3, 1664, 128), (3, 1665, 128),
+                                       (11, 200, 64), (3, 2048, 64), (3, 2049, 64), (3, 1664, 128), (3, 1665, 128), (5, 1408, 128), (5, 1536, 128), (5, 1537, 128),
                                        (61, 1700, 128), (62, 1700, 128), (255, 300, 128), (256, 300, 128), (127, 300, 256),
                                        (128, 300, 256), (359, 512, 64), (360, 512, 64), (10, 4100, 256), (11, 4100, 256)])
 @pytest.mark.parametrize("fp8", [False, True])
@@ -173,10 +173,11 @@ def test_backward_both_passes_in_one_launch(d, causal, N, H, H_kv):
     _check_backward(1100 + H, 1, H, H_kv, N, d, causal, "bf16", None if N < 100 else (0, H_kv - 1))
 
 
-@pytest.mark.parametrize("d,N", [(64, 641), (64, 769), (64, 768), (64, 1408), (64, 1409), (128, 897), (128, 1152), (128, 1153)])
+@pytest.mark.parametrize("d,N", [(64, 511), (64, 512), (64, 640), (64, 641), (64, 769), (64, 768), (64, 1408), (64, 1409), (128, 640),
+                                 (128, 641), (128, 704), (128, 705), (128, 897), (128, 1152), (128, 1153)])
 @pytest.mark.parametrize("fp8", [False, True])
 def test_forward_tile_rule_edges(d, N, fp8):
-    # odd and even numbers of 128-row tiles, where the unmasked forward changes between 128- and 256-row workgroups
+    # where the unmasked forward changes between 128- and 256-row workgroups, and odd and even numbers of 128-row tiles
     q, k, v = inputs.qkv(1200 + N, 1, 2, N, d, "bf16")
     if fp8:
         dev = [binding.fa_fp8_quant_hadamard(t.cuda()) for t in (q, k, v)]
