@@ -1077,6 +1077,82 @@ fa_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, cons
     }
 }
 
+// fp32, N <= 32: one wave does a head by itself, straight from and to memory -- the score tile's operands, a row of K and
+// of Q per lane, need no sharing, and V read down a column is 128 contiguous bytes per half wave.  Neither LDS nor a barrier,
+// so the chip holds as many waves as the registers allow; bound by latency with few heads and by memory with many.
+// The kernel above stages 128 keys for 64 rows of which all but 32 are padding here.  No mask, us, the kernel above / one
+// thread per row and scalar FMAs / this one: 8192 heads N = 1 153 / 94 / 24, N = 16 171 / 123 / 31, N = 32 181 / 168 / 67
+// (4.0 TB/s); 512 heads N = 32 12.4 / 27.1 / 6.3; 1 head N = 32 6.3 / 24.2 / 5.3.
+template <bool CAUSAL>
+__global__ void __launch_bounds__(256, 4)
+fa_fwd_f32_short_kernel(const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+                        float* __restrict__ o, float* __restrict__ lse, int N, int n_heads, int kv_group, float scale) {
+    constexpr int D = 64;
+    const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
+    const int bh = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (bh >= n_heads) return;
+    const size_t head_off = (size_t)bh * N * D;
+    const size_t kv_off = (size_t)(bh / kv_group) * N * D;  // grouped-query: kv_group query heads per K/V head
+    const int row = min(col, N - 1);                        // rows past N compute a copy of row N-1, never stored
+    const float sc = scale * kLog2e;
+    const __amdgpu_buffer_rsrc_t k_rsrc = make_buffer(k + kv_off, (uint32_t)N * D * 4);  // rows past N read as zero
+    const __amdgpu_buffer_rsrc_t v_rsrc = make_buffer(v + kv_off, (uint32_t)N * D * 4);
+
+    // S^T = K Q^T: step i contracts head-dim elements {i, 32 + i}
+    f32x4 kreg[D / 8], qreg[D / 8];
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j) {
+        kreg[j] = __builtin_bit_cast(f32x4, buffer_load_16B(k_rsrc, (col * D + half * (D / 2) + 4 * j) * 4));
+        qreg[j] = *reinterpret_cast<const f32x4*>(q + head_off + (size_t)row * D + half * (D / 2) + 4 * j);
+    }
+    float vreg[16][2];  // score register r is key 8 (r / 4) + 4 half + r % 4
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+            vreg[r][dt] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                              v_rsrc, ((8 * (r >> 2) + 4 * half + (r & 3)) * D + dt * 32 + col) * 4, 0, 0));
+    f32x16 s, acc[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = acc[0][r] = acc[1][r] = 0.f;
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kreg[j][e], qreg[j][e], s, 0, 0, 0);
+
+    const int bound = (CAUSAL ? row : N - 1) - 4 * half;  // last visible key of the lane's half
+    float m = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        if (8 * (r >> 2) + (r & 3) > bound) s[r] = -INFINITY;
+        m = fmaxf(m, s[r]);
+    }
+    m = max_both_halves(m);
+    const float mb = m == -INFINITY ? 0.f : m * sc;  // every score -inf: P = 0
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        s[r] = fast_exp2(__builtin_fmaf(s[r], sc, -mb));
+        l += s[r];
+    }
+    l = sum_both_halves(l);
+    // O^T = V^T P^T
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vreg[r][dt], s[r], acc[dt], 0, 0, 0);
+
+    if (col >= N) return;
+    const float inv = 1.0f / l;
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 w = {acc[dt][4 * g] * inv, acc[dt][4 * g + 1] * inv, acc[dt][4 * g + 2] * inv, acc[dt][4 * g + 3] * inv};
+            *reinterpret_cast<f32x4*>(o + head_off + (size_t)col * D + dt * 32 + 8 * g + 4 * half) = w;
+        }
+    if (half == 0) lse[(size_t)bh * N + col] = (m * sc + log2f(l)) * kLn2;
+}
+
 // ---------------------------------------------------------------------------------------
 template <typename Tag, int D, int BC, int NW, int RQ, int PD>
 static int launch_16bit(const void* q, const void* k, const void* v, void* o, float* lse, int B, int H, int H_kv, int N,
@@ -1243,7 +1319,14 @@ int launch_fwd_f32(const void* q, const void* k, const void* v, void* o, float* 
     auto kp = static_cast<const float*>(k);
     auto vp = static_cast<const float*>(v);
     auto op = static_cast<float*>(o);
-    if (causal)
+    if (f32_short(N)) {
+        const long heads = (long)B * H;
+        const dim3 waves((unsigned)((heads + 3) / 4));
+        if (causal)
+            hipLaunchKernelGGL(fa_fwd_f32_short_kernel<true>, waves, dim3(256), 0, stream, qp, kp, vp, op, lse, N, (int)heads, H / H_kv, scale);
+        else
+            hipLaunchKernelGGL(fa_fwd_f32_short_kernel<false>, waves, dim3(256), 0, stream, qp, kp, vp, op, lse, N, (int)heads, H / H_kv, scale);
+    } else if (causal)
         hipLaunchKernelGGL((fa_fwd_f32_kernel<64, 32, true>), grid, block, 0, stream, qp, kp, vp, op, lse, N, n_qtiles,
                            (int)total, H / H_kv, scale);
     else

@@ -9,6 +9,9 @@
 
 namespace fa {
 
+// Whether an fp32 forward is short enough for fa_fwd_f32_short_kernel.
+inline bool f32_short(int N) { return N <= 32; }
+
 // Whether N rows make an odd number of 128-row tiles.
 inline bool odd_row_tiles(int N) { return ((N + 127) / 128) & 1; }
 

@@ -88,7 +88,9 @@ def test_kernel_name_query_follows_the_launcher():
                     n = name(dtype, N, d, causal)
                     assert n and n.startswith("fa_fwd_") and ("true" if causal else "false") in n
     assert name(binding.FA_F32, 256, 64, False) == "fa_fwd_f32_kernel<64, 32, false>"
-    assert name(binding.FA_F32, 256, 128, False) is None and name(binding.FA_BF16, 256, 96, False) is None
+    assert name(binding.FA_F32, 33, 64, True) == "fa_fwd_f32_kernel<64, 32, true>"
+    assert name(binding.FA_F32, 32, 64, True) == "fa_fwd_f32_short_kernel<true>"
+    assert name(binding.FA_F32, 256, 128, False) is None and name(binding.FA_F32, 32, 128, False) is None and name(binding.FA_BF16, 256, 96, False) is None
     assert name(binding.FA_BF16, 0, 128, False) is None and name(9, 16, 128, False) is None
     # every kernel the benchmark holds a measured HBM-traffic figure for is one the launcher can still choose
     sweep = {name(dt, N, 128, c) for dt in (binding.FA_BF16, binding.FA_FP8_E4M3) for N in bench.SEQLENS

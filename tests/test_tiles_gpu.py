@@ -23,6 +23,17 @@ def test_fp32_tile_and_split_edges(N, causal):
 
 
 @pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("H,H_kv,N", [(1, 1, 1), (3, 3, 2), (6, 2, 7), (4, 1, 16), (9, 9, 31), (10, 5, 32), (700, 700, 9), (5, 5, 33)])
+def test_fp32_short_sequences(H, H_kv, N, causal):
+    # up to 32 keys a wave does a head by itself, four to a workgroup: head counts that fill it and do not
+    q = inputs.normal_tensor(320 + N, "q", (1, H, N, 64), "f32")
+    k, v = (inputs.normal_tensor(320 + N, n, (1, H_kv, N, 64), "f32") for n in ("k", "v"))
+    o, lse = binding.fa_fwd_gqa(q.cuda(), k.cuda(), v.cuda(), 0.125, causal)
+    o_ref, l_ref = oracle.attention_fwd_gqa(f64(q), f64(k), f64(v), 0.125, causal)
+    assert max_abs(f64(o), o_ref) <= 1e-5 and max_abs(f64(lse), l_ref) <= 1e-5  # fp32 sums of at most 64 terms
+
+
+@pytest.mark.parametrize("causal", [False, True])
 def test_fp32_splits_merge_when_their_maxima_differ(causal):
     # scores rise to 80 nats over the sequence: the splits of a row end with different maxima.  A raw score of up
     # to 640 in sums of 64 terms carries about 8 roundings of 2^-24 * 640, times 1 / 8: 4e-5 relative in P, and
