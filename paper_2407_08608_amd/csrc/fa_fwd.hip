@@ -1045,10 +1045,11 @@ fa_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, cons
     float m_all = -INFINITY, l_all = 0.f;
 #pragma unroll
     for (int w = 0; w < SPLITS; ++w) m_all = fmaxf(m_all, lds_m[w][slab * 32 + col]);
+    const float m_ref = m_all == -INFINITY ? 0.f : m_all;  // a row whose every score is -inf: l = 0, L = -inf
 #pragma unroll
     for (int w = 0; w < SPLITS; ++w)
-        l_all += lds_l[w][slab * 32 + col] * fast_exp2((lds_m[w][slab * 32 + col] - m_all) * sc);
-    const float f = fast_exp2((m_run - m_all) * sc) / l_all;
+        l_all += lds_l[w][slab * 32 + col] * fast_exp2((lds_m[w][slab * 32 + col] - m_ref) * sc);
+    const float f = fast_exp2((m_run - m_ref) * sc) / l_all;
     // the K buffers are free: [split][row][d] partial outputs, already scaled
     static_assert(sizeof(lds_k) >= SPLITS * BR * KSTR * sizeof(float), "partial outputs must fit");
     float* part = &lds_k[0][0];

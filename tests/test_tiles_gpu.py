@@ -34,6 +34,27 @@ def test_fp32_short_sequences(H, H_kv, N, causal):
 
 
 @pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("N,hidden", [(20, 20), (100, 100), (100, 40), (300, 300), (300, 64)])
+def test_fp32_rows_whose_every_score_is_minus_infinity(N, hidden, causal):
+    # keys hidden through -inf in one component: a row that sees only such keys has L = -inf (and no output), others
+    # are untouched by them
+    q = inputs.normal_tensor(330, "q", (1, 2, N, 64), "f32")
+    k, v = (inputs.normal_tensor(330, n, (1, 2, N, 64), "f32") for n in ("k", "v"))
+    q[..., 0] = 1.0
+    k[:, :, :hidden, 0] = -np.inf
+    o, lse = (t.cpu().double() for t in binding.fa_fwd(q.cuda(), k.cuda(), v.cuda(), 0.125, causal))
+    s = torch.matmul(q.double(), k.double().transpose(-1, -2).contiguous()) * 0.125
+    if causal:
+        s = s.masked_fill(torch.ones(N, N, dtype=torch.bool).triu(1), -np.inf)
+    ref = torch.logsumexp(s, dim=-1)
+    seen = torch.isfinite(ref)
+    assert (lse[~seen] == -np.inf).all() and torch.isnan(o[~seen]).all()
+    assert float(torch.where(seen, lse - ref, 0.0).abs().max()) <= 2e-5
+    o_ref = torch.matmul(torch.softmax(s, dim=-1), v.double())
+    assert float(torch.where(seen[..., None], o - o_ref, 0.0).abs().max()) <= 2e-5  # fp32 sums of at most 300 terms
+
+
+@pytest.mark.parametrize("causal", [False, True])
 def test_fp32_splits_merge_when_their_maxima_differ(causal):
     # scores rise to 80 nats over the sequence: the splits of a row end with different maxima.  A raw score of up
     # to 640 in sums of 64 terms carries about 8 roundings of 2^-24 * 640, times 1 / 8: 4e-5 relative in P, and
