@@ -21,7 +21,7 @@
  *     never synchronise, allocate or free device memory, throw, or abort.
  *   - The return value is an fa_status.  Every argument and size check precedes the first
  *     launch: on any status other than FA_OK and FA_ERR_LAUNCH nothing has been enqueued.
- *     FA_ERR_LAUNCH means the HIP runtime refused a launch; calls made of several kernels
+ *     FA_ERR_LAUNCH means the HIP runtime refused a launch; calls made of several launches
  *     (fa_bwd*: two, or three with dq == q or dq == dout; fa_fp8_quant_hadamard with
  *     per_tensor = 1: four) stop at the refused one, and the outputs are then undefined.
  *     fa_status_string() names a status.
@@ -31,6 +31,8 @@
  *   - Size limits: B*H*N < 2^31 rows (else FA_ERR_SHAPE) and, because one head is
  *     addressed through 32-bit byte offsets, 4*N*d <= 0x7ff00000 (else
  *     FA_ERR_UNSUPPORTED): N <= 4 192 256 at d = 128, twice that at d = 64, half at 256.
+ *     HIP refuses a launch of 2^32 threads or more (FA_ERR_LAUNCH): a request of so many short sequences
+ *     that its kernel needs them, B*H of 8 million or more, has to be split by the caller.
  *   - Thread-safe: no mutable global state.
  */
 #ifndef FA_MI355_H

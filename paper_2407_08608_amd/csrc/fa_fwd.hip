@@ -916,8 +916,8 @@ fa_fwd_pingpong_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
 template <int D, int BC, bool CAUSAL>
 __global__ void __launch_bounds__(512, 2)
 fa_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
-                  float* __restrict__ o, float* __restrict__ lse, int N, int n_qtiles, int total_wg, int kv_group,
-                  float scale) {
+                  float* __restrict__ o, float* __restrict__ lse, int N, int n_qtiles, int total_wg, int first_head,
+                  int kv_group, float scale) {
     static_assert(D == 64 && BC == 32, "one 32-key score tile per wave and block, two 32-column output tiles");
     constexpr int NT = 512, SLABS = 2, SPLITS = 4;
     constexpr int BR = 32 * SLABS;    // query rows per workgroup
@@ -934,7 +934,7 @@ fa_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, cons
     const int slab = wave & 1, split = wave >> 1;
 
     const WorkItem item = work_item<CAUSAL>(blockIdx.x, total_wg, n_qtiles);
-    const int bh = item.head, qt = CAUSAL ? n_qtiles - 1 - item.tile : item.tile;  // the last rows see the most keys
+    const int bh = first_head + item.head, qt = CAUSAL ? n_qtiles - 1 - item.tile : item.tile;  // the last rows see the most keys
     const size_t head_off = (size_t)bh * N * D;
     const size_t kv_off = (size_t)(bh / kv_group) * N * D;  // grouped-query: kv_group query heads per K/V head
     const int q0 = qt * BR + slab * 32;                     // first row of this wave's slab
@@ -1315,25 +1315,33 @@ int launch_fwd_f32(const void* q, const void* k, const void* v, void* o, float* 
     int n_qtiles = (N + BR - 1) / BR;
     long total = (long)B * H * n_qtiles;
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
-    dim3 grid((unsigned)total), block(512);
     auto qp = static_cast<const float*>(q);
     auto kp = static_cast<const float*>(k);
     auto vp = static_cast<const float*>(v);
     auto op = static_cast<float*>(o);
+    const long heads = (long)B * H;
     if (f32_short(N)) {
-        const long heads = (long)B * H;
         const dim3 waves((unsigned)((heads + 3) / 4));
         if (causal)
             hipLaunchKernelGGL(fa_fwd_f32_short_kernel<true>, waves, dim3(256), 0, stream, qp, kp, vp, op, lse, N, (int)heads, H / H_kv, scale);
         else
             hipLaunchKernelGGL(fa_fwd_f32_short_kernel<false>, waves, dim3(256), 0, stream, qp, kp, vp, op, lse, N, (int)heads, H / H_kv, scale);
-    } else if (causal)
-        hipLaunchKernelGGL((fa_fwd_f32_kernel<64, 32, true>), grid, block, 0, stream, qp, kp, vp, op, lse, N, n_qtiles,
-                           (int)total, H / H_kv, scale);
-    else
-        hipLaunchKernelGGL((fa_fwd_f32_kernel<64, 32, false>), grid, block, 0, stream, qp, kp, vp, op, lse, N,
-                           n_qtiles, (int)total, H / H_kv, scale);
-    return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
+        return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
+    }
+    // HIP takes fewer than 2^32 threads along a grid's x: beyond that, as many heads at a time as fit
+    constexpr int kThreads = 512;
+    const long most = ((1L << 32) - 1) / kThreads / n_qtiles;
+    for (long head = 0; head < heads; head += most) {
+        const int items = (int)((heads - head < most ? heads - head : most) * n_qtiles);
+        if (causal)
+            hipLaunchKernelGGL((fa_fwd_f32_kernel<64, 32, true>), dim3((unsigned)items), dim3(kThreads), 0, stream, qp, kp, vp, op, lse, N,
+                               n_qtiles, items, (int)head, H / H_kv, scale);
+        else
+            hipLaunchKernelGGL((fa_fwd_f32_kernel<64, 32, false>), dim3((unsigned)items), dim3(kThreads), 0, stream, qp, kp, vp, op, lse, N,
+                               n_qtiles, items, (int)head, H / H_kv, scale);
+        if (hipGetLastError() != hipSuccess) return FA_ERR_LAUNCH;
+    }
+    return FA_OK;
 }
 
 }  // namespace fa

@@ -33,6 +33,24 @@ def test_fp32_short_sequences(H, H_kv, N, causal):
     assert max_abs(f64(o), o_ref) <= 1e-5 and max_abs(f64(lse), l_ref) <= 1e-5  # fp32 sums of at most 64 terms
 
 
+def test_fp32_more_heads_than_one_launch_takes():
+    # a launch of 512-thread workgroups takes 2^23 - 1 of them: here a few heads more, of 33 rows (q is zero but for the
+    # heads at the seam and at the end, so that L = log(33) and O = mean(V) elsewhere)
+    H, N, seam = 2 ** 23 + 5, 33, 2 ** 23 - 1
+    if torch.cuda.mem_get_info()[0] < 180 * 2 ** 30:
+        pytest.skip("needs 150 GB of device memory")
+    q = torch.zeros((1, H, N, 64), device="cuda")
+    o, lse = torch.empty_like(q), torch.empty((1, H, N), device="cuda")
+    q[:, seam - 2:] = inputs.normal_tensor(340, "q", (1, H - seam + 2, N, 64), "f32").cuda()
+    k, v = (inputs.normal_tensor(340, n, (1, 1, N, 64), "f32") for n in ("k", "v"))
+    binding.fa_fwd_gqa(q, k.cuda(), v.cuda(), 0.125, False, o=o, lse=lse)
+    for h in (slice(0, 2), slice(seam // 2, seam // 2 + 2), slice(seam - 2, H)):
+        o_ref, l_ref = oracle.attention_fwd_gqa(f64(q[:, h]), f64(k), f64(v), 0.125, False)
+        assert max_abs(f64(o[:, h]), o_ref) <= 2e-5 and max_abs(f64(lse[:, h]), l_ref) <= 2e-5
+    del q, o, lse
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("N,hidden", [(20, 20), (100, 100), (100, 40), (300, 300), (300, 64)])
 def test_fp32_rows_whose_every_score_is_minus_infinity(N, hidden, causal):
