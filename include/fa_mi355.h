@@ -22,7 +22,7 @@
  *   - The return value is an fa_status.  Every argument and size check precedes the first
  *     launch: on any status other than FA_OK and FA_ERR_LAUNCH nothing has been enqueued.
  *     FA_ERR_LAUNCH means the HIP runtime refused a launch; calls made of several launches
- *     (fa_bwd*: two, or three with dq == q or dq == dout; fa_fp8_quant_hadamard with
+ *     (fa_bwd*: one to three; fa_fp8_quant_hadamard with
  *     per_tensor = 1: four) stop at the refused one, and the outputs are then undefined.
  *     fa_status_string() names a status.
  *   - Supported head dimensions: d in {64, 128, 256}.  N >= 1 (any N; rows past N are
@@ -149,7 +149,7 @@ int fa_bwd(const void* q, const void* k, const void* v, const void* o, const flo
  *   - The array is per GPU and shared by every call on that GPU: two calls that may run
  *     concurrently on one GPU (different streams, different host threads) race on it and must be
  *     serialised by the caller; calls on one stream are ordered and safe.  Nothing in it needs
- *     clearing between calls (the first kernel of a call overwrites what the others read).
+ *     clearing between calls (a call reads nothing there that it has not written).
  *   - The array's device address is looked up once per GPU on the first call made with that GPU
  *     current; if that lookup fails the call returns FA_ERR_LAUNCH.
  */

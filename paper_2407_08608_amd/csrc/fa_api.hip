@@ -219,7 +219,7 @@ int fa_bwd_noalloc(const void* q, const void* k, const void* v, const void* o, c
     forget_stale_hip_error();
     void* scratch = noalloc_scratch_on_current_device();
     if (!scratch) return FA_ERR_LAUNCH;
-    // D is written in full by the first kernel before the others read it: nothing to clear
+    // a call reads no D that it has not written: nothing to clear
     return fa::launch_bwd(q, k, v, o, lse, dout, dq, dk, dv, scratch, B, H, H, N, d, scale, causal, dtype,
                           static_cast<hipStream_t>(stream));
 }

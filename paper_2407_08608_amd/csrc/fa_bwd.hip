@@ -2,7 +2,7 @@
 // Algorithm 3's recomputation of P from L and its D = rowsum(dO o O)).
 //
 //   dQ pass    : one workgroup per tile of queries (dQ_i on chip).  Its prologue computes D = rowsum(dO o O) of
-//                its rows and leaves it in the workspace; loop over key blocks:
+//                its rows and leaves it in the workspace (or finds it there); loop over key blocks:
 //                S^T = K_j Q_i^T, dP^T = V_j dO_i^T, P = exp(S - L), dS = P o (dP - D),
 //                dQ_i^T += K_j^T dS^T
 //   dK/dV pass : one workgroup per block of 128 keys (64 at d = 256), dK_j, dV_j kept on chip; loop over
@@ -255,9 +255,9 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
             load_ld(it + 1);
         }
 
-        // One wave per SIMD: nothing but this wave's own instruction stream can keep the matrix
-        // pipe busy while the exponentials run.  The iteration is therefore software-pipelined by
-        // hand over its two 32-query sub-tiles (the intra-warpgroup overlap of the paper's
+        // The SIMD's other wave belongs to another workgroup and is not in step with this one: to count on
+        // it alone would leave the matrix pipe idle whenever both run exponentials.  The iteration is
+        // therefore software-pipelined by hand over its two 32-query sub-tiles (the intra-warpgroup overlap of the paper's
         // Algorithm 2, applied to the backward pass):
         //   stage 1: S, dP of sub-tile 0                      (MFMA only)
         //   stage 2: S, dP of sub-tile 1  ||  P, dS of sub-tile 0
@@ -449,7 +449,7 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
 //             key tiles at d = 128, one at d = 256) for sub-tile g;
 //   dK, dV  : by columns -- a wave accumulates two key tiles x 64 columns, from the P and dS of both sub-tiles.
 // P and dS, packed, are already the A operands of the second half (lane = key), so what the waves exchange is raw
-// registers, 1 KiB per 32 x 16 piece through the LDS, with one barrier per iteration.  At d = 128 a row operand and a
+// registers, 1 KiB per 32 x 16 piece through the LDS, with one barrier more per iteration.  At d = 128 a row operand and a
 // transposed operand serve two MFMAs each (48 LDS operand reads per wave and iteration instead of 96); at d = 256
 // the four waves cover all 256 columns from one computation of S and dP (no second workgroup that repeats it: 64
 // MFMAs instead of 96 per 32 keys).
@@ -1361,10 +1361,9 @@ fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             // ---- P = exp(S - L), dS = P o (dP - D), packed as the B operand of the dQ product
             // keys past N, and keys after the query when causal, get S = -inf (P = 0): one uniform branch per
             // block, not a select per element in every block
-            constexpr bool MASK_BRANCH = true;
             const bool need_mask = (key0 + BC > N) || (CAUSAL && key0 + BC - 1 > wave_q0);
             const int limit = CAUSAL ? min(qi, N - 1) : N - 1;  // last visible key
-            if (MASK_BRANCH && need_mask) {
+            if (need_mask) {
                 // compile-time key offsets against one per-lane bound (kept opaque: the compiler otherwise
                 // hoists 32 per-element key indices out of the block loop into registers of their own)
                 int bound = limit - key0 - 4 * half;
@@ -1381,11 +1380,7 @@ fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 float ds[16];
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    float p = fast_exp2(__builtin_fmaf(sacc[kt][r], sc, -l2));
-                    if (!MASK_BRANCH && need_mask) {
-                        const int key = key0 + kt * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                        p = key > limit ? 0.f : p;
-                    }
+                    const float p = fast_exp2(__builtin_fmaf(sacc[kt][r], sc, -l2));
                     ds[r] = NEG_D_START ? p * pacc[kt][r] : p * (pacc[kt][r] - dq_row);
                 }
 #pragma unroll

@@ -912,7 +912,7 @@ fa_fwd_pingpong_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
 //   O^T += V^T P^T: score register r of a lane is key 8 (r / 4) + 4 half + r % 4, so the register itself is the B
 //     operand of the step that contracts this pair of keys; A is V read down a column (rows padded to 288 bytes: the
 //     two rows of a step lie in different halves of the banks).
-// B = 2, H = 8, N = 1000: 857 us with one thread per row and scalar FMAs, 42 us so (97 TFLOP/s).
+// B = 2, H = 8, N = 1000: 867 us with one thread per row and scalar FMAs, 42 us so (97 TFLOP/s).
 template <int D, int BC, bool CAUSAL>
 __global__ void __launch_bounds__(512, 2)
 fa_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,

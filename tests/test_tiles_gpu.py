@@ -149,19 +149,39 @@ def test_backward_on_both_sides_of_the_one_launch_rule(d, causal, N, most):
         _check_backward(850 + H, 1, H, H, N, d, causal, "bf16")
 
 
-@pytest.mark.parametrize("d", [64, 128])
-def test_backward_with_a_very_low_logsumexp(d):
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,H", [(64, 2), (64, 300), (128, 2), (128, 300), (256, 2)])
+def test_backward_with_a_very_low_logsumexp(d, H, causal):
     # scores near -140 (-200 in log2 units) everywhere: exp2 of a padding key's zero score against such an L overflows, and
-    # must not reach dQ through the zero rows past N (N = 70 leaves 26 of them)
-    q, k, v = (inputs.normal_tensor(950, n, (1, 2, 70, d), "f32") for n in ("q", "k", "v"))
+    # must not reach dQ through the zero rows past N (N = 70 leaves 26 of them).  Few and many workgroups.
+    N = 70
+    q, k, v = (inputs.normal_tensor(950, n, (1, H, N, d), "f32") for n in ("q", "k", "v"))
     q, k = q * 0.1 + 10.0, k * 0.1 - 14.0 / d ** 0.5
     q, k, v = (t.to(torch.bfloat16) for t in (q, k, v))
-    dout = inputs.normal_tensor(951, "do", (1, 2, 70, d), "bf16")
-    for causal in (False, True):
-        o, lse = binding.fa_fwd(q.cuda(), k.cuda(), v.cuda(), d ** -0.5, causal)
-        assert float(lse.max()) < -100.0
-        got = binding.fa_bwd(q.cuda(), k.cuda(), v.cuda(), o, lse, dout.cuda(), d ** -0.5, causal)
-        assert all(torch.isfinite(t).all() for t in got)
+    dout = inputs.normal_tensor(951, "do", (1, H, N, d), "bf16")
+    o, lse = binding.fa_fwd(q.cuda(), k.cuda(), v.cuda(), d ** -0.5, causal)
+    assert float(lse.max()) < -100.0
+    got = binding.fa_bwd(q.cuda(), k.cuda(), v.cuda(), o, lse, dout.cuda(), d ** -0.5, causal)
+    assert all(torch.isfinite(t).all() for t in got)
+    for h in (0, H - 1):
+        # K and Q are nearly constant over the rows, so dQ and dK are small differences of large sums and each element
+        # gets the bound of its own sum: P, dS and the outputs are rounded to 2^-9 (2^-8 leaves as much again for the
+        # fp32 scores of up to 2^12, whose roundings move P by less than 2^-10), and D carries the rounding of O
+        q64, k64, v64, do64 = (f64(t[0, h]) for t in (q, k, v, dout))
+        s = q64 @ k64.T * d ** -0.5
+        if causal:
+            s = np.where(np.tri(N, dtype=bool), s, -np.inf)
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        p /= p.sum(axis=1, keepdims=True)
+        out = p @ v64
+        ds = p * (do64 @ v64.T - (do64 * out).sum(axis=1, keepdims=True))
+        d_err = p * (np.abs(do64) * np.abs(out)).sum(axis=1, keepdims=True)
+        dp_err = p * (np.abs(do64) @ np.abs(v64).T)
+        ds_err = 2.0 ** -8 * (np.abs(ds) + d_err) + 2.0 ** -10 * dp_err
+        for g, ref, err in ((got[0], ds @ k64 * d ** -0.5, ds_err @ np.abs(k64) * d ** -0.5),
+                            (got[1], ds.T @ q64 * d ** -0.5, ds_err.T @ np.abs(q64) * d ** -0.5),
+                            (got[2], p.T @ do64, 2.0 ** -8 * p.T @ np.abs(do64))):
+            assert (np.abs(f64(g[0, h]) - ref) <= err + 2.0 ** -8 * np.abs(ref)).all()
 
 
 @pytest.mark.parametrize("causal", [False, True])
@@ -174,17 +194,9 @@ def test_backward_four_wave_query_tiles(d, N, causal):
 @pytest.mark.parametrize("d,causal,N", [(64, True, 3072), (64, True, 3073), (128, True, 1536), (128, True, 1537), (64, False, 1280),
                                         (128, False, 1281)])
 def test_backward_query_tile_rule_edges(d, causal, N):
-    # on both sides of the length up to which the 128-query tiles are used, with more tiles than the few-workgroup form
-    # takes (one head's gradients are held against the oracle; the heads share K and V)
-    H = 24
-    q, dout = (inputs.normal_tensor(990, n, (1, H, N, d), "bf16") for n in ("q", "do"))
-    k, v = (inputs.normal_tensor(990, n, (1, 1, N, d), "bf16") for n in ("k", "v"))
-    qg, kg, vg, dog = (t.cuda() for t in (q, k, v, dout))
-    o, lse = binding.fa_fwd_gqa(qg, kg, vg, d ** -0.5, causal)
-    dq = binding.fa_bwd_gqa(qg, kg, vg, o, lse, dog, d ** -0.5, causal)[0]
-    ref = oracle.attention_bwd_gqa(f64(q[:, 5:6]), f64(k), f64(v), f64(dout[:, 5:6]), d ** -0.5, causal)["dq"]
-    g = f64(dq[:, 5:6])
-    assert rmse(g, ref) <= REL_RMSE * float(np.sqrt(np.mean(ref * ref)))
+    # on both sides of the length up to which the 128-query tiles are used, with more heads than the few-workgroup forms
+    # take (one of them against the oracle)
+    _check_backward(990, 1, 32, 32, N, d, causal, "bf16", (5,))
 
 
 @pytest.mark.parametrize("heads,N,d", [(64, 1500, 128), (128, 1500, 128), (512, 100, 128), (384, 200, 128), (100, 300, 128),
