@@ -1160,8 +1160,8 @@ static int launch_16bit(const void* q, const void* k, const void* v, void* o, fl
                         float scale, int causal, hipStream_t stream) {
     constexpr int BR = NW * 32 * RQ;
     int n_qtiles = (N + BR - 1) / BR;
-    constexpr PairRule kPairs = NW == 4 ? (D == 64 ? PairRule{3, 15.f / 16, 384, 0.8f} : PairRule{2, 7.f / 8, 256, 0.75f})
-                                        : PairRule{D == 64 ? 2 : 1, 7.f / 8, 1 << 30, 1.f};
+    constexpr PairRule kPairs = NW == 4 ? (D == 64 ? PairRule{3, 15.f / 16, 384, 0.8f, 4} : PairRule{2, 7.f / 8, 256, 0.75f, kAny})
+                                        : (D == 64 ? PairRule{2, 1.f, kAny, 1.f, 0} : PairRule{1, 7.f / 8, kAny, 1.f, kAny});
     const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, kPairs);
     long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
@@ -1184,7 +1184,7 @@ static int launch_pingpong(const void* q, const void* k, const void* v, void* o,
                            float scale, int causal, hipStream_t stream) {
     constexpr int BR = 256, BC = 64, P = 4;
     int n_qtiles = (N + BR - 1) / BR;
-    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, PairRule{1, 27.f / 32, 1 << 30, 1.f});
+    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, PairRule{1, 27.f / 32, kAny, 1.f, kAny});
     long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
     const dim3 grid = forward_grid((long)B * H, n_qtiles, total, causal, paired), block(512);
@@ -1206,7 +1206,7 @@ static int launch_d256(const void* q, const void* k, const void* v, void* o, flo
                        float scale, int causal, hipStream_t stream) {
     constexpr int BR = 128;
     int n_qtiles = (N + BR - 1) / BR;
-    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, PairRule{1, 7.f / 8, 128, 0.7f});
+    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, PairRule{1, 7.f / 8, 128, 0.7f, kAny});
     long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
     const dim3 grid = forward_grid((long)B * H, n_qtiles, total, causal, paired), block(256);

@@ -577,8 +577,8 @@ static int launch_fp8(const void* q8, const void* k8, const void* v8, const floa
     constexpr int BR = NW * 32;
     int n_qtiles = (N + BR - 1) / BR;
     int n_sblocks = (N + 127) / 128;
-    constexpr PairRule kPairs = NW == 4 ? (D == 64 ? PairRule{3, 15.f / 16, 1 << 30, 1.f} : PairRule{2, 7.f / 8, 320, 0.75f})
-                                        : PairRule{D == 64 ? 2 : 1, 0.9f, 1 << 30, 1.f};
+    constexpr PairRule kPairs = NW == 4 ? (D == 64 ? PairRule{3, 15.f / 16, kAny, 1.f, 2} : PairRule{2, 7.f / 8, 320, 0.75f, kAny})
+                                        : (D == 64 ? PairRule{2, 1.f, kAny, 1.f, 0} : PairRule{1, 0.9f, kAny, 1.f, kAny});
     const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, kPairs);
     long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
@@ -607,8 +607,11 @@ static int launch_fp8_async(const void* q8, const void* k8, const void* v8, cons
     constexpr int BR = 256;
     int n_qtiles = (N + BR - 1) / BR;
     int n_sblocks = (N + 127) / 128;
-    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles,
-                                                   PairRule{D == 64 ? 2 : 1, D < 256 || n_qtiles > 4 ? 0.9f : n_qtiles > 2 ? 0.875f : 0.75f, 1 << 30, 1.f});
+    // d = 256: short tiles win as pairs a little earlier, above all in the first round (us, pairs / single: 192 x 300 30.0 /
+    // 31.0 at a share of 0.75, 448 x 300 59.3 / 63.9 and 112 x 1024 53.9 / 54.7 at 0.88, but 384 x 450 73.9 / 63.9 at 0.75)
+    const bool first_round = (long)B * H * ((n_qtiles + 1) / 2) <= 256;
+    const float share = D < 256 || n_qtiles > 4 ? 0.9f : n_qtiles > 2 ? (first_round ? 0.875f : 0.9f) : (first_round ? 0.75f : 0.875f);
+    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, D == 64 ? PairRule{2, 1.f, kAny, 1.f, 0} : PairRule{1, share, kAny, 1.f, kAny});
     long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
     const dim3 grid = forward_grid((long)B * H, n_qtiles, total, causal, paired), block(512);

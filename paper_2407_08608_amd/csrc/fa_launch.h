@@ -19,10 +19,11 @@ inline bool odd_row_tiles(int N) { return ((N + 127) / 128) & 1; }
 // they are the better choice when they fill whole rounds of the chip; what decides is the share of the rounds that is
 // work (a pair without a partner, the middle tile of an odd number, counts half).  A round is one workgroup on each of
 // the 256 CUs while all pairs are resident, `per_cu` (workgroups of the kernel that a CU holds) on each beyond.  Against
-// single tiles dealt longest first pairs win from `share` on.  With `many_heads` heads or more they win from `many_share`
-// on: single tiles read the K and V of all heads at once, which costs most where few rows share a read.  On less than one
-// workgroup per CU pairs win for long sequences only, a few of which they finish as soon on two thirds of the chip; single
-// tiles even out by themselves three to a CU and, two to a CU, while both fit.
+// single tiles dealt longest first pairs win from `share` on, with up to `most_tiles` tiles: where two or three workgroups
+// share a CU, single tiles even out by themselves.  With `many_heads` heads or more pairs win from `many_share` on: single
+// tiles read the K and V of all heads at once, which costs most where few rows share a read.  On at most one workgroup per
+// CU single tiles lose to pairs only over long sequences (most of all a few very long ones, which pairs finish as soon on
+// two thirds of the chip), unless a CU holds but one.
 // Causal, bf16 unless said, us, pairs / single tiles (share, heads x N):
 //   ping-pong     1.00 151 / 159 (128 x 2048), 0.88 67.8 / 71.6 (56 x 2048), 0.84 53.9 / 56.1 (72 x 1408), 0.75 197 / 209
 //                 (12 x 8192);  0.75 176 / 154 (64 x 3001), 0.25 99.5 / 90.1 (8 x 4096)
@@ -32,25 +33,28 @@ inline bool odd_row_tiles(int N) { return ((N + 127) / 128) & 1; }
 //                 (512 x 640);  0.88 243 / 223 (32 x 3500: lost), 0.88 648 / 593 (80 x 3500: lost)
 //   FP8 d = 128   1.00 96.6 / 101 (128 x 2048);  0.83 163 / 148 (128 x 2500), 0.75 126 / 106 (64 x 3001)
 //   FP8 d = 256   1.00 118 / 125 (256 x 1024);  0.75 588 / 486 (48 x 6000)
-//   d = 64, 8w    0.75 308 / 323 (6 x 16384), 1.00 167 / 180 (16 x 8192);  0.56 318 / 249 (48 x 6000)
-//   d = 64, 4w    1.00 21.1 / 22.8 (768 x 256);  1.00 49.0 / 46.5 (64 x 2048)
-// Over 4400 causal shapes the rule is 0.1 to 0.5 % off the better of the two on average, by kernel, and at one of them
+//   d = 64, 8w    0.75 308 / 323 (6 x 16384), 1.00 on half the slots 167 / 180 (16 x 8192);  1.00 158 / 155 (64 x 4096: never
+//                 beyond one per CU)
+//   d = 64, 4w    1.00 21.1 / 22.8 (768 x 256);  1.00 49.0 / 46.5 (64 x 2048: up to 4 tiles, FP8 2)
+// Over 4400 causal shapes the rule is up to 0.5 % off the better of the two on average, by kernel, and at one of them
 // (d = 256, 144 x 150, 1 us) more than 2 % slower than always pairing.
 struct PairRule {
     int per_cu;
     float share;
     int many_heads;
     float many_share;
+    int most_tiles;
 };
+constexpr int kAny = 0x7fffffff;
 inline bool pair_causal_tiles(long heads, int n_qtiles, const PairRule& rule) {
     constexpr long kCus = 256;
+    if (n_qtiles < 2) return true;  // nothing to deal out: items, in runs of heads per XCD (FP8 1024 x 100 17.1 / 17.8)
     const long pairs = heads * ((n_qtiles + 1) / 2);
     const long slots = pairs <= kCus * rule.per_cu ? kCus : kCus * rule.per_cu, rounds = (pairs + slots - 1) / slots;
     const float work = (float)(heads * n_qtiles) / (float)(2 * slots * rounds);
-    if (n_qtiles < 2) return false;
-    if (pairs <= kCus && n_qtiles >= 32) return work >= 2.f / 3;
-    if ((rule.per_cu == 3 && n_qtiles > 4) || (rule.per_cu > 1 && pairs <= kCus && n_qtiles < 16)) return false;
-    return work >= (heads >= rule.many_heads ? rule.many_share : rule.share);
+    if (pairs <= kCus && (n_qtiles >= 32 || rule.per_cu > 1))
+        return rule.per_cu < 3 && n_qtiles >= 16 && work >= (n_qtiles >= 32 ? 2.f / 3 : 7.f / 8);
+    return n_qtiles <= rule.most_tiles && work >= (heads >= rule.many_heads ? rule.many_share : rule.share);
 }
 
 // The grid of a forward launch of `total` work items (query_tiles): heads x tiles for single causal tiles (of 128 rows

@@ -203,7 +203,7 @@ def test_backward_query_tile_rule_edges(d, causal, N):
                                        (7, 1409, 128), (256, 129, 256), (300, 300, 256), (5, 700, 256), (9, 1300, 64),
                                        (11, 200, 64), (3, 2048, 64), (3, 2049, 64), (3, 1664, 128), (3, 1665, 128), (5, 1408, 128), (5, 1536, 128), (5, 1537, 128),
                                        (61, 1700, 128), (62, 1700, 128), (255, 300, 128), (256, 300, 128), (127, 300, 256),
-                                       (128, 300, 256), (359, 512, 64), (360, 512, 64), (10, 4100, 256), (11, 4100, 256)])
+                                       (128, 300, 256), (359, 512, 64), (360, 512, 64), (10, 4100, 64), (11, 4100, 64), (250, 300, 256), (10, 4100, 256), (11, 4100, 256)])
 @pytest.mark.parametrize("fp8", [False, True])
 def test_causal_forward_paired_and_single_tiles(heads, N, d, fp8):
     # head counts on both sides of the rule that pairs causal query tiles, with odd and even tile counts; every row of
