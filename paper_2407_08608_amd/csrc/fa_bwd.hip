@@ -797,61 +797,20 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
 }
 
 // ---------------------------------------------------------------------------------------
-// A wave's private tiles of 32 rows of two tensors (first, second), staged straight from global memory into two LDS
-// stages that no other wave touches.  The tiles are unpadded; 16-byte chunk c of row r sits at c ^ swizzle(r),
-// applied through the global address a lane fetches: row reads (16 rows at one chunk) and transposing reads (4 rows x
-// 4 chunks) both hit every bank once.
+// A wave's private tiles of 32 rows of two tensors (first, second) in two LDS stages (WaveTile).
 template <int D>
-struct WaveTiles {
+struct WaveTiles : WaveTile<D> {
     static_assert(D == 64 || D == 128, "two stages of a wave's tiles must fit a quarter of the LDS");
-    static constexpr int ROWS = 32, ROWB = D * 2, KS = D / 16, DT = D / 32;
-    static constexpr int CPR = D / 8;             // 16-byte chunks per row
-    static constexpr int TILE_B = ROWS * ROWB;    // one tensor's tile
+    using Tile = WaveTile<D>;
+    using Tile::TILE_B;
     static constexpr int STAGE_B = 2 * TILE_B;    // first, second
-    static constexpr int RPI = 1024 / ROWB;       // rows per staging instruction (1 KiB)
-    static constexpr int NI = ROWS / RPI;         // staging instructions per tile
-    static_assert(NI % 4 == 0 && 4 * RPI % 16 == 0, "swizzle(r) has period 16, the rows of four instructions");
     uint32_t stage0;
-    int src[4];             // byte offset within a tile for instructions 0..3 (the pattern repeats every 4)
-    int row_ofs[KS];        // row operands: lane (col, half) takes 8 elements from 16 ks + 8 half of row col
-    int tr_ofs[DT][2];      // transposed operands of rows 0..15; + 16 rows leaves the swizzle as it is
-
-    static __device__ __forceinline__ int swizzle(int r) {
-        return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
-    }
-    __device__ __forceinline__ WaveTiles(uint32_t base, int lane) : stage0(base) {
-        const int col = lane & 31, half = lane >> 5, tr_row = (lane & 15) >> 2, quad = lane & 3, blk = (lane >> 4) & 1;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = i * RPI + lane / CPR;
-            src[i] = r * ROWB + ((lane % CPR) ^ swizzle(r)) * 16;
-        }
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) row_ofs[ks] = col * ROWB + (((2 * ks + half) ^ swizzle(col)) << 4);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int hi = 0; hi < 2; ++hi) {
-                const int r = 4 * half + tr_row + 8 * hi;
-                tr_ofs[dt][hi] = r * ROWB + (((4 * dt + 2 * blk + (quad >> 1)) ^ swizzle(r)) << 4) + 8 * (quad & 1);
-            }
-    }
+    __device__ __forceinline__ WaveTiles(uint32_t base, int lane) : Tile(lane), stage0(base) {}
     // Instruction n of 2 NI that bring tile t of both heads into stage st (rows past a resource's end arrive as zeros).
-    // One per MFMA step: in a burst, the wave sits about 100 cycles in the issue of each, 64 bytes per clock being
-    // what a CU's vector memory path moves.
-    static constexpr int NREQ = 2 * NI;
-    static_assert(NREQ == 2 * KS, "one per MFMA step of the two score products");
+    static constexpr int NREQ = 2 * Tile::NI;
+    static_assert(NREQ == 2 * Tile::KS, "one per MFMA step of the two score products");
     __device__ __forceinline__ void request(const BufferWords& first, const BufferWords& second, int t, int st, int n) const {
-        const int i = n >> 1;
-        global_to_lds_16B(n & 1 ? second : first, stage0 + st * STAGE_B + (n & 1) * TILE_B + i * 1024,
-                          t * TILE_B + src[i & 3] + (i >> 2) * 4096);
-    }
-    // `base`: a stage's address, + TILE_B for the second tensor
-    __device__ __forceinline__ i32x4 row_read(uint32_t base, int ks) const { return lds_load_16B(base + row_ofs[ks]); }
-    __device__ __forceinline__ i32x4 tr_read(uint32_t base, int slab, int dt) const {
-        const uint32_t a = base + slab * 16 * ROWB;
-        const i32x2 lo = lds_read_tr16(a + tr_ofs[dt][0]), hi = lds_read_tr16(a + tr_ofs[dt][1]);
-        return i32x4{lo[0], lo[1], hi[0], hi[1]};
+        Tile::request(n & 1 ? second : first, stage0 + st * STAGE_B + (n & 1) * TILE_B, t, n >> 1);
     }
 };
 

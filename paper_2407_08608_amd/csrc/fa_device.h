@@ -196,6 +196,56 @@ static __device__ __forceinline__ void global_to_lds_16B(const BufferWords& rsrc
                  : "memory", "m0");
 }
 
+// A wave's private tile of 32 rows of a 16-bit tensor, staged straight from global memory into LDS that no other wave
+// touches: no barriers, only the wave's own vmcnt waits.  The tile is unpadded; 16-byte chunk c of row r sits at
+// c ^ swizzle(r), applied through the global address a lane fetches: row reads (16 rows at one chunk) and transposing
+// reads (4 rows x 4 chunks) both hit every bank once.
+template <int D>
+struct WaveTile {
+    static constexpr int ROWS = 32, ROWB = D * 2, KS = D / 16, DT = D / 32;
+    static constexpr int CPR = D / 8;             // 16-byte chunks per row
+    static constexpr int TILE_B = ROWS * ROWB;
+    static constexpr int RPI = 1024 / ROWB;       // rows per staging instruction (1 KiB)
+    static constexpr int NI = ROWS / RPI;         // staging instructions per tile
+    static constexpr int PERIOD = 16 / RPI;       // swizzle(r) has period 16: the rows of so many instructions
+    int src[PERIOD];        // byte offset within a tile for instructions 0 .. PERIOD - 1
+    int row_ofs[KS];        // row operands: lane (col, half) takes 8 elements from 16 ks + 8 half of row col
+    int tr_ofs[DT][2];      // transposed operands of rows 0..15; + 16 rows leaves the swizzle as it is
+
+    static __device__ __forceinline__ int swizzle(int r) {
+        return D == 64 ? (((r >> 1) & 1) << 2) | ((r >> 2) & 3) : ((r & 3) << 2) | ((r >> 2) & 3);
+    }
+    __device__ __forceinline__ explicit WaveTile(int lane) {
+        const int col = lane & 31, half = lane >> 5, tr_row = (lane & 15) >> 2, quad = lane & 3, blk = (lane >> 4) & 1;
+#pragma unroll
+        for (int i = 0; i < PERIOD; ++i) {
+            const int r = i * RPI + lane / CPR;
+            src[i] = r * ROWB + ((lane % CPR) ^ swizzle(r)) * 16;
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) row_ofs[ks] = col * ROWB + (((2 * ks + half) ^ swizzle(col)) << 4);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int hi = 0; hi < 2; ++hi) {
+                const int r = 4 * half + tr_row + 8 * hi;
+                tr_ofs[dt][hi] = r * ROWB + (((4 * dt + 2 * blk + (quad >> 1)) ^ swizzle(r)) << 4) + 8 * (quad & 1);
+            }
+    }
+    // Instruction i of NI that bring tile t of a head to `lds` (rows past the resource's end arrive as zeros).  To be issued
+    // one per MFMA step: in a burst, the wave sits about 100 cycles in the issue of each, 64 bytes per clock being what a
+    // CU's vector memory path moves.
+    __device__ __forceinline__ void request(const BufferWords& rsrc, uint32_t lds, int t, int i) const {
+        global_to_lds_16B(rsrc, lds + i * 1024, t * TILE_B + src[i % PERIOD] + (i / PERIOD) * (PERIOD * 1024));
+    }
+    __device__ __forceinline__ i32x4 row_read(uint32_t base, int ks) const { return lds_load_16B(base + row_ofs[ks]); }
+    __device__ __forceinline__ i32x4 tr_read(uint32_t base, int slab, int dt) const {
+        const uint32_t a = base + slab * 16 * ROWB;
+        const i32x2 lo = lds_read_tr16(a + tr_ofs[dt][0]), hi = lds_read_tr16(a + tr_ofs[dt][1]);
+        return i32x4{lo[0], lo[1], hi[0], hi[1]};
+    }
+};
+
 static __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Stores a wave's 32-row x (32 DT)-column fp32 accumulator tile (MFMA result layout with rows as

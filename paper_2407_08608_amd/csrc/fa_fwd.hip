@@ -54,6 +54,198 @@ struct TileCopy {
     }
 };
 
+// ---------------------------------------------------------------------------------------
+// The forward where its query tiles would leave most of the chip idle (few heads, short sequences): FewForward.
+//
+// A workgroup owns 32 queries instead of 128 or 256 and its NW waves split the keys, tiles of 32 dealt in turn, each with
+// a softmax state and an output accumulator for all columns; the states meet in the LDS at the end, in a fixed order:
+// with M the largest of their references and f = exp(m - M), O = sum f O / sum f l and L = M + log sum f l.  Four to
+// eight times as many workgroups, each with a quarter to an eighth of the serial chain.  A wave stages its own tiles
+// (WaveTile), so the loop has no barrier; what that costs is traffic (K and V come to a CU once per 32 queries), which a
+// chip that is mostly idle has to spare.  V of a tile is requested beside its score MFMAs, K of the wave's next tile beside
+// its products, each into the one stage that its last reader has left: a second stage per tensor gains nothing with one
+// workgroup on a CU and costs the second workgroup (d = 128 causal, 32 heads x 512: 12.8 us with two stages, 10.0 with one).
+template <int D, int NW>
+struct FewForward {
+    using Tile = WaveTile<D>;
+    static constexpr int KS = D / 16, DT = D / 32, CPR = D / 8, KP = 4;
+    static constexpr int PSTR = D + 4;  // row stride of the partial outputs (floats)
+    static constexpr int kPartial = NW * 32 * PSTR * 4;
+    static constexpr int kStages = NW * 2 * Tile::TILE_B;
+    static constexpr int kLds = (kPartial + NW * 32 * 8 > kStages ? kPartial + NW * 32 * 8 : kStages);
+
+    template <typename Tag, bool CAUSAL>
+    static __device__ __forceinline__ void run(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                                               const uint16_t* __restrict__ v, uint16_t* __restrict__ o,
+                                               float* __restrict__ lse, int N, int split, int kv_group, float scale, char* lds) {
+        using E = Elem<Tag>;
+        const int tid = threadIdx.x;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+        const int col = lane & 31, half = lane >> 5;
+        // The tiles of a head share an L2 whatever the number of heads (61 heads x 252, d = 128, no mask: 13.5 us where they do
+        // not, 8.4 so).  split >= 0: grid (heads x R) x ceil(tiles / R), R = 2^split; x / 8 of the ids that land on XCD x % 8 counts
+        // through the groups (head, residue of the tile number mod R) of that XCD, y through the members of a group; causal:
+        // the longest rows first.  split < 0: one id per tile, head by head.
+        const int n_t = (N + 31) / 32;
+        int bh, tile_no;
+        if (split < 0) {
+            const int xcd = blockIdx.x & 7, per = gridDim.x >> 3, rest = gridDim.x & 7;  // the first `rest` XCDs get one more
+            const int id = xcd * per + min(xcd, rest) + ((int)blockIdx.x >> 3);
+            bh = id / n_t;
+            tile_no = id - bh * n_t;
+        } else {
+            const int group = ((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3);
+            bh = group >> split;
+            tile_no = ((int)blockIdx.y << split) + (group & ((1 << split) - 1));
+            if (tile_no >= n_t) return;
+        }
+        const int qt = CAUSAL ? n_t - 1 - tile_no : tile_no;
+        const int q0 = qt * 32, n_tiles = CAUSAL ? qt + 1 : n_t;
+        const int row = min(q0 + col, N - 1);    // rows past N compute a copy of row N-1, never stored
+        const int limit = CAUSAL ? row : N - 1;  // last visible key
+        const size_t head_off = (size_t)bh * N * D, kv_off = (size_t)(bh / kv_group) * N * D;
+        BufferWords k_rsrc = make_buffer_words(k + kv_off, (uint32_t)N * D * 2);
+        BufferWords v_rsrc = make_buffer_words(v + kv_off, (uint32_t)N * D * 2);
+        const Tile tile(lane);
+        const uint32_t kb = lds_address(lds) + wave * (2 * Tile::TILE_B), vb = kb + Tile::TILE_B;
+
+        // (a wave without a tile brings rows that nothing reads, or zeros)
+#pragma unroll
+        for (int i = 0; i < Tile::NI; ++i) tile.request(k_rsrc, kb, wave, i);
+        i32x4 qreg[KS];  // Q^T as the B operand
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            qreg[ks] = *reinterpret_cast<const i32x4*>(q + head_off + (size_t)row * D + ks * 16 + half * 8);
+        f32x16 acc[DT];
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[dt][r] = 0.f;
+        float m_run = -INFINITY, l_run = 0.f;  // reference (raw scores) and this half's row sum of P~
+        const float sc = scale * kLog2e;
+        float sc_v = sc;  // a vector-register copy: an FMA with a scalar-register operand issues at a lower rate
+        asm volatile("" : "+v"(sc_v));
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qreg[ks]));
+
+        for (int t = wave; t < n_tiles; t += NW) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // K has landed
+            if (t + NW >= n_tiles) k_rsrc.w[2] = 0;  // past the wave's last tile: zeros that nothing reads
+            i32x4 ring[KP], tr[KP];
+#pragma unroll
+            for (int u = 0; u < KP; ++u) ring[u] = tile.row_read(kb, u);
+            __builtin_amdgcn_sched_barrier(0);
+            // S^T = K Q^T
+            f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < KS; ++u) {
+                const i32x4 a = ring[u % KP];
+                if (u + KP < KS) ring[u % KP] = tile.row_read(kb, u + KP);
+                tile.request(v_rsrc, vb, t, u);
+                s = E::mma(a, qreg[u], s);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (t * 32 + 32 > N || (CAUSAL && t == qt)) {
+                int bound = limit - t * 32 - 4 * half;  // key 8 (r / 4) + r % 4 of the lane's half is visible up to here
+                asm volatile("" : "+v"(bound));
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (8 * (r >> 2) + (r & 3) > bound) s[r] = -INFINITY;
+            }
+            // the reference is the first tile's row maximum and rises when a tile's exceeds it by more than 2^kLazyLog2
+            float mx[4] = {s[0], s[1], s[2], s[3]};
+#pragma unroll
+            for (int r = 4; r < 16; ++r) mx[r & 3] = fmaxf(mx[r & 3], s[r]);
+            const float m_new = max_both_halves(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])));
+            const bool raise = (m_new - m_run) * sc > kLazyLog2;
+            if (__builtin_amdgcn_ballot_w64(raise) != 0) {
+                const float corr = raise ? fast_exp2((m_run - m_new) * sc) : 1.0f;
+                m_run = raise ? m_new : m_run;
+                l_run *= corr;
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[dt][r] *= corr;
+            }
+            const float mb = m_run == -INFINITY ? 0.f : m_run * sc;  // a row of scores of -inf so far: P = 0
+            float ps[4] = {0.f, 0.f, 0.f, 0.f};
+            i32x4 pb[2];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                s[r] = fast_exp2(__builtin_fmaf(s[r], sc_v, -mb));
+                ps[r & 3] += s[r];
+                if (r & 1) pb[r >> 3][(r >> 1) & 3] = E::pack2(s[r - 1], s[r]);
+            }
+            l_run += (ps[0] + ps[1]) + (ps[2] + ps[3]);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // V has landed
+#pragma unroll
+            for (int u = 0; u < KP; ++u) tr[u] = tile.tr_read(vb, u / DT, u % DT);
+            __builtin_amdgcn_sched_barrier(0);
+            // O^T += V^T P^T
+#pragma unroll
+            for (int u = 0; u < 2 * DT; ++u) {
+                const i32x4 a = tr[u % KP];
+                if (u + KP < 2 * DT) tr[u % KP] = tile.tr_read(vb, (u + KP) / DT, (u + KP) % DT);
+                tile.request(k_rsrc, kb, t + NW, u);
+                acc[u % DT] = E::mma(a, pb[u / DT], acc[u % DT]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last requests: the LDS is about to be reused
+
+        // ---- merge
+        __syncthreads();
+        float* part = reinterpret_cast<float*>(lds);                      // [wave][query][PSTR]
+        float* state = reinterpret_cast<float*>(lds + kPartial);          // [wave][query][m, l]
+        const float l = sum_both_halves(l_run);
+        if (half == 0) {
+            state[(wave * 32 + col) * 2] = m_run;
+            state[(wave * 32 + col) * 2 + 1] = l;
+        }
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const f32x4 w = {acc[dt][4 * g], acc[dt][4 * g + 1], acc[dt][4 * g + 2], acc[dt][4 * g + 3]};
+                *reinterpret_cast<f32x4*>(part + (wave * 32 + col) * PSTR + dt * 32 + 8 * g + 4 * half) = w;
+            }
+        __syncthreads();
+        for (int c = tid; c < 32 * CPR; c += NW * 64) {
+            const int r = c / CPR, cc = (c % CPR) * 8;
+            float m_all = -INFINITY, l_all = 0.f, f[NW];
+#pragma unroll
+            for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, state[(w * 32 + r) * 2]);
+            const float m_ref = m_all == -INFINITY ? 0.f : m_all;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                f[w] = fast_exp2((state[(w * 32 + r) * 2] - m_ref) * sc);
+                l_all += f[w] * state[(w * 32 + r) * 2 + 1];
+            }
+            float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const f32x4 y = *reinterpret_cast<const f32x4*>(part + (w * 32 + r) * PSTR + cc + 4 * h);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[4 * h + e] = __builtin_fmaf(f[w], y[e], x[4 * h + e]);
+                }
+            const float inv = 1.0f / l_all;
+            if (q0 + r < N) {
+                i32x4 y;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] = E::pack2(x[2 * e] * inv, x[2 * e + 1] * inv);
+                *reinterpret_cast<i32x4*>(o + head_off + (size_t)(q0 + r) * D + cc) = y;
+                if (cc == 0) lse[(size_t)bh * N + q0 + r] = (m_all * sc + log2f(l_all)) * kLn2;
+            }
+        }
+    }
+};
+
+// (not in the eight-wave tile at d = 128, which only a forced schedule takes)
+template <int D, int NW>
+constexpr bool kHasFew = D == 64 || NW == 4;
+
 template <typename Tag, int D, int BC, int NW, int RQ, int PD, bool CAUSAL>
 // (the second launch bound is waves per SIMD: two eight-wave workgroups of the d = 64 kernel share a CU)
 __global__ void __launch_bounds__(NW * 64, (D == 64 && NW == 8) ? 4 : (RQ == 1 && D <= 128) ? 2 : 1)
@@ -72,8 +264,16 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     using E = Elem<Tag>;
     using Copy = TileCopy<D, BC, NT>;
 
-    __shared__ __attribute__((aligned(16))) uint16_t lds_k[2][BC * KSTR];
-    __shared__ __attribute__((aligned(16))) uint16_t lds_v[2][BC * VSTR];
+    constexpr int kTileLds = 2 * BC * (KSTR + VSTR) * 2, kFewLds = kHasFew<D, NW> ? FewForward<D, NW>::kLds : 0;
+    __shared__ __attribute__((aligned(1024))) char lds[kTileLds > kFewLds ? kTileLds : kFewLds];
+    if constexpr (kHasFew<D, NW>) {
+        if (paired == kFewForward) {
+            FewForward<D, NW>::template run<Tag, CAUSAL>(q, k, v, o, lse, N, total_wg, kv_group, scale, lds);
+            return;
+        }
+    }
+    uint16_t(*lds_k)[BC * KSTR] = reinterpret_cast<uint16_t(*)[BC * KSTR]>(lds);
+    uint16_t(*lds_v)[BC * VSTR] = reinterpret_cast<uint16_t(*)[BC * VSTR]>(lds + 2 * BC * KSTR * 2);
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
@@ -264,11 +464,13 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     {
         char* patch = (wave < 4 ? reinterpret_cast<char*>(&lds_k[0][0]) : reinterpret_cast<char*>(&lds_v[0][0])) +
                       (wave & 3) * 4096;
-        static_assert(sizeof(lds_k) >= 4 * 4096 && sizeof(lds_v) >= 4 * 4096, "patches must fit");
+        static_assert(2 * BC * KSTR * 2 >= 4 * 4096 && 2 * BC * VSTR * 2 >= 4 * 4096, "patches must fit");
         const int qi = wave_q0 + col;
         const float l = sum_both_halves(l_run);
+        int out_lane = lane;  // opaque: the addresses derived from it are else computed before the loop, and spilled over it
+        asm volatile("" : "+v"(out_lane));
         store_rows_via_lds<Tag, DT>(oacc, 1.0f / l, patch, make_buffer(o + head_off, (uint32_t)N * D * 2), wave_q0,
-                                    lane);
+                                    out_lane);
         if (qi < N && half == 0) lse[(size_t)bh * N + qi] = (m_run + log2f(l)) * kLn2;
     }
     if (pass + 1 < run.n_pass()) __syncthreads();  // the next pass's first tile overwrites the patches
@@ -307,8 +509,15 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
     using E = Elem<Tag>;
     using Copy = TileCopy<D, BC, NT>;
 
-    __shared__ __attribute__((aligned(16))) uint16_t lds_k[2][BC * KSTR];
-    __shared__ __attribute__((aligned(16))) uint16_t lds_v[2][BC * VSTR];
+    constexpr int kLds = 2 * BC * (KSTR + VSTR) * 2;
+    __shared__ __attribute__((aligned(1024))) char lds[kLds];
+    static_assert(FewForward<D, 4>::kLds <= kLds, "both divisions of the work use it");
+    if (paired == kFewForward) {
+        FewForward<D, 4>::template run<Tag, CAUSAL>(q, k, v, o, lse, N, total_wg, kv_group, scale, lds);
+        return;
+    }
+    uint16_t(*lds_k)[BC * KSTR] = reinterpret_cast<uint16_t(*)[BC * KSTR]>(lds);
+    uint16_t(*lds_v)[BC * VSTR] = reinterpret_cast<uint16_t(*)[BC * VSTR]>(lds + 2 * BC * KSTR * 2);
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
@@ -535,10 +744,12 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
     // the loop has passed, so the K buffers are free)
     {
         char* patch = reinterpret_cast<char*>(&lds_k[0][0]) + wave * 4096;
-        static_assert(sizeof(lds_k) >= 4 * 4096, "patches must fit");
+        static_assert(2 * BC * KSTR * 2 >= 4 * 4096, "patches must fit");
         const int qi = wave_q0 + col;
         const float l = sum_both_halves(l_run);
-        store_rows_via_lds<Tag, DT>(oacc, 1.0f / l, patch, make_buffer(o + head_off, (uint32_t)N * D * 2), wave_q0, lane);
+        int out_lane = lane;  // opaque: the addresses derived from it are else computed before the loop, and spilled over it
+        asm volatile("" : "+v"(out_lane));
+        store_rows_via_lds<Tag, DT>(oacc, 1.0f / l, patch, make_buffer(o + head_off, (uint32_t)N * D * 2), wave_q0, out_lane);
         if (qi < N && half == 0) lse[(size_t)bh * N + qi] = (m_run * sc + log2f(l)) * kLn2;
     }
     if (pass + 1 < run.n_pass()) __syncthreads();  // the next pass's first tile overwrites the patches
@@ -594,9 +805,13 @@ fa_fwd_pingpong_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
     static_assert(BC == 64, "the staging pattern below covers 64-row tiles with two loads per wave");
     using E = Elem<Tag>;
 
-    __shared__ __attribute__((aligned(1024))) char lds_k[NS * TILE];
-    __shared__ __attribute__((aligned(1024))) char lds_v[NS * TILE];
-    __shared__ __attribute__((aligned(1024))) char lds_o[8 * 4096];  // output transposition, 4 KiB per wave
+    __shared__ __attribute__((aligned(1024))) char lds[2 * NS * TILE + 8 * 4096];
+    static_assert(FewForward<D, 8>::kLds <= sizeof(lds), "both divisions of the work use it");
+    if (paired == kFewForward) {
+        FewForward<D, 8>::template run<Tag, CAUSAL>(q, k, v, o, lse, N, total_wg, kv_group, scale, lds);
+        return;
+    }
+    char *lds_k = lds, *lds_v = lds + NS * TILE, *lds_o = lds + 2 * NS * TILE;  // lds_o: output transposition, 4 KiB per wave
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -1157,15 +1372,15 @@ fa_fwd_f32_short_kernel(const float* __restrict__ q, const float* __restrict__ k
 // ---------------------------------------------------------------------------------------
 template <typename Tag, int D, int BC, int NW, int RQ, int PD>
 static int launch_16bit(const void* q, const void* k, const void* v, void* o, float* lse, int B, int H, int H_kv, int N,
-                        float scale, int causal, hipStream_t stream) {
+                        float scale, int causal, bool few, hipStream_t stream) {
     constexpr int BR = NW * 32 * RQ;
     int n_qtiles = (N + BR - 1) / BR;
     constexpr PairRule kPairs = NW == 4 ? (D == 64 ? PairRule{3, 15.f / 16, 384, 0.8f, 4} : PairRule{2, 7.f / 8, 256, 0.75f, kAny})
                                         : (D == 64 ? PairRule{2, 1.f, kAny, 1.f, 0} : PairRule{1, 7.f / 8, kAny, 1.f, kAny});
-    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, kPairs);
-    long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
+    const int paired = few ? kFewForward : causal && pair_causal_tiles((long)B * H, n_qtiles, kPairs);
+    long total = few ? few_split((long)B * H, N) : (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
-    const dim3 grid = forward_grid((long)B * H, n_qtiles, total, causal, paired), block(NW * 64);
+    const dim3 grid = forward_grid((long)B * H, N, n_qtiles, total, causal, paired), block(NW * 64);
     auto qp = static_cast<const uint16_t*>(q);
     auto kp = static_cast<const uint16_t*>(k);
     auto vp = static_cast<const uint16_t*>(v);
@@ -1181,13 +1396,13 @@ static int launch_16bit(const void* q, const void* k, const void* v, void* o, fl
 
 template <typename Tag>
 static int launch_pingpong(const void* q, const void* k, const void* v, void* o, float* lse, int B, int H, int H_kv, int N,
-                           float scale, int causal, hipStream_t stream) {
+                           float scale, int causal, bool few, hipStream_t stream) {
     constexpr int BR = 256, BC = 64, P = 4;
     int n_qtiles = (N + BR - 1) / BR;
-    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, PairRule{1, 27.f / 32, kAny, 1.f, kAny});
-    long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
+    const int paired = few ? kFewForward : causal && pair_causal_tiles((long)B * H, n_qtiles, PairRule{1, 27.f / 32, kAny, 1.f, kAny});
+    long total = few ? few_split((long)B * H, N) : (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
-    const dim3 grid = forward_grid((long)B * H, n_qtiles, total, causal, paired), block(512);
+    const dim3 grid = forward_grid((long)B * H, N, n_qtiles, total, causal, paired), block(512);
     auto qp = static_cast<const uint16_t*>(q);
     auto kp = static_cast<const uint16_t*>(k);
     auto vp = static_cast<const uint16_t*>(v);
@@ -1203,13 +1418,13 @@ static int launch_pingpong(const void* q, const void* k, const void* v, void* o,
 
 template <typename Tag>
 static int launch_d256(const void* q, const void* k, const void* v, void* o, float* lse, int B, int H, int H_kv, int N,
-                       float scale, int causal, hipStream_t stream) {
+                       float scale, int causal, bool few, hipStream_t stream) {
     constexpr int BR = 128;
     int n_qtiles = (N + BR - 1) / BR;
-    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, PairRule{1, 7.f / 8, 128, 0.7f, kAny});
-    long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
+    const int paired = few ? kFewForward : causal && pair_causal_tiles((long)B * H, n_qtiles, PairRule{1, 7.f / 8, 128, 0.7f, kAny});
+    long total = few ? few_split((long)B * H, N) : (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
-    const dim3 grid = forward_grid((long)B * H, n_qtiles, total, causal, paired), block(256);
+    const dim3 grid = forward_grid((long)B * H, N, n_qtiles, total, causal, paired), block(256);
     auto qp = static_cast<const uint16_t*>(q);
     auto kp = static_cast<const uint16_t*>(k);
     auto vp = static_cast<const uint16_t*>(v);
@@ -1254,20 +1469,21 @@ static int dispatch_16bit(const void* q, const void* k, const void* v, void* o, 
         if (d != 128) return FA_ERR_UNSUPPORTED;
         switch (schedule) {
             case FA_SCHED_LOCKSTEP_4W:
-                return launch_16bit<Tag, 128, 64, 4, 1, 0>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, stream);
+                return launch_16bit<Tag, 128, 64, 4, 1, 0>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, false, stream);
             case FA_SCHED_LOCKSTEP_8W:
-                return launch_16bit<Tag, 128, 128, 8, 1, 0>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, stream);
-            case FA_SCHED_PINGPONG: return launch_pingpong<Tag>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, stream);
+                return launch_16bit<Tag, 128, 128, 8, 1, 0>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, false, stream);
+            case FA_SCHED_PINGPONG: return launch_pingpong<Tag>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, false, stream);
             default: return FA_ERR_SHAPE;
         }
     }
+    const bool few = few_forward((long)B * H, N, d, causal);
     switch (choose_16bit(d, N, causal)) {
         case Fwd16::kTile4:
-            if (d == 64) return launch_16bit<Tag, 64, 64, 4, 1, 0>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, stream);
-            return launch_16bit<Tag, 128, 64, 4, 1, 0>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, stream);
-        case Fwd16::kTile8: return launch_16bit<Tag, 64, 64, 8, 1, 0>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, stream);
-        case Fwd16::kPingPong: return launch_pingpong<Tag>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, stream);
-        case Fwd16::kD256: return launch_d256<Tag>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, stream);
+            if (d == 64) return launch_16bit<Tag, 64, 64, 4, 1, 0>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, few, stream);
+            return launch_16bit<Tag, 128, 64, 4, 1, 0>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, few, stream);
+        case Fwd16::kTile8: return launch_16bit<Tag, 64, 64, 8, 1, 0>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, few, stream);
+        case Fwd16::kPingPong: return launch_pingpong<Tag>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, few, stream);
+        case Fwd16::kD256: return launch_d256<Tag>(q, k, v, o, lse, B, H, H_kv, N, scale, causal, few, stream);
         default: return FA_ERR_UNSUPPORTED;
     }
 }

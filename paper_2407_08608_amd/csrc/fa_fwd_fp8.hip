@@ -582,7 +582,7 @@ static int launch_fp8(const void* q8, const void* k8, const void* v8, const floa
     const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, kPairs);
     long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
-    const dim3 grid = forward_grid((long)B * H, n_qtiles, total, causal, paired), block(NW * 64);
+    const dim3 grid = forward_grid((long)B * H, N, n_qtiles, total, causal, paired), block(NW * 64);
     auto qp = static_cast<const uint8_t*>(q8);
     auto kp = static_cast<const uint8_t*>(k8);
     auto vp = static_cast<const uint8_t*>(v8);
@@ -614,7 +614,7 @@ static int launch_fp8_async(const void* q8, const void* k8, const void* v8, cons
     const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, D == 64 ? PairRule{2, 1.f, kAny, 1.f, 0} : PairRule{1, share, kAny, 1.f, kAny});
     long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
-    const dim3 grid = forward_grid((long)B * H, n_qtiles, total, causal, paired), block(512);
+    const dim3 grid = forward_grid((long)B * H, N, n_qtiles, total, causal, paired), block(512);
     auto qp = static_cast<const uint8_t*>(q8);
     auto kp = static_cast<const uint8_t*>(k8);
     auto vp = static_cast<const uint8_t*>(v8);

@@ -57,9 +57,51 @@ inline bool pair_causal_tiles(long heads, int n_qtiles, const PairRule& rule) {
     return n_qtiles <= rule.most_tiles && work >= (heads >= rule.many_heads ? rule.many_share : rule.share);
 }
 
+// The launchers' `paired` argument for launches divided by FewForward (fa_fwd.hip); the total number of work items that the
+// kernels take otherwise is few_split() then: log2 of the groups into which a head's tiles go so that the XCDs get the same
+// number of groups each, or -1: no groups, where they would come out too uneven (few tiles; all are on the chip at once).
+constexpr int kFewForward = 2;
+inline int few_split(long heads, int N) {
+    if (heads % 8 == 0) return 0;
+    return N <= 32 * 32 ? -1 : heads % 4 == 0 ? 1 : heads % 2 == 0 ? 2 : 3;
+}
+
+// Whether a 16-bit forward is divided so: workgroups of 32 queries whose waves split the keys, against 128 or 256 queries that
+// walk all of them.  What counts is how often those workgroups fill the CUs (`fillings`) and how long the chain of 32-key
+// tiles is that they shorten; under a causal mask, where the large workgroups wait for their longest, they win further.
+// The kernel stays the same (fa_fwd_kernel_name): this is only its work.  bf16, us, large / these, heads x N:
+//   d = 64   no mask: 16 x 100 5.0 / 4.2, 16 x 333 8.5 / 5.3, 64 x 333 8.8 / 8.3, 4 x 1000 21.5 / 7.4, 4 x 4096 74 / 30, 1 x 16384 279 / 107;
+//            lost: 128 x 128 5.2 / 5.3, 80 x 333 9.6 / 11.1, 28 x 1500 30 / 34, 12 x 4096 77 / 85;  N <= 64: equal to 2 %
+//            causal:  16 x 333 8.7 / 5.1, 16 x 2048 32 / 20, 4 x 4096 77 / 20;  lost: 56 x 1000 19.5 / 21, 40 x 2048 37 / 43
+//   d = 128  no mask: 16 x 100 6.5 / 5.5, 16 x 512 14.3 / 8.2, 32 x 512 15.0 / 12.2, 2 x 8192 167 / 95;
+//            lost: 96 x 100 6.9 / 7.4, 48 x 333 12.5 / 13.1, 24 x 700 21 / 24, 16 x 2048 50 / 59
+//            causal:  16 x 1000 25 / 13.6, 16 x 2048 50 / 40, 4 x 4096 90 / 31;  lost: 48 x 512 15.8 / 16.0, 28 x 1500 36 / 43
+//   d = 256  no mask: 16 x 333 17.5 / 12.3, 4 x 2048 57 / 35;  lost: 28 x 333 17.9 / 21.5, 8 x 2048 62 / 68
+//            causal:  16 x 1000 34 / 28, 2 x 8192 204 / 129;  lost: 32 x 333 18.5 / 19.3, 10 x 2048 61 / 61
+// Drawn on 2900 shapes (heads 1 to 384, N from 24 to 16384): up to 4.6 times as fast.  Over 1500 others in the last third
+// before the rule's edge, odd head counts and shared heads among them, 0.76 of the time on average, 1.02 at worst.
+inline bool few_forward(long heads, int N, int d, int causal) {
+    const long tiles = (N + 31) / 32, round_up = (1L << (few_split(heads, N) > 0 ? few_split(heads, N) : 0)) - 1;
+    float fillings = (float)(heads * ((tiles + round_up) & ~round_up)) / 256.f;
+    if (tiles < 3) return false;
+    if (fillings <= 1.f) return true;
+    if (few_split(heads, N) < 0) fillings *= 1.15f;  // an XCD's share of the tiles cuts through heads
+    auto at = [&](float base, float step, float most) { const float x = base + (float)tiles / step; return fillings <= (x < most ? x : most); };
+    switch (d) {
+        case 64: return causal ? (tiles > 6 ? at(1.5f, 9, tiles < 90 ? 7.25f : 9.5f) : fillings <= 1.75f)
+                               : (tiles > 6 ? at(1.75f, 16, 4.9f) : fillings <= 1.25f);
+        case 128: return tiles > 6 && (causal ? at(1.5f, 18, 4.75f) : fillings <= (tiles < 40 ? 2.f : 3.f));
+        default: return causal && at(0.8f, 48, 2);
+    }
+}
+
 // The grid of a forward launch of `total` work items (query_tiles): heads x tiles for single causal tiles (of 128 rows
-// or more, so at most 65504 of them at the largest N of any head dimension, which a grid's y takes).
-inline dim3 forward_grid(long heads, int n_qtiles, long total, int causal, int paired) {
+// or more, so at most 65504 of them at the largest N of any head dimension, which a grid's y takes) and for FewForward.
+inline dim3 forward_grid(long heads, int N, int n_qtiles, long total, int causal, int paired) {
+    if (paired == kFewForward) {
+        const int split = few_split(heads, N), tiles = (N + 31) / 32;
+        return split < 0 ? dim3((unsigned)(heads * tiles)) : dim3((unsigned)heads << split, (unsigned)((tiles + (1 << split) - 1) >> split));
+    }
     return causal && !paired ? dim3((unsigned)heads, (unsigned)n_qtiles) : dim3((unsigned)total);
 }
 

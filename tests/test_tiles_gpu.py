@@ -320,3 +320,60 @@ def test_backward_writes_shared_head_gradients_inside_the_output(H, H_kv, N):
 def test_backward_row_sums_inside_the_one_launch(d, N, H, H_kv, causal):
     # on both sides of the numbers of tiles and of workgroups up to which the one launch computes D for itself, ragged and not
     _check_backward(1400 + N, 1, H, H_kv, N, d, causal, "bf16")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("H,H_kv,N", [(1, 1, 65), (3, 1, 96), (8, 2, 97), (2, 2, 129), (5, 5, 255), (6, 3, 333), (16, 4, 641), (3, 3, 1025),
+                                      (4, 1, 1409), (2, 2, 2100), (12, 12, 1056)])
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_forward_with_the_keys_split_over_the_waves(d, H, H_kv, N, causal, dtype):
+    # 32-query workgroups of four and eight waves: as many tiles as waves, fewer, ragged last tiles of keys and of queries,
+    # and every way the tiles of a head are dealt to the XCDs (heads a multiple of 8, 4, 2 or odd, short and long)
+    q = inputs.normal_tensor(1600 + N, "q", (1, H, N, d), dtype)
+    k, v = (inputs.normal_tensor(1600 + N, n, (1, H_kv, N, d), dtype) for n in ("k", "v"))
+    o, lse = binding.fa_fwd_gqa(q.cuda(), k.cuda(), v.cuda(), d ** -0.5, causal)
+    o_ref, l_ref = oracle.attention_fwd_gqa(f64(q), f64(k), f64(v), d ** -0.5, causal)
+    assert max_abs(f64(o), o_ref) <= 2e-2 and rmse(f64(o), o_ref) <= 3e-3 and max_abs(f64(lse), l_ref) <= 2e-3
+
+
+@pytest.mark.parametrize("d,causal,N,most", [(64, False, 100, 80), (64, True, 100, 112), (64, False, 1024, 30), (128, False, 100, 64),
+                                             (128, False, 256, 64), (128, True, 512, 38), (128, False, 2048, 12), (256, False, 300, 25),
+                                             (256, True, 1024, 11)])
+def test_forward_on_both_sides_of_the_key_split_rule(d, causal, N, most):
+    # the most heads (a multiple of 8 or not) that are divided so, and the next ones that are not: the same rows
+    # either way, against the oracle and, as P~ is rounded relative to different references, to one another
+    q = inputs.normal_tensor(1700 + N, "q", (1, most + 16, N, d), "bf16")
+    k, v = (inputs.normal_tensor(1700 + N, n, (1, 1, N, d), "bf16") for n in ("k", "v"))
+    o_ref, l_ref = oracle.attention_fwd(f64(q[:, :1]), f64(k), f64(v), d ** -0.5, causal)
+    for H in (most, most + 1, most + 16):
+        o, lse = binding.fa_fwd_gqa(q[:, :H].contiguous().cuda(), k.cuda(), v.cuda(), d ** -0.5, causal)
+        assert max_abs(f64(o[:, :1]), o_ref) <= 2e-2 and rmse(f64(o[:, :1]), o_ref) <= 3e-3
+        assert max_abs(f64(lse[:, :1]), l_ref) <= 2e-3
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,N", [(64, 600), (128, 600), (128, 1500), (256, 600)])
+def test_forward_key_splits_merge_when_their_references_differ(d, N, causal):
+    # every row's maximum rises over the sequence by 80 nats, so the waves of a workgroup end with different references and
+    # raise them in most tiles; a raw score s of up to 80 sqrt(d) is a sum of d fp32 products, error below 2^-20 s scale in
+    # the exponent, and the outputs carry the 16-bit roundings of P~ and O
+    q, k, v = inputs.rising_maximum_qkv(1800, 1, 2, N, d, "bf16")
+    o, lse = binding.fa_fwd(q.cuda(), k.cuda(), v.cuda(), d ** -0.5, causal)
+    o_ref, l_ref = oracle.attention_fwd(f64(q), f64(k), f64(v), d ** -0.5, causal)
+    assert max_abs(f64(o), o_ref) <= 2e-2 + 2.0 ** -8 * np.abs(o_ref).max() and max_abs(f64(lse), l_ref) <= 2e-3
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_forward_key_splits_with_scores_of_minus_infinity(d):
+    # keys hidden through -inf in one component of K: waves whose tiles hold nothing else add nothing to a row
+    N, hidden = 300, 200
+    q, k, v = inputs.qkv(1810, 1, 2, N, d, "bf16")
+    q[..., 0] = 1.0
+    k[:, :, :hidden, 0] = -np.inf
+    o, lse = binding.fa_fwd(q.cuda(), k.cuda(), v.cuda(), d ** -0.5, False)
+    k[..., 0] = torch.where(torch.isinf(k[..., 0]), torch.zeros_like(k[..., 0]), k[..., 0])
+    s = q.double() @ k.double().transpose(-1, -2).contiguous() * d ** -0.5
+    s[..., :hidden] = -np.inf
+    assert max_abs(f64(lse), torch.logsumexp(s, -1).numpy()) <= 2e-3
+    assert max_abs(f64(o), (torch.softmax(s, -1) @ v.double()).numpy()) <= 2e-2
