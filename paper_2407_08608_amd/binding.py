@@ -3,11 +3,20 @@
 Every step of the attention path runs in the library's HIP kernels; PyTorch is used here
 for device memory and streams.  There is no fallback: if the library has not been built
 (`python -m paper_2407_08608_amd.build`), importing a symbol raises.
+
+The calls that programs make over and over go through csrc/fa_binding.cpp when its arguments are plain ones (that file
+says which): the same checks, outputs and library call in native code.  The Python below is the definition; it takes
+everything else, and all of it where the native part has not been built for this Python and torch.
 """
 import ctypes
 import os
 
 import torch
+
+try:
+    from . import _fa_binding as _native
+except ImportError:
+    _native = None
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libfa_mi355.so")
@@ -67,6 +76,9 @@ def lib():
         L.fa_status_string.argtypes = [ci]
         L.fa_status_string.restype = ctypes.c_char_p
         _lib = L
+        if _native is not None:
+            _native.bind(*(ctypes.cast(f, vp).value for f in (L.fa_fwd_gqa, L.fa_fwd_fp8_gqa, L.fa_fp8_quant_hadamard,
+                                                              L.fa_bwd_workspace_bytes, L.fa_bwd_gqa)))
     return _lib
 
 
@@ -85,6 +97,13 @@ def _empty_like(t, dtype):
     return torch.empty_like(t, dtype=dtype, memory_format=torch.contiguous_format)
 
 
+def _outputs(result, what):
+    """What a native call that was made came to: its outputs, or the refusal as an exception."""
+    if type(result) is int:
+        raise FaError(result, what)
+    return result
+
+
 def _check_dev(*ts):
     for t in ts:
         if t is not None and (not t.is_cuda or not t.is_contiguous()):
@@ -94,6 +113,10 @@ def _check_dev(*ts):
 def fa_fwd(q, k, v, scale, causal, o=None, lse=None, dtype=None):
     """O, L = attention forward.  q, k, v: [B,H,N,d] device tensors of one dtype
     (float32 / bfloat16 / float16, or uint8 e4m3 codes with dtype=FA_FP8_E4M3)."""
+    if _native is not None and dtype is None:
+        r = _native.fwd(q, k, v, scale, causal, o, lse, False, _stream)
+        if r is not None:
+            return _outputs(r, "fa_fwd")
     _check_dev(q, k, v, o, lse)
     B, H, N, d = q.shape
     code = dtype if dtype is not None else _DTYPE_CODE[q.dtype]
@@ -110,6 +133,10 @@ def fa_fwd(q, k, v, scale, causal, o=None, lse=None, dtype=None):
 
 def fa_fp8_quant_hadamard(x, signs=None, block_rows=128, per_tensor=False, x8=None, scales=None):
     """codes (uint8 e4m3) and per-block scales of x [B,H,N,d]; signs: int8 [d] device tensor or None."""
+    if _native is not None and block_rows == 128:
+        r = _native.quant(x, signs, per_tensor, x8, scales, _stream)
+        if r is not None:
+            return _outputs(r, "fa_fp8_quant_hadamard")
     _check_dev(x, signs, x8, scales)
     B, H, N, d = x.shape
     nb = -(-N // block_rows)
@@ -127,6 +154,10 @@ def fa_fp8_quant_hadamard(x, signs=None, block_rows=128, per_tensor=False, x8=No
 
 def fa_fwd_fp8(q8, k8, v8, q_scale, k_scale, v_scale, scale, causal, block_rows=128, o=None, lse=None):
     """O (bf16), L from e4m3 codes with per-block scales."""
+    if _native is not None and block_rows == 128:
+        r = _native.fwd_fp8(q8, k8, v8, q_scale, k_scale, v_scale, scale, causal, o, lse, False, _stream)
+        if r is not None:
+            return _outputs(r, "fa_fwd_fp8")
     _check_dev(q8, k8, v8, q_scale, k_scale, v_scale, o, lse)
     B, H, N, d = q8.shape
     if o is None:
@@ -147,6 +178,10 @@ def fa_bwd_workspace_bytes(B, H, N, d, dtype=FA_BF16):
 
 def fa_bwd(q, k, v, o, lse, dout, scale, causal, dq=None, dk=None, dv=None, workspace=None):
     """dQ, dK, dV from the forward's inputs, O, L and dO."""
+    if _native is not None:
+        r = _native.bwd(q, k, v, o, lse, dout, scale, causal, dq, dk, dv, workspace, False, _stream)
+        if r is not None:
+            return _outputs(r, "fa_bwd")
     _check_dev(q, k, v, o, lse, dout, dq, dk, dv, workspace)
     B, H, N, d = q.shape
     code = _DTYPE_CODE[q.dtype]
@@ -199,6 +234,10 @@ def fa_fwd_schedule(q, k, v, scale, causal, schedule, o=None, lse=None):
 
 def fa_fwd_gqa(q, k, v, scale, causal, o=None, lse=None, dtype=None):
     """Grouped-query forward: q [B,H,N,d]; k, v [B,H_kv,N,d] with H_kv dividing H."""
+    if _native is not None and dtype is None:
+        r = _native.fwd(q, k, v, scale, causal, o, lse, True, _stream)
+        if r is not None:
+            return _outputs(r, "fa_fwd_gqa")
     _check_dev(q, k, v, o, lse)
     B, H, N, d = q.shape
     H_kv = k.shape[1]
@@ -216,6 +255,10 @@ def fa_fwd_gqa(q, k, v, scale, causal, o=None, lse=None, dtype=None):
 
 def fa_fwd_fp8_gqa(q8, k8, v8, q_scale, k_scale, v_scale, scale, causal, block_rows=128, o=None, lse=None):
     """Grouped-query FP8 forward: q8 [B,H,N,d]; k8, v8 [B,H_kv,N,d] and their scales [B,H_kv,blocks]."""
+    if _native is not None and block_rows == 128:
+        r = _native.fwd_fp8(q8, k8, v8, q_scale, k_scale, v_scale, scale, causal, o, lse, True, _stream)
+        if r is not None:
+            return _outputs(r, "fa_fwd_fp8_gqa")
     _check_dev(q8, k8, v8, q_scale, k_scale, v_scale, o, lse)
     B, H, N, d = q8.shape
     H_kv = k8.shape[1]
@@ -233,6 +276,10 @@ def fa_fwd_fp8_gqa(q8, k8, v8, q_scale, k_scale, v_scale, scale, causal, block_r
 
 def fa_bwd_gqa(q, k, v, o, lse, dout, scale, causal, dq=None, dk=None, dv=None, workspace=None):
     """Grouped-query backward: dQ [B,H,N,d]; dK, dV [B,H_kv,N,d] (summed over each group's query heads)."""
+    if _native is not None:
+        r = _native.bwd(q, k, v, o, lse, dout, scale, causal, dq, dk, dv, workspace, True, _stream)
+        if r is not None:
+            return _outputs(r, "fa_bwd_gqa")
     _check_dev(q, k, v, o, lse, dout, dq, dk, dv, workspace)
     B, H, N, d = q.shape
     H_kv = k.shape[1]

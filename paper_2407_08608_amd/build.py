@@ -1,8 +1,9 @@
-"""Build libfa_mi355.so in-tree with hipcc for gfx950 (cross-compiles without a GPU)."""
+"""Build libfa_mi355.so in-tree with hipcc for gfx950 (cross-compiles without a GPU), and the native part of binding.py."""
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -45,11 +46,26 @@ def _check_hazards(name):
     return name
 
 
+# The native part of binding.py: host code against torch's C++ interface, which stays out of the library.
+BINDING = os.path.join(HERE, "_fa_binding.so")
+
+
+def _build_binding():
+    import torch
+    root = os.path.dirname(torch.__file__)
+    include = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+               sysconfig.get_paths()["include"]]
+    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall",
+                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+                    *(f for d in include for f in ("-isystem", d)), os.path.join(CSRC, "fa_binding.cpp"), "-o", BINDING,
+                    "-L" + os.path.join(root, "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"], check=True)
+
+
 def build(verbose=True):
     os.makedirs(OBJ, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
-    with ThreadPoolExecutor(max_workers=min(8, len(srcs) + len(HAZARD_CHECKED))) as ex:
-        checks = [ex.submit(_check_hazards, n) for n in HAZARD_CHECKED]
+    with ThreadPoolExecutor(max_workers=min(8, len(srcs) + len(HAZARD_CHECKED) + 1)) as ex:
+        checks = [ex.submit(_build_binding), *(ex.submit(_check_hazards, n) for n in HAZARD_CHECKED)]
         objs = list(ex.map(_compile, srcs))
         for c in checks:
             c.result()

@@ -1,0 +1,105 @@
+"""The native way through the binding (csrc/fa_binding.cpp) against the Python way: the same results, refusals and errors."""
+import pytest
+import torch
+
+from paper_2407_08608_amd import binding
+
+
+def _both(monkeypatch, call):
+    """What `call` returns or raises with the native part and without it."""
+    seen = []
+    for native in (binding._native, None):
+        monkeypatch.setattr(binding, "_native", native)
+        try:
+            seen.append(call())
+        except Exception as e:  # noqa: BLE001 - compared below
+            seen.append(e)
+    return seen
+
+
+def _same_error(a, b):
+    assert isinstance(a, Exception) and type(a) is type(b) and str(a) == str(b), (a, b)
+
+
+def test_the_native_part_is_built():
+    assert binding._native is not None
+
+
+def test_arguments_that_no_way_takes(monkeypatch):
+    # no GPU needed: everything here is refused before the library is called
+    x = torch.zeros(1, 2, 16, 64)
+    for bad in (x, x[..., :32], None, "q", 3):
+        for call in (lambda: binding.fa_fwd(bad, x, x, 0.125, False), lambda: binding.fa_fwd_gqa(bad, x, x, 0.125, True),
+                     lambda: binding.fa_bwd(bad, x, x, x, x, x, 0.125, False), lambda: binding.fa_fp8_quant_hadamard(bad),
+                     lambda: binding.fa_fwd_fp8(bad, x, x, x, x, x, 0.125, False)):
+            _same_error(*_both(monkeypatch, call))
+
+
+def _tensors(dtype=torch.bfloat16, H=4, H_kv=2, N=70, d=64):
+    g = torch.Generator(device="cuda").manual_seed(7)
+    mk = lambda h: torch.randn((2, h, N, d), generator=g, device="cuda").to(dtype)  # noqa: E731
+    return mk(H), mk(H_kv), mk(H_kv), mk(H)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16, torch.float32])
+@pytest.mark.parametrize("scale,causal", [(0.125, False), (0.125, True), (1, 1)])
+def test_both_ways_give_the_same(monkeypatch, dtype, scale, causal):
+    q, k, v, do = _tensors(dtype)
+    full = _tensors(dtype, H_kv=4)[1:3]
+    o, lse = binding.fa_fwd_gqa(q, k, v, scale, causal)
+    signs = torch.ones(64, dtype=torch.int8, device="cuda")
+    codes = [binding.fa_fp8_quant_hadamard(t) for t in (q, k, v)]
+    codes_full = [codes[0]] + [binding.fa_fp8_quant_hadamard(t) for t in full]
+    calls = [lambda: binding.fa_fwd(q, *full, scale, causal), lambda: binding.fa_fwd_gqa(q, k, v, scale, causal),
+             lambda: binding.fa_fp8_quant_hadamard(q, signs), lambda: binding.fa_fp8_quant_hadamard(q, per_tensor=True),
+             lambda: binding.fa_fwd_fp8(*(c[0] for c in codes_full), *(c[1] for c in codes_full), scale, causal),
+             lambda: binding.fa_fwd_fp8_gqa(*(c[0] for c in codes), *(c[1] for c in codes), scale, causal)]
+    if dtype != torch.float32:
+        calls += [lambda: binding.fa_bwd_gqa(q, k, v, o, lse, do, scale, causal),
+                  lambda: binding.fa_bwd(q, *full, o, lse, do, scale, causal)]
+    for call in calls:
+        native, python = _both(monkeypatch, call)
+        assert type(native) is tuple and type(python) is tuple and len(native) == len(python)
+        for a, b in zip(native, python):
+            assert type(a) is torch.Tensor and a.dtype == b.dtype and a.device == b.device and a.stride() == b.stride()
+            assert not a.requires_grad and torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.gpu
+def test_given_outputs_are_the_ones_returned_and_inputs_keep_their_graph(monkeypatch):
+    q, k, v, do = _tensors()
+    q = q.requires_grad_()
+    # a contiguous tensor whose strides are not the ordinary ones (a dimension of size 1)
+    one = torch.empty_strided((1, 4, 70, 64), (7, 70 * 64, 64, 1), dtype=torch.bfloat16, device="cuda").normal_()
+    for native in (binding._native, None):
+        monkeypatch.setattr(binding, "_native", native)
+        o, lse = torch.empty_like(do), torch.empty((2, 4, 70), device="cuda")
+        got = binding.fa_fwd_gqa(q, k, v, 0.125, True, o=o, lse=lse)
+        assert got[0] is o and got[1] is lse and q.requires_grad and not o.requires_grad
+        dk = torch.empty_like(k)
+        grads = binding.fa_bwd_gqa(q, k, v, o, lse, do, 0.125, True, dk=dk)
+        assert grads[1] is dk and not grads[0].requires_grad
+        o1, l1 = binding.fa_fwd(one, one, one, 0.125, False)
+        assert o1.stride() == (4 * 70 * 64, 70 * 64, 64, 1)
+        assert binding.fa_bwd(one, one, one, o1, l1, one, 0.125, False)[0].stride() == one.stride()
+
+
+@pytest.mark.gpu
+def test_both_ways_refuse_the_same(monkeypatch):
+    q, k, v, do = _tensors()
+    lse = torch.empty((2, 4, 70), device="cuda")
+    codes, scales = binding.fa_fp8_quant_hadamard(q)
+    small = torch.empty((16,), dtype=torch.uint8, device="cuda")
+    f32 = q.float()
+    for call in (lambda: binding.fa_fwd(q, k, v, -1.0, False), lambda: binding.fa_fwd(q, k, v, float("nan"), False),
+                 lambda: binding.fa_fwd(q[..., :32].contiguous(), k, v, 0.125, False), lambda: binding.fa_fwd(q.double(), k, v, 0.125, False),
+                 lambda: binding.fa_fwd(q[0], k, v, 0.125, False), lambda: binding.fa_fwd(q.transpose(1, 2), k, v, 0.125, False),
+                 lambda: binding.fa_fwd_gqa(q, q[:, :3].contiguous(), q[:, :3].contiguous(), 0.125, False),
+                 lambda: binding.fa_fwd_gqa(q, k.reshape(-1), v, 0.125, False), lambda: binding.fa_fwd(q, k, v.cpu(), 0.125, False),
+                 lambda: binding.fa_bwd(q, q, q, q, lse, do, 0.125, False, workspace=small),
+                 lambda: binding.fa_bwd(f32, f32, f32, f32, lse, f32, 0.125, False),
+                 lambda: binding.fa_fp8_quant_hadamard(codes), lambda: binding.fa_fp8_quant_hadamard(q, block_rows=64),
+                 lambda: binding.fa_fwd_fp8(codes, codes, codes, scales, scales, scales, 0.0, False),
+                 lambda: binding.fa_fwd(q, k, v, "scale", False)):
+        _same_error(*_both(monkeypatch, call))
