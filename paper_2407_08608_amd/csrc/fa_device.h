@@ -159,7 +159,7 @@ static __device__ __forceinline__ HalfPair both_halves(float x) {
 
 static __device__ __forceinline__ float max_both_halves(float x) {
     HalfPair p = both_halves(x);
-    return fmaxf(p.lo, p.hi);
+    return fmaxf(fmaxf(-INFINITY, p.lo), p.hi);  // one three-way maximum; of the two alone, each would be quieted first
 }
 
 static __device__ __forceinline__ float sum_both_halves(float x) {

@@ -51,6 +51,15 @@ static __device__ __forceinline__ f32x16 mma_fp8(i32x8 a, i32x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0x7F7F7F7F, 0, 0x7F7F7F7F);
 }
 
+// Four values as e4m3 codes, first lowest.  Each conversion writes one half of the word and keeps the other: what the first
+// one keeps is overwritten by the second, so the word starts as whatever its register holds (a zero would cost a move).
+static __device__ __forceinline__ int pack_e4m3(float a, float b, float c, float d) {
+    int word;
+    asm volatile("" : "=v"(word));
+    word = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, word, false);
+    return __builtin_amdgcn_cvt_pk_fp8_f32(c, d, word, true);
+}
+
 // key held in MFMA row i of a 32-key tile
 static __device__ __forceinline__ int key_of_row(int i) {
     int g = i >> 3, hb = (i >> 2) & 1, r = i & 3;
@@ -211,7 +220,7 @@ fa_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ k, 
             // ---- online softmax in log2 units of the real scores.  Independent chains for the maximum
             // and the sum: a wave gets few issue slots while its SIMD sibling streams MFMAs, and one
             // long dependent chain would turn every slot missed into a stall.
-            float mxp[4] = {sacc[0][0], sacc[0][1], sacc[0][2], sacc[0][3]};
+            float mxp[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};  // (a chain that starts from a score pays to quiet it first)
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
@@ -238,7 +247,7 @@ fa_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ k, 
             const float mb = m_run - kPBias - lsv;
             float sc_v = sc;  // a vector-register copy: an FMA with a scalar-register operand issues at a lower rate
             asm volatile("" : "+v"(sc_v));
-            float ps[4] = {0.f, 0.f, 0.f, 0.f};
+            float ps[4];
             i32x8 pb[SL];
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt) {
@@ -253,16 +262,11 @@ fa_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ k, 
                     p[r] = fast_exp2(__builtin_fmaf(sacc[kt][r], sc_v, -mb));
 #endif
 #if FA_ABLATE != 4
-                    ps[r & 3] += p[r];
+                    ps[r & 3] = kt == 0 && r < 4 ? p[r] : ps[r & 3] + p[r];
 #endif
                 }
 #pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    int word = 0;
-                    word = __builtin_amdgcn_cvt_pk_fp8_f32(p[4 * w], p[4 * w + 1], word, false);
-                    word = __builtin_amdgcn_cvt_pk_fp8_f32(p[4 * w + 2], p[4 * w + 3], word, true);
-                    pb[kt >> 1][4 * (kt & 1) + w] = word;
-                }
+                for (int w = 0; w < 4; ++w) pb[kt >> 1][4 * (kt & 1) + w] = pack_e4m3(p[4 * w], p[4 * w + 1], p[4 * w + 2], p[4 * w + 3]);
             }
             float psum = (ps[0] + ps[1]) + (ps[2] + ps[3]);
             if constexpr (SCALED) psum *= __builtin_amdgcn_rcpf(sv_new);
@@ -313,8 +317,10 @@ fa_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ k, 
         char* patch = lds_o + wave * 4096;
         const int qi = wave_q0 + col;
         const float l = sum_both_halves(l_run);
+        int out_lane = lane;  // opaque: the addresses derived from it are else computed before the loop and kept over it
+        asm volatile("" : "+v"(out_lane));
         store_rows_via_lds<bf16_tag, DT>(oacc, 1.0f / l, patch, make_buffer(o + head_off, (uint32_t)N * D * 2),
-                                         wave_q0, lane);
+                                         wave_q0, out_lane);
         if (qi < N && half == 0) lse[(size_t)bh * N + qi] = (m_run + log2f(l) - kPBias) * kLn2;
     }
     }  // passes of a causal pair
@@ -492,7 +498,7 @@ fa_fwd_fp8_async_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict
             }
 
             // ---- reference maximum (see fa_fwd_fp8_kernel: log2 units, V block scale as an exponent offset)
-            float mxp[4] = {sacc[0][0], sacc[0][1], sacc[0][2], sacc[0][3]};
+            float mxp[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};  // (a chain that starts from a score pays to quiet it first)
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
@@ -515,7 +521,7 @@ fa_fwd_fp8_async_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict
             asm volatile("" : "+v"(sc_v));
 
             // ---- P~ = exp2(s sc - mb) as e4m3, and its row sum
-            float ps[4] = {0.f, 0.f, 0.f, 0.f};
+            float ps[4];
             i32x8 pb[SL];
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt) {
@@ -523,15 +529,10 @@ fa_fwd_fp8_async_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     p[r] = fast_exp2(__builtin_fmaf(sacc[kt][r], sc_v, -mb));
-                    ps[r & 3] += p[r];
+                    ps[r & 3] = kt == 0 && r < 4 ? p[r] : ps[r & 3] + p[r];
                 }
 #pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    int word = 0;
-                    word = __builtin_amdgcn_cvt_pk_fp8_f32(p[4 * w], p[4 * w + 1], word, false);
-                    word = __builtin_amdgcn_cvt_pk_fp8_f32(p[4 * w + 2], p[4 * w + 3], word, true);
-                    pb[kt >> 1][4 * (kt & 1) + w] = word;
-                }
+                for (int w = 0; w < 4; ++w) pb[kt >> 1][4 * (kt & 1) + w] = pack_e4m3(p[4 * w], p[4 * w + 1], p[4 * w + 2], p[4 * w + 3]);
             }
 
             // the sum needs the weights without the V scale's exponent offset
@@ -563,8 +564,10 @@ fa_fwd_fp8_async_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict
         char* patch = lds_kv + wave * 4096;
         const int qi = wave_q0 + col;
         const float l = sum_both_halves(l_run);
+        int out_lane = lane;  // opaque: the addresses derived from it are else computed before the loop and kept over it
+        asm volatile("" : "+v"(out_lane));
         store_rows_via_lds<bf16_tag, DT>(oacc, 1.0f / l, patch, make_buffer(o + head_off, (uint32_t)N * D * 2),
-                                         wave_q0, lane);
+                                         wave_q0, out_lane);
         if (qi < N && half == 0) lse[(size_t)bh * N + qi] = (m_run + log2f(l) - kPBias) * kLn2;
     }
     }  // passes of a causal pair
