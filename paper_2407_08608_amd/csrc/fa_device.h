@@ -110,6 +110,10 @@ static __device__ __forceinline__ i32x4 lds_load_16B(uint32_t addr) {
     typedef i32x4 __attribute__((address_space(3))) * lds_vec_ptr;
     return *(lds_vec_ptr)(uintptr_t)addr;
 }
+static __device__ __forceinline__ float lds_load_4B(uint32_t addr) {
+    typedef float __attribute__((address_space(3))) * lds_float_ptr;
+    return *(lds_float_ptr)(uintptr_t)addr;
+}
 static __device__ __forceinline__ f32x4 lds_load_4f(uint32_t addr) {
     typedef f32x4 __attribute__((address_space(3))) * lds_vec_ptr;
     return *(lds_vec_ptr)(uintptr_t)addr;
@@ -194,6 +198,16 @@ static __device__ __forceinline__ void global_to_lds_16B(const BufferWords& rsrc
                  :
                  : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(byte_off), "s"(rsrc.w)
                  : "memory", "m0");
+}
+
+// The resource `bytes` further on: what was at offset `bytes` is at 0 then, what lies past the end still reads as zero.
+// Walking a tensor so costs scalar instructions only, where an offset per load costs a vector one.
+static __device__ __forceinline__ void advance(BufferWords& b, int bytes) {
+    const uint64_t a = (uint64_t)(uint32_t)b.w[0] | (uint64_t)(uint32_t)b.w[1] << 32;
+    const uint64_t n = a + (uint32_t)bytes;
+    b.w[0] = (int)(uint32_t)n;
+    b.w[1] = (int)(uint32_t)(n >> 32);
+    b.w[2] = max(b.w[2] - bytes, 0);  // (no tensor of a head reaches 2^31 bytes)
 }
 
 // A wave's private tile of 32 rows of a 16-bit tensor, staged straight from global memory into LDS that no other wave

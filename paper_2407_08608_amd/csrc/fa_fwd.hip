@@ -1119,32 +1119,36 @@ fa_fwd_pingpong_kernel(const uint16_t* __restrict__ q, const uint16_t* __restric
 // Bound by that instruction: 64 cycles for 4 KFLOP per SIMD, 157 TFLOP/s for the chip, against which the softmax of
 // a 32 x 32 score tile (64 MFMAs) is about a tenth.  Requests in fp32 are mostly small, so the tile is chosen to
 // put work on every SIMD: a workgroup owns 64 query rows in two slabs of 32, and the four waves of a slab split
-// the keys (wave `split` takes keys 32 split .. 32 split + 31 of every 128-key block) with a softmax state each;
-// the four states are merged through the LDS at the end, in a fixed order.  That quarters the serial chain of key
-// blocks and puts two waves on each SIMD, one's softmax under the other's MFMAs.
+// the keys (wave `split` takes the 32-key tiles split, split + 4, ...) with a softmax state each; the four states are
+// merged through the LDS at the end, in a fixed order.  That quarters the serial chain of tiles and puts two waves on
+// each SIMD, one's softmax under the other's MFMAs.  Each wave stages its own tiles straight into LDS of its own, V
+// beside the score MFMAs and the next K beside the products: without a barrier the two waves of a SIMD drift apart and
+// stay there.  (Staged by the workgroup, 128 keys at a time behind a barrier, both waves of a SIMD did their softmax
+// together: B = 2, H = 8, N = 1000 42.3 us, 36.6 so, most of it from the 110 vector instructions
+// per tile that offsets, addresses and needless rescales took: the matrix instruction leaves the vector pipe little room.)
 //   S^T = K Q^T: step i contracts head-dim elements {i, 32 + i}, so a lane's operands are 32 consecutive floats of a
-//     row, four MFMAs to a 16-byte LDS read (rows padded to 272 bytes: 16 rows, 16 chunk positions).
+//     row, four MFMAs to a 16-byte LDS read.
 //   O^T += V^T P^T: score register r of a lane is key 8 (r / 4) + 4 half + r % 4, so the register itself is the B
-//     operand of the step that contracts this pair of keys; A is V read down a column (rows padded to 288 bytes: the
-//     two rows of a step lie in different halves of the banks).
-// B = 2, H = 8, N = 1000: 867 us with one thread per row and scalar FMAs, 42 us so (97 TFLOP/s).
+//     operand of the step that contracts this pair of keys; A is V read down a column.
+//   The tiles are unpadded rows of 256 bytes, 16-byte chunk c of row r at c ^ swizzle(r): sixteen rows at one chunk hit
+//     every bank once (K), and so do the halves of two rows four apart (V).
 template <int D, int BC, bool CAUSAL>
 __global__ void __launch_bounds__(512, 2)
 fa_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
                   float* __restrict__ o, float* __restrict__ lse, int N, int n_qtiles, int total_wg, int first_head,
                   int kv_group, float scale) {
-    static_assert(D == 64 && BC == 32, "one 32-key score tile per wave and block, two 32-column output tiles");
+    static_assert(D == 64 && BC == 32, "one 32-key score tile per step, two 32-column output tiles");
     constexpr int NT = 512, SLABS = 2, SPLITS = 4;
     constexpr int BR = 32 * SLABS;    // query rows per workgroup
-    constexpr int BS = BC * SPLITS;   // keys per staged block
-    constexpr int KSTR = D + 4, VSTR = D + 8;  // LDS row strides (floats)
-    constexpr int CPT = BS * D / 4 / NT;       // 16-byte chunks per thread and tensor
-    __shared__ __attribute__((aligned(16))) float lds_k[2][BS * KSTR];
-    __shared__ __attribute__((aligned(16))) float lds_v[2][BS * VSTR];
+    constexpr int ROWB = D * 4, TILE = BC * ROWB;  // bytes of a row and of a tile
+    constexpr int PSTR = D + 4;       // row stride of the partial outputs (floats)
+    constexpr int NI = TILE / 1024;   // staging instructions per tile (four rows each)
+    constexpr int KP = 2, VP = 4;     // steps by which operand reads lead their MFMAs
+    __shared__ __attribute__((aligned(1024))) char lds[SLABS * SPLITS * 2 * TILE];
     __shared__ float lds_m[SPLITS][BR], lds_l[SPLITS][BR];
 
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int col = lane & 31, half = lane >> 5;
     const int slab = wave & 1, split = wave >> 1;
 
@@ -1155,27 +1159,26 @@ fa_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, cons
     const int q0 = qt * BR + slab * 32;                     // first row of this wave's slab
     const int row = min(q0 + col, N - 1);                   // rows past N compute a copy of row N-1, never stored
     const int limit = CAUSAL ? row : N - 1;                 // last visible key
+    const int n_tiles = CAUSAL ? min(q0 / BC + 1, (N + BC - 1) / BC) : (N + BC - 1) / BC;
     const float sc = scale * kLog2e;
 
-    const __amdgpu_buffer_rsrc_t k_rsrc = make_buffer(k + kv_off, (uint32_t)N * D * 4);
-    const __amdgpu_buffer_rsrc_t v_rsrc = make_buffer(v + kv_off, (uint32_t)N * D * 4);
-    i32x4 kpre[CPT], vpre[CPT];
-    auto load_block = [&](int t) {  // rows past N read as zero
+    // the wave's next tiles (rows past N read as zero)
+    BufferWords k_rsrc = make_buffer_words(k + kv_off, (uint32_t)N * D * 4), v_rsrc = make_buffer_words(v + kv_off, (uint32_t)N * D * 4);
+    advance(k_rsrc, split * TILE);
+    advance(v_rsrc, split * TILE);
+    auto swizzle = [](int r) { return (r & 3) | ((r >> 3) & 1) << 2 | ((r >> 2) & 1) << 3; };
+    const uint32_t kb = lds_address(lds) + wave * (2 * TILE), vb = kb + TILE;
+    int src[NI];  // byte offset within a tile
 #pragma unroll
-        for (int i = 0; i < CPT; ++i) {
-            kpre[i] = buffer_load_16B(k_rsrc, t * BS * D * 4 + (tid + i * NT) * 16);
-            vpre[i] = buffer_load_16B(v_rsrc, t * BS * D * 4 + (tid + i * NT) * 16);
-        }
+    for (int i = 0; i < NI; ++i) {
+        const int r = 4 * i + (lane >> 4);
+        src[i] = r * ROWB + ((lane & 15) ^ swizzle(r)) * 16;
+    }
+    auto request = [&](const BufferWords& rsrc, uint32_t to, int i) __attribute__((always_inline)) {
+        global_to_lds_16B(rsrc, to + i * 1024, src[i]);
     };
-    auto store_block = [&](int st) {
 #pragma unroll
-        for (int i = 0; i < CPT; ++i) {
-            const int c = tid + i * NT, r = c / (D / 4), cc = c % (D / 4);
-            *reinterpret_cast<i32x4*>(lds_k[st] + r * KSTR + cc * 4) = kpre[i];
-            *reinterpret_cast<i32x4*>(lds_v[st] + r * VSTR + cc * 4) = vpre[i];
-        }
-    };
-    load_block(0);
+    for (int i = 0; i < NI; ++i) request(k_rsrc, kb, i);
 
     f32x4 qreg[D / 8];  // Q^T as the B operand: lane (row, half) holds elements 32 half .. 32 half + 31
 #pragma unroll
@@ -1185,69 +1188,103 @@ fa_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, cons
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;
+    // LDS addresses of the operands, opaque: they are else computed again in every tile.  K: chunk 8 half + j of row col.
+    // V: columns col and col + 32 of rows 8 (r / 4) + 4 half + r % 4, r < 8 (16 rows on the swizzle is the same).
+    uint32_t k_at[D / 8], v_at[8][2];
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j) {
+        k_at[j] = kb + col * ROWB + (((8 * half + j) ^ swizzle(col)) << 4);
+        asm volatile("" : "+v"(k_at[j]));
+    }
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt) {
+            const int key = 8 * (r >> 2) + 4 * half + (r & 3);
+            v_at[r][dt] = vb + key * ROWB + ((((col >> 2) + 8 * dt) ^ swizzle(key)) << 4) + 4 * (col & 3);
+            asm volatile("" : "+v"(v_at[r][dt]));
+        }
+    float sc_v = sc;  // a vector-register copy: an FMA with a scalar-register operand issues at a lower rate
+    asm volatile("" : "+v"(sc_v));
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j) asm volatile("" : "+v"(qreg[j]));
 
-    const int last_q = min(qt * BR + BR, N) - 1;
-    const int n_blocks = CAUSAL ? last_q / BS + 1 : (N + BS - 1) / BS;
-    store_block(0);
+    for (int t = split; t < n_tiles; t += SPLITS) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // K has landed, the last V has been read
+        advance(k_rsrc, SPLITS * TILE);
+        if (t + SPLITS >= n_tiles) k_rsrc.w[2] = 0;  // past the wave's last tile: zeros that nothing reads
+        const int key0 = t * BC;
+        f32x16 s;
+        f32x4 ring[KP];  // operand reads lead their MFMAs
 #pragma unroll
-    for (int j = 0; j < D / 8; ++j) asm volatile("" : "+v"(qreg[j]));  // Q loads complete before the loop
-    __syncthreads();
-
-    for (int t = 0; t < n_blocks; ++t) {
-        const int st = t & 1;
-        const bool more = t + 1 < n_blocks;
-        if (more) load_block(t + 1);
-        const int key0 = t * BS + split * BC;  // this wave's keys
-        if (key0 < N && (!CAUSAL || key0 <= q0 + 31)) {
-            f32x16 s;
+        for (int j = 0; j < KP; ++j) ring[j] = __builtin_bit_cast(f32x4, lds_load_16B(k_at[j]));
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[r] = 0.f;
-            const float* krow = lds_k[st] + (split * BC + col) * KSTR + half * (D / 2);
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int j = 0; j < D / 8; ++j) {
-                const f32x4 a = *reinterpret_cast<const f32x4*>(krow + 4 * j);
+        for (int j = 0; j < D / 8; ++j) {
+            const f32x4 a = ring[j % KP];
+            if (j + KP < D / 8) ring[j % KP] = __builtin_bit_cast(f32x4, lds_load_16B(k_at[j + KP]));
+            request(v_rsrc, vb, j);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], qreg[j][e], s, 0, 0, 0);
-            }
-            if (key0 + BC > N || (CAUSAL && key0 + BC - 1 > q0)) {
-                const int bound = limit - key0 - 4 * half;
+            for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], qreg[j][e], s, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        static_assert(NI == D / 8, "one request per operand read, one per pair of products");
+        if (key0 + BC > N || (CAUSAL && key0 + BC - 1 > q0)) {
+            const int bound = limit - key0 - 4 * half;
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (8 * (r >> 2) + (r & 3) > bound) s[r] = -INFINITY;
-            }
-            float mx[4] = {s[0], s[1], s[2], s[3]};
+            for (int r = 0; r < 16; ++r)
+                if (8 * (r >> 2) + (r & 3) > bound) s[r] = -INFINITY;
+        }
+        float mx[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
-            for (int r = 4; r < 16; ++r) mx[r & 3] = fmaxf(mx[r & 3], s[r]);
-            const float m_new = fmaxf(m_run, max_both_halves(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3]))));
-            const float mb = m_new == -INFINITY ? 0.f : m_new * sc;  // a row that sees none of these keys: P = 0
-            if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
-                const float corr = fast_exp2(__builtin_fmaf(m_run, sc, -mb));
-                m_run = m_new;
-                l_run *= corr;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    acc[0][r] *= corr;
-                    acc[1][r] *= corr;
-                }
-            }
-            float ps[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int r = 0; r < 16; ++r) mx[r & 3] = fmaxf(mx[r & 3], s[r]);
+        const float m_new = max_both_halves(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])));
+        // the reference rises when a tile's maximum exceeds it by more than 2^kLazyLog2 (the factor cancels in O / l)
+        const bool raise = (m_new - m_run) * sc > kLazyLog2;
+        if (__builtin_amdgcn_ballot_w64(raise) != 0) {
+            const float corr = raise ? fast_exp2((m_run - m_new) * sc) : 1.0f;
+            m_run = raise ? m_new : m_run;
+            l_run *= corr;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                s[r] = fast_exp2(__builtin_fmaf(s[r], sc, -mb));
-                ps[r & 3] += s[r];
-            }
-            l_run += (ps[0] + ps[1]) + (ps[2] + ps[3]);
-            const float* vrow = lds_v[st] + (split * BC + 4 * half) * VSTR + col;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float* p = vrow + (8 * (r >> 2) + (r & 3)) * VSTR;
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(p[0], s[r], acc[0], 0, 0, 0);
-                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(p[32], s[r], acc[1], 0, 0, 0);
+                acc[0][r] *= corr;
+                acc[1][r] *= corr;
             }
         }
-        if (more) store_block(st ^ 1);
-        __syncthreads();
+        const float mb = m_run == -INFINITY ? 0.f : m_run * sc;  // a row of scores of -inf so far: P = 0
+        float ps[4];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            s[r] = fast_exp2(__builtin_fmaf(s[r], sc_v, -mb));
+            ps[r & 3] = r < 4 ? s[r] : ps[r & 3] + s[r];
+        }
+        l_run += (ps[0] + ps[1]) + (ps[2] + ps[3]);
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // V has landed, K has been read
+        advance(v_rsrc, SPLITS * TILE);
+        auto v_read = [&](int r, int dt) __attribute__((always_inline)) { return lds_load_4B(v_at[r & 7][dt] + (r >> 3) * 16 * ROWB); };
+        float v0[VP], v1[VP];
+#pragma unroll
+        for (int r = 0; r < VP; ++r) {
+            v0[r] = v_read(r, 0);
+            v1[r] = v_read(r, 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float a0 = v0[r % VP], a1 = v1[r % VP];
+            if (r + VP < 16) {
+                v0[r % VP] = v_read(r + VP, 0);
+                v1[r % VP] = v_read(r + VP, 1);
+            }
+            if (r & 1) request(k_rsrc, kb, r >> 1);
+            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, s[r], acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, s[r], acc[1], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last requests: the LDS is about to be reused
 
     // ---- merge the four key splits of a row: with M the largest of their maxima and f = exp(m - M),
     // L = M + log sum f l and O = sum f O / sum f l
@@ -1265,15 +1302,15 @@ fa_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, cons
     for (int w = 0; w < SPLITS; ++w)
         l_all += lds_l[w][slab * 32 + col] * fast_exp2((lds_m[w][slab * 32 + col] - m_ref) * sc);
     const float f = fast_exp2((m_run - m_ref) * sc) / l_all;
-    // the K buffers are free: [split][row][d] partial outputs, already scaled
-    static_assert(sizeof(lds_k) >= SPLITS * BR * KSTR * sizeof(float), "partial outputs must fit");
-    float* part = &lds_k[0][0];
+    // the tiles are free: [split][row][d] partial outputs, already scaled
+    static_assert(sizeof(lds) >= SPLITS * BR * PSTR * sizeof(float), "partial outputs must fit");
+    float* part = reinterpret_cast<float*>(lds);
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             const f32x4 w = {acc[dt][4 * g] * f, acc[dt][4 * g + 1] * f, acc[dt][4 * g + 2] * f, acc[dt][4 * g + 3] * f};
-            *reinterpret_cast<f32x4*>(part + (split * BR + slab * 32 + col) * KSTR + dt * 32 + 8 * g + 4 * half) = w;
+            *reinterpret_cast<f32x4*>(part + (split * BR + slab * 32 + col) * PSTR + dt * 32 + 8 * g + 4 * half) = w;
         }
     if (split == 0 && half == 0 && q0 + col < N) lse[(size_t)bh * N + q0 + col] = (m_all * sc + log2f(l_all)) * kLn2;
     __syncthreads();
@@ -1281,10 +1318,10 @@ fa_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, cons
     for (int i = 0; i < BR * D / 4 / NT; ++i) {
         const int c = tid + i * NT, r = c / (D / 4), cc = (c % (D / 4)) * 4;
         if (qt * BR + r < N) {
-            f32x4 w = *reinterpret_cast<const f32x4*>(part + r * KSTR + cc);
+            f32x4 w = *reinterpret_cast<const f32x4*>(part + r * PSTR + cc);
 #pragma unroll
             for (int sp = 1; sp < SPLITS; ++sp) {
-                const f32x4 x = *reinterpret_cast<const f32x4*>(part + (sp * BR + r) * KSTR + cc);
+                const f32x4 x = *reinterpret_cast<const f32x4*>(part + (sp * BR + r) * PSTR + cc);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) w[e] += x[e];
             }
