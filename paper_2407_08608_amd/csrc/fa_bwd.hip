@@ -797,20 +797,30 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
 }
 
 // ---------------------------------------------------------------------------------------
-// A wave's private tiles of 32 rows of two tensors (first, second) in two LDS stages (WaveTile).
+// A wave's private tiles of 32 rows of two tensors (first, second) in two LDS stages (WaveTile).  The addresses are moved from
+// stage to stage once per tile: a loop body per stage would save that, but the accumulators then change places
+// between the two (64 to 150 register moves a tile, and spills).
 template <int D>
 struct WaveTiles : WaveTile<D> {
     static_assert(D == 64 || D == 128, "two stages of a wave's tiles must fit a quarter of the LDS");
     using Tile = WaveTile<D>;
     using Tile::TILE_B;
     static constexpr int STAGE_B = 2 * TILE_B;    // first, second
-    uint32_t stage0;
-    __device__ __forceinline__ WaveTiles(uint32_t base, int lane) : Tile(lane), stage0(base) {}
-    // Instruction n of 2 NI that bring tile t of both heads into stage st (rows past a resource's end arrive as zeros).
+    using Tile::Tile;
+    // Instruction n of 2 NI that bring the tiles at the resources' starts into stage st
     static constexpr int NREQ = 2 * Tile::NI;
     static_assert(NREQ == 2 * Tile::KS, "one per MFMA step of the two score products");
-    __device__ __forceinline__ void request(const BufferWords& first, const BufferWords& second, int t, int st, int n) const {
-        Tile::request(n & 1 ? second : first, stage0 + st * STAGE_B + (n & 1) * TILE_B, t, n >> 1);
+    __device__ __forceinline__ void move(int bytes) {
+#pragma unroll
+        for (int ks = 0; ks < Tile::KS; ++ks) this->row_at[ks] += bytes;
+#pragma unroll
+        for (int dt = 0; dt < Tile::DT; ++dt) {
+            this->tr_at[dt][0] += bytes;
+            this->tr_at[dt][1] += bytes;
+        }
+    }
+    __device__ __forceinline__ void request(const BufferWords& first, const BufferWords& second, int st, int n) const {
+        Tile::request(n & 1 ? second : first, st * STAGE_B + (n & 1) * TILE_B, n >> 1);
     }
 };
 
@@ -871,7 +881,7 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
         for (int r = 0; r < 16; ++r) dkacc[dt][r] = dvacc[dt][r] = 0.f;
 
     float* lds_ld = lds_ld_all + wave * 2 * BQ;  // L (log2 units), then -D, of the wave's tile
-    const Tiles tiles(lds_address(lds) + wave * 2 * Tiles::STAGE_B, lane);  // Q, dO
+    Tiles tiles(lds_address(lds) + wave * 2 * Tiles::STAGE_B, lane);  // Q, dO
     const int n_t = (N + BQ - 1) / BQ, t0 = CAUSAL ? key0 / BQ : 0;
 
     float ldpre = 0.f;
@@ -883,6 +893,8 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
         const uint32_t bytes = gi < kv_group ? (uint32_t)N * D * 2 : 0;  // past the last tile: zeros that nothing reads
         q_rsrc = make_buffer_words(q + qhead * N * D, bytes);
         do_rsrc = make_buffer_words(dout + qhead * N * D, bytes);
+        advance(q_rsrc, t * Tiles::TILE_B);
+        advance(do_rsrc, t * Tiles::TILE_B);
         ldrow = t * BQ + col;  // lanes 0..31 carry L, 32..63 carry D
         const size_t row = qhead * N + min(ldrow, N - 1);
         if constexpr (D_READY) {
@@ -897,8 +909,8 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
         }
     };
 
-    // one tile at `base`, while tile t_next of the heads aimed at is requested into stage st_next
-    auto tile = [&](uint32_t base, int q0, int t_next, int st_next) __attribute__((always_inline)) {
+    // the tile that the addresses point at, while the tile aimed at is requested into stage st_next
+    auto tile = [&](int q0, int st_next) __attribute__((always_inline)) {
         f32x4 l4[4];
         f32x16 sacc, pacc;
         const uint32_t ld = lds_address(lds_ld) + 16 * half;
@@ -909,9 +921,9 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
 #pragma unroll
             for (int r = 0; r < 4; ++r) pacc[4 * i + r] = t[r];
         }
-        auto row_read = [&](int u) { return tiles.row_read(base + (u < KS ? 0 : Tiles::TILE_B), u % KS); };
+        auto row_read = [&](int u) { return tiles.row_read(u < KS ? 0 : Tiles::TILE_B, u % KS); };
         auto tr_read = [&](int u) {  // u = (tensor: dO then Q, slab, dt)
-            return tiles.tr_read(base + (u < 2 * DT ? Tiles::TILE_B : 0), (u / DT) % 2, u % DT);
+            return tiles.tr_read(u < 2 * DT ? Tiles::TILE_B : 0, (u / DT) % 2, u % DT);
         };
         i32x4 ring[KP], tr[KP], pa[2], dsa[2];
 #pragma unroll
@@ -932,7 +944,7 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
             const i32x4 a = ring[u % KP];
             if (u + KP < 2 * KS) ring[u % KP] = row_read(u + KP);
             else tr[u + KP - 2 * KS] = tr_read(u + KP - 2 * KS);
-            tiles.request(q_rsrc, do_rsrc, t_next, st_next, u);
+            tiles.request(q_rsrc, do_rsrc, st_next, u);
             if (u == 0) MfmaVgprAcc<Tag>::first(sacc, a, kreg[u]);
             else if (u < KS) MfmaVgprAcc<Tag>::run(sacc, a, kreg[u]);
             else if (u == KS) MfmaVgprAcc<Tag>::start(pacc, a, vreg[u - KS]);
@@ -977,7 +989,7 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
     settle();
     aim(gi, t);
 #pragma unroll
-    for (int n = 0; n < Tiles::NREQ; ++n) tiles.request(q_rsrc, do_rsrc, t, 0, n);
+    for (int n = 0; n < Tiles::NREQ; ++n) tiles.request(q_rsrc, do_rsrc, 0, n);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(kreg[ks]), "+a"(vreg[ks]));
     while (gi < kv_group) {
@@ -997,7 +1009,8 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
         t += NW;
         settle();
         aim(gi, t);
-        tile(tiles.stage0 + st * Tiles::STAGE_B, q0, t, st ^ 1);
+        tile(q0, st ^ 1);
+        tiles.move(st ? -Tiles::STAGE_B : Tiles::STAGE_B);
         st ^= 1;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the zeros of the last request: the LDS is about to be reused
@@ -1055,13 +1068,15 @@ static __device__ __forceinline__ void dq_few(int block, const uint16_t* __restr
     const size_t kv_off = (size_t)(bh / kv_group) * N * D;
     float sc = scale * kLog2e;
     asm volatile("" : "+v"(sc));
-    const BufferWords k_rsrc = make_buffer_words(k + kv_off, (uint32_t)N * D * 2);
-    const BufferWords v_rsrc = make_buffer_words(v + kv_off, (uint32_t)N * D * 2);
-    const Tiles tiles(lds_address(lds) + wave * 2 * Tiles::STAGE_B, lane);  // K, V
+    // the wave's next tiles (rows past N read as zero)
+    BufferWords k_rsrc = make_buffer_words(k + kv_off, (uint32_t)N * D * 2), v_rsrc = make_buffer_words(v + kv_off, (uint32_t)N * D * 2);
+    advance(k_rsrc, wave * Tiles::TILE_B);
+    advance(v_rsrc, wave * Tiles::TILE_B);
+    Tiles tiles(lds_address(lds) + wave * 2 * Tiles::STAGE_B, lane);  // K, V
 
     const int n_tiles = CAUSAL ? qt + 1 : n_t;
 #pragma unroll
-    for (int n = 0; n < Tiles::NREQ; ++n) tiles.request(k_rsrc, v_rsrc, wave, 0, n);
+    for (int n = 0; n < Tiles::NREQ; ++n) tiles.request(k_rsrc, v_rsrc, 0, n);
 
     i32x4 qreg[KS], doreg[KS];
 #pragma unroll
@@ -1092,8 +1107,9 @@ static __device__ __forceinline__ void dq_few(int block, const uint16_t* __restr
     int st = 0;
     for (int t = wave; t < n_tiles; t += NW, st ^= 1) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this tile has landed
-        const uint32_t base = tiles.stage0 + st * Tiles::STAGE_B;
-        auto row_read = [&](int u) { return tiles.row_read(base + (u < KS ? 0 : Tiles::TILE_B), u % KS); };
+        advance(k_rsrc, NW * Tiles::TILE_B);
+        advance(v_rsrc, NW * Tiles::TILE_B);
+        auto row_read = [&](int u) { return tiles.row_read(u < KS ? 0 : Tiles::TILE_B, u % KS); };
         f32x16 sacc, pacc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) pacc[r] = -d_row;  // dP - D comes out of the MFMAs
@@ -1108,9 +1124,9 @@ static __device__ __forceinline__ void dq_few(int block, const uint16_t* __restr
         for (int u = 0; u < 2 * KS; ++u) {
             const i32x4 a = ring[u % KP];
             if (u + KP < 2 * KS) ring[u % KP] = row_read(u + KP);
-            else tr[u + KP - 2 * KS] = tiles.tr_read(base, (u + KP - 2 * KS) / DT, (u + KP - 2 * KS) % DT);
+            else tr[u + KP - 2 * KS] = tiles.tr_read(0, (u + KP - 2 * KS) / DT, (u + KP - 2 * KS) % DT);
             // past this workgroup's last tile these bring rows (or zeros) that nothing reads
-            tiles.request(k_rsrc, v_rsrc, t + NW, st ^ 1, u);
+            tiles.request(k_rsrc, v_rsrc, st ^ 1, u);
             if (u == 0) MfmaVgprAcc<Tag>::first(sacc, a, qreg[u]);
             else if (u < KS) MfmaVgprAcc<Tag>::run(sacc, a, qreg[u]);
             else if (u == KS) MfmaVgprAcc<Tag>::start(pacc, a, doreg[u - KS]);
@@ -1139,10 +1155,11 @@ static __device__ __forceinline__ void dq_few(int block, const uint16_t* __restr
 #pragma unroll
         for (int u = 0; u < 2 * DT; ++u) {
             const i32x4 a = tr[u % KP];
-            if (u + KP < 2 * DT) tr[u % KP] = tiles.tr_read(base, (u + KP) / DT, (u + KP) % DT);
+            if (u + KP < 2 * DT) tr[u % KP] = tiles.tr_read(0, (u + KP) / DT, (u + KP) % DT);
             acc[u % DT] = E::mma(a, dsb[u / DT], acc[u % DT]);
             __builtin_amdgcn_sched_barrier(0);
         }
+        tiles.move(st ? -Tiles::STAGE_B : Tiles::STAGE_B);
     }
 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last request: the LDS is about to be reused

@@ -210,10 +210,12 @@ static __device__ __forceinline__ void advance(BufferWords& b, int bytes) {
     b.w[2] = max(b.w[2] - bytes, 0);  // (no tensor of a head reaches 2^31 bytes)
 }
 
-// A wave's private tile of 32 rows of a 16-bit tensor, staged straight from global memory into LDS that no other wave
-// touches: no barriers, only the wave's own vmcnt waits.  The tile is unpadded; 16-byte chunk c of row r sits at
+// A wave's private tiles of 32 rows of a 16-bit tensor, staged straight from global memory into LDS that no other wave
+// touches: no barriers, only the wave's own vmcnt waits.  A tile is unpadded; 16-byte chunk c of row r sits at
 // c ^ swizzle(r), applied through the global address a lane fetches: row reads (16 rows at one chunk) and transposing
 // reads (4 rows x 4 chunks) both hit every bank once.
+// The lane's LDS addresses are kept, for a tile at `base`; another tile is a compile-time offset in the instruction.  (They
+// are opaque: the compiler would add them up again for every read.)
 template <int D>
 struct WaveTile {
     static constexpr int ROWS = 32, ROWB = D * 2, KS = D / 16, DT = D / 32;
@@ -222,40 +224,46 @@ struct WaveTile {
     static constexpr int RPI = 1024 / ROWB;       // rows per staging instruction (1 KiB)
     static constexpr int NI = ROWS / RPI;         // staging instructions per tile
     static constexpr int PERIOD = 16 / RPI;       // swizzle(r) has period 16: the rows of so many instructions
-    int src[PERIOD];        // byte offset within a tile for instructions 0 .. PERIOD - 1
-    int row_ofs[KS];        // row operands: lane (col, half) takes 8 elements from 16 ks + 8 half of row col
-    int tr_ofs[DT][2];      // transposed operands of rows 0..15; + 16 rows leaves the swizzle as it is
+    uint32_t base;          // LDS address of the first tile
+    int src[NI];            // byte offset within a tile for each staging instruction
+    uint32_t row_at[KS];    // row operands: lane (col, half) takes 8 elements from 16 ks + 8 half of row col
+    uint32_t tr_at[DT][2];  // transposed operands of rows 0..15; + 16 rows leaves the swizzle as it is
 
     static __device__ __forceinline__ int swizzle(int r) {
         return D == 64 ? (((r >> 1) & 1) << 2) | ((r >> 2) & 3) : ((r & 3) << 2) | ((r >> 2) & 3);
     }
-    __device__ __forceinline__ explicit WaveTile(int lane) {
+    __device__ __forceinline__ WaveTile(uint32_t at, int lane) : base(at) {
         const int col = lane & 31, half = lane >> 5, tr_row = (lane & 15) >> 2, quad = lane & 3, blk = (lane >> 4) & 1;
 #pragma unroll
-        for (int i = 0; i < PERIOD; ++i) {
-            const int r = i * RPI + lane / CPR;
-            src[i] = r * ROWB + ((lane % CPR) ^ swizzle(r)) * 16;
+        for (int i = 0; i < NI; ++i) {
+            const int r = (i % PERIOD) * RPI + lane / CPR;
+            src[i] = r * ROWB + ((lane % CPR) ^ swizzle(r)) * 16 + (i / PERIOD) * (PERIOD * 1024);
+            asm volatile("" : "+v"(src[i]));
         }
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) row_ofs[ks] = col * ROWB + (((2 * ks + half) ^ swizzle(col)) << 4);
+        for (int ks = 0; ks < KS; ++ks) {
+            row_at[ks] = at + col * ROWB + (((2 * ks + half) ^ swizzle(col)) << 4);
+            asm volatile("" : "+v"(row_at[ks]));
+        }
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int hi = 0; hi < 2; ++hi) {
                 const int r = 4 * half + tr_row + 8 * hi;
-                tr_ofs[dt][hi] = r * ROWB + (((4 * dt + 2 * blk + (quad >> 1)) ^ swizzle(r)) << 4) + 8 * (quad & 1);
+                tr_at[dt][hi] = at + r * ROWB + (((4 * dt + 2 * blk + (quad >> 1)) ^ swizzle(r)) << 4) + 8 * (quad & 1);
+                asm volatile("" : "+v"(tr_at[dt][hi]));
             }
     }
-    // Instruction i of NI that bring tile t of a head to `lds` (rows past the resource's end arrive as zeros).  To be issued
-    // one per MFMA step: in a burst, the wave sits about 100 cycles in the issue of each, 64 bytes per clock being what a
-    // CU's vector memory path moves.
-    __device__ __forceinline__ void request(const BufferWords& rsrc, uint32_t lds, int t, int i) const {
-        global_to_lds_16B(rsrc, lds + i * 1024, t * TILE_B + src[i % PERIOD] + (i / PERIOD) * (PERIOD * 1024));
+    // Instruction i of NI that bring the tile at the resource's start to base + offset (rows past its end arrive as zeros).
+    // To be issued one per MFMA step: in a burst, the wave sits about 100 cycles in the issue of each, 64 bytes per clock
+    // being what a CU's vector memory path moves.
+    __device__ __forceinline__ void request(const BufferWords& rsrc, uint32_t offset, int i) const {
+        global_to_lds_16B(rsrc, base + offset + i * 1024, src[i]);
     }
-    __device__ __forceinline__ i32x4 row_read(uint32_t base, int ks) const { return lds_load_16B(base + row_ofs[ks]); }
-    __device__ __forceinline__ i32x4 tr_read(uint32_t base, int slab, int dt) const {
-        const uint32_t a = base + slab * 16 * ROWB;
-        const i32x2 lo = lds_read_tr16(a + tr_ofs[dt][0]), hi = lds_read_tr16(a + tr_ofs[dt][1]);
+    __device__ __forceinline__ i32x4 row_read(int offset, int ks) const { return lds_load_16B(row_at[ks] + offset); }
+    __device__ __forceinline__ i32x4 tr_read(int offset, int slab, int dt) const {
+        const int a = offset + slab * 16 * ROWB;
+        const i32x2 lo = lds_read_tr16(tr_at[dt][0] + a), hi = lds_read_tr16(tr_at[dt][1] + a);
         return i32x4{lo[0], lo[1], hi[0], hi[1]};
     }
 };

@@ -104,14 +104,16 @@ struct FewForward {
         const int row = min(q0 + col, N - 1);    // rows past N compute a copy of row N-1, never stored
         const int limit = CAUSAL ? row : N - 1;  // last visible key
         const size_t head_off = (size_t)bh * N * D, kv_off = (size_t)(bh / kv_group) * N * D;
-        BufferWords k_rsrc = make_buffer_words(k + kv_off, (uint32_t)N * D * 2);
-        BufferWords v_rsrc = make_buffer_words(v + kv_off, (uint32_t)N * D * 2);
-        const Tile tile(lane);
-        const uint32_t kb = lds_address(lds) + wave * (2 * Tile::TILE_B), vb = kb + Tile::TILE_B;
+        const Tile tile(lds_address(lds) + wave * (2 * Tile::TILE_B), lane);
+        constexpr int kK = 0, kV = Tile::TILE_B;  // the two tiles
+        // the wave's next tiles (rows past N read as zero)
+        BufferWords k_rsrc = make_buffer_words(k + kv_off, (uint32_t)N * D * 2), v_rsrc = make_buffer_words(v + kv_off, (uint32_t)N * D * 2);
+        advance(k_rsrc, wave * Tile::TILE_B);
+        advance(v_rsrc, wave * Tile::TILE_B);
 
         // (a wave without a tile brings rows that nothing reads, or zeros)
 #pragma unroll
-        for (int i = 0; i < Tile::NI; ++i) tile.request(k_rsrc, kb, wave, i);
+        for (int i = 0; i < Tile::NI; ++i) tile.request(k_rsrc, kK, i);
         i32x4 qreg[KS];  // Q^T as the B operand
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
@@ -130,18 +132,19 @@ struct FewForward {
 
         for (int t = wave; t < n_tiles; t += NW) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // K has landed
+            advance(k_rsrc, NW * Tile::TILE_B);
             if (t + NW >= n_tiles) k_rsrc.w[2] = 0;  // past the wave's last tile: zeros that nothing reads
             i32x4 ring[KP], tr[KP];
 #pragma unroll
-            for (int u = 0; u < KP; ++u) ring[u] = tile.row_read(kb, u);
+            for (int u = 0; u < KP; ++u) ring[u] = tile.row_read(kK, u);
             __builtin_amdgcn_sched_barrier(0);
             // S^T = K Q^T
             f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int u = 0; u < KS; ++u) {
                 const i32x4 a = ring[u % KP];
-                if (u + KP < KS) ring[u % KP] = tile.row_read(kb, u + KP);
-                tile.request(v_rsrc, vb, t, u);
+                if (u + KP < KS) ring[u % KP] = tile.row_read(kK, u + KP);
+                tile.request(v_rsrc, kV, u);
                 s = E::mma(a, qreg[u], s);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -153,9 +156,9 @@ struct FewForward {
                     if (8 * (r >> 2) + (r & 3) > bound) s[r] = -INFINITY;
             }
             // the reference is the first tile's row maximum and rises when a tile's exceeds it by more than 2^kLazyLog2
-            float mx[4] = {s[0], s[1], s[2], s[3]};
+            float mx[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
-            for (int r = 4; r < 16; ++r) mx[r & 3] = fmaxf(mx[r & 3], s[r]);
+            for (int r = 0; r < 16; ++r) mx[r & 3] = fmaxf(mx[r & 3], s[r]);
             const float m_new = max_both_halves(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])));
             const bool raise = (m_new - m_run) * sc > kLazyLog2;
             if (__builtin_amdgcn_ballot_w64(raise) != 0) {
@@ -168,25 +171,26 @@ struct FewForward {
                     for (int r = 0; r < 16; ++r) acc[dt][r] *= corr;
             }
             const float mb = m_run == -INFINITY ? 0.f : m_run * sc;  // a row of scores of -inf so far: P = 0
-            float ps[4] = {0.f, 0.f, 0.f, 0.f};
+            float ps[4];
             i32x4 pb[2];
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 s[r] = fast_exp2(__builtin_fmaf(s[r], sc_v, -mb));
-                ps[r & 3] += s[r];
+                ps[r & 3] = r < 4 ? s[r] : ps[r & 3] + s[r];
                 if (r & 1) pb[r >> 3][(r >> 1) & 3] = E::pack2(s[r - 1], s[r]);
             }
             l_run += (ps[0] + ps[1]) + (ps[2] + ps[3]);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // V has landed
+            advance(v_rsrc, NW * Tile::TILE_B);
 #pragma unroll
-            for (int u = 0; u < KP; ++u) tr[u] = tile.tr_read(vb, u / DT, u % DT);
+            for (int u = 0; u < KP; ++u) tr[u] = tile.tr_read(kV, u / DT, u % DT);
             __builtin_amdgcn_sched_barrier(0);
             // O^T += V^T P^T
 #pragma unroll
             for (int u = 0; u < 2 * DT; ++u) {
                 const i32x4 a = tr[u % KP];
-                if (u + KP < 2 * DT) tr[u % KP] = tile.tr_read(vb, (u + KP) / DT, (u + KP) % DT);
-                tile.request(k_rsrc, kb, t + NW, u);
+                if (u + KP < 2 * DT) tr[u % KP] = tile.tr_read(kV, (u + KP) / DT, (u + KP) % DT);
+                tile.request(k_rsrc, kK, u);
                 acc[u % DT] = E::mma(a, pb[u / DT], acc[u % DT]);
                 __builtin_amdgcn_sched_barrier(0);
             }
