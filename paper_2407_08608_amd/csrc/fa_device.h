@@ -305,6 +305,91 @@ static __device__ __forceinline__ void store_rows_via_lds(const f32x16 (&acc)[DT
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// Forward launches divided by keys (FewForward, FewFp8Forward): the pieces that do not depend on the data type.
+//
+// The head and the 32-query tile of a workgroup.  The tiles of a head share an L2 whatever the number of heads (d = 128, 61
+// heads x 252, no mask: 13.5 us where they do not, 8.4 so).  split >= 0: grid (heads x R) x ceil(tiles / R), R = 2^split;
+// x / 8 of the ids that land on XCD x % 8 counts through the groups (head, residue of the tile number mod R) of that XCD,
+// y through the members of a group; causal: the longest rows first.  split < 0: one id per tile, head by head.
+struct KeySplitTile {
+    int head, tile, n_tiles;  // tile >= n_tiles: nothing to do
+};
+static __device__ __forceinline__ KeySplitTile key_split_tile(int N, int split) {
+    const int n_t = (N + 31) / 32;
+    if (split < 0) {
+        const int xcd = blockIdx.x & 7, per = gridDim.x >> 3, rest = gridDim.x & 7;  // the first `rest` XCDs get one more
+        const int id = xcd * per + min(xcd, rest) + ((int)blockIdx.x >> 3);
+        return {id / n_t, id % n_t, n_t};
+    }
+    const int group = ((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3);
+    return {group >> split, ((int)blockIdx.y << split) + (group & ((1 << split) - 1)), n_t};
+}
+
+// The end of such a workgroup of NT threads: the states (m: reference in log2 units, l: the lane half's row sum, acc: O^T
+// accumulator, lane column = query) of its first NW waves, which split the keys of 32 queries, become O and L.  With M the
+// largest m and f = 2^(m - M), O = sum f acc / sum f l and L = ln 2 (M + log2 sum f l - bias); fixed order.  Every wave of
+// the workgroup calls this; no LDS access or load to LDS may be pending but the caller's own wave's.
+template <int D, int NW>
+struct KeySplitMerge {
+    static constexpr int PSTR = D + 4;  // row stride of the partial outputs (floats)
+    static constexpr int kPartial = NW * 32 * PSTR * 4, kLds = kPartial + NW * 32 * 8;
+    template <typename Tag, int NT>
+    static __device__ __forceinline__ void run(const f32x16 (&acc)[D / 32], float m, float l_half, float bias, char* lds, int wave,
+                                               int lane, uint16_t* o_head, float* lse_head, int q0, int N) {
+        using E = Elem<Tag>;
+        constexpr int CPR = D / 8;
+        const int col = lane & 31, half = lane >> 5;
+        __syncthreads();
+        float* part = reinterpret_cast<float*>(lds);              // [wave][query][PSTR]
+        float* state = reinterpret_cast<float*>(lds + kPartial);  // [wave][query][m, l]
+        const float l = sum_both_halves(l_half);
+        if (wave < NW) {
+            if (half == 0) {
+                state[(wave * 32 + col) * 2] = m;
+                state[(wave * 32 + col) * 2 + 1] = l;
+            }
+#pragma unroll
+            for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const f32x4 w = {acc[dt][4 * g], acc[dt][4 * g + 1], acc[dt][4 * g + 2], acc[dt][4 * g + 3]};
+                    *reinterpret_cast<f32x4*>(part + (wave * 32 + col) * PSTR + dt * 32 + 8 * g + 4 * half) = w;
+                }
+        }
+        __syncthreads();
+        for (int c = threadIdx.x; c < 32 * CPR; c += NT) {
+            const int r = c / CPR, cc = (c % CPR) * 8;
+            float m_all = -INFINITY, l_all = 0.f, f[NW];
+#pragma unroll
+            for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, state[(w * 32 + r) * 2]);
+            const float m_ref = m_all == -INFINITY ? 0.f : m_all;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                f[w] = fast_exp2(state[(w * 32 + r) * 2] - m_ref);
+                l_all += f[w] * state[(w * 32 + r) * 2 + 1];
+            }
+            float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const f32x4 y = *reinterpret_cast<const f32x4*>(part + (w * 32 + r) * PSTR + cc + 4 * h);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[4 * h + e] = __builtin_fmaf(f[w], y[e], x[4 * h + e]);
+                }
+            const float inv = 1.0f / l_all;
+            if (q0 + r < N) {
+                i32x4 y;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] = E::pack2(x[2 * e] * inv, x[2 * e + 1] * inv);
+                *reinterpret_cast<i32x4*>(o_head + (size_t)(q0 + r) * D + cc) = y;
+                if (cc == 0) lse_head[q0 + r] = (m_all + log2f(l_all) - bias) * kLn2;
+            }
+        }
+    }
+};
+
 // The chip deals consecutive workgroup ids round-robin to its 8 XCDs, each with a private
 // L2.  Remap a linear id so that ids landing on one XCD cover a contiguous range of work
 // items (all query tiles of a head share that head's K and V in one L2).

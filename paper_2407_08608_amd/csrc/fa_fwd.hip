@@ -68,11 +68,9 @@ struct TileCopy {
 template <int D, int NW>
 struct FewForward {
     using Tile = WaveTile<D>;
-    static constexpr int KS = D / 16, DT = D / 32, CPR = D / 8, KP = 4;
-    static constexpr int PSTR = D + 4;  // row stride of the partial outputs (floats)
-    static constexpr int kPartial = NW * 32 * PSTR * 4;
+    static constexpr int KS = D / 16, DT = D / 32, KP = 4;
     static constexpr int kStages = NW * 2 * Tile::TILE_B;
-    static constexpr int kLds = (kPartial + NW * 32 * 8 > kStages ? kPartial + NW * 32 * 8 : kStages);
+    static constexpr int kLds = KeySplitMerge<D, NW>::kLds > kStages ? KeySplitMerge<D, NW>::kLds : kStages;
 
     template <typename Tag, bool CAUSAL>
     static __device__ __forceinline__ void run(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
@@ -82,23 +80,9 @@ struct FewForward {
         const int tid = threadIdx.x;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
         const int col = lane & 31, half = lane >> 5;
-        // The tiles of a head share an L2 whatever the number of heads (61 heads x 252, d = 128, no mask: 13.5 us where they do
-        // not, 8.4 so).  split >= 0: grid (heads x R) x ceil(tiles / R), R = 2^split; x / 8 of the ids that land on XCD x % 8 counts
-        // through the groups (head, residue of the tile number mod R) of that XCD, y through the members of a group; causal:
-        // the longest rows first.  split < 0: one id per tile, head by head.
-        const int n_t = (N + 31) / 32;
-        int bh, tile_no;
-        if (split < 0) {
-            const int xcd = blockIdx.x & 7, per = gridDim.x >> 3, rest = gridDim.x & 7;  // the first `rest` XCDs get one more
-            const int id = xcd * per + min(xcd, rest) + ((int)blockIdx.x >> 3);
-            bh = id / n_t;
-            tile_no = id - bh * n_t;
-        } else {
-            const int group = ((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3);
-            bh = group >> split;
-            tile_no = ((int)blockIdx.y << split) + (group & ((1 << split) - 1));
-            if (tile_no >= n_t) return;
-        }
+        const KeySplitTile item = key_split_tile(N, split);
+        if (item.tile >= item.n_tiles) return;
+        const int bh = item.head, n_t = item.n_tiles, tile_no = item.tile;
         const int qt = CAUSAL ? n_t - 1 - tile_no : tile_no;
         const int q0 = qt * 32, n_tiles = CAUSAL ? qt + 1 : n_t;
         const int row = min(q0 + col, N - 1);    // rows past N compute a copy of row N-1, never stored
@@ -166,9 +150,12 @@ struct FewForward {
                 m_run = raise ? m_new : m_run;
                 l_run *= corr;
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt)
+                for (int dt = 0; dt < DT; ++dt) {
+                    if constexpr (D == 256) asm volatile("" : "+a"(acc[dt]));  // (copied out of the accumulation half here, not in every tile)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) acc[dt][r] *= corr;
+                    if constexpr (D == 256) asm volatile("" : "+a"(acc[dt]));
+                }
             }
             const float mb = m_run == -INFINITY ? 0.f : m_run * sc;  // a row of scores of -inf so far: P = 0
             float ps[4];
@@ -197,52 +184,7 @@ struct FewForward {
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last requests: the LDS is about to be reused
 
-        // ---- merge
-        __syncthreads();
-        float* part = reinterpret_cast<float*>(lds);                      // [wave][query][PSTR]
-        float* state = reinterpret_cast<float*>(lds + kPartial);          // [wave][query][m, l]
-        const float l = sum_both_halves(l_run);
-        if (half == 0) {
-            state[(wave * 32 + col) * 2] = m_run;
-            state[(wave * 32 + col) * 2 + 1] = l;
-        }
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const f32x4 w = {acc[dt][4 * g], acc[dt][4 * g + 1], acc[dt][4 * g + 2], acc[dt][4 * g + 3]};
-                *reinterpret_cast<f32x4*>(part + (wave * 32 + col) * PSTR + dt * 32 + 8 * g + 4 * half) = w;
-            }
-        __syncthreads();
-        for (int c = tid; c < 32 * CPR; c += NW * 64) {
-            const int r = c / CPR, cc = (c % CPR) * 8;
-            float m_all = -INFINITY, l_all = 0.f, f[NW];
-#pragma unroll
-            for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, state[(w * 32 + r) * 2]);
-            const float m_ref = m_all == -INFINITY ? 0.f : m_all;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                f[w] = fast_exp2((state[(w * 32 + r) * 2] - m_ref) * sc);
-                l_all += f[w] * state[(w * 32 + r) * 2 + 1];
-            }
-            float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int w = 0; w < NW; ++w)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const f32x4 y = *reinterpret_cast<const f32x4*>(part + (w * 32 + r) * PSTR + cc + 4 * h);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) x[4 * h + e] = __builtin_fmaf(f[w], y[e], x[4 * h + e]);
-                }
-            const float inv = 1.0f / l_all;
-            if (q0 + r < N) {
-                i32x4 y;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) y[e] = E::pack2(x[2 * e] * inv, x[2 * e + 1] * inv);
-                *reinterpret_cast<i32x4*>(o + head_off + (size_t)(q0 + r) * D + cc) = y;
-                if (cc == 0) lse[(size_t)bh * N + q0 + r] = (m_all * sc + log2f(l_all)) * kLn2;
-            }
-        }
+        KeySplitMerge<D, NW>::template run<Tag, NW * 64>(acc, m_run * sc, l_run, 0.f, lds, wave, lane, o + head_off, lse + (size_t)bh * N, q0, N);
     }
 };
 

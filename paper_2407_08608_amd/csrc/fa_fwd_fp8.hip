@@ -66,6 +66,209 @@ static __device__ __forceinline__ int key_of_row(int i) {
     return 16 * (g >> 1) + 8 * hb + 4 * (g & 1) + r;
 }
 
+// Swizzles of unpadded e4m3 tiles: the 16-byte chunk c of tile row r sits at chunk c ^ k(r) (K, read by rows) or c ^ v(r) (V,
+// read transposed) of its LDS row.  256-byte rows fill the 64 banks once: sixteen rows need sixteen different chunk positions
+// (K row reads), eight rows x two chunks likewise (V transposing reads).  Two 128-byte rows (four 64-byte rows) share the
+// banks, so pairs (fours) of rows share a swizzle value.
+template <int D>
+struct Fp8Swizzle {
+    static __device__ __forceinline__ int k(int r) { return D == 256 ? (r & 15) : D == 128 ? ((r >> 1) & 7) : ((r >> 2) & 3); }
+    static __device__ __forceinline__ int v(int r) { return D == 256 ? ((r & 7) << 1) : D == 128 ? (((r >> 1) & 3) << 1) : (((r >> 2) & 1) << 1); }
+};
+
+// ---------------------------------------------------------------------------------------
+// The FP8 forward where its query tiles would leave most of the chip idle (as FewForward in fa_fwd.hip): a workgroup of NW
+// waves owns 32 queries, and NS of the waves split the keys, tiles of 64 dealt in turn, each staged by the wave that works it
+// (V beside the scores, K of its next tile beside the products: no barrier), each with a softmax state and an accumulator for
+// all columns, merged through the LDS at the end.  The arithmetic of a tile is that of the kernels below.
+// (At d = 256 the tiles of eight waves do not fit the LDS: four of them split, the others wait for the merge.)
+template <int D, int NW, int NS>
+struct FewFp8Forward {
+    static constexpr int BK = 64, ROWB = D, TILE = BK * ROWB;  // keys, row bytes and bytes of a tile
+    static constexpr int KS = D / 64, DT = D / 32;
+    static constexpr int CPR = ROWB / 16, RPI = 1024 / ROWB, NI = TILE / 1024, PERIOD = 16 / RPI;  // (16 rows: both swizzles' period)
+    static constexpr int kStages = NS * 2 * TILE;
+    static constexpr int kLds = KeySplitMerge<D, NS>::kLds > kStages ? KeySplitMerge<D, NS>::kLds : kStages;
+
+    template <bool CAUSAL, bool SCALED>
+    static __device__ __forceinline__ void run(const uint8_t* __restrict__ q, const uint8_t* __restrict__ k, const uint8_t* __restrict__ v,
+                                               const float* __restrict__ q_scale, const float* __restrict__ k_scale,
+                                               const float* __restrict__ v_scale, uint16_t* __restrict__ o, float* __restrict__ lse,
+                                               int N, int split, int n_sblocks, int kv_group, float scale, char* lds) {
+        using Swizzle = Fp8Swizzle<D>;
+        const int tid = threadIdx.x;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+        const int col = lane & 31, half = lane >> 5;
+        const KeySplitTile item = key_split_tile(N, split);
+        if (item.tile >= item.n_tiles) return;
+        const int bh = item.head, kv_bh = bh / kv_group;
+        const int qt = CAUSAL ? item.n_tiles - 1 - item.tile : item.tile;
+        const int q0 = qt * 32, n_tiles = CAUSAL ? q0 / BK + 1 : (N + BK - 1) / BK;
+        const int row = min(q0 + col, N - 1);    // rows past N compute a copy of row N-1, never stored
+        const int limit = CAUSAL ? row : N - 1;  // last visible key
+
+        f32x16 oacc[DT];
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
+        // m: running (lazily raised) maximum, in log2 units, of the real scores plus log2 of their V block's scale
+        float m_run = -INFINITY, l_run = 0.f;
+
+        if (wave < NS) {
+            const uint32_t kb = lds_address(lds) + wave * (2 * TILE), vb = kb + TILE;
+            // the wave's next tiles (rows past N read as zero)
+            BufferWords k_rsrc = make_buffer_words(k + (size_t)kv_bh * N * D, (uint32_t)N * D);
+            BufferWords v_rsrc = make_buffer_words(v + (size_t)kv_bh * N * D, (uint32_t)N * D);
+            advance(k_rsrc, wave * TILE);
+            advance(v_rsrc, wave * TILE);
+            int k_src[PERIOD], v_src[PERIOD];  // byte offsets within a tile of the first staging instructions
+#pragma unroll
+            for (int i = 0; i < PERIOD; ++i) {
+                const int r = i * RPI + lane / CPR, c = lane % CPR;
+                k_src[i] = r * ROWB + ((c ^ Swizzle::k(r)) << 4);
+                v_src[i] = r * ROWB + ((c ^ Swizzle::v(r)) << 4);
+            }
+            auto request = [&](const BufferWords& rsrc, uint32_t to, const int (&src)[PERIOD], int i) __attribute__((always_inline)) {
+                global_to_lds_16B(rsrc, to + i * 1024, src[i % PERIOD] + (i / PERIOD) * (PERIOD * 1024));
+            };
+            // (a wave without a tile brings rows that nothing reads, or zeros)
+#pragma unroll
+            for (int i = 0; i < NI; ++i) request(k_rsrc, kb, k_src, i);
+            i32x8 qreg[KS];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const uint8_t* p = q + ((size_t)bh * N + row) * D + ks * 64 + half * 32;
+                const i32x4 lo = *reinterpret_cast<const i32x4*>(p), hi = *reinterpret_cast<const i32x4*>(p + 16);
+                qreg[ks] = i32x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            }
+            float sc_q = scale * kLog2e;
+            if constexpr (SCALED) sc_q *= q_scale[(size_t)bh * n_sblocks + q0 / 128];
+            // operand addresses: K row key_of_row(col), V rows 8 half + (lane / 2) % 8 (+ 16, 32, 48: the swizzle stays)
+            const int krow = key_of_row(col), tr_row = (lane & 15) >> 1, blk = (lane >> 4) & 1;
+            uint32_t k_at[KS][2], v_at[DT];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    k_at[ks][j] = kb + krow * ROWB + (((4 * ks + 2 * half + j) ^ Swizzle::k(krow)) << 4);
+                    asm volatile("" : "+v"(k_at[ks][j]));
+                }
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                v_at[dt] = vb + (8 * half + tr_row) * ROWB + (((2 * dt + blk) ^ Swizzle::v(tr_row)) << 4) + 8 * (lane & 1);
+                asm volatile("" : "+v"(v_at[dt]));
+            }
+            auto k_read = [&](int u) __attribute__((always_inline)) {  // u = (ks, 32-key half of the tile)
+                const i32x4 lo = lds_load_16B(k_at[u / 2][0] + (u % 2) * 32 * ROWB), hi = lds_load_16B(k_at[u / 2][1] + (u % 2) * 32 * ROWB);
+                return i32x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            };
+            auto v_read = [&](int dt) __attribute__((always_inline)) {
+                i32x8 a;
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const i32x2 w = lds_read_tr8(v_at[dt] + 16 * x * ROWB);
+                    a[2 * x] = w[0];
+                    a[2 * x + 1] = w[1];
+                }
+                return a;
+            };
+            static_assert(NI == 2 * 2 * KS && NI == 2 * DT, "two staging instructions per MFMA");
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qreg[ks]));
+
+            for (int t = wave; t < n_tiles; t += NS) {
+                float sk = 1.0f, sv = 1.0f;
+                if constexpr (SCALED) {
+                    sk = k_scale[(size_t)kv_bh * n_sblocks + t / 2];
+                    sv = v_scale[(size_t)kv_bh * n_sblocks + t / 2];
+                }
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // K has landed, the last V has been read
+                advance(k_rsrc, NS * TILE);
+                if (t + NS >= n_tiles) k_rsrc.w[2] = 0;  // past the wave's last tile: zeros that nothing reads
+                // S^T = K Q^T (rows permuted by key_of_row)
+                f32x16 s[2];
+                const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                i32x8 next = k_read(0);
+#pragma unroll
+                for (int u = 0; u < 2 * KS; ++u) {
+                    const i32x8 a = next;
+                    if (u + 1 < 2 * KS) next = k_read(u + 1);
+                    request(v_rsrc, vb, v_src, 2 * u);
+                    request(v_rsrc, vb, v_src, 2 * u + 1);
+                    s[u % 2] = mma_fp8(a, qreg[u / 2], u < 2 ? zero : s[u % 2]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (t * BK + BK > N || (CAUSAL && t * BK + BK - 1 > q0)) {
+                    int bound = limit - t * BK - 8 * half;  // register r of a 32-key half is key 16 (r / 8) + 8 half + r % 8
+                    asm volatile("" : "+v"(bound));
+#pragma unroll
+                    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            if (kt * 32 + 16 * (r >> 3) + (r & 7) > bound) s[kt][r] = -INFINITY;
+                }
+                // reference maximum, P~ as e4m3, row sum: see fa_fwd_fp8_kernel
+                float mxp[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) mxp[r & 3] = fmaxf(mxp[r & 3], s[kt][r]);
+                const float sc = sc_q * sk;
+                float lsv = 0.f;
+                if constexpr (SCALED) lsv = __builtin_amdgcn_logf(sv);  // log2
+                const float mx = max_both_halves(fmaxf(fmaxf(mxp[0], mxp[1]), fmaxf(mxp[2], mxp[3]))) * sc + lsv;
+                const bool raise = mx - m_run > kLazyLog2;
+                if (__builtin_amdgcn_ballot_w64(raise) != 0) {
+                    const float f = raise ? fast_exp2(m_run - mx) : 1.0f;
+                    m_run = raise ? mx : m_run;
+                    l_run *= f;
+#pragma unroll
+                    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) oacc[dt][r] *= f;
+                }
+                const float mb = m_run == -INFINITY ? 0.f : m_run - kPBias - lsv;  // a row of scores of -inf so far: P = 0
+                float sc_v = sc;  // a vector-register copy: an FMA with a scalar-register operand issues at a lower rate
+                asm volatile("" : "+v"(sc_v));
+                float ps[4];
+                i32x8 pb;
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt) {
+                    float p[16];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        p[r] = fast_exp2(__builtin_fmaf(s[kt][r], sc_v, -mb));
+                        ps[r & 3] = kt == 0 && r < 4 ? p[r] : ps[r & 3] + p[r];
+                    }
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) pb[4 * kt + w] = pack_e4m3(p[4 * w], p[4 * w + 1], p[4 * w + 2], p[4 * w + 3]);
+                }
+                float psum = (ps[0] + ps[1]) + (ps[2] + ps[3]);
+                if constexpr (SCALED) psum *= __builtin_amdgcn_rcpf(sv);
+                l_run += psum;
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // V has landed, K has been read
+                advance(v_rsrc, NS * TILE);
+                // O^T += V^T P~^T
+                next = v_read(0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) {
+                    const i32x8 a = next;
+                    if (dt + 1 < DT) next = v_read(dt + 1);
+                    request(k_rsrc, kb, k_src, 2 * dt);
+                    request(k_rsrc, kb, k_src, 2 * dt + 1);
+                    oacc[dt] = mma_fp8(a, pb, oacc[dt]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last requests: the LDS is about to be reused
+        }
+        KeySplitMerge<D, NS>::template run<bf16_tag, NW * 64>(oacc, m_run, l_run, kPBias, lds, wave, lane, o + (size_t)bh * N * D,
+                                                              lse + (size_t)bh * N, q0, N);
+    }
+};
+
 template <int D, int BC, int NW, bool CAUSAL, bool SCALED>
 __global__ void __launch_bounds__(NW * 64, D <= 128 ? 2 : 1)
 fa_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ k, const uint8_t* __restrict__ v,
@@ -86,9 +289,21 @@ fa_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ k, 
     static_assert(BC % 64 == 0 && 128 % BC == 0, "key block must tile the 128-row quantisation block");
     static_assert((BC * CPR) % NT == 0, "tile must divide evenly over the workgroup");
 
-    __shared__ __attribute__((aligned(16))) uint8_t lds_k[2][BC * KSTR];
-    __shared__ __attribute__((aligned(16))) uint8_t lds_v[2][BC * VSTR];
-    __shared__ __attribute__((aligned(128))) char lds_o[NW * 4096];  // output transposition, 4 KiB per wave
+    // K blocks, V blocks, output transposition (4 KiB per wave)
+    constexpr int kKLds = 2 * BC * KSTR, kVLds = 2 * BC * VSTR, kTileLds = kKLds + kVLds + NW * 4096;
+    static_assert(kKLds % 128 == 0 && kVLds % 128 == 0, "aligned parts");
+    constexpr bool kHasFew = NW == 4;  // (the eight-wave instantiations are measurement builds')
+    constexpr int kFewLds = kHasFew ? FewFp8Forward<D, 4, 4>::kLds : 0;
+    __shared__ __attribute__((aligned(1024))) char lds[kTileLds > kFewLds ? kTileLds : kFewLds];
+    if constexpr (kHasFew) {
+        if (paired == kFewForward) {
+            FewFp8Forward<D, 4, 4>::template run<CAUSAL, SCALED>(q, k, v, q_scale, k_scale, v_scale, o, lse, N, total_wg, n_sblocks, kv_group, scale, lds);
+            return;
+        }
+    }
+    uint8_t(*lds_k)[BC * KSTR] = reinterpret_cast<uint8_t(*)[BC * KSTR]>(lds);
+    uint8_t(*lds_v)[BC * VSTR] = reinterpret_cast<uint8_t(*)[BC * VSTR]>(lds + kKLds);
+    char* lds_o = lds + kKLds + kVLds;
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
@@ -354,7 +569,12 @@ fa_fwd_fp8_async_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict
 
     // K stages, then V stages.  The output transposition at the end of a tile reuses the stages (every read
     // of them is behind a barrier by then and no load is in flight).
-    __shared__ __attribute__((aligned(1024))) char lds_kv[2 * NS * TILE];
+    using Few = FewFp8Forward<D, NW, D == 256 ? 4 : 8>;
+    __shared__ __attribute__((aligned(1024))) char lds_kv[2 * NS * TILE > Few::kLds ? 2 * NS * TILE : Few::kLds];
+    if (paired == kFewForward) {
+        Few::template run<CAUSAL, SCALED>(q, k, v, q_scale, k_scale, v_scale, o, lse, N, total_wg, n_sblocks, kv_group, scale, lds_kv);
+        return;
+    }
     char* const lds_k = lds_kv;
     char* const lds_v = lds_kv + NS * TILE;
     static_assert(2 * NS * TILE >= NW * 4096, "output patches must fit the stages");
@@ -372,12 +592,8 @@ fa_fwd_fp8_async_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict
     const BufferWords k_rsrc = make_buffer_words(k + (size_t)kv_bh * N * D, (uint32_t)N * D);
     const BufferWords v_rsrc = make_buffer_words(v + (size_t)kv_bh * N * D, (uint32_t)N * D);
 
-    // The swizzles: the 16-byte chunk c of tile row r sits at chunk c ^ k_swz(r) (K) or c ^ v_swz(r) (V) of
-    // its LDS row.  256-byte rows fill the 64 banks once: sixteen rows need sixteen different chunk
-    // positions (K row reads), eight rows x two chunks likewise (V transposing reads).  Two 128-byte rows
-    // (four 64-byte rows) share the banks, so pairs (fours) of rows share a swizzle value.
-    auto k_swz = [](int r) { return D == 256 ? (r & 15) : D == 128 ? ((r >> 1) & 7) : ((r >> 2) & 3); };
-    auto v_swz = [](int r) { return D == 256 ? ((r & 7) << 1) : D == 128 ? (((r >> 1) & 3) << 1) : (((r >> 2) & 1) << 1); };
+    auto k_swz = [](int r) { return Fp8Swizzle<D>::k(r); };
+    auto v_swz = [](int r) { return Fp8Swizzle<D>::v(r); };
     // ---- staging: a load instruction fills 1 KiB = RPG rows; wave w loads groups w, w + 8, ... of a tile;
     // lane L fills chunk L % CPR of row L / CPR of its group with the global chunk the swizzle maps there
     constexpr int CPR = ROWB / 16, RPG = 1024 / ROWB;
@@ -582,8 +798,9 @@ static int launch_fp8(const void* q8, const void* k8, const void* v8, const floa
     int n_sblocks = (N + 127) / 128;
     constexpr PairRule kPairs = NW == 4 ? (D == 64 ? PairRule{3, 15.f / 16, kAny, 1.f, 2} : PairRule{2, 7.f / 8, 320, 0.75f, kAny})
                                         : (D == 64 ? PairRule{2, 1.f, kAny, 1.f, 0} : PairRule{1, 0.9f, kAny, 1.f, kAny});
-    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, kPairs);
-    long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
+    const bool few = NW == 4 && few_forward_fp8((long)B * H, N, D, causal);
+    const int paired = few ? kFewForward : causal && pair_causal_tiles((long)B * H, n_qtiles, kPairs);
+    long total = few ? few_split((long)B * H, N) : (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
     const dim3 grid = forward_grid((long)B * H, N, n_qtiles, total, causal, paired), block(NW * 64);
     auto qp = static_cast<const uint8_t*>(q8);
@@ -614,8 +831,10 @@ static int launch_fp8_async(const void* q8, const void* k8, const void* v8, cons
     // 31.0 at a share of 0.75, 448 x 300 59.3 / 63.9 and 112 x 1024 53.9 / 54.7 at 0.88, but 384 x 450 73.9 / 63.9 at 0.75)
     const bool first_round = (long)B * H * ((n_qtiles + 1) / 2) <= 256;
     const float share = D < 256 || n_qtiles > 4 ? 0.9f : n_qtiles > 2 ? (first_round ? 0.875f : 0.9f) : (first_round ? 0.75f : 0.875f);
-    const int paired = causal && pair_causal_tiles((long)B * H, n_qtiles, D == 64 ? PairRule{2, 1.f, kAny, 1.f, 0} : PairRule{1, share, kAny, 1.f, kAny});
-    long total = (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
+    const bool few = few_forward_fp8((long)B * H, N, D, causal);
+    const int paired = few ? kFewForward
+                           : causal && pair_causal_tiles((long)B * H, n_qtiles, D == 64 ? PairRule{2, 1.f, kAny, 1.f, 0} : PairRule{1, share, kAny, 1.f, kAny});
+    long total = few ? few_split((long)B * H, N) : (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
     const dim3 grid = forward_grid((long)B * H, N, n_qtiles, total, causal, paired), block(512);
     auto qp = static_cast<const uint8_t*>(q8);

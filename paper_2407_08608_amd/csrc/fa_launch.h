@@ -57,7 +57,7 @@ inline bool pair_causal_tiles(long heads, int n_qtiles, const PairRule& rule) {
     return n_qtiles <= rule.most_tiles && work >= (heads >= rule.many_heads ? rule.many_share : rule.share);
 }
 
-// The launchers' `paired` argument for launches divided by FewForward (fa_fwd.hip); the total number of work items that the
+// The launchers' `paired` argument for launches divided by FewForward (fa_fwd.hip) or FewFp8Forward (fa_fwd_fp8.hip); the total number of work items that the
 // kernels take otherwise is few_split() then: log2 of the groups into which a head's tiles go so that the XCDs get the same
 // number of groups each, or -1: no groups, where they would come out too uneven (few tiles; all are on the chip at once).
 constexpr int kFewForward = 2;
@@ -65,6 +65,22 @@ inline int few_split(long heads, int N) {
     if (heads % 8 == 0) return 0;
     return N <= 32 * 32 ? -1 : heads % 4 == 0 ? 1 : heads % 2 == 0 ? 2 : 3;
 }
+
+// How often workgroups of 32 queries fill the CUs, by what the rules below go, and the tiles of 32 rows of a head.
+struct KeySplitFill {
+    long tiles;
+    float fillings;
+    KeySplitFill(long heads, int N) : tiles((N + 31) / 32) {
+        const int split = few_split(heads, N);
+        const long round_up = (1L << (split > 0 ? split : 0)) - 1;
+        fillings = (float)(heads * ((tiles + round_up) & ~round_up)) / 256.f;
+        if (split < 0 && fillings > 1.f) fillings *= 1.15f;  // an XCD's share of the tiles cuts through heads
+    }
+    bool at(float base, float step, float most) const {  // at most that many: more with a longer chain
+        const float x = base + (float)tiles / step;
+        return fillings <= (x < most ? x : most);
+    }
+};
 
 // Whether a 16-bit forward is divided so: workgroups of 32 queries whose waves split the keys, against 128 or 256 queries that
 // walk all of them.  What counts is how often those workgroups fill the CUs (`fillings`) and how long the chain of 32-key
@@ -76,22 +92,40 @@ inline int few_split(long heads, int N) {
 //   d = 128  no mask: 16 x 100 6.5 / 5.5, 16 x 512 14.3 / 8.2, 32 x 512 15.0 / 12.2, 2 x 8192 167 / 95;
 //            lost: 96 x 100 6.9 / 7.4, 48 x 333 12.5 / 13.1, 24 x 700 21 / 24, 16 x 2048 50 / 59
 //            causal:  16 x 1000 25 / 13.6, 16 x 2048 50 / 40, 4 x 4096 90 / 31;  lost: 48 x 512 15.8 / 16.0, 28 x 1500 36 / 43
-//   d = 256  no mask: 16 x 333 17.5 / 12.3, 4 x 2048 57 / 35;  lost: 28 x 333 17.9 / 21.5, 8 x 2048 62 / 68
-//            causal:  16 x 1000 34 / 28, 2 x 8192 204 / 129;  lost: 32 x 333 18.5 / 19.3, 10 x 2048 61 / 61
+//   d = 256  no mask: 16 x 333 17.5 / 12.0, 4 x 2048 57 / 32;  lost: 28 x 333 17.9 / 21.5, 8 x 2048 62 / 62
+//            causal:  16 x 1000 34 / 27, 2 x 8192 204 / 117;  lost: 32 x 333 18.5 / 19.5, 12 x 2048 61 / 61
 // Drawn on 2900 shapes (heads 1 to 384, N from 24 to 16384): up to 4.6 times as fast.  Over 1500 others in the last third
 // before the rule's edge, odd head counts and shared heads among them, 0.76 of the time on average, 1.02 at worst.
 inline bool few_forward(long heads, int N, int d, int causal) {
-    const long tiles = (N + 31) / 32, round_up = (1L << (few_split(heads, N) > 0 ? few_split(heads, N) : 0)) - 1;
-    float fillings = (float)(heads * ((tiles + round_up) & ~round_up)) / 256.f;
-    if (tiles < 3) return false;
-    if (fillings <= 1.f) return true;
-    if (few_split(heads, N) < 0) fillings *= 1.15f;  // an XCD's share of the tiles cuts through heads
-    auto at = [&](float base, float step, float most) { const float x = base + (float)tiles / step; return fillings <= (x < most ? x : most); };
+    const KeySplitFill fill(heads, N);
+    if (fill.tiles < 3) return false;
+    if (fill.fillings <= 1.f) return true;
     switch (d) {
-        case 64: return causal ? (tiles > 6 ? at(1.5f, 9, tiles < 90 ? 7.25f : 9.5f) : fillings <= 1.75f)
-                               : (tiles > 6 ? at(1.75f, 16, 4.9f) : fillings <= 1.25f);
-        case 128: return tiles > 6 && (causal ? at(1.5f, 18, 4.75f) : fillings <= (tiles < 40 ? 2.f : 3.f));
-        default: return causal && at(0.8f, 48, 2);
+        case 64: return causal ? (fill.tiles > 6 ? fill.at(1.5f, 9, fill.tiles < 90 ? 7.25f : 9.5f) : fill.fillings <= 1.75f)
+                               : (fill.tiles > 6 ? fill.at(1.75f, 16, 4.9f) : fill.fillings <= 1.25f);
+        case 128: return fill.tiles > 6 && (causal ? fill.at(1.5f, 18, 4.75f) : fill.fillings <= (fill.tiles < 40 ? 2.f : 3.f));
+        default: return causal && fill.at(0.7f, 28, 2.9f);
+    }
+}
+
+// The same for the FP8 forward (FewFp8Forward).  us, large / these, heads x N:
+//   d = 64   no mask: 16 x 333 7.9 / 5.6, 4 x 4096 71 / 27, 1 x 16384 270 / 87;  lost: 128 x 256 8.4 / 8.8, 48 x 1000 21 / 22
+//            causal:  16 x 1000 14 / 8.1, 8 x 4096 68 / 33;  lost: 96 x 512 10.8 / 11.0
+//   d = 128  no mask: 16 x 512 11.2 / 7.2, 2 x 8192 168 / 71;  N <= 128: level;  lost: 48 x 333 9.5 / 11.1, 16 x 2048 46 / 54 (causal 45 / 34)
+//            causal:  16 x 1000 18 / 9.7, 8 x 4096 84 / 48;  lost: 48 x 512 11.8 / 12.3
+//   d = 256  no mask: 16 x 333 14.0 / 7.1, 4 x 2048 64 / 19;  lost: 48 x 333 15.0 / 16.3, 20 x 2048 69 / 79
+//            causal:  16 x 1000 33 / 17, 4 x 8192 206 / 107;  lost: 32 x 1500 53 / 57
+// Drawn on 2900 shapes.  The error against 64 bits is smaller so (each part of the keys gets its own reference): d = 128,
+// 4 heads x 1600 with outliers 1.01e-2 / 0.85e-2.
+inline bool few_forward_fp8(long heads, int N, int d, int causal) {
+    const KeySplitFill fill(heads, N);
+    if (fill.tiles < (d == 128 ? 5 : 3)) return false;
+    if (fill.fillings <= 1.f) return true;
+    if (fill.tiles <= (d == 64 ? 4 : 6)) return false;
+    switch (d) {
+        case 64: return causal ? fill.at(1.25f, 5.5f, 11.5f) : fill.at(1.4f, 12, 6);
+        case 128: return causal ? fill.at(1.4f, 20, 7) : fill.fillings <= (fill.tiles < 32 ? 2.f : fill.tiles < 56 ? 3.f : 4.f);
+        default: return causal ? fill.at(1.5f, 20, 7) : fill.fillings <= (fill.tiles < 20 ? 2.f : fill.tiles < 32 ? 2.5f : fill.tiles < 64 ? 3.f : 4.f);
     }
 }
 

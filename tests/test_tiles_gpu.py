@@ -337,9 +337,9 @@ def test_forward_with_the_keys_split_over_the_waves(d, H, H_kv, N, causal, dtype
     assert max_abs(f64(o), o_ref) <= 2e-2 and rmse(f64(o), o_ref) <= 3e-3 and max_abs(f64(lse), l_ref) <= 2e-3
 
 
-@pytest.mark.parametrize("d,causal,N,most", [(64, False, 100, 80), (64, True, 100, 112), (64, False, 1024, 30), (128, False, 100, 64),
-                                             (128, False, 256, 64), (128, True, 512, 38), (128, False, 2048, 12), (256, False, 300, 25),
-                                             (256, True, 1024, 11)])
+@pytest.mark.parametrize("d,causal,N,most", [(64, False, 100, 69), (64, False, 100, 80), (64, True, 100, 97), (64, False, 1024, 26),
+                                             (128, False, 100, 64), (128, False, 256, 56), (128, True, 512, 33), (128, False, 2048, 12),
+                                             (256, False, 300, 25), (256, True, 1024, 12)])
 def test_forward_on_both_sides_of_the_key_split_rule(d, causal, N, most):
     # the most heads (a multiple of 8 or not) that are divided so, and the next ones that are not: the same rows
     # either way, against the oracle and, as P~ is rounded relative to different references, to one another
@@ -377,3 +377,32 @@ def test_forward_key_splits_with_scores_of_minus_infinity(d):
     s[..., :hidden] = -np.inf
     assert max_abs(f64(lse), torch.logsumexp(s, -1).numpy()) <= 2e-3
     assert max_abs(f64(o), (torch.softmax(s, -1) @ v.double()).numpy()) <= 2e-2
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("H,H_kv,N", [(1, 1, 65), (3, 1, 127), (8, 2, 129), (2, 2, 160), (5, 5, 255), (6, 3, 333), (16, 4, 641), (3, 3, 1025),
+                                      (4, 1, 1409), (2, 2, 2100)])
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_fp8_forward_with_the_keys_split_over_the_waves(d, H, H_kv, N, causal):
+    # 32-query workgroups of four and eight waves over 64-key tiles: fewer tiles than waves and more, ragged last tiles of keys
+    # and of queries, tiles that share a 128-row scale block, every way the tiles of a head are dealt to the XCDs
+    q = inputs.normal_tensor(1900 + N, "q", (1, H, N, d), "bf16")
+    k, v = (inputs.normal_tensor(1900 + N, n, (1, H_kv, N, d), "bf16") for n in ("k", "v"))
+    v[:, :, N // 2:] *= 30.0  # block scales that differ between the splits
+    dev = [binding.fa_fp8_quant_hadamard(t.cuda()) for t in (q, k, v)]
+    o, lse = binding.fa_fwd_fp8_gqa(*(p[0] for p in dev), *(p[1] for p in dev), d ** -0.5, causal)
+    codes = [[a.cpu().numpy() for a in p] for p in dev]
+    check_fp8_against_model_oracle(o, lse, [c[0] for c in codes], [c[1] for c in codes], d ** -0.5, causal, kv_heads=H_kv)
+
+
+@pytest.mark.parametrize("d,causal,N,most", [(64, False, 256, 57), (64, True, 512, 57), (64, False, 1024, 32), (128, False, 256, 56), (128, True, 512, 30),
+                                             (128, False, 2048, 16), (256, False, 300, 44), (256, True, 1024, 21)])
+def test_fp8_forward_on_both_sides_of_the_key_split_rule(d, causal, N, most):
+    # the most heads (a multiple of 8 or not) that are divided so, and the next ones that are not: the first head against the oracle
+    q = inputs.normal_tensor(1950 + N, "q", (1, most + 16, N, d), "bf16")
+    k, v = (inputs.normal_tensor(1950 + N, n, (1, 1, N, d), "bf16") for n in ("k", "v"))
+    for H in (most, most + 1, most + 16):
+        dev = [binding.fa_fp8_quant_hadamard(t.cuda()) for t in (q[:, :H].contiguous(), k, v)]
+        o, lse = binding.fa_fwd_fp8_gqa(*(p[0] for p in dev), *(p[1] for p in dev), d ** -0.5, causal)
+        (qc, qs), kc, vc = [[a.cpu().numpy() for a in p] for p in dev]
+        check_fp8_against_model_oracle(o[:, :1], lse[:, :1], (qc[:, :1], kc[0], vc[0]), (qs[:, :1], kc[1], vc[1]), d ** -0.5, causal, kv_heads=1)
