@@ -207,7 +207,9 @@ static __device__ __forceinline__ void advance(BufferWords& b, int bytes) {
     const uint64_t n = a + (uint32_t)bytes;
     b.w[0] = (int)(uint32_t)n;
     b.w[1] = (int)(uint32_t)(n >> 32);
-    b.w[2] = max(b.w[2] - bytes, 0);  // (no tensor of a head reaches 2^31 bytes)
+    int left = b.w[2];  // (written out: the compiler makes a vector instruction of a saturating difference)
+    asm("s_sub_u32 %0, %0, %1\n\ts_cselect_b32 %0, 0, %0" : "+s"(left) : "s"(bytes) : "scc");
+    b.w[2] = left;
 }
 
 // A wave's private tiles of 32 rows of a 16-bit tensor, staged straight from global memory into LDS that no other wave

@@ -4,9 +4,8 @@
 // the key/value blocks of that head (paper Algorithm 1: T_r query tiles on the grid, T_c
 // key blocks in the inner loop).  Per block: S^T = K_j Q_i^T on MFMA, online softmax with
 // running row maximum m and row sum l, O^T += V_j^T P^T on MFMA, O rescaled by
-// exp(m_old - m_new); epilogue O / l and L = m + log l.  K_j and V_j are staged through a
-// double-buffered LDS ring that the next block's global loads fill while the current block
-// is being computed (the role the producer warpgroup plays in the paper).
+// exp(m_old - m_new); epilogue O / l and L = m + log l.  K_j and V_j are staged in the LDS, the next block's while the
+// current one is being computed (the role the producer warpgroup plays in the paper).
 #include <type_traits>
 
 #include "fa_device.h"
@@ -192,38 +191,87 @@ struct FewForward {
 template <int D, int NW>
 constexpr bool kHasFew = D == 64 || NW == 4;
 
+// The lane, counted anew: a register less over a loop that has none to spare, for what comes before and after it.
+static __device__ __forceinline__ int lane_again() {
+    int lane;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(lane));
+    return lane;
+}
+
+// The K and V tiles of fa_fwd_16bit_kernel, BC rows each, brought by all its waves from global memory straight into the LDS:
+// no staging registers and no LDS writes.  They are laid out as a WaveTile is.  Row and column operands differ from one
+// another by a bit pattern in the chunk number alone, so a lane keeps one address per tensor and the rest is an exclusive or.
+// Two stages for K; two for V where they cost no workgroup on the CU, else one: at d = 128 and four waves 48 KiB instead of
+// 64, three workgroups on a CU (and three waves' worth of registers) instead of two.
+template <int D, int BC, int NW>
+struct SharedTiles {
+    static constexpr int ROWB = D * 2, CPR = D / 8, RPI = 1024 / ROWB;  // (as in WaveTile)
+    static constexpr int TILE_B = BC * ROWB;
+    static constexpr int NI = TILE_B / 1024 / NW;           // staging instructions of a wave for a tile
+    static constexpr int VS = D == 128 && NW == 4 ? 1 : 2;  // stages of V
+    static constexpr int kV = 2 * TILE_B, kLds = (2 + VS) * TILE_B;
+    uint32_t mine;       // LDS address of what this wave brings of a tile at the start
+    int src[NI];         // byte offset within a tile for each staging instruction
+    uint32_t row0, tr0;  // this stage's operands: K row `col`, elements 8 half...; V rows 4 half + tr_row, transposed
+
+    __device__ __forceinline__ SharedTiles(uint32_t at, int wave, int lane) : mine(at + wave * (NI * 1024)) {
+        const int col = lane & 31, half = lane >> 5, tr_row = (lane & 15) >> 2, quad = lane & 3, blk = (lane >> 4) & 1;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int r = (wave * NI + i) * RPI + lane / CPR;
+            src[i] = r * ROWB + ((lane % CPR) ^ WaveTile<D>::swizzle(r)) * 16;
+            asm volatile("" : "+v"(src[i]));
+        }
+        row0 = at + col * ROWB + ((half ^ WaveTile<D>::swizzle(col)) << 4);
+        const int r = 4 * half + tr_row;
+        tr0 = at + kV + r * ROWB + (((2 * blk + (quad >> 1)) ^ WaveTile<D>::swizzle(r)) << 4) + 8 * (quad & 1);
+        asm volatile("" : "+v"(row0), "+v"(tr0));
+    }
+    // Instruction i of the wave's NI that bring the tile at the resource's start to `offset` (rows past its end: zeros).
+    __device__ __forceinline__ void request(const BufferWords& rsrc, uint32_t offset, int i) const {
+        global_to_lds_16B(rsrc, mine + offset + i * 1024, src[i]);
+    }
+    __device__ __forceinline__ void other_stage(int step) {
+        row0 += step;
+        if constexpr (VS == 2) tr0 += step;
+        asm volatile("" : "+v"(row0), "+v"(tr0));
+    }
+    __device__ __forceinline__ i32x4 row_read(int kt, int ks) const { return lds_load_16B((row0 ^ (ks << 5)) + kt * 32 * ROWB); }
+    __device__ __forceinline__ i32x4 tr_read(int slab, int dt) const {
+        const uint32_t a = tr0 ^ (dt << 6);
+        const i32x2 lo = lds_read_tr16(a + slab * 16 * ROWB), hi = lds_read_tr16((a ^ 32) + (slab * 16 + 8) * ROWB);
+        return i32x4{lo[0], lo[1], hi[0], hi[1]};
+    }
+};
+
 template <typename Tag, int D, int BC, int NW, int RQ, int PD, bool CAUSAL>
-// (the second launch bound is waves per SIMD: two eight-wave workgroups of the d = 64 kernel share a CU)
-__global__ void __launch_bounds__(NW * 64, (D == 64 && NW == 8) ? 4 : (RQ == 1 && D <= 128) ? 2 : 1)
+// (The second launch bound is waves per SIMD.  bf16, us, heads x N, against tiles staged through registers and written to the
+// LDS, two workgroups of the d = 128 form on a CU instead of three and three of the four-wave d = 64 form instead of four:
+// d = 128 causal 512 x 512 67.1 -> 63.7, 160 x 512 24.7 -> 20.7, 160 x 1400 112 -> 95.6; no mask 512 x 512 92.2 -> 75.8,
+// 48 x 512 16.3 -> 15.5.
+// d = 64 causal 160 x 1024 38.1 -> 33.2, 512 x 512 38.7 -> 35.6; no mask 64 x 4096 277 -> 269, 512 x 512 49.8 -> 45.6.)
+__global__ void __launch_bounds__(NW * 64, D == 64 ? 4 : NW == 4 ? 3 : 2)
 fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     const uint16_t* __restrict__ v, uint16_t* __restrict__ o, float* __restrict__ lse,
                     int N, int n_qtiles, int total_wg, int paired, int kv_group, float scale) {
     [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
-    constexpr int NT = NW * 64;
     constexpr int BR = NW * 32 * RQ;
-    constexpr int KSTR = D + 8;   // +16 B per row: 128-bit row reads hit distinct banks
-    constexpr int VSTR = D + 32;  // +64 B per row: the 4-row transposing reads hit distinct banks
     constexpr int KT = BC / 32;   // 32-key score tiles per block
     constexpr int KS = D / 16;    // MFMA steps along the head dimension
     constexpr int DT = D / 32;    // 32-column output tiles
     constexpr int SL = BC / 16;   // 16-key MFMA steps along the keys
     using E = Elem<Tag>;
-    using Copy = TileCopy<D, BC, NT>;
+    using Tiles = SharedTiles<D, BC, NW>;
 
-    constexpr int kTileLds = 2 * BC * (KSTR + VSTR) * 2, kFewLds = kHasFew<D, NW> ? FewForward<D, NW>::kLds : 0;
-    __shared__ __attribute__((aligned(1024))) char lds[kTileLds > kFewLds ? kTileLds : kFewLds];
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
     if constexpr (kHasFew<D, NW>) {
         if (paired == kFewForward) {
             FewForward<D, NW>::template run<Tag, CAUSAL>(q, k, v, o, lse, N, total_wg, kv_group, scale, lds);
             return;
         }
     }
-    uint16_t(*lds_k)[BC * KSTR] = reinterpret_cast<uint16_t(*)[BC * KSTR]>(lds);
-    uint16_t(*lds_v)[BC * VSTR] = reinterpret_cast<uint16_t(*)[BC * VSTR]>(lds + 2 * BC * KSTR * 2);
-
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
-    const int col = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
 
     const TileRun run = query_tiles<CAUSAL>(total_wg, n_qtiles, paired);
     const int bh = run.head;
@@ -237,15 +285,35 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     const float sc = scale * kLog2e;  // exp(scale*s - scale*m) = exp2(sc*s - sc*m)
     float sc_v = sc;  // a vector-register copy: an FMA with a scalar-register operand issues at a lower rate
     asm volatile("" : "+v"(sc_v));
+    Tiles tiles(lds_address(lds), wave, lane);
+    int step = Tiles::TILE_B;  // from the stage being read to the other one
+    // Where a wave issues its requests: beside the score MFMAs at d = 128 (in a burst it sits about 100 cycles in each: 48 heads
+    // x 512 16.9 us, so 15.5), at once at d = 64, which has fewer of them and gains from the compiler's order of the operand
+    // reads, that requests between them would pin (causal 160 x 2048 104 us at once, 107 between).
+    constexpr bool kSpread = D == 128;
+    // all but the last `n` requests of every wave have arrived, and no wave reads any more what it read before
+    auto landed = [&](auto n) __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(decltype(n)::value) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
 
 #pragma nounroll
     for (int pass = 0; pass < run.n_pass(); ++pass) {
     // every LDS read of the previous pass was followed by a barrier
     const int qt = pass == 0 ? run.tile : run.second;
     const int wave_q0 = qt * BR + wave * (32 * RQ);
+    const int lane_now = lane_again(), col = lane_now & 31, half = lane_now >> 5;
+    BufferWords k_rsrc = make_buffer_words(kh, (uint32_t)N * D * 2), v_rsrc = make_buffer_words(vh, (uint32_t)N * D * 2);
+    const int stage0 = step > 0 ? 0 : Tiles::TILE_B;
+#pragma unroll
+    for (int i = 0; i < Tiles::NI; ++i) {
+        tiles.request(k_rsrc, stage0, i);
+        if constexpr (Tiles::VS == 2) tiles.request(v_rsrc, Tiles::kV + stage0, i);
+    }
 
     // Q_i^T as the B operand, resident in registers for the whole loop
-    static_assert(RQ == 1 && PD == 0, "one 32-row slab per wave, operand reads scheduled by the compiler");
+    static_assert(RQ == 1 && PD == 0, "one 32-row slab per wave");
     i32x4 qreg[KS];
     {
         int row = min(wave_q0 + col, N - 1);  // rows past N compute a copy of row N-1, never stored
@@ -265,49 +333,64 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     int last_q = min(qt * BR + BR, N) - 1;
     int n_blocks = CAUSAL ? (last_q / BC + 1) : ((N + BC - 1) / BC);
 
-    i32x4 kpre[Copy::kPerThread], vpre[Copy::kPerThread];
-    const __amdgpu_buffer_rsrc_t k_rsrc = make_buffer(kh, (uint32_t)N * D * 2);
-    const __amdgpu_buffer_rsrc_t v_rsrc = make_buffer(vh, (uint32_t)N * D * 2);
-    Copy::from_global(k_rsrc, 0, tid, kpre);
-    Copy::from_global(v_rsrc, 0, tid, vpre);
-    Copy::template to_lds<KSTR>(lds_k[0], tid, kpre);
-    Copy::template to_lds<VSTR>(lds_v[0], tid, vpre);
-    // Pin the Q loads' completion here.  Left to itself the compiler sinks them to the loop
-    // entry, and the vmcnt waits it then needs at their first use sit inside the loop body,
-    // where on every later iteration they would wait for the K/V prefetch just issued.
+    // (pins the Q loads' completion here: the compiler's waits for them would otherwise sit inside the loop)
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qreg[ks]));
-    __syncthreads();
-
-    // transposing V read: lane -> (row within a 4-key group, 4-column chunk) of its 16-lane group
-    const int tr_row = (lane & 15) >> 2;
-    const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    landed(std::integral_constant<int, 0>{});
 
     for (int t = 0; t < n_blocks; ++t) {
-        const int st = t & 1;
         const int key0 = t * BC;
         const bool more = (t + 1 < n_blocks);
-        if (more) {
-            Copy::from_global(k_rsrc, (key0 + BC) * D * 2, tid, kpre);
-            Copy::from_global(v_rsrc, (key0 + BC) * D * 2, tid, vpre);
+        // K of the next block, and V of the next block or, where it has one stage, of this one; V goes first
+        advance(k_rsrc, Tiles::TILE_B);
+        if (!more) k_rsrc.w[2] = 0;  // past the last block: zeros that nothing reads
+        if constexpr (Tiles::VS == 2) {
+            advance(v_rsrc, Tiles::TILE_B);
+            if (!more) v_rsrc.w[2] = 0;
         }
+        const int k_to = step > 0 ? Tiles::TILE_B : 0, v_to = Tiles::kV + (Tiles::VS == 2 ? k_to : 0);
+        auto request = [&](int i) __attribute__((always_inline)) {
+            if (i < Tiles::NI) tiles.request(v_rsrc, v_to, i);
+            else if (i < 2 * Tiles::NI) tiles.request(k_rsrc, k_to, i - Tiles::NI);
+        };
 
         // a wave whose queries all precede this block has nothing to add (causal)
         const bool wave_active = !CAUSAL || key0 <= wave_q0 + 32 * RQ - 1;
+        // (opaque: as the other arm of the branch below, this makes the accumulators change registers in every block)
+        int all_now = __builtin_amdgcn_readfirstlane(kSpread && wave_active ? 0 : 1);
+        asm volatile("" : "+s"(all_now));
+        if (!kSpread || (CAUSAL && all_now != 0))
+#pragma unroll
+            for (int i = 0; i < 2 * Tiles::NI; ++i) request(i);
+        i32x4 pb[SL];
         if (wave_active) {
             // ---- GEMM0: S^T = K_j Q_i^T, then the mask: keys past N, and keys after the query when causal
             f32x16 sacc[KT];
             const bool need_mask = (key0 + BC > N) || (CAUSAL && key0 + BC - 1 > wave_q0);
-            auto scores = [&]() __attribute__((always_inline)) {
+            auto scores = [&](auto first) __attribute__((always_inline)) {
                 const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                const uint16_t* ks_base = lds_k[st] + col * KSTR + half * 8;
+                if constexpr (kSpread && decltype(first)::value) {
+                    static_assert(!kSpread || 2 * Tiles::NI <= KS, "a request per step");
+                    i32x4 next[KT];
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
+                    for (int kt = 0; kt < KT; ++kt) next[kt] = tiles.row_read(kt, 0);
 #pragma unroll
-                    for (int kt = 0; kt < KT; ++kt) {
-                        i32x4 a = *reinterpret_cast<const i32x4*>(ks_base + kt * 32 * KSTR + ks * 16);
-                        sacc[kt] = E::mma(a, qreg[ks], ks == 0 ? zero : sacc[kt]);
+                    for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+                        for (int kt = 0; kt < KT; ++kt) {
+                            const i32x4 a = next[kt];
+                            if (ks + 1 < KS) next[kt] = tiles.row_read(kt, ks + 1);
+                            if (kt == 0) request(ks);
+                            sacc[kt] = E::mma(a, qreg[ks], ks == 0 ? zero : sacc[kt]);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
                     }
+                } else {
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                        for (int kt = 0; kt < KT; ++kt) sacc[kt] = E::mma(tiles.row_read(kt, ks), qreg[ks], ks == 0 ? zero : sacc[kt]);
+                }
                 if (need_mask) {
                     const int qi = wave_q0 + col;
                     const int limit = CAUSAL ? min(qi, N - 1) : N - 1;  // last visible key
@@ -344,7 +427,6 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                 }
             };
             // P~ = exp2(s c - m) packed as the operand for GEMM1; returns this lane's part of the row sum
-            i32x4 pb[SL];
             auto probabilities = [&]() __attribute__((always_inline)) {
                 float ps[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -373,51 +455,43 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             // either way.  A block that does exceed it (scores that rose by more than 14 in log2 units
             // since the reference was set: rare) is computed again from the K tile, which is still in
             // LDS, with its own maximum as the new reference.
-            scores();
+            scores(std::true_type{});
             if (t == 0) move_reference(true, std::true_type{});
             float blk = probabilities();
             const bool over = max_both_halves(blk) > kRaiseAbove;
             if (__builtin_amdgcn_ballot_w64(over) != 0) {
-                scores();
+                scores(std::false_type{});
                 move_reference(over, std::false_type{});
                 blk = probabilities();
             }
             l_run += blk;
-
+        }
+        if constexpr (Tiles::VS == 1) {  // V of this block; K of the next stays on its way
+            landed(std::integral_constant<int, Tiles::NI>{});
+            advance(v_rsrc, Tiles::TILE_B);
+        }
+        if (wave_active) {
             // ---- GEMM1: O^T += V_j^T P^T
-            const uint16_t* vs_base = lds_v[st] + (4 * half + tr_row) * VSTR + tr_col;
 #pragma unroll
             for (int sl = 0; sl < SL; ++sl)
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt) {
-                    const uint16_t* p0 = vs_base + (sl * 16) * VSTR + dt * 32;
-                    i32x2 lo = lds_read_tr16(p0);
-                    i32x2 hi = lds_read_tr16(p0 + 8 * VSTR);
-                    i32x4 a = {lo[0], lo[1], hi[0], hi[1]};
-                    oacc[dt] = E::mma(a, pb[sl], oacc[dt]);
-                }
+                for (int dt = 0; dt < DT; ++dt) oacc[dt] = E::mma(tiles.tr_read(sl, dt), pb[sl], oacc[dt]);
         }
-
-        if (more) {
-            Copy::template to_lds<KSTR>(lds_k[st ^ 1], tid, kpre);
-            Copy::template to_lds<VSTR>(lds_v[st ^ 1], tid, vpre);
-        }
-        __syncthreads();
+        tiles.other_stage(step);
+        step = -step;
+        landed(std::integral_constant<int, 0>{});
     }
 
     // ---- epilogue: O / l, L = m + log l.  Every LDS read of the loop was followed by a barrier,
     // so the K and V buffers are free: each wave takes 4 KiB of them to transpose its output tile.
     {
-        char* patch = (wave < 4 ? reinterpret_cast<char*>(&lds_k[0][0]) : reinterpret_cast<char*>(&lds_v[0][0])) +
-                      (wave & 3) * 4096;
-        static_assert(2 * BC * KSTR * 2 >= 4 * 4096 && 2 * BC * VSTR * 2 >= 4 * 4096, "patches must fit");
-        const int qi = wave_q0 + col;
+        static_assert(Tiles::kLds >= NW * 4096, "patches must fit");
+        char* patch = lds + wave * 4096;
+        const int out_lane = lane_again(), qi = wave_q0 + (out_lane & 31);
         const float l = sum_both_halves(l_run);
-        int out_lane = lane;  // opaque: the addresses derived from it are else computed before the loop, and spilled over it
-        asm volatile("" : "+v"(out_lane));
         store_rows_via_lds<Tag, DT>(oacc, 1.0f / l, patch, make_buffer(o + head_off, (uint32_t)N * D * 2), wave_q0,
                                     out_lane);
-        if (qi < N && half == 0) lse[(size_t)bh * N + qi] = (m_run + log2f(l)) * kLn2;
+        if (qi < N && out_lane < 32) lse[(size_t)bh * N + qi] = (m_run + log2f(l)) * kLn2;
     }
     if (pass + 1 < run.n_pass()) __syncthreads();  // the next pass's first tile overwrites the patches
     }  // passes of a causal pair
@@ -1364,15 +1438,18 @@ static int launch_16bit(const void* q, const void* k, const void* v, void* o, fl
     long total = few ? few_split((long)B * H, N) : (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
     const dim3 grid = forward_grid((long)B * H, N, n_qtiles, total, causal, paired), block(NW * 64);
+    int lds = SharedTiles<D, BC, NW>::kLds;
+    if constexpr (kHasFew<D, NW>)
+        if (few) lds = FewForward<D, NW>::kLds;
     auto qp = static_cast<const uint16_t*>(q);
     auto kp = static_cast<const uint16_t*>(k);
     auto vp = static_cast<const uint16_t*>(v);
     auto op = static_cast<uint16_t*>(o);
     if (causal)
-        hipLaunchKernelGGL((fa_fwd_16bit_kernel<Tag, D, BC, NW, RQ, PD, true>), grid, block, 0, stream, qp, kp, vp,
+        hipLaunchKernelGGL((fa_fwd_16bit_kernel<Tag, D, BC, NW, RQ, PD, true>), grid, block, lds, stream, qp, kp, vp,
                            op, lse, N, n_qtiles, (int)total, paired, H / H_kv, scale);
     else
-        hipLaunchKernelGGL((fa_fwd_16bit_kernel<Tag, D, BC, NW, RQ, PD, false>), grid, block, 0, stream, qp, kp, vp,
+        hipLaunchKernelGGL((fa_fwd_16bit_kernel<Tag, D, BC, NW, RQ, PD, false>), grid, block, lds, stream, qp, kp, vp,
                            op, lse, N, n_qtiles, (int)total, paired, H / H_kv, scale);
     return hipGetLastError() == hipSuccess ? FA_OK : FA_ERR_LAUNCH;
 }

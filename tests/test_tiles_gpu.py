@@ -406,3 +406,22 @@ def test_fp8_forward_on_both_sides_of_the_key_split_rule(d, causal, N, most):
         o, lse = binding.fa_fwd_fp8_gqa(*(p[0] for p in dev), *(p[1] for p in dev), d ** -0.5, causal)
         (qc, qs), kc, vc = [[a.cpu().numpy() for a in p] for p in dev]
         check_fp8_against_model_oracle(o[:, :1], lse[:, :1], (qc[:, :1], kc[0], vc[0]), (qs[:, :1], kc[1], vc[1]), d ** -0.5, causal, kv_heads=1)
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("rising", [False, True])
+@pytest.mark.parametrize("d,N,H", [(64, 1, 1300), (64, 63, 1300), (64, 65, 1300), (64, 128, 600), (64, 129, 600), (64, 321, 300), (64, 641, 300),
+                                   (128, 1, 1300), (128, 64, 1300), (128, 127, 1300), (128, 193, 600), (128, 256, 600), (128, 577, 300)])
+def test_forward_shared_tiles(d, N, H, rising, causal):
+    # many heads, so 128 or 256 queries a workgroup: one key block, the second stage, an odd and an even number of blocks
+    # before a causal pair's second tile, ragged last blocks of keys and of queries; with rising maxima a block's scores
+    # are computed a second time, from either stage of K, while the next tiles arrive
+    dtype = "f16" if H == 600 else "bf16"
+    pick = [0, H // 2, H - 1]
+    q, k, v = inputs.rising_maximum_qkv(1900 + N, 1, 1, N, d, dtype) if rising else inputs.qkv(1900 + N, 1, 1, N, d, dtype)
+    o_ref, l_ref = oracle.attention_fwd(f64(q), f64(k), f64(v), d ** -0.5, causal)
+    o, lse = binding.fa_fwd_gqa(q.expand(1, H, N, d).contiguous().cuda(), k.cuda(), v.cuda(), d ** -0.5, causal)
+    assert torch.equal(o, o[:, :1].expand_as(o)) and torch.equal(lse, lse[:, :1].expand_as(lse))  # every head alike
+    for h in pick:
+        assert max_abs(f64(o[:, h:h + 1]), o_ref) <= 2e-2 + (2.0 ** -8 * np.abs(o_ref).max() if rising else 0)  # roundings of P~ and O
+        assert max_abs(f64(lse[:, h:h + 1]), l_ref) <= 2e-3
