@@ -245,12 +245,12 @@ struct SharedTiles {
 };
 
 template <typename Tag, int D, int BC, int NW, int RQ, int PD, bool CAUSAL>
-// (The second launch bound is waves per SIMD.  bf16, us, heads x N, against tiles staged through registers and written to the
+// (512 threads: the four-wave tiles also run FewForward with eight waves.  The second launch bound is waves per SIMD.  bf16, us, heads x N, against tiles staged through registers and written to the
 // LDS, two workgroups of the d = 128 form on a CU instead of three and three of the four-wave d = 64 form instead of four:
 // d = 128 causal 512 x 512 67.1 -> 63.7, 160 x 512 24.7 -> 20.7, 160 x 1400 112 -> 95.6; no mask 512 x 512 92.2 -> 75.8,
 // 48 x 512 16.3 -> 15.5.
 // d = 64 causal 160 x 1024 38.1 -> 33.2, 512 x 512 38.7 -> 35.6; no mask 64 x 4096 277 -> 269, 512 x 512 49.8 -> 45.6.)
-__global__ void __launch_bounds__(NW * 64, D == 64 ? 4 : NW == 4 ? 3 : 2)
+__global__ void __launch_bounds__(512, D == 64 ? 4 : NW == 4 ? 3 : 2)
 fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     const uint16_t* __restrict__ v, uint16_t* __restrict__ o, float* __restrict__ lse,
                     int N, int n_qtiles, int total_wg, int paired, int kv_group, float scale) {
@@ -267,6 +267,12 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     if constexpr (kHasFew<D, NW>) {
         if (paired == kFewForward) {
             FewForward<D, NW>::template run<Tag, CAUSAL>(q, k, v, o, lse, N, total_wg, kv_group, scale, lds);
+            return;
+        }
+    }
+    if constexpr (NW == 4) {
+        if (paired == kFewForward8) {
+            FewForward<D, 8>::template run<Tag, CAUSAL>(q, k, v, o, lse, N, total_wg, kv_group, scale, lds);
             return;
         }
     }
@@ -1434,13 +1440,14 @@ static int launch_16bit(const void* q, const void* k, const void* v, void* o, fl
     int n_qtiles = (N + BR - 1) / BR;
     constexpr PairRule kPairs = NW == 4 ? (D == 64 ? PairRule{3, 15.f / 16, 384, 0.8f, 4} : PairRule{2, 7.f / 8, 256, 0.75f, kAny})
                                         : (D == 64 ? PairRule{2, 1.f, kAny, 1.f, 0} : PairRule{1, 7.f / 8, kAny, 1.f, kAny});
-    const int paired = few ? kFewForward : causal && pair_causal_tiles((long)B * H, n_qtiles, kPairs);
+    const int few_waves = few && NW == 4 ? few_forward_waves((long)B * H, N, D, causal) : NW;
+    const int paired = few_waves != NW ? kFewForward8 : few ? kFewForward : causal && pair_causal_tiles((long)B * H, n_qtiles, kPairs);
     long total = few ? few_split((long)B * H, N) : (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
-    const dim3 grid = forward_grid((long)B * H, N, n_qtiles, total, causal, paired), block(NW * 64);
+    const dim3 grid = forward_grid((long)B * H, N, n_qtiles, total, causal, few ? kFewForward : paired), block(few_waves * 64);
     int lds = SharedTiles<D, BC, NW>::kLds;
     if constexpr (kHasFew<D, NW>)
-        if (few) lds = FewForward<D, NW>::kLds;
+        if (few) lds = few_waves == 8 ? FewForward<D, 8>::kLds : FewForward<D, 4>::kLds;
     auto qp = static_cast<const uint16_t*>(q);
     auto kp = static_cast<const uint16_t*>(k);
     auto vp = static_cast<const uint16_t*>(v);
@@ -1506,16 +1513,18 @@ static int launch_d256(const void* q, const void* k, const void* v, void* o, flo
 //   d = 256: the 128-register output accumulator allows only one wave per SIMD; fa_fwd_d256_kernel
 //     pipelines the softmax of one block under the score MFMAs of the next inside that wave.
 // us, 128 / 256 rows, heads x N, each in the better order of work:
-//   d = 64   causal:  16 x 1300 21.3 / 28.4, 16 x 2048 31.4 / 41.6, 80 x 2048 59.6 / 58.9, 192 x 2048 131 / 132
-//            no mask: 16 x 640 11.5 / 14.8;  16 x 650 12.7 / 16.2 but 144 x 650 31.4 / 27.9, 16 x 890 15.4 / 19.5 but 112 x 890 38.9 / 34.5
-//   d = 128  causal:  16 x 1408 32.4 / 34.9, 80 x 1408 54.6 / 57.4;  16 x 1500 34.9 / 38.5 but 80 x 1500 60.8 / 58.0;
-//                     16 x 1600 35.9 / 39.0, 64 x 1600 56.5 / 57.9, 192 x 1600 166 / 187 (13 tiles of 128 rows, 7 of 256)
-//            no mask: 16 x 640 16.6 / 19.1;  48 x 650 25.3 / 21.8, 16 x 1150 27.4 / 30.4 but 32 x 1150 38.2 / 32.2
+//   d = 64   causal:  16 x 2560 25.2 / 31.7, 64 x 2560 64.5 / 68.7, 32 x 4096 87.8 / 87.3, 48 x 6144 237 / 239;  24 x 8192 214 / 225
+//                     but 16 x 8192 161 / 155, 8 x 16384 313 / 300 (four workgroups on every CU, one of them with the longest tile)
+//            no mask: 16 x 700 9.2 / 10.2, 40 x 896 18.6 / 19.8, 256 x 896 62 / 67;  32 x 1024 16.5 / 21.4 but 128 x 1024 42.2 / 40.7
+//   d = 128  causal:  16 x 1920 27.6 / 35.3, 64 x 1920 74 / 78, 112 x 1920 107 / 149;  16 x 2048 31 / 38 but 48 x 2048 63.1 / 61.9
+//            no mask: 16 x 768 13.8 / 17.9, 64 x 768 27.4 / 27.1, 256 x 896 104 / 129;  32 x 960 23 / 27 but 48 x 960 31.0 / 29.9
+//   (within the lines the 128-row tiles lose where they just spill over into another round: 129 heads x 704 60 / 53, 774
+//    workgroups on 768 places; heads of 112, 144 and 192 x 650 win 22, 7 and 23 %)
 enum class Fwd16 { kTile4, kTile8, kPingPong, kD256, kNone };
 static Fwd16 choose_16bit(int d, int N, int causal) {
     switch (d) {
-        case 64: return N <= (causal ? 2048 : 640) ? Fwd16::kTile4 : Fwd16::kTile8;
-        case 128: return N <= (causal ? 1408 : 640) || (causal && odd_row_tiles(N) && N <= 1664) ? Fwd16::kTile4 : Fwd16::kPingPong;
+        case 64: return N <= (causal ? 6144 : 896) ? Fwd16::kTile4 : Fwd16::kTile8;
+        case 128: return N <= (causal ? 1920 : 896) ? Fwd16::kTile4 : Fwd16::kPingPong;
         case 256: return Fwd16::kD256;
         default: return Fwd16::kNone;
     }

@@ -60,7 +60,7 @@ inline bool pair_causal_tiles(long heads, int n_qtiles, const PairRule& rule) {
 // The launchers' `paired` argument for launches divided by FewForward (fa_fwd.hip) or FewFp8Forward (fa_fwd_fp8.hip); the total number of work items that the
 // kernels take otherwise is few_split() then: log2 of the groups into which a head's tiles go so that the XCDs get the same
 // number of groups each, or -1: no groups, where they would come out too uneven (few tiles; all are on the chip at once).
-constexpr int kFewForward = 2;
+constexpr int kFewForward = 2, kFewForward8 = 3;  // (by as many waves as the kernel's tiles have; by eight where those have four)
 inline int few_split(long heads, int N) {
     if (heads % 8 == 0) return 0;
     return N <= 32 * 32 ? -1 : heads % 4 == 0 ? 1 : heads % 2 == 0 ? 2 : 3;
@@ -106,6 +106,18 @@ inline bool few_forward(long heads, int N, int d, int causal) {
         case 128: return fill.tiles > 6 && (causal ? fill.at(1.5f, 18, 4.75f) : fill.fillings <= (fill.tiles < 40 ? 2.f : 3.f));
         default: return causal && fill.at(0.7f, 28, 2.9f);
     }
+}
+
+// How many waves such a workgroup has in the four-wave tile kernels: eight halve the chain of a long sequence, four let
+// twice as many workgroups share a CU.  bf16, us, eight / four, heads x N:
+//   d = 64   no mask: 8 x 700 7.4 / 7.4, 16 x 700 10.2 / 9.2, 32 x 700 14.4 / 11.7;  causal: 8 x 2049 13.1 / 14.5, 6 x 3000 16.3 / 18.3,
+//            8 x 2560 18.2 / 17.2, 5 x 3669 19.6 / 22.4, 16 x 2049 22.7 / 19.0, 6 x 4096 26.1 / 25.5, 6 x 6144 48.6 / 51.8, 8 x 6144 62 / 58
+//   d = 128  no mask: 16 x 700 17.9 / 13.6;  causal: 6 x 1600 14.7 / 16.1, 12 x 1600 24.6 / 18.7, 16 x 1700 35 / 27
+inline int few_forward_waves(long heads, int N, int d, int causal) {
+    if (N <= (causal ? (d == 64 ? 2048 : 1408) : 640)) return 4;
+    const KeySplitFill fill(heads, N);
+    const float most = !causal ? 1.f : d == 128 ? 1.5f : fill.tiles > 150 ? (float)fill.tiles / 42 : 2.4f;
+    return fill.fillings <= most ? 8 : 4;
 }
 
 // The same for the FP8 forward (FewFp8Forward).  us, large / these, heads x N:

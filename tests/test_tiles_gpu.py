@@ -425,3 +425,18 @@ def test_forward_shared_tiles(d, N, H, rising, causal):
     for h in pick:
         assert max_abs(f64(o[:, h:h + 1]), o_ref) <= 2e-2 + (2.0 ** -8 * np.abs(o_ref).max() if rising else 0)  # roundings of P~ and O
         assert max_abs(f64(lse[:, h:h + 1]), l_ref) <= 2e-3
+
+
+@pytest.mark.parametrize("d,causal,N,heads", [(64, False, 700, (8, 16)), (64, True, 2049, (8, 16)), (64, True, 3000, (5, 6, 7)), (64, True, 6144, (2, 8)),
+                                              (64, True, 6145, (2,)), (64, False, 897, (16,)), (128, False, 700, (8, 16)), (128, True, 1409, (4, 12)),
+                                              (128, True, 1920, (3, 16)), (128, True, 1921, (3,)), (128, False, 897, (4,))])
+def test_forward_key_splits_of_four_and_eight_waves(d, causal, N, heads):
+    # head counts on both sides of the rule that gives the key-split workgroups of the four-wave kernels eight waves, and
+    # both sides of the lines between the kernels
+    q = inputs.normal_tensor(1960 + N, "q", (1, max(heads), N, d), "bf16")
+    k, v = (inputs.normal_tensor(1960 + N, n, (1, 1, N, d), "bf16") for n in ("k", "v"))
+    o_ref, l_ref = oracle.attention_fwd(f64(q[:, :1]), f64(k), f64(v), d ** -0.5, causal)
+    for H in heads:
+        o, lse = binding.fa_fwd_gqa(q[:, :H].contiguous().cuda(), k.cuda(), v.cuda(), d ** -0.5, causal)
+        assert max_abs(f64(o[:, :1]), o_ref) <= 2e-2 and rmse(f64(o[:, :1]), o_ref) <= 3e-3
+        assert max_abs(f64(lse[:, :1]), l_ref) <= 2e-3
