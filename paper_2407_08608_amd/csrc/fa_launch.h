@@ -86,16 +86,16 @@ struct KeySplitFill {
 // walk all of them.  What counts is how often those workgroups fill the CUs (`fillings`) and how long the chain of 32-key
 // tiles is that they shorten; under a causal mask, where the large workgroups wait for their longest, they win further.
 // The kernel stays the same (fa_fwd_kernel_name): this is only its work.  bf16, us, large / these, heads x N:
-//   d = 64   no mask: 16 x 100 5.0 / 4.2, 16 x 333 8.5 / 5.3, 64 x 333 8.8 / 8.3, 4 x 1000 21.5 / 7.4, 4 x 4096 74 / 30, 1 x 16384 279 / 107;
-//            lost: 128 x 128 5.2 / 5.3, 80 x 333 9.6 / 11.1, 28 x 1500 30 / 34, 12 x 4096 77 / 85;  N <= 64: equal to 2 %
-//            causal:  16 x 333 8.7 / 5.1, 16 x 2048 32 / 20, 4 x 4096 77 / 20;  lost: 56 x 1000 19.5 / 21, 40 x 2048 37 / 43
-//   d = 128  no mask: 16 x 100 6.5 / 5.5, 16 x 512 14.3 / 8.2, 32 x 512 15.0 / 12.2, 2 x 8192 167 / 95;
-//            lost: 96 x 100 6.9 / 7.4, 48 x 333 12.5 / 13.1, 24 x 700 21 / 24, 16 x 2048 50 / 59
-//            causal:  16 x 1000 25 / 13.6, 16 x 2048 50 / 40, 4 x 4096 90 / 31;  lost: 48 x 512 15.8 / 16.0, 28 x 1500 36 / 43
+//   d = 64   no mask: 72 x 96 5.8 / 4.9, 32 x 512 10.1 / 8.1, 16 x 1400 21.0 / 16.6, 1 x 4096 50 / 19.5;
+//            lost: 72 x 256 7.4 / 8.1, 24 x 1400 25.9 / 27.4;  N <= 64: equal to 2 %
+//            causal:  32 x 512 10.9 / 7.1, 16 x 2000 29.6 / 18.4, 8 x 4096 54 / 32;  lost: 24 x 3000 46.0 / 48.5
+//   d = 128  no mask: 80 x 96 7.1 / 6.0, 16 x 512 13.5 / 8.6, 32 x 512 14.2 / 12.2, 8 x 2000 41 / 28;
+//            lost: 96 x 100 6.9 / 7.4, 16 x 1400 30.5 / 31.0, 8 x 3000 61.9 / 63.7
+//            causal:  32 x 512 15.7 / 10.5, 16 x 1000 25.1 / 13.9, 16 x 2000 45.9 / 31.2, 8 x 4096 90 / 54
 //   d = 256  no mask: 16 x 333 17.5 / 12.0, 4 x 2048 57 / 32;  lost: 28 x 333 17.9 / 21.5, 8 x 2048 62 / 62
 //            causal:  16 x 1000 34 / 27, 2 x 8192 204 / 117;  lost: 32 x 333 18.5 / 19.5, 12 x 2048 61 / 61
-// Drawn on 2900 shapes (heads 1 to 384, N from 24 to 16384): up to 4.6 times as fast.  Over 1500 others in the last third
-// before the rule's edge, odd head counts and shared heads among them, 0.76 of the time on average, 1.02 at worst.
+// Drawn on 2900 shapes (heads 1 to 384, N from 24 to 16384), before the 128-row tiles gained 5 to 20 %: up to 4.6 times as
+// fast.  Over 1500 others in the last third before the rule's edge 0.76 of the time on average, 1.02 at worst then.
 inline bool few_forward(long heads, int N, int d, int causal) {
     const KeySplitFill fill(heads, N);
     if (fill.tiles < 3) return false;
