@@ -4,8 +4,9 @@
 //   a tuple   the outputs, as the Python code returns them;
 //   an int    the status of a call that the library refused;
 //   None      where anything is out of the ordinary -- another type than a plain tensor, number or bool, a layout or
-//             dtype that the Python code refuses or treats apart, a dispatch mode, an allocation that failed: binding.py then
-//             takes its own way, and reports what it finds.
+//             dtype that the Python code refuses or treats apart, a torch function or dispatch mode, an allocation that
+//             failed: binding.py then takes its own way, and reports what it finds.
+// An exception raised in Python code that runs inside (a Python allocator, say) is passed on as it is.
 // The library's functions come in as addresses (bind), so there is one copy of it in the process.  The GIL is released
 // around the library call, as ctypes does.
 // Host time of a call, us, ctypes and torch.empty / so: fa_fwd 8.9 / 5.9, fa_bwd 12.1 / 7.6,
@@ -14,6 +15,7 @@
 
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/fa_mi355.h"
@@ -35,7 +37,8 @@ struct Arguments {
     bool ok = true;
 
     Arguments(PyObject* const* a, Py_ssize_t count, Py_ssize_t expected) : args(a), n(count), ok(count == expected) {
-        if (lib.fwd == nullptr || at::impl::torch_function_mode_enabled()) ok = false;
+        if (lib.fwd == nullptr || at::impl::torch_function_mode_enabled() || c10::impl::TorchDispatchModeTLS::any_modes_set())
+            ok = false;
     }
     bool given(Py_ssize_t i) const { return ok && args[i] != Py_None; }
     // a plain contiguous device tensor
@@ -138,15 +141,15 @@ PyObject* result(int status, const Arguments& a, const Py_ssize_t (&index)[K], c
     return out;
 }
 
-// Runs `body`; an exception is a case for the Python code
+// Runs `body`; an exception is a case for the Python code, but for one that Python has set already
 template <typename Body>
 PyObject* native(Body&& body) {
     try {
         PyObject* r = body();
         if (r) return r;
-        if (PyErr_Occurred()) return nullptr;
     } catch (...) {
     }
+    if (PyErr_Occurred()) return nullptr;
     Py_RETURN_NONE;
 }
 

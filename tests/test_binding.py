@@ -1,6 +1,9 @@
 """The native way through the binding (csrc/fa_binding.cpp) against the Python way: the same results, refusals and errors."""
+import math
+
 import pytest
 import torch
+from torch.utils._python_dispatch import TorchDispatchMode
 
 from paper_2407_08608_amd import binding
 
@@ -33,6 +36,40 @@ def test_arguments_that_no_way_takes(monkeypatch):
                      lambda: binding.fa_bwd(bad, x, x, x, x, x, 0.125, False), lambda: binding.fa_fp8_quant_hadamard(bad),
                      lambda: binding.fa_fwd_fp8(bad, x, x, x, x, x, 0.125, False)):
             _same_error(*_both(monkeypatch, call))
+
+
+def _device_typed(*size, dtype=torch.bfloat16):
+    # a plain tensor that says it is on the device, over no memory at all: for calls that end before any is touched
+    device, nbytes = torch.device("cuda", 0), math.prod(size) * dtype.itemsize
+    stride = [math.prod(size[i + 1:]) for i in range(len(size))]
+    storage = torch._C._construct_storage_from_data_pointer(4096, device, nbytes)
+    return torch._C._construct_CUDA_Tensor_From_Storage_And_Metadata(
+        {"nbytes": nbytes, "data_ptr": 4096, "size": size, "stride": stride, "dtype": dtype, "device": device,
+         "storage_offset": 0}, storage)
+
+
+def _allocating_calls():
+    # one of every kind that allocates its outputs
+    x, c, s = _device_typed(1, 2, 16, 64), _device_typed(1, 2, 16, 64, dtype=torch.uint8), _device_typed(1, 2, 1, dtype=torch.float32)
+    lse, ws = _device_typed(1, 2, 16, dtype=torch.float32), _device_typed(4096, dtype=torch.uint8)
+    return [lambda: binding.fa_fwd(x, x, x, 0.125, False), lambda: binding.fa_fwd_gqa(x, x, x, 0.125, True),
+            lambda: binding.fa_fp8_quant_hadamard(x), lambda: binding.fa_fwd_fp8(c, c, c, s, s, s, 0.125, False),
+            lambda: binding.fa_fwd_fp8_gqa(c, c, c, s, s, s, 0.125, True), lambda: binding.fa_bwd(x, x, x, x, lse, x, 0.125, False, workspace=ws),
+            lambda: binding.fa_bwd_gqa(x, x, x, x, lse, x, 0.125, True, workspace=ws)]
+
+
+def test_an_exception_of_a_dispatch_mode_reaches_the_caller(monkeypatch):
+    class Refuse(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            raise LookupError(f"no {func}")
+
+    binding.lib()
+    monkeypatch.setattr(binding, "_stream", lambda: 0)
+    for call in _allocating_calls():
+        with Refuse():
+            a, b = _both(monkeypatch, call)
+        assert type(a) is LookupError
+        _same_error(a, b)
 
 
 def _tensors(dtype=torch.bfloat16, H=4, H_kv=2, N=70, d=64):
