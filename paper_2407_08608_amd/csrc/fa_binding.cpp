@@ -58,14 +58,15 @@ struct Arguments {
         ok = false;
         return 0;
     }
-    // what the function args[i] says is the current stream, asked when everything else is in order
+    // What the function args[i] says is the current stream, asked when everything else is in order.  Its failure is a case for
+    // the Python code, which asks again; what is no Exception (an interrupt from the keyboard comes only once) stays set.
     void* stream(Py_ssize_t i) {
         if (!ok) return nullptr;
         PyObject* handle = PyObject_CallNoArgs(args[i]);
         void* p = handle ? PyLong_AsVoidPtr(handle) : nullptr;
         Py_XDECREF(handle);
         if (PyErr_Occurred()) {
-            PyErr_Clear();
+            if (PyErr_ExceptionMatches(PyExc_Exception)) PyErr_Clear();
             ok = false;
         }
         return p;

@@ -72,6 +72,21 @@ def test_an_exception_of_a_dispatch_mode_reaches_the_caller(monkeypatch):
         _same_error(a, b)
 
 
+@pytest.mark.skipif(binding._native is None, reason="the native part has not been built")
+def test_an_interrupt_in_the_middle_of_a_call_is_not_lost(monkeypatch):
+    binding.lib()
+    for call in _allocating_calls():
+        raised = []
+
+        def stream():  # a key press comes once; should the call go on, it ends here
+            raised.append(KeyboardInterrupt() if not raised else LookupError())
+            raise raised[-1]
+
+        monkeypatch.setattr(binding, "_stream", stream)
+        with pytest.raises(KeyboardInterrupt):
+            call()
+
+
 def _tensors(dtype=torch.bfloat16, H=4, H_kv=2, N=70, d=64):
     g = torch.Generator(device="cuda").manual_seed(7)
     mk = lambda h: torch.randn((2, h, N, d), generator=g, device="cuda").to(dtype)  # noqa: E731
