@@ -46,17 +46,21 @@ def _check_hazards(name):
     return name
 
 
-# The native part of binding.py: host code against torch's C++ interface, which stays out of the library.
-BINDING = os.path.join(HERE, "_fa_binding.so")
+# The native part of binding.py: host code against torch's C++ interface, which stays out of the library.  Object layouts
+# of this Python and this torch go into it: the name keeps other Pythons from finding it, the module refuses another torch.
+BINDING = os.path.join(HERE, "_fa_binding" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 
 def _build_binding():
     import torch
+    for old in glob.glob(os.path.join(HERE, "_fa_binding*.so")):
+        os.unlink(old)
     root = os.path.dirname(torch.__file__)
     include = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
                sysconfig.get_paths()["include"]]
     subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall",
                     f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+                    f'-DFA_TORCH_VERSION="{torch.__version__}"',
                     *(f for d in include for f in ("-isystem", d)), os.path.join(CSRC, "fa_binding.cpp"), "-o", BINDING,
                     "-L" + os.path.join(root, "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"], check=True)
 

@@ -293,6 +293,19 @@ PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
 PyMethodDef methods[] = {FA_METHOD(bind), FA_METHOD(fwd), FA_METHOD(fwd_fp8), FA_METHOD(quant), FA_METHOD(bwd), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fa_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
+// Whether the torch of this process is the one that this file was compiled against; if not, ImportError is set
+bool same_torch() {
+    PyObject* torch = PyImport_ImportModule("torch");
+    PyObject* version = torch ? PyObject_GetAttrString(torch, "__version__") : nullptr;
+    PyObject* text = version ? PyObject_Str(version) : nullptr;
+    const bool same = text && PyUnicode_CompareWithASCIIString(text, FA_TORCH_VERSION) == 0;
+    if (text && !same) PyErr_Format(PyExc_ImportError, "built for torch " FA_TORCH_VERSION ", not for %U", text);
+    Py_XDECREF(text);
+    Py_XDECREF(version);
+    Py_XDECREF(torch);
+    return same;
+}
+
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fa_binding() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__fa_binding() { return same_torch() ? PyModule_Create(&module) : nullptr; }

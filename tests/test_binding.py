@@ -1,5 +1,9 @@
 """The native way through the binding (csrc/fa_binding.cpp) against the Python way: the same results, refusals and errors."""
 import math
+import os
+import subprocess
+import sys
+import sysconfig
 
 import pytest
 import torch
@@ -26,6 +30,17 @@ def _same_error(a, b):
 
 def test_the_native_part_is_built():
     assert binding._native is not None
+
+
+@pytest.mark.skipif(binding._native is None, reason="the native part has not been built")
+def test_the_native_part_is_for_this_python_and_this_torch_only():
+    assert binding._native.__file__.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    code = ("import torch; torch.__version__ = '0.0'\n"
+            "from paper_2407_08608_amd import binding; assert binding._native is None\n"
+            "try:\n    from paper_2407_08608_amd import _fa_binding\n"
+            "except ImportError as e:\n    assert 'not for 0.0' in str(e)\n"
+            "else:\n    raise SystemExit(1)\n")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
 
 
 def test_arguments_that_no_way_takes(monkeypatch):
