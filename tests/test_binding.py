@@ -9,7 +9,7 @@ import pytest
 import torch
 from torch.utils._python_dispatch import TorchDispatchMode
 
-from paper_2407_08608_amd import binding
+from paper_2407_08608_amd import binding, build
 
 
 def _both(monkeypatch, call):
@@ -28,8 +28,26 @@ def _same_error(a, b):
     assert isinstance(a, Exception) and type(a) is type(b) and str(a) == str(b), (a, b)
 
 
-def test_the_native_part_is_built():
+@pytest.mark.skipif(not os.path.exists(build.BINDING), reason="the native part has not been built")
+def test_the_native_part_is_taken_where_it_is_built():
     assert binding._native is not None
+
+
+def test_the_library_is_built_without_a_compiler_for_the_native_part(monkeypatch, tmp_path, capsys):
+    linked = []
+
+    def run(command, **_):
+        if command[0] == "no-such-compiler":
+            raise FileNotFoundError(command[0])
+        linked.append(command[-1])
+
+    monkeypatch.setenv("CXX", "no-such-compiler")
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setattr(build, "_compile", lambda src: src + ".o")
+    monkeypatch.setattr(build, "_check_hazards", lambda name: name)
+    monkeypatch.setattr(build.subprocess, "run", run)
+    assert build.build(verbose=False) == build.LIB
+    assert linked and linked[0].endswith(".hip.o") and "no-such-compiler" in capsys.readouterr().err
 
 
 @pytest.mark.skipif(binding._native is None, reason="the native part has not been built")
