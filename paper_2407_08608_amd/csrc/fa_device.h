@@ -307,6 +307,13 @@ static __device__ __forceinline__ void store_rows_via_lds(const f32x16 (&acc)[DT
     }
 }
 
+// The item of workgroup `id` of `total` where every XCD takes a run of consecutive items, whatever the total: ids go to the
+// XCDs in turn, and the first total % 8 XCDs get one more.
+static __device__ __forceinline__ int xcd_run(int id, int total) {
+    const int xcd = id & 7;
+    return xcd * (total >> 3) + min(xcd, total & 7) + (id >> 3);
+}
+
 // ---------------------------------------------------------------------------------------
 // Forward launches divided by keys (FewForward, FewFp8Forward): the pieces that do not depend on the data type.
 //
@@ -320,8 +327,7 @@ struct KeySplitTile {
 static __device__ __forceinline__ KeySplitTile key_split_tile(int N, int split) {
     const int n_t = (N + 31) / 32;
     if (split < 0) {
-        const int xcd = blockIdx.x & 7, per = gridDim.x >> 3, rest = gridDim.x & 7;  // the first `rest` XCDs get one more
-        const int id = xcd * per + min(xcd, rest) + ((int)blockIdx.x >> 3);
+        const int id = xcd_run(blockIdx.x, gridDim.x);
         return {id / n_t, id % n_t, n_t};
     }
     const int group = ((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3);
@@ -425,17 +431,28 @@ static __device__ __forceinline__ WorkItem work_item(int block, int total, int n
 // the workgroup two divisions) or, `paired`, tiles i and n_qtiles-1-i one after the other, the longer first: items that
 // all cover the same number of key blocks (with an odd tile count the middle tile is an item of its own).  Pairs start
 // half as many workgroups, which is the better choice when the items fill whole rounds of the chip (pair_causal_tiles).
+// BY_XCD (the 128-row 16-bit tiles): the tiles of a head stay on one XCD also where the number of items or heads is no
+// multiple of 8; otherwise they go to all eight, each of which reads the head's K and V.  Items: runs of them per XCD.  Single
+// tiles: a row of the grid starts at XCD y heads % 8, so its heads are turned by as much, but for the last heads % 8, whose
+// tiles move on from row to row and keep the XCDs even (all tiles of a head on one XCD: 107 heads x 400, d = 64, 16.9 us instead
+// of 10.8).  `total` is the number of heads then.  bf16, us, heads x N, spread / kept:
+//   no mask  d = 64  85 x 710 22.4 / 20.9, 139 x 648 32.4 / 28.7;  d = 128  85 x 648 33.0 / 28.3, 121 x 896 76.4 / 64.8
+//   causal   d = 64  107 x 957 27.0 / 25.4;  d = 128  83 x 1024 40.1 / 33.8, 95 x 1665 113 / 96
+// Three of these workgroups share a CU, so more K and V pass through an L2 at a time than with two, and with the tiles spread
+// these calls fell behind the 256-row tiles.
 struct TileRun {
     int head, tile, second;
     __device__ __forceinline__ int n_pass() const { return second < 0 ? 1 : 2; }
 };
-template <bool CAUSAL>
+template <bool CAUSAL, bool BY_XCD = false>
 static __device__ __forceinline__ TileRun query_tiles(int total, int n_qtiles, int paired) {
-    const int n_items = CAUSAL ? (n_qtiles + 1) / 2 : n_qtiles, id = xcd_contiguous(blockIdx.x, total);
+    const int n_items = CAUSAL ? (n_qtiles + 1) / 2 : n_qtiles;
+    const int id = BY_XCD ? xcd_run(blockIdx.x, total) : xcd_contiguous(blockIdx.x, total);
     const bool single = CAUSAL && !paired;
     // (both ways without a branch: with one the code behind it is laid out differently, and pairs took 2.5 % longer at
     // d = 64, 16 x 8192, and d = 128, 256 x 300)
-    const int head = single ? (int)blockIdx.x : id / n_items, i = single ? (int)blockIdx.y : id - head * n_items;
+    const int x = blockIdx.x, y = blockIdx.y, turned = BY_XCD && x < (total & ~7) ? (x & ~7) | ((x + y * total) & 7) : x;
+    const int head = single ? turned : id / n_items, i = single ? y : id - head * n_items;
     return {head, CAUSAL ? n_qtiles - 1 - i : i, CAUSAL && !single && n_qtiles - 1 - i != i ? i : -1};
 }
 

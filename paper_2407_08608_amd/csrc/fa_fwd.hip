@@ -279,7 +279,7 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
 
-    const TileRun run = query_tiles<CAUSAL>(total_wg, n_qtiles, paired);
+    const TileRun run = query_tiles<CAUSAL, NW == 4>(total_wg, n_qtiles, paired);
     const int bh = run.head;
 
     const size_t head_off = (size_t)bh * N * D;
@@ -1445,6 +1445,7 @@ static int launch_16bit(const void* q, const void* k, const void* v, void* o, fl
     long total = few ? few_split((long)B * H, N) : (long)B * H * (paired ? (n_qtiles + 1) / 2 : n_qtiles);
     if (total > 0x7fffffffL) return FA_ERR_SHAPE;
     const dim3 grid = forward_grid((long)B * H, N, n_qtiles, total, causal, few ? kFewForward : paired), block(few_waves * 64);
+    if (causal && !paired) total = (long)B * H;  // (query_tiles)
     int lds = SharedTiles<D, BC, NW>::kLds;
     if constexpr (kHasFew<D, NW>)
         if (few) lds = few_waves == 8 ? FewForward<D, 8>::kLds : FewForward<D, 4>::kLds;

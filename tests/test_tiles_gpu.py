@@ -440,3 +440,18 @@ def test_forward_key_splits_of_four_and_eight_waves(d, causal, N, heads):
         o, lse = binding.fa_fwd_gqa(q[:, :H].contiguous().cuda(), k.cuda(), v.cuda(), d ** -0.5, causal)
         assert max_abs(f64(o[:, :1]), o_ref) <= 2e-2 and rmse(f64(o[:, :1]), o_ref) <= 3e-3
         assert max_abs(f64(lse[:, :1]), l_ref) <= 2e-3
+
+
+@pytest.mark.parametrize("d,causal,N,H", [(64, False, 700, 85), (64, False, 129, 333), (128, False, 300, 61), (128, False, 700, 67), (64, True, 957, 107),
+                                          (64, True, 2100, 41), (128, True, 1024, 83), (128, True, 300, 94), (64, True, 512, 381),
+                                          (128, True, 512, 255), (128, True, 650, 420)])
+def test_forward_tiles_of_a_head_on_one_xcd(d, causal, N, H):
+    # heads and work items that are no multiple of 8, without a mask, as single causal tiles and as pairs: every tile of every
+    # head is done (the outputs start as NaN), and by itself (every head has the same rows)
+    q, k, v = inputs.qkv(2000 + N, 1, 1, N, d, "bf16")
+    o_ref, l_ref = oracle.attention_fwd(f64(q), f64(k), f64(v), d ** -0.5, causal)
+    o = torch.full((1, H, N, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((1, H, N), float("nan"), device="cuda")
+    binding.fa_fwd_gqa(q.expand(1, H, N, d).contiguous().cuda(), k.cuda(), v.cuda(), d ** -0.5, causal, o=o, lse=lse)
+    assert torch.equal(o, o[:, :1].expand_as(o)) and torch.equal(lse, lse[:, :1].expand_as(lse))
+    assert max_abs(f64(o[:, :1]), o_ref) <= 2e-2 and rmse(f64(o[:, :1]), o_ref) <= 3e-3 and max_abs(f64(lse[:, :1]), l_ref) <= 2e-3
