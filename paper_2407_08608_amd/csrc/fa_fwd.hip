@@ -244,17 +244,12 @@ struct SharedTiles {
     }
 };
 
+// The query tiles of a workgroup, its keys walked by all waves together.
 template <typename Tag, int D, int BC, int NW, int RQ, int PD, bool CAUSAL>
-// (512 threads: the four-wave tiles also run FewForward with eight waves.  The second launch bound is waves per SIMD.  bf16, us, heads x N, against tiles staged through registers and written to the
-// LDS, two workgroups of the d = 128 form on a CU instead of three and three of the four-wave d = 64 form instead of four:
-// d = 128 causal 512 x 512 67.1 -> 63.7, 160 x 512 24.7 -> 20.7, 160 x 1400 112 -> 95.6; no mask 512 x 512 92.2 -> 75.8,
-// 48 x 512 16.3 -> 15.5.
-// d = 64 causal 160 x 1024 38.1 -> 33.2, 512 x 512 38.7 -> 35.6; no mask 64 x 4096 277 -> 269, 512 x 512 49.8 -> 45.6.)
-__global__ void __launch_bounds__(512, D == 64 ? 4 : NW == 4 ? 3 : 2)
-fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
-                    const uint16_t* __restrict__ v, uint16_t* __restrict__ o, float* __restrict__ lse,
-                    int N, int n_qtiles, int total_wg, int paired, int kv_group, float scale) {
-    [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
+static __device__ __forceinline__ void shared_tiles_forward(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                                                            const uint16_t* __restrict__ v, uint16_t* __restrict__ o,
+                                                            float* __restrict__ lse, int N, int n_qtiles, int total_wg, int paired,
+                                                            int kv_group, float scale, char* lds) {
     constexpr int BR = NW * 32 * RQ;
     constexpr int KT = BC / 32;   // 32-key score tiles per block
     constexpr int KS = D / 16;    // MFMA steps along the head dimension
@@ -263,19 +258,6 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     using E = Elem<Tag>;
     using Tiles = SharedTiles<D, BC, NW>;
 
-    extern __shared__ __attribute__((aligned(1024))) char lds[];
-    if constexpr (kHasFew<D, NW>) {
-        if (paired == kFewForward) {
-            FewForward<D, NW>::template run<Tag, CAUSAL>(q, k, v, o, lse, N, total_wg, kv_group, scale, lds);
-            return;
-        }
-    }
-    if constexpr (NW == 4) {
-        if (paired == kFewForward8) {
-            FewForward<D, 8>::template run<Tag, CAUSAL>(q, k, v, o, lse, N, total_wg, kv_group, scale, lds);
-            return;
-        }
-    }
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
 
@@ -363,9 +345,11 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         // a wave whose queries all precede this block has nothing to add (causal)
         const bool wave_active = !CAUSAL || key0 <= wave_q0 + 32 * RQ - 1;
         // (opaque: as the other arm of the branch below, this makes the accumulators change registers in every block)
+        // The last block's requests would bring nothing: with four waves at d = 64 they are left out (16 heads x 64 3.34 us
+        // with, 3.27 without; 348 x 100 7.35 / 6.92), with eight the branch costs more (64 x 2048 73.1 / 74.9).
         int all_now = __builtin_amdgcn_readfirstlane(kSpread && wave_active ? 0 : 1);
         asm volatile("" : "+s"(all_now));
-        if (!kSpread || (CAUSAL && all_now != 0))
+        if (kSpread ? CAUSAL && all_now != 0 : NW == 8 || more)
 #pragma unroll
             for (int i = 0; i < 2 * Tiles::NI; ++i) request(i);
         i32x4 pb[SL];
@@ -501,6 +485,34 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     }
     if (pass + 1 < run.n_pass()) __syncthreads();  // the next pass's first tile overwrites the patches
     }  // passes of a causal pair
+}
+
+template <typename Tag, int D, int BC, int NW, int RQ, int PD, bool CAUSAL>
+// (512 threads: the four-wave tiles also run FewForward with eight waves.  The second launch bound is waves per SIMD.
+// bf16, us, heads x N, against tiles staged through registers and written to the LDS, two workgroups of the d = 128 form on a CU
+// instead of three and three of the four-wave d = 64 form instead of four:
+// d = 128 causal 512 x 512 67.1 -> 63.7, 160 x 512 24.7 -> 20.7, 160 x 1400 112 -> 95.6; no mask 512 x 512 92.2 -> 75.8,
+// 48 x 512 16.3 -> 15.5.
+// d = 64 causal 160 x 1024 38.1 -> 33.2, 512 x 512 38.7 -> 35.6; no mask 64 x 4096 277 -> 269, 512 x 512 49.8 -> 45.6.)
+__global__ void __launch_bounds__(512, D == 64 ? 4 : NW == 4 ? 3 : 2)
+fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                    const uint16_t* __restrict__ v, uint16_t* __restrict__ o, float* __restrict__ lse,
+                    int N, int n_qtiles, int total_wg, int paired, int kv_group, float scale) {
+    [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    // (the shared tiles come first: behind the code of the key splits the smallest calls took 0.1 us longer, d = 64 causal
+    // 32 x 64 3.93 us instead of 3.80, and more scalar registers were spilled)
+    if (__builtin_expect(paired < kFewForward, 1)) {
+        shared_tiles_forward<Tag, D, BC, NW, RQ, PD, CAUSAL>(q, k, v, o, lse, N, n_qtiles, total_wg, paired, kv_group, scale, lds);
+        return;
+    }
+    if constexpr (NW == 4) {
+        if (paired == kFewForward8) {
+            FewForward<D, 8>::template run<Tag, CAUSAL>(q, k, v, o, lse, N, total_wg, kv_group, scale, lds);
+            return;
+        }
+    }
+    if constexpr (kHasFew<D, NW>) FewForward<D, NW>::template run<Tag, CAUSAL>(q, k, v, o, lse, N, total_wg, kv_group, scale, lds);
 }
 
 // ---------------------------------------------------------------------------------------
