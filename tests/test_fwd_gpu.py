@@ -57,8 +57,8 @@ def test_fp32_ragged(N, causal):
 @pytest.mark.parametrize("d", [64, 128, 256])
 @pytest.mark.parametrize("N", [1, 7, 64, 129, 257, 1000, 1500])
 def test_16bit_small_and_ragged(N, d, causal, dtype):
-    # N = 64..1500 spans 1..24 key blocks with ragged tails; several query tiles per head; 1000 and
-    # 1500 keys sit on either side of the lengths where the 256-query tiles take over
+    # N = 64..1500 spans 1..24 key blocks with ragged tails; several query tiles per head; from 65 keys on
+    # so few heads are divided by keys
     q, k, v = inputs.qkv(3 + N, 2, 3, N, d, dtype)
     _check_full(q, k, v, d ** -0.5, causal)
 
@@ -76,9 +76,8 @@ def test_bf16_every_block_visited_once(N, causal):
 @pytest.mark.parametrize("N,causal", [(1024, False), (1031, False), (1100, False), (1345, False), (2049, False),
                                       (4096, True), (4129, True), (4200, True)])
 def test_16bit_d128_pingpong_kernel_ragged(N, causal, dtype):
-    # head dimension 128 above 640 keys (causal: above 1408) runs the eight-wave ping-pong kernel
-    # with its own staging ring and 256-row query tiles: whole and ragged tiles, ragged key blocks,
-    # a single query tile with all four staged blocks in use, and the causal diagonal
+    # head dimension 128 above 896 keys (causal: above 1920) runs the eight-wave ping-pong kernel, which divides so few heads by
+    # keys (its staging ring and 256-row tiles, with more heads: test_forward_main_loops)
     B, H = (1, 2) if causal else (2, 2)
     q, k, v = inputs.qkv(70 + N, B, H, N, 128, dtype)
     _check_full(q, k, v, 128 ** -0.5, causal)
@@ -120,8 +119,8 @@ def test_bf16_large_scores_stay_finite():
 @pytest.mark.parametrize("N,d", [(2300, 128), (2300, 256), (2300, 64), (600, 128)])
 def test_bf16_row_maxima_that_rise_block_after_block(N, d, causal):
     # scores grow from ~0 at the first key to ~80 at the last: the lazily raised reference maximum must
-    # move (and O, l be rescaled) a dozen times per row; the ping-pong (d = 128) and pipelined (d = 256)
-    # kernels compute that rescale one block behind the scores
+    # move (and O, l be rescaled) a dozen times per row.  Two heads are divided by keys; the ping-pong (d = 128) and
+    # pipelined (d = 256) loops, which rescale one block behind the scores: test_forward_main_loops
     q, k, v = inputs.rising_maximum_qkv(8, 1, 2, N, d, "bf16")
     _check_full(q, k, v, d ** -0.5, causal, o_tol=4e-2, r_tol=6e-3, l_tol=5e-2)
 

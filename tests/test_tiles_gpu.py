@@ -203,11 +203,12 @@ def test_backward_query_tile_rule_edges(d, causal, N):
                                        (7, 1409, 128), (256, 129, 256), (300, 300, 256), (5, 700, 256), (9, 1300, 64),
                                        (11, 200, 64), (3, 2048, 64), (3, 2049, 64), (3, 1664, 128), (3, 1665, 128), (5, 1408, 128), (5, 1536, 128), (5, 1537, 128),
                                        (61, 1700, 128), (62, 1700, 128), (255, 300, 128), (256, 300, 128), (127, 300, 256),
-                                       (128, 300, 256), (359, 512, 64), (360, 512, 64), (10, 4100, 64), (11, 4100, 64), (250, 300, 256), (10, 4100, 256), (11, 4100, 256)])
+                                       (128, 300, 256), (359, 512, 64), (360, 512, 64), (10, 4100, 64), (11, 4100, 64), (250, 300, 256), (10, 4100, 256), (11, 4100, 256),
+                                       (64, 2048, 128), (65, 2048, 128), (51, 2300, 128), (64, 2300, 128), (19, 6400, 64), (16, 6400, 64), (24, 4100, 256)])
 @pytest.mark.parametrize("fp8", [False, True])
 def test_causal_forward_paired_and_single_tiles(heads, N, d, fp8):
-    # head counts on both sides of the rule that pairs causal query tiles, with odd and even tile counts; every row of
-    # the first, a middle and the last head against the oracle
+    # head counts on both sides of the rule that pairs causal query tiles, with odd and even tile counts (few heads of a long
+    # sequence are divided by keys instead); every row of the first, a middle and the last head against the oracle
     pick = sorted({0, heads // 2, heads - 1})
     q = inputs.normal_tensor(1000 + N, "q", (1, heads, N, d), "bf16")
     k, v = (inputs.normal_tensor(1000 + N, n, (1, 1, N, d), "bf16") for n in ("k", "v"))
@@ -239,7 +240,8 @@ def test_backward_both_passes_in_one_launch(d, causal, N, H, H_kv):
                                  (128, 641), (128, 704), (128, 705), (128, 897), (128, 1152), (128, 1153)])
 @pytest.mark.parametrize("fp8", [False, True])
 def test_forward_tile_rule_edges(d, N, fp8):
-    # where the unmasked forward changes between 128- and 256-row workgroups, and odd and even numbers of 128-row tiles
+    # where the unmasked forward changes between 128- and 256-row workgroups, and odd and even numbers of 128-row tiles, with
+    # two heads: all but d = 128 with FP8 to 128 keys are divided by keys (with many heads: test_forward_main_loops)
     q, k, v = inputs.qkv(1200 + N, 1, 2, N, d, "bf16")
     if fp8:
         dev = [binding.fa_fp8_quant_hadamard(t.cuda()) for t in (q, k, v)]
@@ -455,3 +457,88 @@ def test_forward_tiles_of_a_head_on_one_xcd(d, causal, N, H):
     binding.fa_fwd_gqa(q.expand(1, H, N, d).contiguous().cuda(), k.cuda(), v.cuda(), d ** -0.5, causal, o=o, lse=lse)
     assert torch.equal(o, o[:, :1].expand_as(o)) and torch.equal(lse, lse[:, :1].expand_as(lse))
     assert max_abs(f64(o[:, :1]), o_ref) <= 2e-2 and rmse(f64(o[:, :1]), o_ref) <= 3e-3 and max_abs(f64(lse[:, :1]), l_ref) <= 2e-3
+
+
+# (fp8, d, causal, N, heads, kernel): enough heads that no key split is made, so that the kernel's own loop runs; checked
+# against the rules on the CPU in test_division_host.py
+MAIN_LOOPS = ([(False, 128, False, N, 24, "fa_fwd_pingpong_kernel") for N in (897, 1024, 1031, 1100, 1152, 1153, 1345, 2049)] +
+              [(False, 128, True, N, H, "fa_fwd_pingpong_kernel") for N, H in ((1921, 24), (4096, 16), (4129, 16), (4200, 17))] +
+              [(False, 64, False, N, 48, "fa_fwd_16bit_kernel<bf16_tag, 64, 64, 8,") for N in (897, 1031, 1408, 1409)] +
+              [(False, 64, True, N, H, "fa_fwd_16bit_kernel<bf16_tag, 64, 64, 8,") for N, H in ((6145, 16), (6273, 19), (6400, 19))] +
+              [(False, 64, False, N, 48, "fa_fwd_16bit_kernel<bf16_tag, 64, 64, 4,") for N in (640, 641, 768, 769, 896)] +
+              [(False, 128, False, N, 48, "fa_fwd_16bit_kernel<bf16_tag, 128, 64, 4,") for N in (640, 641, 704, 705, 896)] +
+              [(False, 64, True, 6144, 16, "fa_fwd_16bit_kernel<bf16_tag, 64, 64, 4,"),
+               (False, 128, True, 1920, 24, "fa_fwd_16bit_kernel<bf16_tag, 128, 64, 4,")] +
+              [(False, 256, False, N, H, "fa_fwd_d256_kernel") for N, H in ((65, 200), (300, 60), (1000, 24), (1031, 24), (2049, 16))] +
+              [(False, 256, True, N, H, "fa_fwd_d256_kernel") for N, H in ((300, 60), (1031, 24), (2100, 24))] +
+              [(True, 64, False, N, H, "fa_fwd_fp8_kernel<64, 64, 4,") for N, H in ((130, 130), (511, 64))] +
+              [(True, 64, False, N, 48, "fa_fwd_fp8_async_kernel<64,") for N in (512, 641, 1409)] +
+              [(True, 128, False, N, 48, "fa_fwd_fp8_kernel<128, 64, 4,") for N in (640, 704)] +
+              [(True, 128, False, N, 48, "fa_fwd_fp8_async_kernel<128,") for N in (705, 897, 1153)] +
+              [(True, 256, False, N, H, "fa_fwd_fp8_async_kernel<256,") for N, H in ((300, 64), (700, 48), (1031, 48))])
+
+
+@pytest.mark.parametrize("rising", [False, True])
+@pytest.mark.parametrize("fp8,d,causal,N,H", [c[:5] for c in MAIN_LOOPS])
+def test_forward_main_loops(fp8, d, causal, N, H, rising):
+    # every kernel's own loop on both sides of the lengths between the kernels: whole and ragged tiles and key blocks, odd and
+    # even numbers of tiles, the causal diagonal; with rising maxima the references move in every block of a row, one block
+    # behind the scores in the pipelined kernels.  Every head has the same rows.
+    q, k, v = inputs.rising_maximum_qkv(2100 + N, 1, 1, N, d, "bf16") if rising else inputs.qkv(2100 + N, 1, 1, N, d, "bf16")
+    many = q.expand(1, H, N, d).contiguous()
+    if fp8:
+        dev = [binding.fa_fp8_quant_hadamard(t.cuda()) for t in (many, k, v)]
+        o, lse = binding.fa_fwd_fp8_gqa(*(p[0] for p in dev), *(p[1] for p in dev), d ** -0.5, causal)
+        (qc, qs), kc, vc = [[a.cpu().numpy() for a in p] for p in dev]
+        check_fp8_against_model_oracle(o[:, :1], lse[:, :1], (qc[:, :1], kc[0], vc[0]), (qs[:, :1], kc[1], vc[1]), d ** -0.5, causal, kv_heads=1)
+    else:
+        o, lse = binding.fa_fwd_gqa(many.cuda(), k.cuda(), v.cuda(), d ** -0.5, causal)
+        o_ref, l_ref = oracle.attention_fwd(f64(q), f64(k), f64(v), d ** -0.5, causal)
+        # (rising: scores of up to 80 nats are sums of d fp32 products, and few keys carry a row: the roundings of P~ and O)
+        assert max_abs(f64(o[:, :1]), o_ref) <= 2e-2 + (2.0 ** -8 * np.abs(o_ref).max() if rising else 0)
+        assert rmse(f64(o[:, :1]), o_ref) <= (6e-3 if rising else 3e-3) and max_abs(f64(lse[:, :1]), l_ref) <= 2e-3
+    assert torch.equal(o, o[:, :1].expand_as(o)) and torch.equal(lse, lse[:, :1].expand_as(lse))
+
+
+def _bits(t):
+    return t.view(torch.int16 if t.dtype != torch.float32 else torch.int32)
+
+
+# (dtype, d, N, heads): key splits of four and eight waves, the 128- and 256-row loops, d = 256, both fp32 kernels, FP8
+_FORMS_FWD = [("bf16", 64, 300, 2), ("f16", 64, 700, 2), ("bf16", 128, 300, 2), ("bf16", 128, 1500, 2), ("bf16", 256, 300, 2), ("f16", 64, 300, 300),
+              ("bf16", 128, 300, 200), ("f16", 128, 2300, 24), ("bf16", 64, 1500, 48), ("bf16", 256, 300, 60), ("f32", 64, 20, 3), ("f32", 64, 300, 3),
+              ("fp8", 64, 300, 2), ("fp8", 64, 300, 120), ("fp8", 64, 700, 60), ("fp8", 128, 300, 2), ("fp8", 128, 300, 100), ("fp8", 128, 1500, 24),
+              ("fp8", 256, 300, 2), ("fp8", 256, 300, 64)]
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype,d,N,H", _FORMS_FWD)
+def test_forward_rows_with_scores_of_nan_or_infinity(dtype, d, N, H, causal):
+    # a NaN in a query's row, or a key whose score is NaN or +inf for the rows that see it: those rows have no output and no
+    # logsumexp (inf - inf in the softmax), every other row keeps its bits
+    q = inputs.normal_tensor(2200 + N, "q", (1, H, N, d), "bf16" if dtype == "fp8" else dtype).cuda()
+    k, v = (inputs.normal_tensor(2200 + N, n, (1, 1, N, d), "bf16" if dtype == "fp8" else dtype).cuda() for n in ("k", "v"))
+    q[..., 0] = 1.0
+    if dtype == "fp8":
+        (q, qs), (k, ks), (v, vs) = (binding.fa_fp8_quant_hadamard(t) for t in (q, k, v))
+        run = lambda q, k: binding.fa_fwd_fp8_gqa(q, k, v, qs, ks, vs, d ** -0.5, causal)  # noqa: E731
+        nan, kinds = 0x7F, ("nan",)  # (e4m3 has no infinity)
+    else:
+        run = lambda q, k: binding.fa_fwd_gqa(q, k, v, d ** -0.5, causal)  # noqa: E731
+        nan, kinds = float("nan"), ("nan", "inf")
+    o, lse = run(q, k)
+    assert torch.isfinite(o).all() and torch.isfinite(lse).all()
+
+    def check(o2, l2, hit):
+        assert torch.isnan(o2[hit]).all() and not torch.isfinite(l2[hit]).any()
+        assert torch.equal(_bits(o2[~hit]), _bits(o[~hit])) and torch.equal(_bits(l2[~hit]), _bits(lse[~hit]))
+
+    for i in (0, N // 2, N - 1):
+        q2, hit = q.clone(), torch.zeros((1, H, N), dtype=torch.bool, device="cuda")
+        q2[:, ::2, i, 5], hit[:, ::2, i] = nan, True
+        check(*run(q2, k), hit)
+    for j in (0, 40 % N, N - 1):
+        for kind in kinds:
+            k2, hit = k.clone(), torch.zeros((1, H, N), dtype=torch.bool, device="cuda")
+            k2[:, :, j, 0], hit[:, :, j if causal else 0:] = nan if kind == "nan" else float("inf"), True
+            check(*run(q, k2), hit)
