@@ -167,9 +167,10 @@ int fa_bwd_noalloc(const void* q, const void* k, const void* v, const void* o, c
  */
 typedef enum {
     FA_SCHED_AUTO = 0,        /* the library's choice by shape */
-    FA_SCHED_LOCKSTEP_4W = 1, /* 128-query tile, 4 waves in lock-step, K/V staged through registers;
-                                 softmax/GEMM overlap only across two resident workgroups */
-    FA_SCHED_LOCKSTEP_8W = 2, /* 256-query tile, 8 waves in lock-step, K/V staged through registers */
+    FA_SCHED_LOCKSTEP_4W = 1, /* 128-query tile, 4 waves in lock-step, K/V staged asynchronously into the LDS (two
+                                 stages of K, one of V); softmax/GEMM overlap only across three resident workgroups */
+    FA_SCHED_LOCKSTEP_8W = 2, /* 256-query tile, 8 waves in lock-step, K/V staged asynchronously into the LDS (two
+                                 stages each); one workgroup per CU */
     FA_SCHED_PINGPONG = 3     /* 256-query tile, two wave groups alternating GEMMs and softmax,
                                  K/V staged asynchronously into a 4-deep LDS ring */
 } fa_schedule;

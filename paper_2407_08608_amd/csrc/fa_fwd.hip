@@ -1526,13 +1526,15 @@ static int launch_d256(const void* q, const void* k, const void* v, void* o, flo
 //   d = 256: the 128-register output accumulator allows only one wave per SIMD; fa_fwd_d256_kernel
 //     pipelines the softmax of one block under the score MFMAs of the next inside that wave.
 // us, 128 / 256 rows, heads x N, each in the better order of work:
-//   d = 64   causal:  16 x 2560 25.2 / 31.7, 64 x 2560 64.5 / 68.7, 32 x 4096 87.8 / 87.3, 48 x 6144 237 / 239;  24 x 8192 214 / 225
-//                     but 16 x 8192 161 / 155, 8 x 16384 313 / 300 (four workgroups on every CU, one of them with the longest tile)
-//            no mask: 16 x 700 9.2 / 10.2, 40 x 896 18.6 / 19.8, 256 x 896 62 / 67;  32 x 1024 16.5 / 21.4 but 128 x 1024 42.2 / 40.7
-//   d = 128  causal:  16 x 1920 27.6 / 35.3, 64 x 1920 74 / 78, 112 x 1920 107 / 149;  16 x 2048 31 / 38 but 48 x 2048 63.1 / 61.9
-//            no mask: 16 x 768 13.8 / 17.9, 64 x 768 27.4 / 27.1, 256 x 896 104 / 129;  32 x 960 23 / 27 but 48 x 960 31.0 / 29.9
-//   (within the lines the 128-row tiles lose where they just spill over into another round: 129 heads x 704 60 / 53, 774
-//    workgroups on 768 places; heads of 112, 144 and 192 x 650 win 22, 7 and 23 %)
+//   d = 64   causal:  16 x 2560 36.0 / 45.8, 64 x 2560 70.4 / 75.5, 32 x 4096 89.8 / 94.5, 48 x 6144 261 / 273;
+//                     16 x 8192 172 / 177, 24 x 8192 226 / 238, 8 x 16384 329 / 333
+//            no mask: 16 x 700 12.3 / 15.4, 139 x 648 30.1 / 30.0, 40 x 896 18.9 / 20.3, 256 x 896 71.6 / 79.8;
+//                     32 x 1024 18.4 / 22.2, 512 x 1024 170 / 178 but 128 x 1024 46.1 / 45.1
+//   d = 128  causal:  16 x 1920 43.5 / 46.1, 64 x 1920 86.7 / 89.0, 112 x 1920 127 / 175;  16 x 2048 46.9 / 50.3, 48 x 2048 68.4 / 70.6
+//            no mask: 85 x 648 30.0 / 31.9, 129 x 704 49.5 / 54.6, 16 x 768 17.9 / 21.7, 64 x 768 29.3 / 29.2, 256 x 896 118 / 152;
+//                     32 x 960 26.1 / 30.2, 512 x 1024 270 / 341 but 48 x 960 32.7 / 32.2
+//   Of 740 shapes without a mask and 4500 causal ones within the lines none took over 2 % longer than with the lines at 640 keys
+//   (causal: 2048 and 1408) and the tiles of that time; beyond them most numbers of heads still win, a few lose up to 3 %.
 enum class Fwd16 { kTile4, kTile8, kPingPong, kD256, kNone };
 static Fwd16 choose_16bit(int d, int N, int causal) {
     switch (d) {

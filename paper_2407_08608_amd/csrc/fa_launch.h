@@ -18,7 +18,9 @@ inline bool odd_row_tiles(int N) { return ((N + 127) / 128) & 1; }
 // Whether a causal forward launch pairs its query tiles (query_tiles in fa_device.h).  Pairs all take the same time, so
 // they are the better choice when they fill whole rounds of the chip; what decides is the share of the rounds that is
 // work (a pair without a partner, the middle tile of an odd number, counts half).  A round is one workgroup on each of
-// the 256 CUs while all pairs are resident, `per_cu` (workgroups of the kernel that a CU holds) on each beyond.  Against
+// the 256 CUs while 256 per_cu pairs take them all, `per_cu` on each beyond.  (A fitted number with the rest of a rule: the
+// workgroups that a CU holds, but one less for the four-wave tiles, 16-bit and FP8 d = 64, whose rules were drawn when
+// they took more registers.)  Against
 // single tiles dealt longest first pairs win from `share` on, with up to `most_tiles` tiles: where two or three workgroups
 // share a CU, single tiles even out by themselves.  With `many_heads` heads or more pairs win from `many_share` on: single
 // tiles read the K and V of all heads at once, which costs most where few rows share a read.  On at most one workgroup per
@@ -27,17 +29,18 @@ inline bool odd_row_tiles(int N) { return ((N + 127) / 128) & 1; }
 // Causal, bf16 unless said, us, pairs / single tiles (share, heads x N):
 //   ping-pong     1.00 151 / 159 (128 x 2048), 0.88 67.8 / 71.6 (56 x 2048), 0.84 53.9 / 56.1 (72 x 1408), 0.75 197 / 209
 //                 (12 x 8192);  0.75 176 / 154 (64 x 3001), 0.25 99.5 / 90.1 (8 x 4096)
-//   d = 128, 4w   1.00 61.0 / 69.6 (512 x 512), 0.94 52.4 / 54.1 (96 x 1200), 0.83 84.2 / 89.6 (640 x 512);
-//                 0.86 106 / 97 (160 x 1300), 0.69 133 / 119 (192 x 1300)
+//   d = 128, 4w   1.00 78.8 / 79.5 (512 x 512), 0.83 87.5 / 102 (640 x 512), 0.85 223 / 225 (390 x 1183);  0.94 59.5 / 53.4
+//                 (96 x 1200: lost), 0.75 29.0 / 24.8 (256 x 384: lost);  0.86 120 / 102 (160 x 1300), 0.69 134 / 120 (192 x 1300)
 //   d = 256       1.00 79.7 / 94.1 (256 x 512), 1.00 107 / 115 (128 x 1024), 0.81 441 / 536 (224 x 1664), 0.83 227 / 301
 //                 (512 x 640);  0.88 243 / 223 (32 x 3500: lost), 0.88 648 / 593 (80 x 3500: lost)
 //   FP8 d = 128   1.00 96.6 / 101 (128 x 2048);  0.83 163 / 148 (128 x 2500), 0.75 126 / 106 (64 x 3001)
 //   FP8 d = 256   1.00 118 / 125 (256 x 1024);  0.75 588 / 486 (48 x 6000)
 //   d = 64, 8w    0.75 308 / 323 (6 x 16384), 1.00 on half the slots 167 / 180 (16 x 8192);  1.00 158 / 155 (64 x 4096: never
 //                 beyond one per CU)
-//   d = 64, 4w    1.00 21.1 / 22.8 (768 x 256);  1.00 49.0 / 46.5 (64 x 2048: up to 4 tiles, FP8 2)
-// Over 4400 causal shapes the rule is up to 0.5 % off the better of the two on average, by kernel, and at one of them
-// (d = 256, 144 x 150, 1 us) more than 2 % slower than always pairing.
+//   d = 64, 4w    1.00 28.7 / 29.4 (768 x 256), 1.00 32.2 / 33.0 (384 x 512);  1.00 52.2 / 48.7 (64 x 2048: up to 4 tiles, FP8 2)
+// Over 4500 causal shapes of the four-wave 16-bit tiles as they are the rule is 0.1 % (d = 64) and 0.5 % (d = 128) off the better
+// of the two on average; at d = 128 one shape in 23 is more than 2 % off, 21 % at worst.  The other kernels' rules were
+// drawn on 4400 shapes, up to 0.5 % off on average, by kernel, before the key splits took the shapes of few heads.
 struct PairRule {
     int per_cu;
     float share;
@@ -57,9 +60,12 @@ inline bool pair_causal_tiles(long heads, int n_qtiles, const PairRule& rule) {
     return n_qtiles <= rule.most_tiles && work >= (heads >= rule.many_heads ? rule.many_share : rule.share);
 }
 
-// The launchers' `paired` argument for launches divided by FewForward (fa_fwd.hip) or FewFp8Forward (fa_fwd_fp8.hip); the total number of work items that the
-// kernels take otherwise is few_split() then: log2 of the groups into which a head's tiles go so that the XCDs get the same
-// number of groups each, or -1: no groups, where they would come out too uneven (few tiles; all are on the chip at once).
+// How a forward launch is divided goes to its kernel in two arguments, `paired` and `total_wg`:
+//   0  single query tiles: the number of work items (the 128-row 16-bit tiles: of heads, query_tiles)
+//   1  causal pairs of tiles: the number of work items
+//   2, 3  key splits, by FewForward (fa_fwd.hip) or FewFp8Forward (fa_fwd_fp8.hip): few_split(), log2 of the groups into which a
+//      head's tiles go so that the XCDs get the same number of groups each, or -1: no groups, where they would come out too
+//      uneven (few tiles; all are on the chip at once)
 constexpr int kFewForward = 2, kFewForward8 = 3;  // (by as many waves as the kernel's tiles have; by eight where those have four)
 inline int few_split(long heads, int N) {
     if (heads % 8 == 0) return 0;
@@ -94,8 +100,9 @@ struct KeySplitFill {
 //            causal:  32 x 512 15.7 / 10.5, 16 x 1000 25.1 / 13.9, 16 x 2000 45.9 / 31.2, 8 x 4096 90 / 54
 //   d = 256  no mask: 16 x 333 17.5 / 12.0, 4 x 2048 57 / 32;  lost: 28 x 333 17.9 / 21.5, 8 x 2048 62 / 62
 //            causal:  16 x 1000 34 / 27, 2 x 8192 204 / 117;  lost: 32 x 333 18.5 / 19.5, 12 x 2048 61 / 61
-// Drawn on 2900 shapes (heads 1 to 384, N from 24 to 16384), before the 128-row tiles gained 5 to 20 %: up to 4.6 times as
-// fast.  Over 1500 others in the last third before the rule's edge 0.76 of the time on average, 1.02 at worst then.
+// Drawn on 2900 shapes (heads 1 to 384, N from 24 to 16384): up to 4.6 times as fast.  Against the tiles as they are now,
+// over 1710 others in the last third before the rule's edge: 0.79 of the time on average, 8 of them above 1.02, at worst 1.06
+// (d = 64 causal, 24 x 2929 51.9 / 48.9).
 inline bool few_forward(long heads, int N, int d, int causal) {
     const KeySplitFill fill(heads, N);
     if (fill.tiles < 3) return false;
@@ -127,8 +134,9 @@ inline int few_forward_waves(long heads, int N, int d, int causal) {
 //            causal:  16 x 1000 18 / 9.7, 8 x 4096 84 / 48;  lost: 48 x 512 11.8 / 12.3
 //   d = 256  no mask: 16 x 333 14.0 / 7.1, 4 x 2048 64 / 19;  lost: 48 x 333 15.0 / 16.3, 20 x 2048 69 / 79
 //            causal:  16 x 1000 33 / 17, 4 x 8192 206 / 107;  lost: 32 x 1500 53 / 57
-// Drawn on 2900 shapes.  The error against 64 bits is smaller so (each part of the keys gets its own reference): d = 128,
-// 4 heads x 1600 with outliers 1.01e-2 / 0.85e-2.
+// Drawn on 2900 shapes.  Over 790 others in the last third before the edge 0.81 of the time on average, 12 of them above 1.02,
+// at worst 1.12 (d = 256 causal, 40 x 438 20.2 / 18.1).  The error against 64 bits is smaller so (each part of the keys gets its own
+// reference), with outliers, 4 heads x 1600: d = 64 1.01e-2 / 0.66e-2, d = 128 1.01e-2 / 0.85e-2, d = 256 causal 1.48e-2 / 1.36e-2.
 inline bool few_forward_fp8(long heads, int N, int d, int causal) {
     const KeySplitFill fill(heads, N);
     if (fill.tiles < (d == 128 ? 5 : 3)) return false;
