@@ -29,9 +29,9 @@ def _compile(src):
     return obj
 
 
-# Sources with MFMAs written as inline assembly: their device assembly is generated once more as
-# text and checked for instructions that touch an MFMA result too early (mfma_hazard_check.py).
-HAZARD_CHECKED = ["fa_bwd.hip", "fa_fwd.hip"]
+# Sources with MFMAs or loads written as inline assembly: their device assembly is generated once more as text and checked
+# for instructions that touch an MFMA result, or write what such an instruction reads, too close to it (mfma_hazard_check.py).
+HAZARD_CHECKED = ["fa_bwd.hip", "fa_fwd.hip", "fa_fwd_fp8.hip"]
 
 
 def _check_hazards(name):
@@ -39,10 +39,11 @@ def _check_hazards(name):
     src, listing = os.path.join(CSRC, name), os.path.join(OBJ, name + ".s")
     subprocess.run([HIPCC, *FLAGS, *EXTRA_FLAGS.get(name, []), "-S", "--cuda-device-only", src, "-o", listing],
                    check=True, stderr=subprocess.DEVNULL)
-    problems = mfma_hazard_check.check(open(listing).read())
+    text = open(listing).read()
+    problems = mfma_hazard_check.check(text) + mfma_hazard_check.check_loads(text)
     if problems:
         lines = "\n".join(f"  {f} +{ln}: {text} ({waited} wait states)" for f, ln, text, waited in problems[:20])
-        raise RuntimeError(f"{name}: {len(problems)} accesses to the result of an inline-assembly MFMA come too early:\n{lines}")
+        raise RuntimeError(f"{name}: {len(problems)} instructions come too close to an inline-assembly MFMA or load:\n{lines}")
     return name
 
 

@@ -193,10 +193,14 @@ static __device__ __forceinline__ BufferWords make_buffer_words(const void* base
     b.w = i32x4{(int)(uint32_t)a, (int)(uint32_t)((a >> 32) & 0xFFFF), (int)bytes, 0x00020000};
     return b;
 }
+// A resource in registers that a vector instruction has written must be five wait states old, which the compiler does not see
+// to ahead of inline assembly: where it spills scalar registers and brings the resource back right ahead of a load (the build's
+// hazard check says so), RELOADED makes them up.  (Everywhere, that costs the kernels 0 to 3 %.)
+template <bool RELOADED = false>
 static __device__ __forceinline__ void global_to_lds_16B(const BufferWords& rsrc, uint32_t lds_base, int byte_off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop %3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                  :
-                 : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(byte_off), "s"(rsrc.w)
+                 : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(byte_off), "s"(rsrc.w), "n"(RELOADED ? 3 : 0)
                  : "memory", "m0");
 }
 

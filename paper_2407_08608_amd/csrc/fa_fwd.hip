@@ -229,7 +229,7 @@ struct SharedTiles {
     }
     // Instruction i of the wave's NI that bring the tile at the resource's start to `offset` (rows past its end: zeros).
     __device__ __forceinline__ void request(const BufferWords& rsrc, uint32_t offset, int i) const {
-        global_to_lds_16B(rsrc, mine + offset + i * 1024, src[i]);
+        global_to_lds_16B<D == 128 && NW == 8>(rsrc, mine + offset + i * 1024, src[i]);
     }
     __device__ __forceinline__ void other_stage(int step) {
         row0 += step;

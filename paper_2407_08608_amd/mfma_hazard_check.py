@@ -1,4 +1,4 @@
-"""Static check of compiled gfx950 assembly: hand-written MFMAs and their neighbours keep their distance.
+"""Static check of compiled gfx950 assembly: hand-written instructions and their neighbours keep their distance.
 
 Some kernels issue `v_mfma_*` through inline assembly so that the accumulator lands in ordinary
 registers.  The compiler's hazard recogniser does not look inside inline assembly, so nothing
@@ -23,6 +23,11 @@ branches in the same way.
 The 8-pass 32x32x16 MFMA needs 11 wait states before a VALU read of its result and the 16-pass
 32x32x64 e4m3 MFMA 19; the compiler leaves 12 (20) or more in the code it schedules itself, and those
 are the defaults here.
+
+`check_loads` does the same for hand-written memory instructions: a scalar register that one of them reads (its resource)
+must not have been written by a vector instruction in the five wait states before it.  Such writes are rarely in the source;
+a scalar register that was spilled comes back through v_readlane, which the compiler may put right ahead of the
+assembly that uses it.
 """
 import re
 import sys
@@ -125,9 +130,8 @@ def _walk(lines, labels, func, start, pending, written, track_new, need, need_16
             return
 
 
-def check(asm_text, need=12, need_16_pass=20, horizon=64):
-    """Returns a list of (function, line number within the function, instruction, wait states so far)."""
-    problems = []
+def _functions(asm_text):
+    """(name, numbered lines, label -> index) of every function of a listing."""
     funcs, cur = [], None
     for raw in asm_text.split("\n"):
         m = re.match(r"^(_Z\w+):", raw)
@@ -142,15 +146,74 @@ def check(asm_text, need=12, need_16_pass=20, horizon=64):
         if lab:
             labels[lab.group(1)] = len(lines)
         lines.append((len(lines) + 1, raw))
-    for name, lines, labels in funcs:
+    return funcs
+
+
+def check(asm_text, need=12, need_16_pass=20, horizon=64):
+    """Returns a list of (function, line number within the function, instruction, wait states so far)."""
+    problems = []
+    for name, lines, labels in _functions(asm_text):
         _walk(lines, labels, name, 0, [], [], True, need, need_16_pass, horizon, problems, 0)
+    return sorted(set(problems), key=problems.index)
+
+
+SGPR_LOAD_STATES = 5  # between a vector instruction's write of a scalar register and a memory instruction that reads it
+_SGPR = re.compile(r"\bs(?:\[(\d+):(\d+)\]|(\d+)\b)")
+
+
+def _sgprs(text):
+    out = set()
+    for m in _SGPR.finditer(text):
+        out.update(range(int(m.group(1)), int(m.group(2)) + 1) if m.group(1) else [int(m.group(3))])
+    return out
+
+
+def _walk_loads(lines, labels, func, start, written, track_new, problems, depth):
+    """As _walk, for scalar registers written by vector instructions: `written` holds [registers, wait states so far]."""
+    in_asm = False
+    for idx in range(start, len(lines)):
+        ln, raw = lines[idx]
+        stripped = raw.strip()
+        if stripped.startswith((";;#ASMSTART", ";;#ASMEND")):
+            in_asm = stripped.startswith(";;#ASMSTART")
+            continue
+        parsed = _parse(raw)
+        if parsed is None:
+            continue
+        text, op, args, states = parsed
+        if in_asm and op.startswith(("buffer_", "global_", "flat_", "scratch_")):
+            read = _sgprs(args)
+            problems.extend((func, ln, text, waited) for regs, waited in written if regs & read)
+        written = [[regs, waited + states] for regs, waited in written if waited + states < SGPR_LOAD_STATES]
+        if op.startswith("v_") and track_new:
+            operands = args.split(",")
+            regs = _sgprs(",".join(operands[:2 if "_co_" in op or "div_scale" in op else 1]))
+            if regs:
+                written.append([regs, 0])
+        if op.startswith("s_cbranch") or op == "s_branch":
+            target = labels.get(args.strip())
+            if written and target is not None and depth < 4:
+                _walk_loads(lines, labels, func, target, written, False, problems, depth + 1)
+            if op == "s_branch":
+                written = []  # what follows is reached by other branches only
+        if not track_new and not written:
+            return
+
+
+def check_loads(asm_text):
+    """Hand-written memory instructions that read a scalar register too soon after a vector instruction wrote it, as check()
+    reports."""
+    problems = []
+    for name, lines, labels in _functions(asm_text):
+        _walk_loads(lines, labels, name, 0, [], True, problems, 0)
     return sorted(set(problems), key=problems.index)
 
 
 def main(argv):
     bad = 0
     for path in argv[1:]:
-        for func, ln, text, waited in check(open(path).read()):
+        listing = open(path).read()
+        for func, ln, text, waited in check(listing) + check_loads(listing):
             print(f"{path}: {func} +{ln}: `{text}` only {waited} wait states after the write of its registers")
             bad += 1
     return 1 if bad else 0

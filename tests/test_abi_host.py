@@ -172,6 +172,29 @@ def test_mfma_hazard_checker_finds_planted_late_operand_writes():
     assert hz.check(kernel + "\tv_mov_b32_e32 v0, v50\n\tv_mfma_f32_32x32x16_bf16 v[16:31], v[0:3], v[4:7], 0\n") == []
 
 
+def test_hazard_checker_finds_planted_late_resource_writes():
+    # a vector instruction's write of a scalar register must be five wait states ahead of a hand-written load that reads it
+    from paper_2407_08608_amd import mfma_hazard_check as hz
+    kernel = "_Z6kernelv:\n"
+    load = "\t;;#ASMSTART\n\ts_mov_b32 m0, s1\n\ts_nop 0\n\tbuffer_load_dwordx4 v180, s[4:7], 0 offen lds\n\t;;#ASMEND\n"
+    other = "\ts_add_i32 s20, s21, s22\n"
+    for write in ("v_readlane_b32 s7, v206, 10", "v_readfirstlane_b32 s4, v3", "v_cmp_gt_i32_e64 s[6:7], v0, v1",
+                  "v_add_co_u32_e64 v2, s[4:5], v0, v1"):
+        w = "\t" + write + "\n"
+        assert len(hz.check_loads(kernel + w + load)) == 1 and len(hz.check_loads(kernel + w + other * 2 + load)) == 1, write
+        assert hz.check_loads(kernel + w + other * 3 + load) == [] and hz.check_loads(kernel + w + "\ts_nop 2\n" + load) == []
+    # registers that the load does not read, scalar writes (interlocked), loads that the compiler placed itself
+    for harmless in ("v_readlane_b32 s8, v206, 10", "s_mov_b32 s7, s9", "v_readlane_b32 s1, v206, 10", "v_mov_b32_e32 v7, s4"):
+        assert hz.check_loads(kernel + "\t" + harmless + "\n" + load) == [], harmless
+    assert hz.check_loads(kernel + "\tv_readlane_b32 s7, v206, 10\n\tbuffer_load_dwordx4 v180, s[4:7], 0 offen\n") == []
+    # the write at a loop's end and the load at its head; the write before a jump, and not what the listing puts in between
+    loop = kernel + ".LBB0_1:\n" + load + "\tv_readlane_b32 s5, v206, 8\n"
+    assert len(hz.check_loads(loop + "\ts_cbranch_scc1 .LBB0_1\n")) == 1
+    assert hz.check_loads(loop + other * 2 + "\ts_cbranch_scc1 .LBB0_1\n") == []
+    jump = kernel + "\tv_readlane_b32 s5, v206, 8\n\ts_branch .LBB0_2\n.LBB0_1:\n" + "%s" + "\ts_endpgm\n.LBB0_2:\n" + "%s"
+    assert hz.check_loads(jump % (load, other)) == [] and len(hz.check_loads(jump % (other, load))) == 1
+
+
 def test_bench_refuses_more_than_one_gpu_with_a_message():
     # the build measures one GPU; the benchmark says so instead of printing a line for several
     import subprocess
