@@ -331,7 +331,8 @@ struct KeySplitTile {
 static __device__ __forceinline__ KeySplitTile key_split_tile(int N, int split) {
     const int n_t = (N + 31) / 32;
     if (split < 0) {
-        const int id = xcd_run(blockIdx.x, gridDim.x);
+        const int xcd = blockIdx.x & 7, per = gridDim.x >> 3, rest = gridDim.x & 7;  // the first `rest` XCDs get one more
+        const int id = xcd * per + min(xcd, rest) + ((int)blockIdx.x >> 3);
         return {id / n_t, id % n_t, n_t};
     }
     const int group = ((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3);
@@ -453,10 +454,12 @@ static __device__ __forceinline__ TileRun query_tiles(int total, int n_qtiles, i
     const int n_items = CAUSAL ? (n_qtiles + 1) / 2 : n_qtiles;
     const int id = BY_XCD ? xcd_run(blockIdx.x, total) : xcd_contiguous(blockIdx.x, total);
     const bool single = CAUSAL && !paired;
+    int single_head = blockIdx.x;
+    if constexpr (CAUSAL && BY_XCD)
+        if (single_head < (total & ~7)) single_head = (single_head & ~7) | ((single_head + (int)blockIdx.y * total) & 7);
     // (both ways without a branch: with one the code behind it is laid out differently, and pairs took 2.5 % longer at
     // d = 64, 16 x 8192, and d = 128, 256 x 300)
-    const int x = blockIdx.x, y = blockIdx.y, turned = BY_XCD && x < (total & ~7) ? (x & ~7) | ((x + y * total) & 7) : x;
-    const int head = single ? turned : id / n_items, i = single ? y : id - head * n_items;
+    const int head = single ? single_head : id / n_items, i = single ? (int)blockIdx.y : id - head * n_items;
     return {head, CAUSAL ? n_qtiles - 1 - i : i, CAUSAL && !single && n_qtiles - 1 - i != i ? i : -1};
 }
 
