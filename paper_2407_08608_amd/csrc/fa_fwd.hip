@@ -294,10 +294,16 @@ static __device__ __forceinline__ void shared_tiles_forward(const uint16_t* __re
     const int lane_now = lane_again(), col = lane_now & 31, half = lane_now >> 5;
     BufferWords k_rsrc = make_buffer_words(kh, (uint32_t)N * D * 2), v_rsrc = make_buffer_words(vh, (uint32_t)N * D * 2);
     const int stage0 = step > 0 ? 0 : Tiles::TILE_B;
+    // Q ahead of the first tiles, or behind: its loads wait for the requests to be issued.  bf16, us, heads x N, behind / ahead:
+    // d = 64 four waves, no mask 296 x 99 6.85 / 6.40, 348 x 116 7.72 / 7.40, 512 x 512 51.5 / 51.7;  causal 296 x 99 7.29 / 7.15
+    // but 128 x 512 11.2 / 11.6;  eight waves 24 x 2048 41.5 / 42.1;  d = 128 level
+    constexpr bool kQFirst = D == 64 && NW == 4 && !CAUSAL;
+    if constexpr (!kQFirst) {
 #pragma unroll
-    for (int i = 0; i < Tiles::NI; ++i) {
-        tiles.request(k_rsrc, stage0, i);
-        if constexpr (Tiles::VS == 2) tiles.request(v_rsrc, Tiles::kV + stage0, i);
+        for (int i = 0; i < Tiles::NI; ++i) {
+            tiles.request(k_rsrc, stage0, i);
+            if constexpr (Tiles::VS == 2) tiles.request(v_rsrc, Tiles::kV + stage0, i);
+        }
     }
 
     // Q_i^T as the B operand, resident in registers for the whole loop
@@ -308,6 +314,14 @@ static __device__ __forceinline__ void shared_tiles_forward(const uint16_t* __re
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
             qreg[ks] = *reinterpret_cast<const i32x4*>(qh + (size_t)row * D + ks * 16 + half * 8);
+    }
+    if constexpr (kQFirst) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < Tiles::NI; ++i) {
+            tiles.request(k_rsrc, stage0, i);
+            if constexpr (Tiles::VS == 2) tiles.request(v_rsrc, Tiles::kV + stage0, i);
+        }
     }
 
     f32x16 oacc[DT];
@@ -345,11 +359,9 @@ static __device__ __forceinline__ void shared_tiles_forward(const uint16_t* __re
         // a wave whose queries all precede this block has nothing to add (causal)
         const bool wave_active = !CAUSAL || key0 <= wave_q0 + 32 * RQ - 1;
         // (opaque: as the other arm of the branch below, this makes the accumulators change registers in every block)
-        // The last block's requests would bring nothing: with four waves at d = 64 they are left out (16 heads x 64 3.34 us
-        // with, 3.27 without; 348 x 100 7.35 / 6.92), with eight the branch costs more (64 x 2048 73.1 / 74.9).
         int all_now = __builtin_amdgcn_readfirstlane(kSpread && wave_active ? 0 : 1);
         asm volatile("" : "+s"(all_now));
-        if (kSpread ? CAUSAL && all_now != 0 : NW == 8 || more)
+        if (!kSpread || (CAUSAL && all_now != 0))
 #pragma unroll
             for (int i = 0; i < 2 * Tiles::NI; ++i) request(i);
         i32x4 pb[SL];
@@ -500,8 +512,8 @@ fa_fwd_16bit_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     int N, int n_qtiles, int total_wg, int paired, int kv_group, float scale) {
     [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    // (the shared tiles come first: behind the code of the key splits the smallest calls took 0.1 us longer, d = 64 causal
-    // 32 x 64 3.93 us instead of 3.80, and more scalar registers were spilled)
+    // (the shared tiles come first: behind the code of the key splits the smallest calls took 0.05 to 0.1 us longer, d = 64 causal
+    // 32 x 64 3.93 us instead of 3.86, d = 128 4.95 instead of 4.87, and more scalar registers were spilled)
     if (__builtin_expect(paired < kFewForward, 1)) {
         shared_tiles_forward<Tag, D, BC, NW, RQ, PD, CAUSAL>(q, k, v, o, lse, N, n_qtiles, total_wg, paired, kv_group, scale, lds);
         return;
