@@ -44,6 +44,8 @@ def test_main_loops_are_the_kernels_they_are_meant_for(key_split):
 
 
 def test_tests_of_whole_tiles_make_no_key_split(key_split):
+    for fp8, d, causal, N, B, H, H_kv in test_tiles_gpu.SHARED_HEADS:
+        assert not key_split(fp8, B * H, N, d, causal), (fp8, d, causal, N, B, H)
     for d, N, H in _parameters(test_tiles_gpu.test_forward_shared_tiles, "d", "N", "H"):
         assert not key_split(False, H, N, d, False) and not key_split(False, H, N, d, True), (d, N, H)
     for d, causal, N, H in _parameters(test_tiles_gpu.test_forward_tiles_of_a_head_on_one_xcd, "d", "causal", "N", "H"):

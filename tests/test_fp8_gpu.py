@@ -111,7 +111,8 @@ def _fwd_fp8_gpu(codes, scales, scale, causal):
 @pytest.mark.parametrize("d", [64, 128, 256])
 @pytest.mark.parametrize("N", [1, 100, 256, 700, 1500])
 def test_fp8_forward_matches_model_oracle(N, d, causal, heavy):
-    # 1500 keys: past the length up to which d = 128 keeps its four-wave tile, with a ragged tail
+    # from 129 keys on so few heads are divided by keys, up to a length with a ragged tail; the kernels' own loops with and
+    # without scales: test_forward_main_loops and test_fp8_main_loops_with_and_without_scales
     B, H = 2, 2
     # heavy: the inputs of the paper's error study (section 4.3), N(0,1) + N(0,100) Bernoulli(0.001)
     _, codes, scales = _prepare(30 + N + d, B, H, N, d, heavy=heavy)
@@ -122,7 +123,7 @@ def test_fp8_forward_matches_model_oracle(N, d, causal, heavy):
 
 @pytest.mark.parametrize("heavy", [False, True])
 def test_fp8_forward_d64_eight_wave_tile_ragged(heavy):
-    # d = 64 without a mask switches to its 256-query tile only above 3072 keys
+    # two heads in the eight-wave kernel of d = 64: divided by keys, eight waves to a workgroup
     B, H, N, d = 1, 2, 3300, 64
     _, codes, scales = _prepare(39, B, H, N, d, heavy=heavy)
     o, lse = _fwd_fp8_gpu(codes, scales, d ** -0.5, False)
@@ -163,8 +164,7 @@ def test_fp8_forward_v_scales_jump_up_and_down_by_large_factors(causal):
 @pytest.mark.parametrize("N,d", [(2300, 128), (2300, 256), (3300, 64), (600, 128)])
 def test_fp8_row_maxima_that_rise_block_after_block(N, d, causal):
     # scores grow from ~0 at the first key to ~80 at the last, so the reference maximum (threshold 2 in
-    # log2 units) rises in almost every key block; the d = 256 kernel applies the rescale one block
-    # behind the scores
+    # log2 units) rises in almost every key block, in the parts of the keys that the waves of a workgroup take
     q, k, v = inputs.rising_maximum_qkv(44, 1, 2, N, d, "bf16")
     codes, scales = zip(*[f8.quantize(x.float().numpy(), None, 128) for x in (q, k, v)])
     o, lse = _fwd_fp8_gpu(codes, scales, d ** -0.5, causal)
@@ -175,8 +175,8 @@ def test_fp8_row_maxima_that_rise_block_after_block(N, d, causal):
 @pytest.mark.parametrize("N", [333, 1500])
 @pytest.mark.parametrize("d", [64, 128, 256])
 def test_fp8_unit_scale_entry_point_matches_oracle(d, N, causal):
-    """fa_fwd with dtype e4m3 takes the codes at unit scale: every kernel (the four-wave tiles at 333 keys, the
-    eight-wave tiles at 1500) has an instantiation without block scales of its own."""
+    """fa_fwd with dtype e4m3 takes the codes at unit scale: every kernel (the four-wave one at 333 keys, the
+    eight-wave one at 1500, here divided by keys) has an instantiation without block scales of its own."""
     B, H = 1, 2
     rng = np.random.default_rng(43 + d)
     qc, kc, vc = (f8.e4m3_encode(rng.standard_normal((B, H, N, d))) for _ in range(3))

@@ -30,7 +30,7 @@ def _tensors(seed, B, H, H_kv, N, d, dtype):
 @pytest.mark.parametrize("H,H_kv", [(4, 4), (4, 2), (6, 2), (3, 1)])
 @pytest.mark.parametrize("N,d", [(129, 64), (300, 128), (1100, 128), (200, 256)])
 def test_gqa_forward_16bit(N, d, H, H_kv, causal, dtype):
-    # N = 1100 at d = 128 runs the ping-pong kernel when non-causal, the others the lock-step tiles
+    # so few heads are divided by keys (the kernels' own loops with shared heads: test_main_loops_with_shared_heads)
     B = 2
     q, k, v = _tensors(100 + N + H, B, H, H_kv, N, d, dtype)
     scale = d ** -0.5

@@ -2,8 +2,8 @@
 
 The fixed-shape tests pick lengths by hand; here lengths are drawn around every boundary where the
 launcher changes kernels or a tile becomes ragged (multiples of 32, 64, 128, 256 plus or minus a
-few rows; the lengths 640, 704, 1280, 1408 and 3072 at which the forward switches tiles), with the
-batch, head and group counts drawn as well.  Tolerances are those of the fixed-shape tests.
+few rows, and lengths near those at which a kernel changes), with the batch, head and group counts drawn
+as well, few heads that the forwards divide by keys from 65 (FP8 d = 128: 129) keys on.  Tolerances are those of the fixed-shape tests.
 """
 import numpy as np
 import pytest

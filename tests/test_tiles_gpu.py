@@ -4,6 +4,7 @@ import pytest
 import torch
 
 import oracle
+from oracle import fp8_oracle as f8
 from helpers import check_fp8_against_model_oracle, f64, max_abs, rmse
 from paper_2407_08608_amd import binding, inputs
 
@@ -475,7 +476,10 @@ MAIN_LOOPS = ([(False, 128, False, N, 24, "fa_fwd_pingpong_kernel") for N in (89
               [(True, 64, False, N, 48, "fa_fwd_fp8_async_kernel<64,") for N in (512, 641, 1409)] +
               [(True, 128, False, N, 48, "fa_fwd_fp8_kernel<128, 64, 4,") for N in (640, 704)] +
               [(True, 128, False, N, 48, "fa_fwd_fp8_async_kernel<128,") for N in (705, 897, 1153)] +
-              [(True, 256, False, N, H, "fa_fwd_fp8_async_kernel<256,") for N, H in ((300, 64), (700, 48), (1031, 48))])
+              [(True, 256, False, N, H, "fa_fwd_fp8_async_kernel<256,") for N, H in ((300, 64), (700, 48), (1031, 48))] +
+              [(True, 64, True, N, H, "fa_fwd_fp8_kernel<64, 64, 4,") for N, H in ((700, 65), (2500, 64))] +
+              [(True, 128, True, 1000, 48, "fa_fwd_fp8_kernel<128, 64, 4,"), (True, 128, True, 2000, 25, "fa_fwd_fp8_async_kernel<128,"),
+               (True, 256, True, 700, 48, "fa_fwd_fp8_async_kernel<256,")])
 
 
 @pytest.mark.parametrize("rising", [False, True])
@@ -498,6 +502,58 @@ def test_forward_main_loops(fp8, d, causal, N, H, rising):
         assert max_abs(f64(o[:, :1]), o_ref) <= 2e-2 + (2.0 ** -8 * np.abs(o_ref).max() if rising else 0)
         assert rmse(f64(o[:, :1]), o_ref) <= (6e-3 if rising else 3e-3) and max_abs(f64(lse[:, :1]), l_ref) <= 2e-3
     assert torch.equal(o, o[:, :1].expand_as(o)) and torch.equal(lse, lse[:, :1].expand_as(lse))
+
+
+@pytest.mark.parametrize("scaled", [False, True])
+@pytest.mark.parametrize("d,causal,N,H", [c[1:5] for c in MAIN_LOOPS if c[0]])
+def test_fp8_main_loops_with_and_without_scales(d, causal, N, H, scaled):
+    # block scales of V and K that jump up and down from block to block, by factors on both sides of the lazy-raise threshold,
+    # with an all-zero V block (scale 1) among them; and the instantiations that take the codes at unit scale
+    if scaled:
+        q, k, v = inputs.qkv(2300 + N, 1, 1, N, d, "bf16")
+        for t, f in enumerate([1.0, 64.0, 0.02, 0.0, 3.0, 1.5, 0.001, 200.0] * (N // 1024 + 1)):
+            v[:, :, t * 128:(t + 1) * 128] *= f
+            k[:, :, t * 128:(t + 1) * 128] *= 0.25 * (1 + t % 4)
+        dev = [binding.fa_fp8_quant_hadamard(t.cuda()) for t in (q.expand(1, H, N, d).contiguous(), k, v)]
+        o, lse = binding.fa_fwd_fp8_gqa(*(p[0] for p in dev), *(p[1] for p in dev), d ** -0.5, causal)
+        (qc, qs), (kc, ks), (vc, vs) = [[a.cpu().numpy() for a in p] for p in dev]
+    else:
+        rng = np.random.default_rng(2300 + N + d)
+        qc, kc, vc = (f8.e4m3_encode(rng.standard_normal((1, 1, N, d))) for _ in range(3))
+        qs = ks = vs = np.ones((1, 1, -(-N // 128)), dtype=np.float32)
+        dev = [torch.from_numpy(c).cuda() for c in (qc, kc, vc)]
+        o, lse = binding.fa_fwd_gqa(dev[0].expand(1, H, N, d).contiguous(), *dev[1:], d ** -0.5, causal, dtype=binding.FA_FP8_E4M3)
+    check_fp8_against_model_oracle(o[:, :1], lse[:, :1], (qc[:, :1], kc, vc), (qs[:, :1], ks, vs), d ** -0.5, causal)
+    assert torch.equal(o, o[:, :1].expand_as(o)) and torch.equal(lse, lse[:, :1].expand_as(lse))
+
+
+# (fp8, d, causal, N, B, H, H_kv): shared heads in the kernels' own loops
+SHARED_HEADS = [(False, 64, False, 700, 2, 24, 6), (False, 64, False, 1031, 2, 24, 8), (False, 64, True, 700, 3, 32, 4), (False, 128, False, 300, 2, 33, 11),
+                (False, 128, False, 1100, 2, 16, 4), (False, 128, True, 1000, 2, 32, 8), (False, 128, True, 2300, 2, 16, 2), (False, 256, False, 600, 2, 24, 6),
+                (False, 256, True, 600, 2, 24, 3), (True, 64, False, 700, 2, 32, 8), (True, 64, True, 700, 3, 32, 4), (True, 128, False, 600, 2, 32, 8),
+                (True, 128, False, 1100, 2, 24, 6), (True, 128, True, 2000, 2, 16, 2), (True, 256, False, 700, 2, 24, 6)]
+
+
+@pytest.mark.parametrize("fp8,d,causal,N,B,H,H_kv", SHARED_HEADS)
+def test_main_loops_with_shared_heads(fp8, d, causal, N, B, H, H_kv):
+    # the first and the last group of every batch against the oracle
+    q = inputs.normal_tensor(2400 + N, "q", (B, H, N, d), "bf16")
+    k, v = (inputs.normal_tensor(2400 + N, n, (B, H_kv, N, d), "bf16") for n in ("k", "v"))
+    n = H // H_kv
+    groups = [(b, g) for b in (0, B - 1) for g in (0, H_kv - 1)]
+    if fp8:
+        dev = [binding.fa_fp8_quant_hadamard(t.cuda()) for t in (q, k, v)]
+        o, lse = binding.fa_fwd_fp8_gqa(*(p[0] for p in dev), *(p[1] for p in dev), d ** -0.5, causal)
+        (qc, qs), kc, vc = [[a.cpu().numpy() for a in p] for p in dev]
+        for b, g in groups:
+            of, kv = (slice(b, b + 1), slice(g * n, g * n + n)), (slice(b, b + 1), slice(g, g + 1))
+            check_fp8_against_model_oracle(o[of], lse[of], (qc[of], kc[0][kv], vc[0][kv]), (qs[of], kc[1][kv], vc[1][kv]), d ** -0.5, causal, kv_heads=1)
+        return
+    o, lse = binding.fa_fwd_gqa(q.cuda(), k.cuda(), v.cuda(), d ** -0.5, causal)
+    for b, g in groups:
+        of, kv = (slice(b, b + 1), slice(g * n, g * n + n)), (slice(b, b + 1), slice(g, g + 1))
+        o_ref, l_ref = oracle.attention_fwd_gqa(f64(q[of]), f64(k[kv]), f64(v[kv]), d ** -0.5, causal)
+        assert max_abs(f64(o[of]), o_ref) <= 2e-2 and rmse(f64(o[of]), o_ref) <= 3e-3 and max_abs(f64(lse[of]), l_ref) <= 2e-3
 
 
 def _bits(t):
