@@ -256,3 +256,43 @@ def test_fp8_error_ordering_on_heavy_tailed_inputs_full_gpu_path(N, d, causal):
           f"no_block_quant={no_block:.3e} no_incoherent={no_incoh:.3e}")
     assert full < baseline
     assert full < 5e-2
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("use_signs", [False, True])
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_quant_blocks_beside_the_ordinary_way(d, use_signs, dtype):
+    """One head of blocks whose amax lies on both sides of the range in which the clamp is left out, zeros of both
+    signs, and a last block of one row."""
+    x = inputs.heavy_tailed_tensor(30 + d, "x", (1, 1, 6 * 128 + 1, d), "f32")
+    scale = [1.0, 1e-33, 3e-31, 1e-29, 1e36, 1.0, 1e-34]  # amax about 1e2 of it with outliers
+    for b, s in enumerate(scale):
+        x[:, :, 128 * b:128 * (b + 1)] *= s
+    if not use_signs:
+        x[:, :, 128 * 4] = 2.5e38
+    x[:, :, 5 * 128:6 * 128] *= 0.0  # zeros of either sign
+    x[:, :, 5 * 128 + 7] = 1.0
+    x = x.to(torch.bfloat16) if dtype == "bf16" else x
+    signs = inputs.random_signs(31, d) if use_signs else None
+    codes, scales = _quant_gpu(x, signs)
+    c_ref, s_ref = f8.quantize(x.float().numpy(), None if signs is None else signs.numpy(), 128)
+    np.testing.assert_array_equal(scales.view(np.uint32), s_ref.view(np.uint32))
+    np.testing.assert_array_equal(codes, c_ref)
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_quant_of_infinities_and_nan(d):
+    """amax passes over NaN; a code is that of clamp(y * (448 / amax)), in which a NaN becomes -448."""
+    x = torch.ones(1, 1, 4 * 128, d)
+    x[0, 0, 5, 3] = float("nan")                # block 0: amax 1
+    x[0, 0, 128 + 9, 1] = float("-inf")         # block 1: amax inf, so 448 / amax = 0 and inf * 0 = NaN
+    x[0, 0, 256 + 64, d - 1] = float("nan")     # block 2: both
+    x[0, 0, 256 + 65, 0] = float("inf")
+    codes, scales = _quant_gpu(x, None)
+    top, low = f8.e4m3_encode(np.array([448.0, -448.0]))
+    want = np.full((4 * 128, d), top, np.uint8)
+    want[5, 3] = low
+    want[128:384] = 0
+    want[128 + 9, 1] = want[256 + 64, d - 1] = want[256 + 65, 0] = low
+    np.testing.assert_array_equal(codes[0, 0], want)
+    np.testing.assert_array_equal(scales[0, 0], np.array([1 / 448, np.inf, np.inf, 1 / 448], np.float32))
