@@ -96,7 +96,7 @@ static __device__ __forceinline__ void store_keys_via_lds(const f32x16 (&acc)[2]
     for (int i = 0; i < 4; ++i) {
         const int key = 8 * i + (lane >> 3), pos = (lane & 7) * 16;
         const i32x4 x = *reinterpret_cast<const i32x4*>(patch + key * 128 + (pos ^ ((key & 4) << 3)));
-        __builtin_amdgcn_raw_buffer_store_b128(x, rsrc, (key0 + key) * ROWB + col_byte + pos, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(x, rsrc, (key0 + key) * ROWB + col_byte + pos, 0, kStreamed);
     }
 }
 

@@ -276,12 +276,19 @@ struct WaveTile {
 
 static __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+constexpr int kStreamed = 2;  // the cache policy bit of a raw buffer store that makes it non-temporal
+
 // Stores a wave's 32-row x (32 DT)-column fp32 accumulator tile (MFMA result layout with rows as
 // lane columns: lane (col, half) holds row `col`; register r of tile dt is column
 // 32 dt + 8 (r / 4) + 4 half + r % 4) as 16-bit elements, scaled by `factor`.  Stored straight from
 // that layout every store instruction would touch 32 rows with 16 bytes each; instead the tile
 // goes through `patch` (4 KiB of LDS private to the wave), 128 bytes of every row at a time, and
-// leaves as whole 128-byte lines: 16-byte chunk c of row r sits at chunk c ^ (r % 8) of the patch.
+// leaves as whole 128-byte lines: 16-byte chunk c of row r sits at chunk c ^ (r % 8) of the patch.  The stores are marked
+// non-temporal (kStreamed): kept in the L2 until the launch ends, the outputs would displace what other workgroups still
+// read.  Over 600 drawn launches (forward, FP8 forward, backward with its key blocks' stores so too) 0.98 of the time, 0.81
+// at best (d = 256 causal, 488 heads x 128) and none above 1.02; d = 128 causal 512 x 512 75.0 -> 72.8 us, 256 x 512 at d = 64
+// 20.8 -> 20.2.  (Written through instead (sc1), small launches take 2 to 3 % longer; the pre-pass's codes, which the next
+// launch reads, and the few-workgroup forms' outputs gain nothing.)
 // `rsrc` covers the [rows][32 DT] destination; rows at or past its end are dropped by the hardware.
 template <typename Tag, int DT>
 static __device__ __forceinline__ void store_rows_via_lds(const f32x16 (&acc)[DT], float factor, char* patch,
@@ -306,7 +313,7 @@ static __device__ __forceinline__ void store_rows_via_lds(const f32x16 (&acc)[DT
         for (int i = 0; i < 4; ++i) {
             const int r = 8 * i + (lane >> 3), pc = lane & 7;
             const i32x4 w = *reinterpret_cast<const i32x4*>(patch + r * 128 + (pc << 4));
-            __builtin_amdgcn_raw_buffer_store_b128(w, rsrc, (row0 + r) * ROWB + hd * 128 + ((pc ^ (r & 7)) << 4), 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(w, rsrc, (row0 + r) * ROWB + hd * 128 + ((pc ^ (r & 7)) << 4), 0, kStreamed);
         }
     }
 }
