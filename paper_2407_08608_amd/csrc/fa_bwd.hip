@@ -838,8 +838,13 @@ constexpr int few_lds_bytes(int d) {
 // fixed order.  Four times as many workgroups, each with a quarter of the serial chain.  What it costs is operand
 // traffic: a Q / dO tile is staged for one wave instead of four and an operand read serves one MFMA, which a chip
 // that is mostly idle has to spare.  A wave stages its own tiles (32 queries of Q and dO), so the loop has no barrier.
-// bf16, B = 1, H = 32 on 4 K/V heads, N = 2048, d = 128, causal (64 workgroups of 128 keys, the longest 256 iterations):
-// whole backward 476 -> 223 us.
+// One wave to a SIMD issues an instruction every four to five cycles, so what a tile takes is its instructions: 500 became 360 of
+// 32 MFMAs.  The mask is put on in a branch that only the tile on the diagonal takes, the next tile of the same head is aimed at
+// by two additions, MFMA and staging request share their wait states, and the waits for the score products stand a step
+// later.  A tile's first operands are read under the last products of the one before.  Requests go out two to a step of
+// the first product: one to a step of both, they came late where many workgroups ask for the same lines.
+// bf16, this pass of d = 128, H = 32 on 4, N = 2048 causal 126 -> 109 us, no mask (whole) 8 on 1 x 2368 143 -> 128.  (Not kept: eight
+// waves in pairs that share tiles and trade P and dS through the LDS, which put all of them in step: 177.)
 template <typename Tag, int D, bool CAUSAL, bool D_READY>
 static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                 const uint16_t* __restrict__ v, const uint16_t* __restrict__ o,
@@ -884,134 +889,166 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
     Tiles tiles(lds_address(lds) + wave * 2 * Tiles::STAGE_B, lane);  // Q, dO
     const int n_t = (N + BQ - 1) / BQ, t0 = CAUSAL ? key0 / BQ : 0;
 
+    // ---- this wave's tiles: numbers wave, wave + NW, ... of the group's tiles in order
+    const int n_all = kv_group * (n_t - t0), mine = (n_all - wave + NW - 1) / NW;
+    int gi = 0, t = t0 + wave;  // the tile aimed at
     float ldpre = 0.f;
     int ldrow = 0;
-    i32x4 opre[KS], dopre[KS];  // without D in the workspace: the lane's half of a row of O and of dO
+    const float* ld_head = lse;  // lanes 0..31 carry L, 32..63 carry D
+    i32x4 opre[KS], dopre[KS];   // without D in the workspace: the lane's half of a row of O and of dO
     BufferWords q_rsrc, do_rsrc;
-    auto aim = [&](int gi, int t) __attribute__((always_inline)) {  // the next requests: tile t of query head gi of the group
-        const size_t qhead = (size_t)bh * kv_group + min(gi, kv_group - 1);
-        const uint32_t bytes = gi < kv_group ? (uint32_t)N * D * 2 : 0;  // past the last tile: zeros that nothing reads
+    auto aim_rows = [&]() __attribute__((always_inline)) {
+        const int row = min(ldrow, N - 1);
+        ldpre = ld_head[row];
+        if constexpr (!D_READY) {
+            const size_t at = ((size_t)bh * kv_group + gi) * N + row;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                opre[ks] = *reinterpret_cast<const i32x4*>(o + at * D + ks * 16 + half * 8);
+                dopre[ks] = *reinterpret_cast<const i32x4*>(dout + at * D + ks * 16 + half * 8);
+            }
+        }
+    };
+    auto aim_head = [&]() __attribute__((always_inline)) {  // the next requests: tile t, counted on into the next query heads
+        while (t >= n_t) {
+            t -= n_t - t0;
+            ++gi;
+        }
+        const size_t qhead = (size_t)bh * kv_group + gi;
+        const uint32_t bytes = (uint32_t)N * D * 2;
         q_rsrc = make_buffer_words(q + qhead * N * D, bytes);
         do_rsrc = make_buffer_words(dout + qhead * N * D, bytes);
         advance(q_rsrc, t * Tiles::TILE_B);
         advance(do_rsrc, t * Tiles::TILE_B);
-        ldrow = t * BQ + col;  // lanes 0..31 carry L, 32..63 carry D
-        const size_t row = qhead * N + min(ldrow, N - 1);
-        if constexpr (D_READY) {
-            ldpre = (half ? dvec : lse)[row];
-        } else {
-            ldpre = lse[row];
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                opre[ks] = *reinterpret_cast<const i32x4*>(o + row * D + ks * 16 + half * 8);
-                dopre[ks] = *reinterpret_cast<const i32x4*>(dout + row * D + ks * 16 + half * 8);
-            }
+        ldrow = t * BQ + col;
+        ld_head = (D_READY && half ? dvec : lse) + qhead * N;
+    };
+    auto aim_next = [&](bool any) __attribute__((always_inline)) {
+        t += NW;
+        if (__builtin_expect(any & (t < n_t), 1)) {  // the same head, which costs a few instructions only
+            advance(q_rsrc, NW * Tiles::TILE_B);
+            advance(do_rsrc, NW * Tiles::TILE_B);
+            ldrow += NW * BQ;
+            aim_rows();
+        } else if (any) {
+            aim_head();
+            aim_rows();
+        } else {  // past the last tile: zeros that nothing reads
+            q_rsrc.w[2] = do_rsrc.w[2] = 0;
         }
     };
-
-    // the tile that the addresses point at, while the tile aimed at is requested into stage st_next
-    auto tile = [&](int q0, int st_next) __attribute__((always_inline)) {
-        f32x4 l4[4];
-        f32x16 sacc, pacc;
-        const uint32_t ld = lds_address(lds_ld) + 16 * half;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {  // register r of 16 is query row 8 (r / 4) + 4 half + r % 4
-            l4[i] = lds_load_4f(ld + 32 * i);
-            const f32x4 t = lds_load_4f(ld + 128 + 32 * i);  // dP starts from -D
-#pragma unroll
-            for (int r = 0; r < 4; ++r) pacc[4 * i + r] = t[r];
-        }
-        auto row_read = [&](int u) { return tiles.row_read(u < KS ? 0 : Tiles::TILE_B, u % KS); };
-        auto tr_read = [&](int u) {  // u = (tensor: dO then Q, slab, dt)
-            return tiles.tr_read(u < 2 * DT ? Tiles::TILE_B : 0, (u / DT) % 2, u % DT);
-        };
-        i32x4 ring[KP], tr[KP], pa[2], dsa[2];
-#pragma unroll
-        for (int u = 0; u < KP; ++u) ring[u] = row_read(u);
-        int first_visible = my_key - q0 - 4 * half;  // of the lane's query rows
-        asm volatile("" : "+v"(first_visible));
-        auto probability = [&](int rr) __attribute__((always_inline)) {
-            float x = fast_exp2(__builtin_fmaf(sacc[rr], sc, -l4[rr >> 2][rr & 3]));
-            // (only the tile on the diagonal needs it, but a second body for the others would cost more: the
-            // accumulators then change halves of the register file in every tile)
-            if (CAUSAL && 8 * (rr >> 2) + (rr & 3) < first_visible) x = 0.f;
-            sacc[rr] = x;
-            if (rr & 1) pa[rr >> 3][(rr >> 1) & 3] = E::pack2(sacc[rr - 1], x);
-        };
-        // S, then dP beside P
-#pragma unroll
-        for (int u = 0; u < 2 * KS; ++u) {
-            const i32x4 a = ring[u % KP];
-            if (u + KP < 2 * KS) ring[u % KP] = row_read(u + KP);
-            else tr[u + KP - 2 * KS] = tr_read(u + KP - 2 * KS);
-            tiles.request(q_rsrc, do_rsrc, st_next, u);
-            if (u == 0) MfmaVgprAcc<Tag>::first(sacc, a, kreg[u]);
-            else if (u < KS) MfmaVgprAcc<Tag>::run(sacc, a, kreg[u]);
-            else if (u == KS) MfmaVgprAcc<Tag>::start(pacc, a, vreg[u - KS]);
-            else MfmaVgprAcc<Tag>::run(pacc, a, vreg[u - KS]);
-            if (u == KS) mfma_result_wait(sacc);
-            if (u >= KS) {
-#pragma unroll
-                for (int n = 0; n < 16 / KS; ++n) probability((u - KS) * (16 / KS) + n);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // dV beside dS, then dK
-        constexpr int GE = 16 / (2 * DT);  // gradients per MFMA of the dV group
-#pragma unroll
-        for (int u = 0; u < 4 * DT; ++u) {
-            const i32x4 b = tr[u % KP];
-            if (u + KP < 4 * DT) tr[u % KP] = tr_read(u + KP);
-            if (u < 2 * DT) {
-                dvacc[u % DT] = E::mma(pa[u / DT], b, dvacc[u % DT]);
-                if (u == 0) mfma_result_wait(pacc);
-#pragma unroll
-                for (int n = 0; n < GE; ++n) {
-                    const int rr = u * GE + n;
-                    pacc[rr] *= sacc[rr];
-                    if (rr & 1) dsa[rr >> 3][(rr >> 1) & 3] = E::pack2(pacc[rr - 1], pacc[rr]);
-                }
-            } else {
-                dkacc[u % DT] = E::mma(dsa[(u - 2 * DT) / DT], b, dkacc[u % DT]);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-
-    // ---- this wave's tiles: numbers wave, wave + NW, ... of the group's tiles in order
-    int gi = 0, t = t0 + wave, st = 0;
-    auto settle = [&]() {  // carry a tile number past the last tile over to the next query head
-        while (t >= n_t && gi < kv_group) {
-            t -= n_t - t0;
-            ++gi;
-        }
-    };
-    settle();
-    aim(gi, t);
-#pragma unroll
-    for (int n = 0; n < Tiles::NREQ; ++n) tiles.request(q_rsrc, do_rsrc, 0, n);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(kreg[ks]), "+a"(vreg[ks]));
-    while (gi < kv_group) {
-        const int q0 = t * BQ;
-        // rows past N get L = +inf so that P = exp2(0 - inf) = 0, and D = 0.  (Keys past N need nothing: what their
-        // lanes compute goes to rows of dK and dV that are not stored.)
-        float d_row = ldpre;
+    // L and -D of the tile aimed at go where its products find them.  Rows past N get L = +inf so that P = exp2(0 - inf) = 0,
+    // and D = 0.  (Keys past N need nothing: what their lanes compute goes to rows of dK and dV that are not stored.)
+    const float ld_factor = half ? -1.f : kLog2e, ld_none = half ? 0.f : INFINITY;
+    auto put_rows = [&]() __attribute__((always_inline)) {
+        float x = ldpre;
         if constexpr (!D_READY) {
-            d_row = 0.f;
+            float d_row = 0.f;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) d_row = dot8<Tag>(opre[ks], dopre[ks], d_row);
             d_row = sum_both_halves(d_row);
+            x = half ? d_row : x;
         }
-        const float x = ldrow < N ? (half ? -d_row : ldpre * kLog2e) : (half ? 0.f : INFINITY);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this tile has landed
-        lds_ld[lane] = x;
-        t += NW;
-        settle();
-        aim(gi, t);
-        tile(q0, st ^ 1);
-        tiles.move(st ? -Tiles::STAGE_B : Tiles::STAGE_B);
-        st ^= 1;
+        x *= ld_factor;
+        lds_ld[lane] = ldrow < N ? x : ld_none;
+    };
+    auto row_read = [&](int u) { return tiles.row_read(u < KS ? 0 : Tiles::TILE_B, u % KS); };
+    auto tr_read = [&](int u) {  // u = (tensor: dO then Q, slab, dt)
+        return tiles.tr_read(u < 2 * DT ? Tiles::TILE_B : 0, (u / DT) % 2, u % DT);
+    };
+    i32x4 ring[KP];  // the first row operands of a tile are read under the last products of the one before
+
+    // The tile whose first operands are in `ring`, while the tile aimed at is requested into the other stage
+    auto tile = [&](int q0, int st, int left) __attribute__((always_inline)) {  // `left`: tiles after this one
+        f32x4 l4[4];
+        f32x16 sacc, pacc;
+        const uint32_t ld = lds_address(lds_ld) + 16 * half;
+        const uint32_t next = tiles.base + (st ^ 1) * Tiles::STAGE_B;
+        i32x4 tr[KP], pa[2], dsa[2];
+        auto probability = [&](int rr) __attribute__((always_inline)) {
+            sacc[rr] = fast_exp2(__builtin_fmaf(sacc[rr], sc, -l4[rr >> 2][rr & 3]));
+            if (rr & 1) pa[rr >> 3][(rr >> 1) & 3] = E::pack2(sacc[rr - 1], sacc[rr]);
+        };
+        // S, then dP beside P, which starts one step late: the wait for S has passed by then
+        static_for<2 * KS>([&](auto step) __attribute__((always_inline)) {
+            constexpr int u = decltype(step)::value;
+            const i32x4 a = ring[u % KP];
+            if constexpr (u + KP < 2 * KS) ring[u % KP] = row_read(u + KP);
+            else tr[u + KP - 2 * KS] = tr_read(u + KP - 2 * KS);
+            if constexpr (u < 4) {  // register r of 16 is query row 8 (r / 4) + 4 half + r % 4
+                l4[u] = lds_load_4f(ld + 32 * u);
+                const f32x4 x = lds_load_4f(ld + 128 + 32 * u);  // dP starts from -D
+#pragma unroll
+                for (int r = 0; r < 4; ++r) pacc[4 * u + r] = x[r];
+            }
+            if constexpr (u < KS) global_to_lds_16B(do_rsrc, next + Tiles::TILE_B + u * 1024, tiles.src[u]);
+            if constexpr (u == 0) MfmaVgprAcc<Tag>::template first_and_load<u * 1024>(sacc, a, kreg[u], q_rsrc, next, tiles.src[u]);
+            else if constexpr (u < KS) MfmaVgprAcc<Tag>::template run_and_load<u * 1024>(sacc, a, kreg[u], q_rsrc, next, tiles.src[u]);
+            else if constexpr (u == KS) MfmaVgprAcc<Tag>::start(pacc, a, vreg[u - KS]);
+            else MfmaVgprAcc<Tag>::run(pacc, a, vreg[u - KS]);
+            if constexpr (u == KS + 1) mfma_result_wait_rest<4>(sacc);
+            if constexpr (u > KS) {
+                constexpr int i = u - KS - 1;
+#pragma unroll
+                for (int rr = i * 16 / (KS - 1); rr < (i + 1) * 16 / (KS - 1); ++rr) probability(rr);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        if (CAUSAL && __builtin_expect(q0 == key0, 0)) {  // the tile on the diagonal
+            const int first_visible = my_key - q0 - 4 * half;  // of the lane's query rows
+#pragma unroll
+            for (int rr = 0; rr < 16; ++rr) {
+                if (8 * (rr >> 2) + (rr & 3) < first_visible) sacc[rr] = 0.f;
+                if (rr & 1) pa[rr >> 3][(rr >> 1) & 3] = E::pack2(sacc[rr - 1], sacc[rr]);
+            }
+        }
+        // dV beside dS, which starts one step late likewise, then dK
+        constexpr int GE = 16 / (2 * DT);  // gradients per MFMA of the dV group
+        static_for<4 * DT>([&](auto step) __attribute__((always_inline)) {
+            constexpr int u = decltype(step)::value;
+            const i32x4 b = tr[u % KP];
+            if constexpr (u + KP < 4 * DT) tr[u % KP] = tr_read(u + KP);
+            if constexpr (u == 4 * DT - 2) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the next tile has landed
+                if (D_READY || left > 0) put_rows();
+                tiles.move(st ? -Tiles::STAGE_B : Tiles::STAGE_B);
+            }
+            if constexpr (u >= 4 * DT - 2)
+#pragma unroll
+                for (int i = 0; i < KP / 2; ++i) ring[(u - (4 * DT - 2)) * (KP / 2) + i] = row_read((u - (4 * DT - 2)) * (KP / 2) + i);
+            if constexpr (u < 2 * DT) dvacc[u % DT] = E::mma(pa[u / DT], b, dvacc[u % DT]);
+            else dkacc[u % DT] = E::mma(dsa[(u - 2 * DT) / DT], b, dkacc[u % DT]);
+            if constexpr (u == 1) mfma_result_wait_rest<1>(pacc);
+            if constexpr (u >= 1 && u <= 2 * DT)
+#pragma unroll
+                for (int n = 0; n < GE; ++n) {
+                    const int rr = (u - 1) * GE + n;
+                    pacc[rr] *= sacc[rr];
+                    if (rr & 1) dsa[rr >> 3][(rr >> 1) & 3] = E::pack2(pacc[rr - 1], pacc[rr]);
+                }
+            if constexpr (u == 4 * DT - 1) aim_next(left > 1);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+
+    if (mine > 0) {
+        aim_head();
+        aim_rows();
+#pragma unroll
+        for (int n = 0; n < Tiles::NREQ; ++n) tiles.request(q_rsrc, do_rsrc, 0, n);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(kreg[ks]), "+a"(vreg[ks]));
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        put_rows();
+#pragma unroll
+        for (int u = 0; u < KP; ++u) ring[u] = row_read(u);
+        int q0 = t * BQ;
+        aim_next(mine > 1);
+        for (int n = 0, st = 0; n < mine; ++n, st ^= 1) {
+            const int q0_next = t * BQ;
+            tile(q0, st, mine - 1 - n);
+            q0 = q0_next;
+        }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the zeros of the last request: the LDS is about to be reused
 
@@ -1109,39 +1146,43 @@ static __device__ __forceinline__ void dq_few(int block, const uint16_t* __restr
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this tile has landed
         advance(k_rsrc, NW * Tiles::TILE_B);
         advance(v_rsrc, NW * Tiles::TILE_B);
-        auto row_read = [&](int u) { return tiles.row_read(u < KS ? 0 : Tiles::TILE_B, u % KS); };
+        i32x4 ring[KP];
+#pragma unroll
+        for (int u = 0; u < KP; ++u) ring[u] = tiles.row_read(0, u);
+        const uint32_t next = tiles.base + (st ^ 1) * Tiles::STAGE_B;
+        auto issue = [&](auto step, f32x16& c, const i32x4& a, const i32x4& b) __attribute__((always_inline)) {
+            // past this workgroup's last tile the requests bring rows (or zeros) that nothing reads
+            constexpr int u = decltype(step)::value, to = (u & 1) * Tiles::TILE_B + (u >> 1) * 1024;
+            const BufferWords& rsrc = u & 1 ? v_rsrc : k_rsrc;
+            if constexpr (u == 0) MfmaVgprAcc<Tag>::template first_and_load<to>(c, a, b, rsrc, next, tiles.src[u >> 1]);
+            else if constexpr (u == KS) MfmaVgprAcc<Tag>::template start_and_load<to>(c, a, b, rsrc, next, tiles.src[u >> 1]);
+            else MfmaVgprAcc<Tag>::template run_and_load<to>(c, a, b, rsrc, next, tiles.src[u >> 1]);
+        };
         f32x16 sacc, pacc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) pacc[r] = -d_row;  // dP - D comes out of the MFMAs
-        i32x4 ring[KP], tr[KP], dsb[2];
-#pragma unroll
-        for (int u = 0; u < KP; ++u) ring[u] = row_read(u);
-        __builtin_amdgcn_sched_barrier(0);
-        int bound = limit - t * BK - 4 * half;  // key 8 (r / 4) + r % 4 of the lane's half is visible up to here
-        asm volatile("" : "+v"(bound));
-        // S^T, then dP^T beside P
-#pragma unroll
-        for (int u = 0; u < 2 * KS; ++u) {
+        i32x4 tr[KP], dsb[2];
+        // S^T, then dP^T beside P, which starts one step late: the wait for S has passed by then
+        static_for<2 * KS>([&](auto step) __attribute__((always_inline)) {
+            constexpr int u = decltype(step)::value;
             const i32x4 a = ring[u % KP];
-            if (u + KP < 2 * KS) ring[u % KP] = row_read(u + KP);
+            if constexpr (u + KP < 2 * KS) ring[u % KP] = tiles.row_read(u + KP < KS ? 0 : Tiles::TILE_B, (u + KP) % KS);
             else tr[u + KP - 2 * KS] = tiles.tr_read(0, (u + KP - 2 * KS) / DT, (u + KP - 2 * KS) % DT);
-            // past this workgroup's last tile these bring rows (or zeros) that nothing reads
-            tiles.request(k_rsrc, v_rsrc, st ^ 1, u);
-            if (u == 0) MfmaVgprAcc<Tag>::first(sacc, a, qreg[u]);
-            else if (u < KS) MfmaVgprAcc<Tag>::run(sacc, a, qreg[u]);
-            else if (u == KS) MfmaVgprAcc<Tag>::start(pacc, a, doreg[u - KS]);
-            else MfmaVgprAcc<Tag>::run(pacc, a, doreg[u - KS]);
-            if (u == KS) mfma_result_wait(sacc);
-            if (u >= KS) {
+            if constexpr (u < KS) issue(step, sacc, a, qreg[u]);
+            else issue(step, pacc, a, doreg[u - KS]);
+            if constexpr (u == KS + 1) mfma_result_wait_rest<7>(sacc);
+            if constexpr (u > KS) {
+                constexpr int i = u - KS - 1;
 #pragma unroll
-                for (int n = 0; n < 16 / KS; ++n) {
-                    const int r = (u - KS) * (16 / KS) + n;
-                    sacc[r] = fast_exp2(__builtin_fmaf(sacc[r], sc, -l2));
-                    // keys past N (K = 0, but their P may be anything) and keys after the query
-                    if (8 * (r >> 2) + (r & 3) > bound) sacc[r] = 0.f;
-                }
+                for (int r = i * 16 / (KS - 1); r < (i + 1) * 16 / (KS - 1); ++r) sacc[r] = fast_exp2(__builtin_fmaf(sacc[r], sc, -l2));
             }
             __builtin_amdgcn_sched_barrier(0);
+        });
+        if (__builtin_expect(t == n_t - 1 || (CAUSAL && t == qt), 0)) {  // keys past N (K = 0, but their P may be anything) and keys after the query
+            const int bound = limit - t * BK - 4 * half;                 // key 8 (r / 4) + r % 4 of the lane's half is visible up to here
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (8 * (r >> 2) + (r & 3) > bound) sacc[r] = 0.f;
         }
         mfma_result_wait(pacc);
 #pragma unroll
@@ -1183,27 +1224,218 @@ static __device__ __forceinline__ void dq_few(int block, const uint16_t* __restr
     }
 }
 
-// One launch for either pass or for both: workgroups 0 .. n_dkdv - 1 take 32 keys each, the rest 32 queries each.
-// With both in one launch the dQ work fills the CUs that the shorter key blocks of a causal dK/dV pass leave idle.
+// The dQ pass with 128 queries to a workgroup, 32 to each of its four waves, which walk all the keys together: every tile of
+// K and V is staged once for the four of them, three tiles ahead into a ring of eight, one barrier to a tile.  The last product
+// comes one tile late, beside the next tile's dS; without that, 128 queries took 68.3 us where these take 63.5 and 32 queries 96.6
+// (bf16, D and this pass, d = 128, H = 32 on 4, N = 2048 causal).
+template <typename Tag, int D, bool CAUSAL, bool D_READY>
+static __device__ __forceinline__ void dq_rows(int block, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                                               const uint16_t* __restrict__ v, const uint16_t* __restrict__ o,
+                                               const uint16_t* __restrict__ dout, const float* __restrict__ lse,
+                                               float* __restrict__ dvec, uint16_t* __restrict__ dq, int N,
+                                               int n_heads, int kv_group, float scale, char* lds) {
+    using Tiles = WaveTiles<D>;
+    constexpr int NW = 4, BR = 32 * NW, BK = Tiles::ROWS, STAGES = 8, LEAD = 3;
+    constexpr int KS = D / 16, DT = D / 32;
+    constexpr int KP = D == 128 ? 8 : 4;      // steps by which operand reads lead their MFMAs
+    constexpr int PER = Tiles::NREQ / NW;     // staging instructions of a wave per tile
+    static_assert(few_lds_bytes(D) >= STAGES * Tiles::STAGE_B, "the ring must fit");
+    using E = Elem<Tag>;
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int col = lane & 31, half = lane >> 5;
+    const int bh = block % n_heads;
+    const int n_t = (N + BK - 1) / BK, n_q = (N + BR - 1) / BR;
+    const int qt = CAUSAL ? n_q - 1 - block / n_heads : block / n_heads;  // the longest rows first
+    const int q0 = qt * BR + wave * 32;
+    const int row = min(q0 + col, N - 1);  // rows past N compute a copy of row N-1, never stored
+    const int limit = CAUSAL ? row : N - 1;  // last visible key
+    const size_t head_off = (size_t)bh * N * D;
+    const size_t kv_off = (size_t)(bh / kv_group) * N * D;
+    float sc = scale * kLog2e;
+    asm volatile("" : "+v"(sc));
+    // the next tile to be requested (rows past N, and tiles past the last one, read as zero)
+    BufferWords k_rsrc = make_buffer_words(k + kv_off, (uint32_t)N * D * 2), v_rsrc = make_buffer_words(v + kv_off, (uint32_t)N * D * 2);
+    Tiles tiles(lds_address(lds), lane);  // K, V
+    int src[PER / 2];                     // of the wave's pieces of a tile
+#pragma unroll
+    for (int i = 0; i < PER / 2; ++i) {
+        src[i] = Tiles::src_of(wave * (PER / 2) + i, lane);
+        asm volatile("" : "+v"(src[i]));
+    }
+    const uint32_t piece = tiles.base + wave * (PER / 2) * 1024;
+    auto request = [&](int st, int n) __attribute__((always_inline)) {  // instruction n of PER
+        global_to_lds_16B(n & 1 ? v_rsrc : k_rsrc, piece + st * Tiles::STAGE_B + (n & 1) * Tiles::TILE_B + (n >> 1) * 1024, src[n >> 1]);
+    };
+    auto next_tile = [&]() __attribute__((always_inline)) {
+        advance(k_rsrc, Tiles::TILE_B);
+        advance(v_rsrc, Tiles::TILE_B);
+    };
+
+    const int n_tiles = CAUSAL ? min((qt + 1) * NW, n_t) : n_t;
+#pragma unroll
+    for (int st = 0; st < LEAD; ++st) {
+#pragma unroll
+        for (int n = 0; n < PER; ++n) request(st, n);
+        next_tile();
+    }
+
+    i32x4 qreg[KS], doreg[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const size_t off = head_off + (size_t)row * D + ks * 16 + half * 8;
+        qreg[ks] = *reinterpret_cast<const i32x4*>(q + off);
+        doreg[ks] = *reinterpret_cast<const i32x4*>(dout + off);
+    }
+    float d_row = 0.f;  // D = rowsum(dO o O)
+    if constexpr (D_READY) {
+        d_row = dvec[(size_t)bh * N + row];
+    } else {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            d_row = dot8<Tag>(*reinterpret_cast<const i32x4*>(o + head_off + (size_t)row * D + ks * 16 + half * 8), doreg[ks], d_row);
+        d_row = sum_both_halves(d_row);
+        if (half == 0 && q0 + col < N) dvec[(size_t)bh * N + q0 + col] = d_row;
+    }
+    const float l2 = lse[(size_t)bh * N + row] * kLog2e;
+    f32x16 acc[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[dt][r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(qreg[ks]), "+a"(doreg[ks]));
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // from here on the wave's requests are all that the counter counts
+
+    auto arrive = [&]() __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((LEAD - 1) * PER) : "memory");  // the wave's pieces of the next tile have landed
+        __builtin_amdgcn_s_barrier();  // everyone's have, and the tile before this one is done with
+        asm volatile("" ::: "memory");
+    };
+    const int own_tiles = CAUSAL ? min(n_tiles, qt * NW + wave + 1) : n_tiles;  // that concern the wave
+    i32x4 ring[KP], ds[2];  // the next tile's first row operands; dS^T of the tile before, whose product comes one tile late
+    arrive();
+#pragma unroll
+    for (int u = 0; u < KP; ++u) ring[u] = tiles.row_read(0, u);
+    auto tr_read = [&](int u) { return tiles.tr_read(0, u / DT, u % DT); };
+    int st = 0, t = 0, tr_move = 0;
+    auto tile = [&](auto first_tile) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first_tile)::value;
+        const uint32_t next = piece + (st + LEAD) % STAGES * Tiles::STAGE_B;
+        const int row_move = st == STAGES - 1 ? -(STAGES - 1) * Tiles::STAGE_B : Tiles::STAGE_B;
+        f32x16 sacc, pacc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) pacc[r] = -d_row;  // dP - D comes out of the MFMAs
+        i32x4 tr[KP], ds_new[2];
+        // S^T, then dP^T beside P, which starts one step late: the wait for S has passed by then
+        static_for<2 * KS>([&](auto step) __attribute__((always_inline)) {
+            constexpr int u = decltype(step)::value;
+            const i32x4 a = ring[u % KP];
+            if constexpr (u + KP < 2 * KS) ring[u % KP] = tiles.row_read(u + KP < KS ? 0 : Tiles::TILE_B, (u + KP) % KS);
+            else if constexpr (!FIRST) tr[u + KP - 2 * KS] = tr_read(u + KP - 2 * KS);
+            f32x16& c = u < KS ? sacc : pacc;
+            const i32x4& b = u < KS ? qreg[u % KS] : doreg[u % KS];
+            constexpr int EVERY = 2 * KS / PER, n = u / EVERY, to = (n & 1) * Tiles::TILE_B + (n >> 1) * 1024;
+            const BufferWords& rsrc = n & 1 ? v_rsrc : k_rsrc;
+            if constexpr (u == 0) MfmaVgprAcc<Tag>::template first_and_load<to>(c, a, b, rsrc, next, src[n >> 1]);
+            else if constexpr (u == KS) MfmaVgprAcc<Tag>::template start_and_load<to>(c, a, b, rsrc, next, src[n >> 1]);
+            else if constexpr (u % EVERY == 0) MfmaVgprAcc<Tag>::template run_and_load<to>(c, a, b, rsrc, next, src[n >> 1]);
+            else MfmaVgprAcc<Tag>::run(c, a, b);
+            if constexpr (u == KS + 1) mfma_result_wait_rest<7>(sacc);
+            if constexpr (u > KS) {
+                constexpr int i = u - KS - 1;
+#pragma unroll
+                for (int r = i * 16 / (KS - 1); r < (i + 1) * 16 / (KS - 1); ++r) sacc[r] = fast_exp2(__builtin_fmaf(sacc[r], sc, -l2));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        if (__builtin_expect(t == n_t - 1 || (CAUSAL && t * BK == q0), 0)) {  // keys past N (K = 0, but their P may be anything) and keys after the query
+            const int bound = limit - t * BK - 4 * half;                      // key 8 (r / 4) + r % 4 of the lane's half is visible up to here
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (8 * (r >> 2) + (r & 3) > bound) sacc[r] = 0.f;
+        }
+        // dQ^T += K^T dS^T of the tile before beside this one's dS, and at the end the next tile's first operands
+        static_for<2 * DT>([&](auto step) __attribute__((always_inline)) {
+            constexpr int u = decltype(step)::value;
+            i32x4 a = {};
+            if constexpr (!FIRST) {
+                a = tr[u % KP];
+                if constexpr (u + KP < 2 * DT) tr[u % KP] = tr_read(u + KP);
+            }
+            if constexpr (u == 2 * DT - KP) {
+                next_tile();
+                arrive();
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) tiles.row_at[ks] += row_move;
+                if constexpr (!FIRST)
+#pragma unroll
+                    for (int dt = 0; dt < DT; ++dt) {
+                        tiles.tr_at[dt][0] += tr_move;
+                        tiles.tr_at[dt][1] += tr_move;
+                    }
+            }
+            if constexpr (u >= 2 * DT - KP) ring[u - (2 * DT - KP)] = tiles.row_read(0, u - (2 * DT - KP));
+            if constexpr (!FIRST) acc[u % DT] = E::mma(a, ds[u / DT], acc[u % DT]);
+            if constexpr (u == 1) {
+                if constexpr (FIRST) mfma_result_wait(pacc);
+                else mfma_result_wait_rest<8>(pacc);
+            }
+            if constexpr (u > 0)
+#pragma unroll
+                for (int r = (u - 1) * 16 / (2 * DT - 1); r < u * 16 / (2 * DT - 1); ++r) {
+                    pacc[r] *= sacc[r];
+                    if (r & 1) ds_new[r >> 3][(r >> 1) & 3] = E::pack2(pacc[r - 1], pacc[r]);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        ds[0] = ds_new[0];
+        ds[1] = ds_new[1];
+        tr_move = row_move;
+        st = (st + 1) % STAGES;
+        ++t;
+    };
+    tile(std::true_type{});
+    while (t < own_tiles) tile(std::false_type{});
+#pragma unroll
+    for (int u = 0; u < 2 * DT; ++u) acc[u % DT] = E::mma(tr_read(u), ds[u / DT], acc[u % DT]);
+    for (; t < n_tiles; ++t) {  // the others' last tiles
+#pragma unroll
+        for (int n = 0; n < PER; ++n) request((st + LEAD) % STAGES, n);
+        next_tile();
+        arrive();
+        st = (st + 1) % STAGES;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last requests: the LDS is about to be reused
+    __syncthreads();
+    store_rows_via_lds<Tag, DT>(acc, scale, lds + wave * 4096, make_buffer(dq + head_off, (uint32_t)N * D * 2), q0, lane);
+}
+
+// One launch for the dK/dV pass or for both: n_dkdv workgroups take 32 keys each, the others 32 or 128 queries each
+// (choose_bwd_forms).  With both in one launch the dQ work fills the CUs that the shorter key blocks of a causal dK/dV pass leave
+// idle.  (dQ alone comes here where it has to follow the dK/dV pass.)
 // D_READY: D is in the workspace already; otherwise both kinds compute it for the rows they work on (the dK/dV kind
 // once per tile; own_row_sums says when).
-// bf16 causal, whole backward, us, two launches / one and the row sums: d = 128 H = 4, N = 1024 27 / 17, H = 16 on 4,
-// N = 2048 126 / 97, H = 32 on 4, N = 2048 217 / 195; d = 64 H = 16, N = 1024 22.5 / 18.9.  Where neither pass leaves
-// CUs idle the two take the same time.
+constexpr int kDqRows = 1, kDqFirst = 2;  // dq_form: 128 queries to a workgroup; dQ work ahead of the key blocks
 template <typename Tag, int D, bool CAUSAL, bool D_READY>
 __global__ void __launch_bounds__(256, D == 64 ? 2 : 1)
 fa_bwd_few_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                   const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
                   float* __restrict__ dvec, uint16_t* __restrict__ dq, uint16_t* __restrict__ dk,
-                  uint16_t* __restrict__ dv, int N, int n_dkdv, int n_heads, int kv_group, float scale) {
+                  uint16_t* __restrict__ dv, int N, int n_dkdv, int dq_form, int n_heads, int kv_group, float scale) {
     [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
     __shared__ __attribute__((aligned(1024))) char lds[few_lds_bytes(D)];
     __shared__ __attribute__((aligned(16))) float lds_ld[4 * 64];
-    const int block = blockIdx.x;
-    if (block < n_dkdv)
-        dkdv_few<Tag, D, CAUSAL, D_READY>(block, q, k, v, o, dout, lse, dvec, dk, dv, N, n_heads / kv_group, kv_group, scale, lds, lds_ld);
+    const int n_dq = gridDim.x - n_dkdv, block = blockIdx.x;
+    const bool dq_first = dq_form & kDqFirst, is_dq = dq_first ? block < n_dq : block >= n_dkdv;
+    const int id = block - (is_dq == dq_first ? 0 : is_dq ? n_dkdv : n_dq);
+    if (!is_dq)
+        dkdv_few<Tag, D, CAUSAL, D_READY>(id, q, k, v, o, dout, lse, dvec, dk, dv, N, n_heads / kv_group, kv_group, scale, lds, lds_ld);
+    else if (dq_form & kDqRows)
+        dq_rows<Tag, D, CAUSAL, D_READY>(id, q, k, v, o, dout, lse, dvec, dq, N, n_heads, kv_group, scale, lds);
     else
-        dq_few<Tag, D, CAUSAL, D_READY>(block - n_dkdv, q, k, v, o, dout, lse, dvec, dq, N, n_heads, kv_group, scale, lds);
+        dq_few<Tag, D, CAUSAL, D_READY>(id, q, k, v, o, dout, lse, dvec, dq, N, n_heads, kv_group, scale, lds);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1570,43 +1802,52 @@ size_t bwd_workspace_bytes(int B, int H, int N, int d) {
 
 // Which forms the two passes take at d = 64 and 128.  The 32-query / 32-key forms (fa_bwd_few_kernel) make four times as
 // many workgroups, each with a quarter of the serial chain, at a higher price per MFMA, so what counts is how often they
-// fill the chip (`chip`: how many it holds at once) and how long the chain is that they shorten: every limit below grows
-// with the chain, in 32-row tiles, up to `most` fillings.  Under a causal mask, where the large forms idle at the short
-// end, they grow further.  The dQ pass takes the form by itself only at d = 128 without a mask (over long sequences);
-// elsewhere the one launch covers what it would win.
-// Whole backward, bf16, us; large forms, dQ alone in its form, dK/dV alone in its, both in one launch:
-//   d = 128 causal   N = 128:  H = 64 21.5, 19.3, 17.2, 14.9;  H = 96 22.0, 25.3, 23.2, 20.6;  H = 128 22.4, 25.8, 23.6, 25.9
-//           causal   N = 512:  H = 32 42.4, 38.3, 38.5, 32.3;  H = 64 45.0, 55.1, 54.4, 61.4
-//           causal   N = 2048: H = 16 129, 112, 130, 112;  H = 24 136, 144, 164, 167;  H = 32 on 4 472, 501, 226, 199
-//           no mask  N = 512:  H = 20 40.0, 39.6, 40.0, 29.3;  H = 32 41.0, 40.7, 41.2, 38.4
-//           no mask  N = 4096: H = 6 250, 225, 265, 241;  N = 1024: H = 32 on 8 141, 157, 81.5, 97.6
-//   d = 64  causal   N = 256:  H = 64 18.3, 16.4, 16.5, 14.6;  H = 192 22.8, 30.3, 29.7, 34.5
-//           causal   N = 1536: H = 40 72.8, 77.4, 79.9, 79.5
-//           no mask  N = 640:  H = 28 32.5, 33.0, 32.6, 25.0;  N = 777: H = 28 41.0, 41.0, 40.1, 33.5
-// Over about 2600 shapes (heads 1 to 512, groups of 1 to 32, N from 16 to 16384) the choice is 0.4 % off the best of the
-// five on average.
+// fill the chip (kChip: how many it holds at once) and how long the chain is that they shorten: the limits grow with the
+// chain, in 32-row tiles.  Under a causal mask, where the large forms idle at the short end, they grow further, and with
+// four or more query heads to a key/value head, whose key blocks are long chains, once more.
+// In the one launch the dQ pass has 32 queries to a workgroup, its waves splitting the keys, or 128 (kDqRows): a quarter of the
+// staging, starts and ends, but the whole chain.  128 win from `longest` fillings on, and beside long key blocks always
+// (`uneven`: but where both kinds take equally long and come out as one and a half rounds).  Whichever has the longer
+// chains goes first: key blocks of a group of g have g / 4 of the 128-query workgroups'.
+// Whole backward, bf16, us; large forms, dK/dV alone in its 32-key form, one launch (lost to the large forms: the last two):
+//   d = 128 causal   30 x 512 41.8, 38.1, 27.0;  14 on 7 x 4608 399, 354, 300;  32 on 4 x 2048 472, 226, 142;
+//                    32 on 4 x 3584 877, 387, 442;  24 on 12 x 4096 386, 387, 389
+//           no mask  32 x 512 40.6, 39.9, 30.4;  9 x 3584 243, 270, 229;  8 on 1 x 512 127, 52, 35;  90 on 45 x 1024 208, 309, 312;
+//                    109 x 113 20.8, 23.4, 22.7
+//   d = 64  causal   42 x 1024 52.8, 52.3, 41.2;  10 x 5120 217, 190, 138;  72 on 9 x 512 107, 40, 30;  77 x 1536 113, 168, 163;
+//                    109 x 320 23.5, 29.2, 26.4
+//           no mask  22 x 1536 80.4, 77.5, 65.3;  40 on 5 x 512 99, 37, 27;  57 x 512 28.6, 37.6, 36.1;  15 x 3328 175, 186, 198
+// One launch; 32 queries, 128 behind the key blocks, 128 ahead of them (the last two: 32 stay):
+//   d = 128 causal   32 x 512 30.8, 32.6, 26.1;  64 x 256 28.3, 27.1, 23.7;  16 on 8 x 1024 35.8, 37.5, 31.0;  8 x 1024 21.4, 33.9, 28.9;
+//                    4 on 2 x 1024 21.0, 27.3, 27.4
+//           no mask  8 x 2048 76, 85, 70;  64 on 8 x 256 25.4, 25.0, 25.0;  2 x 4096 73, 119, 86;  8 on 4 x 1024 26.4, 29.7, 29.8
+//   d = 64           32 on 4 x 1024, no mask 58.1, 56.0, 59.8;  64 on 8 x 512, causal 30.4, 28.5, 30.9;  16 x 1024, causal 18.8, 26.8, 22.6
+// Over 7300 drawn shapes (1 to 256 heads, groups of 1 to 8, N from 64 to 8192) 0.3 to 1.4 % off the best of five on average,
+// by head dimension and mask.
 struct BwdForms {
-    bool dq_few, dkdv_few, one_launch;
+    bool dkdv_few, one_launch;
+    int dq_form;
 };
 template <int D>
 inline BwdForms choose_bwd_forms(long heads, long kv_heads, int N, int causal) {
-    if constexpr (D > 128) return {false, false, false};
+    if constexpr (D > 128) return {false, false, 0};
     struct Limit {  // workgroups, in fillings of the chip: min(most, base + tiles / step)
         float base, step, most;
         float at(long tiles) const { const float x = base + (float)tiles / step; return x < most ? x : most; }
     };
     constexpr int kChip = D == 64 ? 512 : 256;
-    const Limit one = D == 64 ? (causal ? Limit{1.25f, 8, 9} : Limit{1.25f, 12, 4.5f}) : (causal ? Limit{2, 6, 9} : Limit{2.25f, 12, 5});
+    const Limit one = D == 64 ? (causal ? Limit{3.6f, 16, 10} : Limit{2.05f, 24, 5.8f}) : (causal ? Limit{5.8f, 22, 12} : Limit{3.6f, 26, 6.5f});
     const Limit key = D == 64 ? (causal ? Limit{1, 64, 4} : Limit{1, 128, 3}) : (causal ? Limit{1, 32, 4} : Limit{1, 32, 2});
-    const Limit query = D == 128 && !causal ? Limit{1, 32, 3} : Limit{0, 1, 0};
-    // with shared heads and few key blocks, dQ work beside them is worth more
-    const float shared_keys = D == 64 ? 0.5f : (causal ? 0.75f : 0.25f), shared_queries = D == 64 && !causal ? 2 : 3;
-
     const long tiles = (N + 31) / 32, group = heads / kv_heads, chain = tiles * group;
     const float q = (float)(heads * tiles) / kChip, k = (float)(kv_heads * tiles) / kChip;  // fillings
-    const float both = tiles > 2 ? one.at(tiles) : 1.25f;
-    const bool one_launch = q + k <= both || (group > 1 && tiles >= 16 && k <= shared_keys && q <= shared_queries * both);
-    return {one_launch || (tiles > 2 && q <= query.at(tiles)), one_launch || (chain >= 6 && k <= key.at(chain)), one_launch};
+    float both = tiles > 4 ? one.at(tiles) : tiles < 3 ? 1.25f : D == 64 ? 2.f : 3.2f;
+    if (D == 128 && causal && tiles > 4) both = both < 2.8f + (float)tiles / 6 ? both : 2.8f + (float)tiles / 6;
+    if (group >= 4 && tiles >= 16) both *= D == 64 ? 1.8f : causal ? 1.35f : 1.f;
+    const float rows = (float)(heads * ((N + 127) / 128)) / kChip;  // fillings by workgroups of 128 queries
+    const Limit longest = causal ? Limit{0.2f, 200, 0.62f} : group == 1 ? Limit{0.18f, 400, 0.5f} : Limit{0.2f, 160, 0.65f};
+    const bool uneven = !causal && group == 4 && tiles > 48 && rows > 0.42f && rows < 0.9f;
+    const bool wide = tiles > 2 && (group >= 4 && tiles > 4 ? !uneven : rows >= longest.at(tiles));
+    return {chain >= 6 && k <= key.at(chain), q + k <= both, wide ? kDqRows | (group <= (causal ? 4 : 2) ? kDqFirst : 0) : 0};
 }
 
 // Whether the one launch that runs both passes computes D for itself: cheaper than a launch for it (2.7 us and the gap
@@ -1660,16 +1901,17 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
                            d_ready ? nullptr : u16(o), u16(dout), lse, dvec, static_cast<uint16_t*>(dq), N, tiles, items,
                            H / H_kv, scale);
     };
-    // workgroups of 32 queries / of 32 keys, when a pass is to use them
+    // workgroups of 32 or 128 queries / of 32 keys, when a pass is to use them
     const BwdForms forms = choose_bwd_forms<D>((long)B * H, (long)B * H_kv, N, causal);
-    const long dq_few = forms.dq_few ? (long)B * H * ((N + 31) / 32) : 0;
-    const long dkdv_few = forms.dkdv_few ? (long)B * H_kv * ((N + 31) / 32) : 0;
+    const int few_rows = forms.dq_form & kDqRows ? 128 : 32;
+    const long dq_few = forms.one_launch ? (long)B * H * ((N + few_rows - 1) / few_rows) : 0;
+    const long dkdv_few = forms.dkdv_few || forms.one_launch ? (long)B * H_kv * ((N + 31) / 32) : 0;
     auto few = [&](long n_dkdv, long n_dq, bool d_ready) {
         if constexpr (D <= 128) {
             auto run = [&](auto kernel) {
                 hipLaunchKernelGGL(kernel, dim3((unsigned)(n_dkdv + n_dq)), dim3(256), 0, stream, u16(q), u16(k), u16(v),
                                    u16(o), u16(dout), lse, dvec, static_cast<uint16_t*>(dq),
-                                   static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv), N, (int)n_dkdv, B * H, H / H_kv, scale);
+                                   static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv), N, (int)n_dkdv, forms.dq_form, B * H, H / H_kv, scale);
             };
             if (d_ready) causal ? run(fa_bwd_few_kernel<Tag, D, true, true>) : run(fa_bwd_few_kernel<Tag, D, false, true>);
             else causal ? run(fa_bwd_few_kernel<Tag, D, true, false>) : run(fa_bwd_few_kernel<Tag, D, false, false>);

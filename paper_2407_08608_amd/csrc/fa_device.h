@@ -30,6 +30,15 @@ typedef __attribute__((ext_vector_type(2))) int i32x2;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 
+// f(0), f(1), ..., f(N - 1), each with its number as a type
+template <int N, typename F, int I = 0>
+static __device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, F, I + 1>(static_cast<F&&>(f));
+    }
+}
+
 struct bf16_tag {};
 struct f16_tag {};
 
@@ -67,6 +76,11 @@ template <> struct Elem<f16_tag> {
     }
 };
 
+// A buffer resource as four scalar registers, for loads written as inline assembly (global_to_lds_16B)
+struct BufferWords {
+    i32x4 w;
+};
+
 // The same MFMA written as inline assembly, to choose the half of the register file each operand
 // lives in.  A kernel that needs more than 256 registers per lane gets MFMA results in the
 // accumulation half by default, where no VALU instruction can read them: a score tile that the
@@ -77,6 +91,8 @@ template <> struct Elem<f16_tag> {
 // that was filled with values has to be start(), which keeps the two wait states an MFMA needs behind
 // a VALU write of its operands (the compiler may put the copy that fills it directly in front).
 template <typename Tag> struct MfmaVgprAcc;
+// The _and_load forms also issue a global_to_lds_16B: the MFMA stands between the instruction that sets m0 and the load, in
+// place of the wait state that the load needs there.
 #define FA_DEFINE_MFMA_VGPR_ACC(TAG, OPCODE)                                                          \
     template <> struct MfmaVgprAcc<TAG> {                                                             \
         static __device__ __forceinline__ void run(f32x16& acc, const i32x4& a, const i32x4& b) {     \
@@ -87,6 +103,27 @@ template <typename Tag> struct MfmaVgprAcc;
         }                                                                                             \
         static __device__ __forceinline__ void first(f32x16& acc, const i32x4& a, const i32x4& b) {   \
             asm volatile(OPCODE " %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "a"(b));                      \
+        }                                                                                             \
+        template <int LDS_OFF>                                                                        \
+        static __device__ __forceinline__ void run_and_load(f32x16& acc, const i32x4& a, const i32x4& b, const BufferWords& rsrc, \
+                                                            uint32_t lds_base, int byte_off) {        \
+            asm volatile("s_add_u32 m0, %3, %4\n\t" OPCODE " %0, %1, %2, %0\n\tbuffer_load_dwordx4 %5, %6, 0 offen lds" \
+                         : "+v"(acc) : "v"(a), "a"(b), "s"(lds_base), "n"(LDS_OFF), "v"(byte_off), "s"(rsrc.w) \
+                         : "memory", "m0", "scc");                                                    \
+        }                                                                                             \
+        template <int LDS_OFF>                                                                        \
+        static __device__ __forceinline__ void start_and_load(f32x16& acc, const i32x4& a, const i32x4& b, const BufferWords& rsrc, \
+                                                              uint32_t lds_base, int byte_off) {      \
+            asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 0\n\t" OPCODE " %0, %1, %2, %0\n\tbuffer_load_dwordx4 %5, %6, 0 offen lds" \
+                         : "+v"(acc) : "v"(a), "a"(b), "s"(lds_base), "n"(LDS_OFF), "v"(byte_off), "s"(rsrc.w) \
+                         : "memory", "m0", "scc");                                                    \
+        }                                                                                             \
+        template <int LDS_OFF>                                                                        \
+        static __device__ __forceinline__ void first_and_load(f32x16& acc, const i32x4& a, const i32x4& b, const BufferWords& rsrc, \
+                                                              uint32_t lds_base, int byte_off) {      \
+            asm volatile("s_add_u32 m0, %3, %4\n\t" OPCODE " %0, %1, %2, 0\n\tbuffer_load_dwordx4 %5, %6, 0 offen lds" \
+                         : "=&v"(acc) : "v"(a), "a"(b), "s"(lds_base), "n"(LDS_OFF), "v"(byte_off), "s"(rsrc.w) \
+                         : "memory", "m0", "scc");                                                    \
         }                                                                                             \
     };
 FA_DEFINE_MFMA_VGPR_ACC(bf16_tag, "v_mfma_f32_32x32x16_bf16")
@@ -101,6 +138,9 @@ static __device__ __forceinline__ void mfma_result_wait(f32x16& x, f32x16& y) {
     asm volatile("s_nop 12" : "+v"(x), "+v"(y));
 }
 static __device__ __forceinline__ void mfma_result_wait(f32x16& x) { asm volatile("s_nop 12" : "+v"(x)); }
+// The same where at least 12 - STATES instructions stand between.
+template <int STATES>
+static __device__ __forceinline__ void mfma_result_wait_rest(f32x16& x) { asm volatile("s_nop %1" : "+v"(x) : "n"(STATES - 1)); }
 
 // 32-bit LDS byte address of a __shared__ object, and loads through such an address: a base kept
 // in one register with compile-time offsets lets every read use the instruction's immediate
@@ -184,9 +224,6 @@ static __device__ __forceinline__ i32x4 buffer_load_16B(__amdgpu_buffer_rsrc_t r
 // store zeros.  Written as inline assembly on purpose: the compiler then does not know that the
 // load writes LDS and does not drain all outstanding loads before every later LDS read; the
 // caller orders the two with an explicit vmcnt wait and a barrier.
-struct BufferWords {
-    i32x4 w;
-};
 static __device__ __forceinline__ BufferWords make_buffer_words(const void* base, uint32_t bytes) {
     const uint64_t a = reinterpret_cast<uint64_t>(base);
     BufferWords b;
@@ -238,12 +275,16 @@ struct WaveTile {
     static __device__ __forceinline__ int swizzle(int r) {
         return D == 64 ? (((r >> 1) & 1) << 2) | ((r >> 2) & 3) : ((r & 3) << 2) | ((r >> 2) & 3);
     }
+    // The lane's byte offset within a tile for staging instruction i
+    static __device__ __forceinline__ int src_of(int i, int lane) {
+        const int r = (i % PERIOD) * RPI + lane / CPR;
+        return r * ROWB + ((lane % CPR) ^ swizzle(r)) * 16 + (i / PERIOD) * (PERIOD * 1024);
+    }
     __device__ __forceinline__ WaveTile(uint32_t at, int lane) : base(at) {
         const int col = lane & 31, half = lane >> 5, tr_row = (lane & 15) >> 2, quad = lane & 3, blk = (lane >> 4) & 1;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-            const int r = (i % PERIOD) * RPI + lane / CPR;
-            src[i] = r * ROWB + ((lane % CPR) ^ swizzle(r)) * 16 + (i / PERIOD) * (PERIOD * 1024);
+            src[i] = src_of(i, lane);
             asm volatile("" : "+v"(src[i]));
         }
 #pragma unroll

@@ -598,3 +598,14 @@ def test_forward_rows_with_scores_of_nan_or_infinity(dtype, d, N, H, causal):
             k2, hit = k.clone(), torch.zeros((1, H, N), dtype=torch.bool, device="cuda")
             k2[:, :, j, 0], hit[:, :, j if causal else 0:] = nan if kind == "nan" else float("inf"), True
             check(*run(q, k2), hit)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d,causal,N,H,H_kv", [(128, True, 129, 30, 30), (128, True, 256, 32, 32), (128, False, 160, 32, 32), (128, False, 97, 60, 60),
+                                               (64, True, 257, 56, 56), (64, False, 385, 40, 20), (64, False, 160, 51, 51), (64, False, 159, 110, 55),
+                                               (128, True, 161, 8, 2), (128, False, 288, 8, 1), (64, True, 193, 8, 2), (64, False, 511, 16, 2)])
+def test_backward_128_query_workgroups_beside_key_blocks(d, causal, N, H, H_kv, dtype):
+    # one launch whose dQ work has 128 queries to a workgroup, ahead of the key blocks (groups up to four) and behind them: a
+    # last workgroup of one row, of one and of four waves, fewer tiles than are staged ahead, ragged last tiles, waves that end up to
+    # three tiles before the others; (64, False, 160, 51): D computed in this launch
+    _check_backward(2500 + N, 1, H, H_kv, N, d, causal, dtype, (0, H_kv - 1))
