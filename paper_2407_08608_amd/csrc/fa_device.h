@@ -280,8 +280,13 @@ struct WaveTile {
         const int r = (i % PERIOD) * RPI + lane / CPR;
         return r * ROWB + ((lane % CPR) ^ swizzle(r)) * 16 + (i / PERIOD) * (PERIOD * 1024);
     }
+    // Its offset within a tile of the transposed operand of columns 32 dt .. 32 dt + 31
+    static __device__ __forceinline__ uint32_t tr_of(int dt, int hi, int lane) {
+        const int half = lane >> 5, tr_row = (lane & 15) >> 2, quad = lane & 3, blk = (lane >> 4) & 1, r = 4 * half + tr_row + 8 * hi;
+        return r * ROWB + (((4 * dt + 2 * blk + (quad >> 1)) ^ swizzle(r)) << 4) + 8 * (quad & 1);
+    }
     __device__ __forceinline__ WaveTile(uint32_t at, int lane) : base(at) {
-        const int col = lane & 31, half = lane >> 5, tr_row = (lane & 15) >> 2, quad = lane & 3, blk = (lane >> 4) & 1;
+        const int col = lane & 31, half = lane >> 5;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             src[i] = src_of(i, lane);
@@ -296,8 +301,7 @@ struct WaveTile {
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int hi = 0; hi < 2; ++hi) {
-                const int r = 4 * half + tr_row + 8 * hi;
-                tr_at[dt][hi] = at + r * ROWB + (((4 * dt + 2 * blk + (quad >> 1)) ^ swizzle(r)) << 4) + 8 * (quad & 1);
+                tr_at[dt][hi] = at + tr_of(dt, hi, lane);
                 asm volatile("" : "+v"(tr_at[dt][hi]));
             }
     }

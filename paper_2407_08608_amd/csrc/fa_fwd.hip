@@ -552,25 +552,21 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
                    uint16_t* __restrict__ o, float* __restrict__ lse, int N, int n_qtiles, int total_wg,
                    int paired, int kv_group, float scale) {
     [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
-    constexpr int D = 256, BC = 64, NT = 256, BR = 128;
-    constexpr int KSTR = D + 8;   // +16 B per row: 128-bit row reads hit distinct banks
-    constexpr int VSTR = D + 32;  // +64 B per row: the 4-row transposing reads hit distinct banks
+    constexpr int D = 256, BC = 64, BR = 128;
     constexpr int KS = D / 16, DT = D / 32, KP = 4;
     using E = Elem<Tag>;
-    using Copy = TileCopy<D, BC, NT>;
+    using Tile = WaveTile<D>;                // the layout of 32 rows in the LDS; a block is two of them
+    constexpr int BLOCK_B = 2 * Tile::TILE_B;  // K and V have two stages each
 
-    constexpr int kLds = 2 * BC * (KSTR + VSTR) * 2;
+    constexpr int kLds = FewForward<D, 4>::kLds > 4 * BLOCK_B ? FewForward<D, 4>::kLds : 4 * BLOCK_B;
     __shared__ __attribute__((aligned(1024))) char lds[kLds];
     static_assert(FewForward<D, 4>::kLds <= kLds, "both divisions of the work use it");
     if (paired == kFewForward) {
         FewForward<D, 4>::template run<Tag, CAUSAL>(q, k, v, o, lse, N, total_wg, kv_group, scale, lds);
         return;
     }
-    uint16_t(*lds_k)[BC * KSTR] = reinterpret_cast<uint16_t(*)[BC * KSTR]>(lds);
-    uint16_t(*lds_v)[BC * VSTR] = reinterpret_cast<uint16_t(*)[BC * VSTR]>(lds + 2 * BC * KSTR * 2);
-
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int col = lane & 31, half = lane >> 5;
 
     const TileRun run = query_tiles<CAUSAL>(total_wg, n_qtiles, paired);
@@ -580,16 +576,40 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
     const size_t kv_off = (size_t)(bh / kv_group) * N * D;
     const uint16_t* qh = q + head_off;
     const float sc = scale * kLog2e;
-    const __amdgpu_buffer_rsrc_t k_rsrc = make_buffer(k + kv_off, (uint32_t)N * D * 2);
-    const __amdgpu_buffer_rsrc_t v_rsrc = make_buffer(v + kv_off, (uint32_t)N * D * 2);
-    const int tr_row = (lane & 15) >> 2;
-    const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    // Addresses: row operands of K, transposed operands of V in the first stages (columns from 128 on, 16 rows and the second
+    // stage further are offsets), and where the lane fetches the wave's quarter of a block
+    const uint32_t k_at = lds_address(lds), v_at = k_at + 2 * BLOCK_B, piece = k_at + wave * (BLOCK_B / 4);
+    uint32_t row_at[KS / 2], tr_at[DT / 2][2];
+    int src[8];
+#pragma unroll
+    for (int ks = 0; ks < KS / 2; ++ks) {
+        row_at[ks] = k_at + col * Tile::ROWB + (((2 * ks + half) ^ Tile::swizzle(col)) << 4);
+        asm volatile("" : "+v"(row_at[ks]));
+    }
+#pragma unroll
+    for (int dt = 0; dt < DT / 2; ++dt)
+#pragma unroll
+        for (int hi = 0; hi < 2; ++hi) {
+            tr_at[dt][hi] = v_at + Tile::tr_of(dt, hi, lane);
+            asm volatile("" : "+v"(tr_at[dt][hi]));
+        }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        src[i] = wave * (BLOCK_B / 4) + Tile::src_of(i, lane);
+        asm volatile("" : "+v"(src[i]));
+    }
 
 #pragma nounroll
     for (int pass = 0; pass < run.n_pass(); ++pass) {
     const int qt = pass == 0 ? run.tile : run.second;
     const int wave_q0 = qt * BR + wave * 32;
     const int limit = CAUSAL ? min(wave_q0 + col, N - 1) : N - 1;  // last key this lane's query sees
+
+    // the next blocks of K and V to be requested (rows past N, and blocks past the last one, read as zero)
+    BufferWords k_rsrc = make_buffer_words(k + kv_off, (uint32_t)N * D * 2), v_rsrc = make_buffer_words(v + kv_off, (uint32_t)N * D * 2);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) global_to_lds_16B(k_rsrc, piece + i * 1024, src[i]);
+    advance(k_rsrc, BLOCK_B);
 
     // Q_i^T as the B operand of S^T = K Q^T, resident for the whole loop
     i32x4 qreg[KS];
@@ -628,66 +648,45 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
         for (int i = 8 * part; i < 8 * part + 8; ++i)
             mxp[i & 3] = i < 4 ? s[0][i] : fmaxf(mxp[i & 3], s[i >> 4][i & 15]);
     };
-    // K rows for S^T (A operand), 32 steps (kt, ks); the scores land in ordinary registers
-    auto score_step = [&](f32x16 (&s)[2], uint32_t k_rows, i32x4 (&abuf)[KP], int u) {
-        constexpr int NU = 2 * KS;
-        const int kt = u / KS, ks = u % KS;
-        const i32x4 a = abuf[u % KP];
-        if (u + KP < NU) {
-            const int w = u + KP;
-            abuf[u % KP] = lds_load_16B(k_rows + ((w / KS) * 32 * KSTR + (w % KS) * 16) * 2);
-        }
-        if (ks == 0) MfmaVgprAcc<Tag>::first(s[kt], a, qreg[ks]);
-        else MfmaVgprAcc<Tag>::run(s[kt], a, qreg[ks]);
-    };
-    auto score_prefetch = [&](uint32_t k_rows, i32x4 (&abuf)[KP]) {
-#pragma unroll
-        for (int u = 0; u < KP; ++u) abuf[u] = lds_load_16B(k_rows + ((u / KS) * 32 * KSTR + (u % KS) * 16) * 2);
-    };
+    // K rows for S^T (A operand) in stage ST, 32 steps (kt, ks); the scores land in ordinary registers
+    auto row_read = [&](int st, int u) { return lds_load_16B(row_at[u % (KS / 2)] + st * BLOCK_B + (u / KS) * Tile::TILE_B + (u % KS / (KS / 2)) * 256); };
 
-    // Staging, global -> registers -> LDS, one 16-byte chunk per thread at a time.  A block's K and V
+    // Staging, global -> LDS without registers (global_to_lds_16B), a quarter of a block by each wave.  A block's K and V
     // are 64 KiB, half of what the CU's vector memory path moves in the time of the block's MFMAs:
     // issued in one burst the loads make every wave sit in its own issue for over a thousand
-    // cycles.  They are spread over the MFMA steps instead, one chunk every CH_EVERY steps, and
-    // each chunk is written to the LDS a stage later, when it has long arrived:
-    //   stage A of block t: load K(t+2) chunks          | write the V(t+1) chunks loaded in block t-1
-    //   stage B of block t: write those K(t+2) chunks   | load V(t+2) chunks
-    // (K(t+2) replaces K(t), last read in block t-1; V(t+1) replaces V(t-1), last read in block t-1;
-    // both become visible at the barrier that ends block t.)  Blocks past the end read as zero.
-    constexpr int NCH = Copy::kPerThread, CH_EVERY = 2 * KS / NCH;
-    static_assert(NCH * CH_EVERY == 2 * KS && 4 * DT == 2 * KS, "one chunk every CH_EVERY steps of either stage");
-    i32x4 kpre[NCH], vpre[NCH];
-    auto load_chunk = [&](__amdgpu_buffer_rsrc_t rsrc, int block_idx, int i) {
-        return buffer_load_16B(rsrc, block_idx * BC * D * 2 + (tid + i * NT) * 16);
+    // cycles.  They are spread over the steps of stage A, one every second step: K(t+2) replaces K(t), V(t+1) replaces V(t-1),
+    // both last read in block t-1, and both are there at the barrier that ends block t.
+    auto blocks_landed = [&]() __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
     };
-    auto store_chunk = [&](uint16_t* lds, int stride, int i, const i32x4& x) {
-        const int c = tid + i * NT;
-        *reinterpret_cast<i32x4*>(lds + (c / (D / 8)) * stride + (c % (D / 8)) * 8) = x;
-    };
-    Copy::from_global(k_rsrc, 0, tid, kpre);
-    Copy::from_global(v_rsrc, 0, tid, vpre);
-    Copy::template to_lds<KSTR>(lds_k[0], tid, kpre);
-    Copy::template to_lds<VSTR>(lds_v[0], tid, vpre);
-    Copy::from_global(k_rsrc, BC * D * 2, tid, kpre);  // K(1)
-    Copy::from_global(v_rsrc, BC * D * 2, tid, vpre);  // V(1), written to the LDS during block 0
     // the Q loads complete here and Q moves to the accumulation half
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(qreg[ks]));
-    __syncthreads();
+    blocks_landed();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        global_to_lds_16B(v_rsrc, piece + 2 * BLOCK_B + i * 1024, src[i]);
+        global_to_lds_16B(k_rsrc, piece + BLOCK_B + i * 1024, src[i]);
+    }
+    advance(k_rsrc, BLOCK_B);
+    advance(v_rsrc, BLOCK_B);
 
     // ---- prologue: S(0) and its reference maximum (O and l are still zero: nothing to rescale)
     f32x16 sa[2], sb[2];
     {
-        uint32_t k_rows = lds_address(lds_k[0]) + (col * KSTR + half * 8) * 2;
-        asm volatile("" : "+v"(k_rows));
-        i32x4 abuf[KP];
-        score_prefetch(k_rows, abuf);
+        i32x4 ring[KP];
+#pragma unroll
+        for (int u = 0; u < KP; ++u) ring[u] = row_read(0, u);
 #pragma unroll
         for (int u = 0; u < 2 * KS; ++u) {
-            score_step(sa, k_rows, abuf, u);
+            const i32x4 a = ring[u % KP];
+            if (u + KP < 2 * KS) ring[u % KP] = row_read(0, u + KP);
+            if (u % KS == 0) MfmaVgprAcc<Tag>::first(sa[u / KS], a, qreg[0]);
+            else MfmaVgprAcc<Tag>::run(sa[u / KS], a, qreg[u % KS]);
             __builtin_amdgcn_sched_barrier(0);
         }
-        Copy::template to_lds<KSTR>(lds_k[1], tid, kpre);
         mfma_result_wait(sa[0], sa[1]);
         if (need_mask(0)) mask_block(0, sa);
 #pragma unroll
@@ -695,28 +694,30 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
         m_run = max_both_halves(fmaxf(fmaxf(mxp[0], mxp[1]), fmaxf(mxp[2], mxp[3])));
         mb = m_run * sc;
     }
-    __syncthreads();
+    blocks_landed();
 
-    // ---- one key block: `cur` holds S(t), `nxt` receives S(t+1)
-    auto block = [&](int t, f32x16 (&cur)[2], f32x16 (&nxt)[2]) {
+    // ---- one key block: `cur` holds S(t), `nxt` receives S(t+1); ST = t % 2
+    auto block = [&](auto stage, int t, f32x16 (&cur)[2], f32x16 (&nxt)[2]) __attribute__((always_inline)) {
+        constexpr int ST = decltype(stage)::value;
         i32x4 pb[4];  // P~(t)^T as B operands, 16 keys each
         float psum = 0.f;
-        uint32_t k_rows = lds_address(lds_k[(t + 1) & 1]) + (col * KSTR + half * 8) * 2;
-        uint32_t v_tr = lds_address(lds_v[t & 1]) + ((4 * half + tr_row) * VSTR + tr_col) * 2;
-        asm volatile("" : "+v"(k_rows), "+v"(v_tr));
 
         // ---- stage A
         {
-            i32x4 abuf[KP];
-            score_prefetch(k_rows, abuf);
+            i32x4 ring[KP];
 #pragma unroll
-            for (int u = 0; u < 2 * KS; ++u) {
-                score_step(nxt, k_rows, abuf, u);
-                if (u % CH_EVERY == 0) {
-                    store_chunk(lds_v[(t + 1) & 1], VSTR, u / CH_EVERY, vpre[u / CH_EVERY]);
-                    kpre[u / CH_EVERY] = load_chunk(k_rsrc, t + 2, u / CH_EVERY);
-                }
-                if (u == 0) {
+            for (int u = 0; u < KP; ++u) ring[u] = row_read(ST ^ 1, u);
+            static_for<2 * KS>([&](auto step) __attribute__((always_inline)) {
+                constexpr int u = decltype(step)::value, ks = u % KS, n = u / 2;
+                constexpr int to = (n & 1 ? 2 + (ST ^ 1) : ST) * BLOCK_B + (n >> 1) * 1024;
+                const i32x4 a = ring[u % KP];
+                if constexpr (u + KP < 2 * KS) ring[u % KP] = row_read(ST ^ 1, u + KP);
+                f32x16& s = nxt[u / KS];
+                const BufferWords& rsrc = n & 1 ? v_rsrc : k_rsrc;
+                if constexpr (ks == 0) MfmaVgprAcc<Tag>::template first_and_load<to>(s, a, qreg[ks], rsrc, piece, src[n >> 1]);
+                else if constexpr (u % 2 == 0) MfmaVgprAcc<Tag>::template run_and_load<to>(s, a, qreg[ks], rsrc, piece, src[n >> 1]);
+                else MfmaVgprAcc<Tag>::run(s, a, qreg[ks]);
+                if constexpr (u == 0) {
                     // Reference maximum for S(t) from the row maxima taken beside the previous block's
                     // products: raised only when they exceed it by more than 2^kLazyLog2 (P~ <= 2^kLazyLog2
                     // otherwise and the factor cancels in O / l).  Every product of the previous block has
@@ -724,7 +725,7 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
                     // rescale of O is in order here.  (Block 0: the prologue has set the reference; no rise.)
                     const float mx = max_both_halves(fmaxf(fmaxf(mxp[0], mxp[1]), fmaxf(mxp[2], mxp[3])));
                     const bool raise = (mx - m_run) * sc > kLazyLog2;
-                    if (__builtin_amdgcn_ballot_w64(raise) != 0) {
+                    if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {
                         const float corr = raise ? fast_exp2((m_run - mx) * sc) : 1.0f;
                         m_run = raise ? mx : m_run;
                         l_run *= corr;
@@ -745,7 +746,9 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
                         pb[2 * kt + (j >> 2)][j & 3] = E::pack2(p0, p1);
                     }
                 __builtin_amdgcn_sched_barrier(0);
-            }
+            });
+            advance(k_rsrc, BLOCK_B);
+            advance(v_rsrc, BLOCK_B);
             l_run += psum;
         }
 
@@ -753,7 +756,7 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
         {
             constexpr int NU = 4 * DT;  // (16-key slab, d-tile)
             auto v_addr = [&](int u, int hi) -> uint32_t {
-                return v_tr + (((u / DT) * 16 + hi * 8) * VSTR + (u % DT) * 32) * 2;
+                return tr_at[u % (DT / 2)][hi] + ST * BLOCK_B + (u / DT) * 16 * Tile::ROWB + (u % DT / (DT / 2)) * 256;
             };
             i32x2 lo[KP], hi[KP];
 #pragma unroll
@@ -772,29 +775,24 @@ fa_fwd_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
                 }
                 oacc[dt] = E::mma(a, pb[sl], oacc[dt]);
                 if (u == 0) mfma_result_wait(nxt[0], nxt[1]);  // written by MFMAs the hazard checker cannot see
-                if (u == 1 && mask_next) mask_block(t + 1, nxt);
+                if (u == 1 && __builtin_expect(mask_next, 0)) mask_block(t + 1, nxt);
                 if (u >= 2 && u < 6) max_part(nxt, u - 2);
-                if (u % CH_EVERY == 0) {
-                    store_chunk(lds_k[t & 1], KSTR, u / CH_EVERY, kpre[u / CH_EVERY]);
-                    vpre[u / CH_EVERY] = load_chunk(v_rsrc, t + 2, u / CH_EVERY);
-                }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
 
-        __syncthreads();
+        blocks_landed();
     };
 
     for (int t = 0; t < n_blocks; t += 2) {
-        block(t, sa, sb);
-        if (t + 1 < n_blocks) block(t + 1, sb, sa);
+        block(std::integral_constant<int, 0>{}, t, sa, sb);
+        if (t + 1 < n_blocks) block(std::integral_constant<int, 1>{}, t + 1, sb, sa);
     }
 
     // ---- epilogue: O / l, L = m + log l, through a 4 KiB LDS patch per wave (the last barrier of
     // the loop has passed, so the K buffers are free)
     {
-        char* patch = reinterpret_cast<char*>(&lds_k[0][0]) + wave * 4096;
-        static_assert(2 * BC * KSTR * 2 >= 4 * 4096, "patches must fit");
+        char* patch = lds + wave * 4096;
         const int qi = wave_q0 + col;
         const float l = sum_both_halves(l_run);
         int out_lane = lane;  // opaque: the addresses derived from it are else computed before the loop, and spilled over it
