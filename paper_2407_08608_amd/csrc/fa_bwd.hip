@@ -465,6 +465,9 @@ fa_bwd_dkdv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
 // 3873 us (this pass 3046 -> 2112, 1.04 PFLOP/s of executed MFMAs); d = 128, B = 4, H = 16, N = 4096 causal 1065 ->
 // 1029 us.  The chip's power, not a pipe, is what is left at these sizes: without the exponentials, the barrier or the
 // row reads the pass gains 1 to 4 %.  Tiles requested two iterations ahead instead of one: no gain.
+// Tiles go straight into the LDS (WaveTile's layout): through registers, 16 loads waited for and 16 LDS stores per iteration at
+// d = 256 (8 and 8 at d = 128) cost the lone wave more.  Whole backward so, us, before / now: d = 256 16 x 8192 3389 / 3210,
+// causal 64 x 2048 566 / 529; d = 128 causal 64 x 4096 925 / 910.
 template <typename Tag, int D, bool CAUSAL>
 __global__ void __launch_bounds__(256, 1)
 fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
@@ -473,23 +476,20 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
                           uint16_t* __restrict__ dv, int N, int n_kblocks, int total_wg, int kv_group, float scale) {
     [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
     static_assert(D == 128 || D == 256, "d = 64 keeps two workgroups per CU (fa_bwd_dkdv_kernel)");
-    constexpr int NT = 256;
+    using Tile = WaveTile<D>;                 // the layout of a sub-tile in the LDS
     constexpr int BQ = 64;                    // queries per iteration, two sub-tiles
     constexpr int KEYT = D == 128 ? 2 : 1;    // key tiles whose scores a wave computes
     constexpr int NKT = 2 * KEYT;             // key tiles per workgroup
     constexpr int BK = 32 * NKT;              // keys per workgroup
     constexpr int KS = D / 16;                // MFMA steps along the head dimension
-    constexpr int RSTR = bwd_row_stride(D);
-    constexpr int TILE_B = BQ * RSTR * 2;     // bytes per Q or dO tile
-    constexpr int DO_DIST = 2 * TILE_B;
-    constexpr int CPR = D / 8;                // 16-byte chunks per row
-    constexpr int QCH = BQ * CPR / NT;        // chunks per thread of a tile
+    constexpr int TILE_B = 2 * Tile::TILE_B;  // bytes per Q or dO tile
+    constexpr int STAGE_B = 2 * TILE_B;       // Q, dO
+    constexpr int NREQ = Tile::NI;            // staging instructions of a wave per iteration: half of them for Q
     constexpr int KP = 4;                     // steps by which row operand reads lead their MFMAs
     constexpr int PIECE = 1024;               // bytes of one exchanged operand: 32 keys x 16 queries
     using E = Elem<Tag>;
 
-    // tiles 0, 1: Q_i double-buffered; tiles 2, 3: dO_i (a fixed distance from the Q tile of the same parity)
-    __shared__ __attribute__((aligned(16))) uint16_t lds_t[4][BQ * RSTR];
+    __shared__ __attribute__((aligned(1024))) char lds_t[2 * STAGE_B];
     __shared__ __attribute__((aligned(16))) char lds_x[2][NKT * 4 * PIECE];  // P, dS: [key tile][sub-tile][slab]
     __shared__ __attribute__((aligned(16))) float lds_l[2][BQ];
     __shared__ __attribute__((aligned(16))) float lds_d[2][BQ];
@@ -543,8 +543,32 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
 
     const int n_qtiles = (N + BQ - 1) / BQ;
     const int it0 = CAUSAL ? key0 / BQ : 0;  // first query tile that can see this key block
-    const int tr_row = (lane & 15) >> 2;
-    const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    // Addresses: row operands of the own sub-tile, transposed operands of this one and the other (16 rows further, dO and, at d = 256,
+    // columns from 128 on of the rows are offsets), in the stage being read, and what the lane fetches of the wave's quarters
+    constexpr int RA = KS < 8 ? KS : 8;
+    uint32_t row_at[RA], tr_own[2][2], tr_oth[2][2];
+    int src[NREQ / 2];
+    const uint32_t lds_base = lds_address(lds_t), piece_at = lds_base + wave * (TILE_B / 4);
+#pragma unroll
+    for (int ks = 0; ks < RA; ++ks) {
+        row_at[ks] = lds_base + g * Tile::TILE_B + col * Tile::ROWB + (((2 * ks + half) ^ Tile::swizzle(col)) << 4);
+        asm volatile("" : "+v"(row_at[ks]));
+    }
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int hi = 0; hi < 2; ++hi) {
+            const uint32_t at = lds_base + Tile::tr_of(col0 / 32 + dt, hi, lane);
+            tr_own[dt][hi] = at + g * Tile::TILE_B;
+            tr_oth[dt][hi] = at + (g ^ 1) * Tile::TILE_B;
+            asm volatile("" : "+v"(tr_own[dt][hi]), "+v"(tr_oth[dt][hi]));
+        }
+#pragma unroll
+    for (int n = 0; n < NREQ / 2; ++n) {
+        src[n] = wave * (TILE_B / 4) + Tile::src_of(n, lane);
+        asm volatile("" : "+v"(src[n]));
+    }
+    int st = 0;  // the stage being read
     // Masked query tiles come first: every tile when the key block is ragged (keys past N), else the tiles on the
     // causal diagonal.  They get a loop of their own so that the main loop has a single straight-line body.
     const int it_masked_end = key0 + BK > N ? n_qtiles : (CAUSAL ? min(n_qtiles, (key0 + BK - 1) / BQ + 1) : it0);
@@ -564,23 +588,15 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
     const size_t qhead = (size_t)bh * kv_group + gi;
     const float* lh = lse + qhead * N;
     const float* dh = dvec + qhead * N;
-    // Rows past N lie outside the buffer resources and read as zero, so every iteration requests and stores a next
+    // The next tiles to be requested.  Rows past N lie outside the resources and read as zero, so every iteration requests a next
     // tile: the one after the last is zeros that nothing reads.
-    const __amdgpu_buffer_rsrc_t q_rsrc = make_buffer(q + qhead * N * D, (uint32_t)N * D * 2);
-    const __amdgpu_buffer_rsrc_t do_rsrc = make_buffer(dout + qhead * N * D, (uint32_t)N * D * 2);
-
-    i32x4 qpre[QCH], dopre[QCH];
+    BufferWords q_rsrc = make_buffer_words(q + qhead * N * D, (uint32_t)N * D * 2), do_rsrc = make_buffer_words(dout + qhead * N * D, (uint32_t)N * D * 2);
+    auto next_tile = [&](int tiles) __attribute__((always_inline)) {
+        advance(q_rsrc, tiles * BQ * D * 2);
+        advance(do_rsrc, tiles * BQ * D * 2);
+    };
     float lpre = 0.f;  // threads 0..63 carry L, 64..127 carry D
     int lrow = 0;
-    auto load_chunk = [&](int it, int c) __attribute__((always_inline)) {  // chunk c of 2 QCH: Q then dO
-        const int off = it * BQ * D * 2 + (tid + (c % QCH) * NT) * 16;
-        if (c < QCH) qpre[c] = buffer_load_16B(q_rsrc, off);
-        else dopre[c - QCH] = buffer_load_16B(do_rsrc, off);
-    };
-    auto store_chunk = [&](int st, int c) __attribute__((always_inline)) {
-        const int e = tid + (c % QCH) * NT, row = e / CPR, cc = e % CPR;
-        *reinterpret_cast<i32x4*>(lds_t[c < QCH ? st : 2 + st] + row * RSTR + cc * 8) = c < QCH ? qpre[c % QCH] : dopre[c % QCH];
-    };
     auto load_ld = [&](int it) __attribute__((always_inline)) {
         if (tid < 2 * BQ) {  // the raw value only: arithmetic on it here would wait for the load on the spot
             lrow = it * BQ + (tid & (BQ - 1));
@@ -594,28 +610,27 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
         else if (tid < 2 * BQ) lds_d[st][tid - BQ] = lrow < N ? -lpre : 0.f;
     };
 
-    if (it0 < n_qtiles) {
-        load_ld(it0);
+    auto landed = [&]() __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    load_ld(it0);
+    next_tile(it0);
 #pragma unroll
-        for (int c = 0; c < 2 * QCH; ++c) load_chunk(it0, c);
-#pragma unroll
-        for (int c = 0; c < 2 * QCH; ++c) store_chunk(0, c);
-        store_ld(0);
-    }
-    __syncthreads();
+    for (int n = 0; n < NREQ; ++n)
+        global_to_lds_16B(n & 1 ? do_rsrc : q_rsrc, piece_at + st * STAGE_B + (n & 1) * TILE_B + (n >> 1) * 1024, src[n >> 1]);
+    next_tile(1);
+    store_ld(st);
+    landed();
 
     auto iteration = [&](int it, auto mask_tag) __attribute__((always_inline)) {
         constexpr bool MASK = decltype(mask_tag)::value;
-        const int st = (it - it0) & 1;
         const int q_first = it * BQ + 32 * g + 4 * half;  // query of score register 0
-
-        // One register per LDS base; every read below adds a compile-time offset.
-        uint32_t q_rows = lds_address(lds_t[st]) + ((32 * g + col) * RSTR + half * 8) * 2;
-        uint32_t tr_own = lds_address(lds_t[st]) + ((32 * g + 4 * half + tr_row) * RSTR + tr_col + col0) * 2;
-        uint32_t tr_oth = lds_address(lds_t[st]) + ((32 * (g ^ 1) + 4 * half + tr_row) * RSTR + tr_col + col0) * 2;
-        uint32_t l_rows = lds_address(lds_l[st]) + 128 * g + 16 * half;
-        uint32_t d_rows = lds_address(lds_d[st]) + 128 * g + 16 * half;
-        asm volatile("" : "+v"(q_rows), "+v"(tr_own), "+v"(tr_oth), "+v"(l_rows), "+v"(d_rows));
+        uint32_t l_rows = lds_address(lds_l[0]) + st * (BQ * 4) + 128 * g + 16 * half;
+        uint32_t d_rows = lds_address(lds_d[0]) + st * (BQ * 4) + 128 * g + 16 * half;
+        asm volatile("" : "+v"(l_rows), "+v"(d_rows));
+        const uint32_t next = piece_at + (st ^ 1) * STAGE_B;
 
         f32x16 sacc[KEYT], pacc[KEYT];
         i32x4 pa[KEYT][2], dsa[KEYT][2];  // [key tile][16-query slab] of the own sub-tile, as A operands
@@ -626,11 +641,11 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
             else mfma_result_wait(x[0]);
         };
         auto row_read = [&](int u) __attribute__((always_inline)) {  // step u of phases 1 (Q) and 2 (dO)
-            return lds_load_16B(q_rows + (u < KS ? 0 : DO_DIST) + (u % KS) * 32);
+            return lds_load_16B(row_at[u % RA] + (u < KS ? 0 : TILE_B) + (u % KS / RA) * 256);
         };
-        auto tr_read = [&](uint32_t base, int tensor, int w) __attribute__((always_inline)) {  // w = (slab, 32 columns)
-            const uint32_t a = base + (tensor ? 0 : DO_DIST) + ((w >> 1) * 16 * RSTR + (w & 1) * 32) * 2;
-            const i32x2 lo = lds_read_tr16(a), hi = lds_read_tr16(a + 8 * RSTR * 2);
+        auto tr_read = [&](const uint32_t (&at)[2][2], int tensor, int w) __attribute__((always_inline)) {  // w = (slab, 32 columns)
+            const int off = (tensor ? 0 : TILE_B) + (w >> 1) * 16 * Tile::ROWB;
+            const i32x2 lo = lds_read_tr16(at[w & 1][0] + off), hi = lds_read_tr16(at[w & 1][1] + off);
             return i32x4{lo[0], lo[1], hi[0], hi[1]};
         };
         auto piece = [&](int tensor, int kt, int sub, int slab) __attribute__((always_inline)) {
@@ -668,32 +683,39 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
             if (rr & 1) pa[i][rr >> 3][(rr >> 1) & 3] = E::pack2(sacc[i][rr - 1], x);
             if ((rr & 7) == 7) send(0, i, rr >> 3, pa[i][rr >> 3]);
         };
-#pragma unroll
-        for (int u = 0; u < 2 * KS; ++u) {
+        static_for<2 * KS>([&](auto step) __attribute__((always_inline)) {
+            constexpr int u = decltype(step)::value, ks = u % KS, n_req = u / 2, to = (n_req & 1) * TILE_B + (n_req >> 1) * 1024;
+            static_assert(NREQ == KS, "one request every second step");
             const i32x4 a = ring[u % KP];
-            if (u + KP < 2 * KS) ring[u % KP] = row_read(u + KP);
-            else if (u + KP - 2 * KS < 4) bdo[u + KP - 2 * KS] = tr_read(tr_own, 0, u + KP - 2 * KS);
-            const int ks = u % KS;
-#pragma unroll
-            for (int i = 0; i < KEYT; ++i) {
-                if (u < KS) {
-                    if (ks == 0) MfmaVgprAcc<Tag>::first(sacc[i], a, kreg[i][ks]);
-                    else MfmaVgprAcc<Tag>::run(sacc[i], a, kreg[i][ks]);
+            if constexpr (u + KP < 2 * KS) ring[u % KP] = row_read(u + KP);
+            else if constexpr (u + KP - 2 * KS < 4) bdo[u + KP - 2 * KS] = tr_read(tr_own, 0, u + KP - 2 * KS);
+            const BufferWords& rsrc = n_req & 1 ? do_rsrc : q_rsrc;
+            static_for<KEYT>([&](auto tile) __attribute__((always_inline)) {
+                constexpr int i = decltype(tile)::value;
+                constexpr bool LOAD = u % 2 == 0 && i == 0;
+                using M = MfmaVgprAcc<Tag>;
+                if constexpr (u < KS) {
+                    if constexpr (ks == 0 && LOAD) M::template first_and_load<to>(sacc[i], a, kreg[i][ks], rsrc, next, src[n_req >> 1]);
+                    else if constexpr (ks == 0) M::first(sacc[i], a, kreg[i][ks]);
+                    else if constexpr (LOAD) M::template run_and_load<to>(sacc[i], a, kreg[i][ks], rsrc, next, src[n_req >> 1]);
+                    else M::run(sacc[i], a, kreg[i][ks]);
                 } else {
-                    if (ks == 0) MfmaVgprAcc<Tag>::start(pacc[i], a, vreg[i][ks]);
-                    else MfmaVgprAcc<Tag>::run(pacc[i], a, vreg[i][ks]);
-                    if (u == KS && i == KEYT - 1) await(sacc);
+                    if constexpr (ks == 0 && LOAD) M::template start_and_load<to>(pacc[i], a, vreg[i][ks], rsrc, next, src[n_req >> 1]);
+                    else if constexpr (ks == 0) M::start(pacc[i], a, vreg[i][ks]);
+                    else if constexpr (LOAD) M::template run_and_load<to>(pacc[i], a, vreg[i][ks], rsrc, next, src[n_req >> 1]);
+                    else M::run(pacc[i], a, vreg[i][ks]);
+                    if constexpr (u == KS && i == KEYT - 1) await(sacc);
                     // 16 KEYT scores over the 16 MFMAs of this phase, none before the wait above
                     constexpr int M0 = KEYT - 1;
-                    const int m = ks * KEYT + i;
+                    constexpr int m = ks * KEYT + i;
 #pragma unroll
                     for (int n = 0; n < 16 * KEYT; ++n)
                         if (m >= M0 && M0 + (n * (16 - M0)) / (16 * KEYT) == m) probability(n);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-            }
-            if (u * 2 * QCH / (2 * KS) != (u + 1) * 2 * QCH / (2 * KS)) load_chunk(it + 1, u * 2 * QCH / (2 * KS));
-        }
+            });
+        });
+        next_tile(1);
 
         // ---- phase 3: dV of the own piece beside dS
         i32x4 bq[4];
@@ -761,9 +783,6 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
 #pragma unroll
                     for (int jj = 0; jj < 2; ++jj) dsf[jj][w] = lds_load_16B(piece(1, acc_tile(jj), g ^ 1, w));
                 }
-#pragma unroll
-                for (int c = 0; c < QCH / 4; ++c)
-                    if (w * 2 + j < 4) store_chunk(st ^ 1, (w * 2 + j) * (QCH / 4) + c);
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
@@ -771,13 +790,21 @@ fa_bwd_dkdv_shared_kernel(const uint16_t* __restrict__ q, const uint16_t* __rest
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 dkacc[j][w & 1] = E::mma(dsf[j][w >> 1], bq[w], dkacc[j][w & 1]);
-#pragma unroll
-                for (int c = 0; c < QCH / 4; ++c)
-                    if (w * 2 + j < 4) store_chunk(st ^ 1, QCH + (w * 2 + j) * (QCH / 4) + c);
                 __builtin_amdgcn_sched_barrier(0);
             }
         store_ld(st ^ 1);
-        __syncthreads();
+        landed();
+        const int move = st ? -STAGE_B : STAGE_B;
+#pragma unroll
+        for (int ks = 0; ks < RA; ++ks) row_at[ks] += move;
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+            for (int hi = 0; hi < 2; ++hi) {
+                tr_own[dt][hi] += move;
+                tr_oth[dt][hi] += move;
+            }
+        st ^= 1;
     };
     int it = it0;
     for (; it < it_masked_end; ++it) iteration(it, std::true_type{});
