@@ -1656,14 +1656,15 @@ fa_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 // ---------------------------------------------------------------------------------------
 // dQ pass at head dimension 256: four waves, one per SIMD (the 128-register accumulator and the Q, dO operands fill the
 // register file), so only the wave's own instruction stream can keep its matrix pipe busy.  Per 64-key block:
-//   S^T   32 MFMAs  ||  dP accumulators set to -D, the first of the next block's global loads
-//   dP^T  32 MFMAs  ||  P = exp2(S c - L), the rest of the loads
-//   dQ^T  32 MFMAs  ||  dS of the second key tile, the next block's LDS writes
+//   S^T   32 MFMAs  ||  dP accumulators set to -D, requests of the next block
+//   dP^T  32 MFMAs  ||  P = exp2(S c - L), requests of the next block
+//   dQ^T  32 MFMAs  ||  dS of the second key tile
 // LDS operand reads lead their MFMAs by KP steps, across the phases (read in the step that used them, they cost the
 // wave the LDS latency 96 times per block).  S and dP are produced by MfmaVgprAcc into ordinary registers, Q, dO and
 // dQ live in the accumulation half; every step ends in a full scheduling barrier, so the order written here is what runs.
 // bf16, whole backward, us, before / so: B = 2, H = 8, N = 8192 3858 / 3452 (this pass 1834 / ~1410, 1.17 PFLOP/s of
-// executed MFMAs), causal 2020 / 1809; B = 8, H = 8, N = 2048 causal 650 / 579.
+// executed MFMAs), causal 2020 / 1809; B = 8, H = 8, N = 2048 causal 650 / 579.  Blocks straight into the LDS instead of through 16
+// registers, with 16 loads waited for and 16 LDS stores per wave: 3197 / 3147, 526 / 518.
 template <typename Tag, bool CAUSAL>
 __global__ void __launch_bounds__(256, 1)
 fa_bwd_dq_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -1671,18 +1672,17 @@ fa_bwd_dq_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
                       float* __restrict__ dvec, uint16_t* __restrict__ dq, int N, int n_qtiles, int total_wg,
                       int kv_group, float scale) {
     [[maybe_unused]] ClockSpan clock_span;  // measurement builds only; empty otherwise
-    constexpr int D = 256, BC = 64, NT = 256, BR = 128;
-    constexpr int KSTR = bwd_row_stride(D);  // K tile: row reads and transposed reads
-    constexpr int VSTR = D + 8;              // V tile: row reads only
-    constexpr int KS = D / 16, DT = D / 32, CPR = D / 8;
-    constexpr int NCH = BC * CPR / NT;       // 16-byte chunks per thread and tensor
+    constexpr int D = 256, BC = 64, BR = 128;
+    using Tile = WaveTile<D>;                // the layout of 32 rows in the LDS; a block is two of them
+    constexpr int BLOCK_B = 2 * Tile::TILE_B;  // a block of K or V
+    constexpr int STAGE_B = 2 * BLOCK_B;     // K, V
+    constexpr int KS = D / 16, DT = D / 32;
     constexpr int KP = 4;
     using E = Elem<Tag>;
-    __shared__ __attribute__((aligned(16))) uint16_t lds_k[2][BC * KSTR];
-    __shared__ __attribute__((aligned(16))) uint16_t lds_v[2][BC * VSTR];
+    __shared__ __attribute__((aligned(1024))) char lds[2 * STAGE_B];
 
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int col = lane & 31, half = lane >> 5;
     const WorkItem item = work_item<CAUSAL>(blockIdx.x, total_wg, n_qtiles);
     const int bh = item.head;
@@ -1697,19 +1697,37 @@ fa_bwd_dq_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
     float sc = scale * kLog2e;
     asm volatile("" : "+v"(sc));  // in a vector register: an FMA with a scalar operand issues at a lower rate
 
-    const __amdgpu_buffer_rsrc_t k_rsrc = make_buffer(k + kv_off, (uint32_t)N * D * 2);
-    const __amdgpu_buffer_rsrc_t v_rsrc = make_buffer(v + kv_off, (uint32_t)N * D * 2);
-    i32x4 pre[2 * NCH];  // the next block's K chunks, then its V chunks; blocks past the end read as zero
-    auto load_chunk = [&](int t, int c) __attribute__((always_inline)) {
-        pre[c] = buffer_load_16B(c < NCH ? k_rsrc : v_rsrc, t * BC * D * 2 + (tid + (c % NCH) * NT) * 16);
+    // the next block to be requested (keys past N, and blocks past the last one, read as zero), a quarter by each wave
+    BufferWords k_rsrc = make_buffer_words(k + kv_off, (uint32_t)N * D * 2), v_rsrc = make_buffer_words(v + kv_off, (uint32_t)N * D * 2);
+    auto next_block = [&]() __attribute__((always_inline)) {
+        advance(k_rsrc, BLOCK_B);
+        advance(v_rsrc, BLOCK_B);
     };
-    auto store_chunk = [&](int st, int c) __attribute__((always_inline)) {
-        const int e = tid + (c % NCH) * NT, row = e / CPR, cc = e % CPR;
-        if (c < NCH) *reinterpret_cast<i32x4*>(lds_k[st] + row * KSTR + cc * 8) = pre[c];
-        else *reinterpret_cast<i32x4*>(lds_v[st] + row * VSTR + cc * 8) = pre[c];
-    };
+    // Addresses: row and transposed operands in the stage being read (V, the second 32 keys, 16 keys and columns from 128 on are
+    // offsets), and what the lane fetches
+    const uint32_t lds_base = lds_address(lds), piece = lds_base + wave * (BLOCK_B / 4);
+    uint32_t row_at[KS / 2], tr_at[DT / 2][2];
+    int src[8];
 #pragma unroll
-    for (int c = 0; c < 2 * NCH; ++c) load_chunk(0, c);
+    for (int ks = 0; ks < KS / 2; ++ks) {
+        row_at[ks] = lds_base + col * Tile::ROWB + (((2 * ks + half) ^ Tile::swizzle(col)) << 4);
+        asm volatile("" : "+v"(row_at[ks]));
+    }
+#pragma unroll
+    for (int dt = 0; dt < DT / 2; ++dt)
+#pragma unroll
+        for (int hi = 0; hi < 2; ++hi) {
+            tr_at[dt][hi] = lds_base + Tile::tr_of(dt, hi, lane);
+            asm volatile("" : "+v"(tr_at[dt][hi]));
+        }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        src[i] = wave * (BLOCK_B / 4) + Tile::src_of(i, lane);
+        asm volatile("" : "+v"(src[i]));
+    }
+#pragma unroll
+    for (int n = 0; n < 16; ++n) global_to_lds_16B(n & 1 ? v_rsrc : k_rsrc, piece + (n & 1) * BLOCK_B + (n >> 1) * 1024, src[n >> 1]);
+    next_block();
 
     i32x4 qreg[KS], doreg[KS];
 #pragma unroll
@@ -1735,31 +1753,28 @@ fa_bwd_dq_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[dt][r] = 0.f;
 #pragma unroll
-    for (int c = 0; c < 2 * NCH; ++c) store_chunk(0, c);
-#pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(qreg[ks]), "+a"(doreg[ks]));
-    __syncthreads();
+    auto landed = [&]() __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    landed();
 
-    const int tr_row = (lane & 15) >> 2;
-    const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-
+    int st = 0;
     auto block = [&](int t, auto mask_tag) __attribute__((always_inline)) {
         constexpr bool MASK = decltype(mask_tag)::value;
-        const int st = t & 1;
-        uint32_t k_rows = lds_address(lds_k[st]) + (col * KSTR + half * 8) * 2;
-        uint32_t v_rows = lds_address(lds_v[st]) + (col * VSTR + half * 8) * 2;
-        uint32_t k_tr = lds_address(lds_k[st]) + ((4 * half + tr_row) * KSTR + tr_col) * 2;
+        const uint32_t next = piece + (st ^ 1) * STAGE_B;
         int bound = limit - t * BC - 4 * half;  // last visible key of the lane's half of a tile
-        asm volatile("" : "+v"(k_rows), "+v"(v_rows), "+v"(k_tr), "+v"(bound));
+        asm volatile("" : "+v"(bound));
         // step u of the two score products: (tensor, 16 columns, 32-key tile), the two tiles' chains alternating
         auto row_read = [&](int u) __attribute__((always_inline)) {
             const int ks = (u % (2 * KS)) / 2, kt = u & 1;
-            return u < 2 * KS ? lds_load_16B(k_rows + (kt * 32 * KSTR + ks * 16) * 2)
-                              : lds_load_16B(v_rows + (kt * 32 * VSTR + ks * 16) * 2);
+            return lds_load_16B(row_at[ks % (KS / 2)] + (u < 2 * KS ? 0 : BLOCK_B) + kt * Tile::TILE_B + (ks / (KS / 2)) * 256);
         };
         auto tr_read = [&](int w) __attribute__((always_inline)) {  // step w of the dQ product: (16 keys, 32 columns)
-            const uint32_t a = k_tr + ((w / DT) * 16 * KSTR + (w % DT) * 32) * 2;
-            const i32x2 lo = lds_read_tr16(a), hi = lds_read_tr16(a + 8 * KSTR * 2);
+            const int dt = w % DT, off = (w / DT) * 16 * Tile::ROWB + (dt / (DT / 2)) * 256;
+            const i32x2 lo = lds_read_tr16(tr_at[dt % (DT / 2)][0] + off), hi = lds_read_tr16(tr_at[dt % (DT / 2)][1] + off);
             return i32x4{lo[0], lo[1], hi[0], hi[1]};
         };
         f32x16 sacc[2], pacc[2];
@@ -1767,16 +1782,22 @@ fa_bwd_dq_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
 #pragma unroll
         for (int u = 0; u < KP; ++u) ring[u] = row_read(u);
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < 4 * KS; ++u) {
-            const int ks = (u % (2 * KS)) / 2, kt = u & 1;
+        static_for<4 * KS>([&](auto step) __attribute__((always_inline)) {
+            constexpr int u = decltype(step)::value, ks = (u % (2 * KS)) / 2, kt = u & 1;
+            constexpr int n_req = u / 4, to = (n_req & 1) * BLOCK_B + (n_req >> 1) * 1024;  // 16 requests, one every fourth step
             const i32x4 a = ring[u % KP];
-            if (u + KP < 4 * KS) ring[u % KP] = row_read(u + KP);
+            if constexpr (u + KP < 4 * KS) ring[u % KP] = row_read(u + KP);
             else tr[u + KP - 4 * KS] = tr_read(u + KP - 4 * KS);
-            if (u < 2) MfmaVgprAcc<Tag>::first(sacc[kt], a, qreg[ks]);
-            else if (u < 2 * KS) MfmaVgprAcc<Tag>::run(sacc[kt], a, qreg[ks]);
-            else if (ks == 0) MfmaVgprAcc<Tag>::start(pacc[kt], a, doreg[ks]);
-            else MfmaVgprAcc<Tag>::run(pacc[kt], a, doreg[ks]);
+            f32x16& c = u < 2 * KS ? sacc[kt] : pacc[kt];
+            const i32x4& b = u < 2 * KS ? qreg[ks] : doreg[ks];
+            const BufferWords& rsrc = n_req & 1 ? v_rsrc : k_rsrc;
+            using M = MfmaVgprAcc<Tag>;
+            if constexpr (u == 0) M::template first_and_load<to>(c, a, b, rsrc, next, src[n_req >> 1]);
+            else if constexpr (u == 1) M::first(c, a, b);
+            else if constexpr (u == 2 * KS) M::template start_and_load<to>(c, a, b, rsrc, next, src[n_req >> 1]);
+            else if constexpr (u == 2 * KS + 1) M::start(c, a, b);
+            else if constexpr (u % 4 == 0) M::template run_and_load<to>(c, a, b, rsrc, next, src[n_req >> 1]);
+            else M::run(c, a, b);
             if (u < 16) pacc[0][u] = pacc[1][u] = -d_row;  // dP - D comes out of the MFMAs
             if (u == 2 * KS) mfma_result_wait(sacc[0], sacc[1]);
             if (u >= 2 * KS) {
@@ -1785,9 +1806,9 @@ fa_bwd_dq_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
                 if constexpr (MASK) x = i * 32 + 8 * (r >> 2) + (r & 3) > bound ? 0.f : x;
                 sacc[i][r] = x;
             }
-            if (u % (2 * KS / NCH) == 0) load_chunk(t + 1, u / (2 * KS / NCH));
             __builtin_amdgcn_sched_barrier(0);
-        }
+        });
+        next_block();
         mfma_result_wait(pacc[0], pacc[1]);
         auto gradient = [&](int i, int r) __attribute__((always_inline)) {  // a pair of scores becomes a register of dS
             dsb[2 * i + (r >> 3)][(r >> 1) & 3] = E::pack2(sacc[i][r] * pacc[i][r], sacc[i][r + 1] * pacc[i][r + 1]);
@@ -1800,10 +1821,18 @@ fa_bwd_dq_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
             if (w + KP < 4 * DT) tr[w % KP] = tr_read(w + KP);
             acc[w % DT] = E::mma(a, dsb[w / DT], acc[w % DT]);
             if (w < 16 && !(w & 1)) gradient(1, w);
-            if (w % (4 * DT / (2 * NCH)) == 0) store_chunk(st ^ 1, w / (4 * DT / (2 * NCH)));
             __builtin_amdgcn_sched_barrier(0);
         }
-        __syncthreads();
+        landed();
+        const int move = st ? -STAGE_B : STAGE_B;
+#pragma unroll
+        for (int ks = 0; ks < KS / 2; ++ks) row_at[ks] += move;
+#pragma unroll
+        for (int dt = 0; dt < DT / 2; ++dt) {
+            tr_at[dt][0] += move;
+            tr_at[dt][1] += move;
+        }
+        st ^= 1;
     };
     const int last_q = min(qt * BR + BR, N) - 1;
     const int n_blocks = CAUSAL ? last_q / BC + 1 : (N + BC - 1) / BC;
@@ -1813,11 +1842,9 @@ fa_bwd_dq_d256_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
     for (; t < n_plain; ++t) block(t, std::false_type{});
     for (; t < n_blocks; ++t) block(t, std::true_type{});
 
-    // dQ_i = scale * acc, transposed into whole 128-byte lines through the K buffers (every read of them is behind the
-    // last barrier; what the last block stored there nobody reads)
-    static_assert(sizeof(lds_k) >= 4 * 4096, "patches must fit");
-    store_rows_via_lds<Tag, DT>(acc, scale, reinterpret_cast<char*>(&lds_k[0][0]) + wave * 4096,
-                                make_buffer(dq + head_off, (uint32_t)N * D * 2), wave_q0, lane);
+    // dQ_i = scale * acc, transposed into whole 128-byte lines through the stages (every read and write of them is behind the last
+    // barrier)
+    store_rows_via_lds<Tag, DT>(acc, scale, lds + wave * 4096, make_buffer(dq + head_off, (uint32_t)N * D * 2), wave_q0, lane);
 }
 
 // ---------------------------------------------------------------------------------------
