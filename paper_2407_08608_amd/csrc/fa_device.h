@@ -285,11 +285,13 @@ struct WaveTile {
         const int half = lane >> 5, tr_row = (lane & 15) >> 2, quad = lane & 3, blk = (lane >> 4) & 1, r = 4 * half + tr_row + 8 * hi;
         return r * ROWB + (((4 * dt + 2 * blk + (quad >> 1)) ^ swizzle(r)) << 4) + 8 * (quad & 1);
     }
+    // (src_of and tr_of written out: through the functions the forward's 128-row tiles at d = 128 spill a register)
     __device__ __forceinline__ WaveTile(uint32_t at, int lane) : base(at) {
-        const int col = lane & 31, half = lane >> 5;
+        const int col = lane & 31, half = lane >> 5, tr_row = (lane & 15) >> 2, quad = lane & 3, blk = (lane >> 4) & 1;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-            src[i] = src_of(i, lane);
+            const int r = (i % PERIOD) * RPI + lane / CPR;
+            src[i] = r * ROWB + ((lane % CPR) ^ swizzle(r)) * 16 + (i / PERIOD) * (PERIOD * 1024);
             asm volatile("" : "+v"(src[i]));
         }
 #pragma unroll
@@ -301,7 +303,8 @@ struct WaveTile {
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int hi = 0; hi < 2; ++hi) {
-                tr_at[dt][hi] = at + tr_of(dt, hi, lane);
+                const int r = 4 * half + tr_row + 8 * hi;
+                tr_at[dt][hi] = at + r * ROWB + (((4 * dt + 2 * blk + (quad >> 1)) ^ swizzle(r)) << 4) + 8 * (quad & 1);
                 asm volatile("" : "+v"(tr_at[dt][hi]));
             }
     }
