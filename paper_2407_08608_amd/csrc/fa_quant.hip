@@ -11,7 +11,8 @@
 //     own chunks.  Eight lanes at d = 128 would need ds_swizzle or one DPP stage more: 23.2 / 24.7 us (32 x 8192).
 //   - rows go through one resource per block: past its end reads give zeros and stores are dropped, so there is no branch
 //     and all loads are in flight at once;
-//   - signs are put on the 16-bit words before they are unpacked, two elements an instruction;
+//   - signs are put on 16-bit words before they are unpacked, two elements an instruction (should any not be 1 or -1, a second
+//     way multiplies by the magnitudes too: 0.1 us of a launch for the look at them);
 //   - 1 / sqrt(d) is a power of two at d = 64 and 256 and goes into the code's factor there, exactly;
 //   - the clamp, which changes nothing in a block of ordinary values, is left to a second way for those that are not;
 //   - lanes trade codes in pairs and store 16 bytes each.
@@ -59,6 +60,12 @@ static __device__ __forceinline__ float larger(float a, float b) {
     return KEEP_NAN ? __builtin_elementwise_maximum(a, b) : fmaxf(a, b);
 }
 
+// Not fused with a sum that takes it
+static __device__ __forceinline__ float rounded_product(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
+
 // 32 values of the block to a lane: 64 took longer at d = 128 (25.3 / 22.8 us, 32 x 8192) and d = 256 (24.9 / 23.8, 16 x 8192)
 constexpr int quant_threads(int d) { return 4 * d; }
 
@@ -85,6 +92,9 @@ fa_quant_kernel(const void* __restrict__ x, uint8_t* __restrict__ x8, float* __r
     const int n_el = min(N - blk * kBlockRows, kBlockRows) * D;
     const float inv_sqrt_d = (float)(1.0 / __builtin_sqrt((double)D));
 
+    // Four signs to a lane, to see whether all are 1 or -1; requested ahead of the rows, so that the branch on it waits for no row
+    int four_signs = 0x01010101;
+    if constexpr (HADAMARD && IN_DTYPE != FA_F32) __builtin_memcpy(&four_signs, signs + 4 * (lane % (D / 4)), 4);
     const __amdgpu_buffer_rsrc_t rsrc = make_buffer(static_cast<const char*>(x) + off * C::ELEM, (uint32_t)(n_el * C::ELEM));
     C raw[PASSES][CH];
 #pragma unroll
@@ -92,7 +102,7 @@ fa_quant_kernel(const void* __restrict__ x, uint8_t* __restrict__ x8, float* __r
 #pragma unroll
         for (int c = 0; c < CH; ++c) raw[ps][c].load(rsrc, ((ps * RPP + row) * D + 8 * (p + LPR * c)) * C::ELEM);
 
-    if constexpr (HADAMARD) {  // the signs go on in the words as they lie in memory
+    if constexpr (HADAMARD && IN_DTYPE != FA_F32) {  // the signs go on in the words as they lie in memory
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             i32x2 s8;
@@ -102,15 +112,8 @@ fa_quant_kernel(const void* __restrict__ x, uint8_t* __restrict__ x8, float* __r
                 const int m = s8[g] & (int)0x80808080;
 #pragma unroll
                 for (int ps = 0; ps < PASSES; ++ps) {
-                    if constexpr (IN_DTYPE == FA_F32) {
-                        raw[ps][c].w[g][0] ^= __builtin_amdgcn_perm(0, m, 0x000c0c0c);
-                        raw[ps][c].w[g][1] ^= __builtin_amdgcn_perm(0, m, 0x010c0c0c);
-                        raw[ps][c].w[g][2] ^= __builtin_amdgcn_perm(0, m, 0x020c0c0c);
-                        raw[ps][c].w[g][3] ^= __builtin_amdgcn_perm(0, m, 0x030c0c0c);
-                    } else {
-                        raw[ps][c].w[0][2 * g] ^= __builtin_amdgcn_perm(0, m, 0x010c000c);
-                        raw[ps][c].w[0][2 * g + 1] ^= __builtin_amdgcn_perm(0, m, 0x030c020c);
-                    }
+                    raw[ps][c].w[0][2 * g] ^= __builtin_amdgcn_perm(0, m, 0x010c000c);
+                    raw[ps][c].w[0][2 * g + 1] ^= __builtin_amdgcn_perm(0, m, 0x030c020c);
                 }
             }
         }
@@ -118,18 +121,39 @@ fa_quant_kernel(const void* __restrict__ x, uint8_t* __restrict__ x8, float* __r
 
     float y[PASSES][CH][8];
 #pragma unroll
-    for (int ps = 0; ps < PASSES; ++ps) {
-        if constexpr (!HADAMARD) {
+    for (int ps = 0; ps < PASSES; ++ps)
 #pragma unroll
-            for (int c = 0; c < CH; ++c)
+        for (int c = 0; c < CH; ++c)
 #pragma unroll
-                for (int t = 0; t < 8; ++t) y[ps][c][t] = raw[ps][c].at(t);
+            for (int t = 0; t < 8; ++t) y[ps][c][t] = raw[ps][c].at(t);
+    if constexpr (HADAMARD) {
+        // what the words do not have yet: the signs of fp32 rows, and magnitudes other than 1
+        auto multiply = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const signed char* at = signs + 8 * (p + LPR * c);
+                if constexpr (IN_DTYPE != FA_F32) asm volatile("" : "+v"(at));  // read again: kept, they would cost the ordinary way registers
+                i32x2 s8;
+                __builtin_memcpy(&s8, at, 8);
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const float s = (float)(signed char)(s8[t >> 2] >> (8 * (t & 3)));
+#pragma unroll
+                    for (int ps = 0; ps < PASSES; ++ps) y[ps][c][t] = rounded_product(y[ps][c][t], IN_DTYPE == FA_F32 ? s : fabsf(s));
+                }
+            }
+        };
+        if constexpr (IN_DTYPE == FA_F32) {
+            multiply();
         } else {
+            const int negative = (four_signs >> 7) & 0x01010101, unit = ((negative << 8) - negative) | 0x01010101;
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(four_signs != unit) != 0, 0)) multiply();
+        }
+#pragma unroll
+        for (int ps = 0; ps < PASSES; ++ps) {
             // element index e = t + 8 p + 8 LPR c
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
-#pragma unroll
-                for (int t = 0; t < 8; ++t) y[ps][c][t] = raw[ps][c].at(t);
 #pragma unroll
                 for (int h = 1; h < 8; h <<= 1)  // strides 1, 2, 4
 #pragma unroll

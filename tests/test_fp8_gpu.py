@@ -296,3 +296,19 @@ def test_quant_of_infinities_and_nan(d):
     want[128 + 9, 1] = want[256 + 64, d - 1] = want[256 + 65, 0] = low
     np.testing.assert_array_equal(codes[0, 0], want)
     np.testing.assert_array_equal(scales[0, 0], np.array([1 / 448, np.inf, np.inf, 1 / 448], np.float32))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("d,other", [(64, {63: 0}), (64, {0: 2, 9: -128}), (128, {127: 0}), (128, {5: -3, 70: 127}), (256, {255: 0}),
+                                     (256, {128: -128, 200: 1, 1: 0})])
+def test_quant_multiplies_by_signs_of_any_magnitude(d, other, dtype):
+    """Signs beside 1 and -1 are factors like any other, whichever lane of the kernel's check holds them."""
+    x = inputs.heavy_tailed_tensor(40 + d, "x", (1, 2, 200, d), dtype)
+    signs = inputs.random_signs(41, d)
+    for at, s in other.items():
+        signs[at] = s
+    for per_tensor in (False, True):
+        codes, scales = _quant_gpu(x, signs, per_tensor)
+        c_ref, s_ref = f8.quantize(x.float().numpy(), signs.numpy(), 128, per_tensor)
+        np.testing.assert_array_equal(scales.view(np.uint32), s_ref.view(np.uint32))
+        np.testing.assert_array_equal(codes, c_ref)
