@@ -26,33 +26,6 @@ constexpr float kLazyLog2 = 8.0f;
 // every P~ of a block that stays below it fits fp16 with room to spare)
 constexpr float kRaiseAbove = 16384.0f;
 
-template <int D, int BC, int NT>
-struct TileCopy {
-    static constexpr int kChunksPerRow = D / 8;  // 16-byte chunks of 8 16-bit elements
-    static constexpr int kChunks = BC * kChunksPerRow;
-    static constexpr int kPerThread = kChunks / NT;
-    static_assert(kChunks % NT == 0, "tile must divide evenly over the workgroup");
-
-    // A [BC][D] tile of a row-major [N][D] head is one contiguous run of bytes, so chunk c of the
-    // tile sits at tile_byte_off + 16*c: no per-row address arithmetic.  Rows past N fall outside
-    // the buffer resource and read as zero (their scores are masked anyway).
-    static __device__ __forceinline__ void from_global(__amdgpu_buffer_rsrc_t head, int tile_byte_off, int tid,
-                                                       i32x4 (&regs)[kPerThread]) {
-#pragma unroll
-        for (int i = 0; i < kPerThread; ++i)
-            regs[i] = buffer_load_16B(head, tile_byte_off + (tid + i * NT) * 16);
-    }
-    template <int STRIDE>
-    static __device__ __forceinline__ void to_lds(uint16_t* lds, int tid, const i32x4 (&regs)[kPerThread]) {
-#pragma unroll
-        for (int i = 0; i < kPerThread; ++i) {
-            int c = tid + i * NT;
-            int row = c / kChunksPerRow, col = c % kChunksPerRow;
-            *reinterpret_cast<i32x4*>(lds + row * STRIDE + col * 8) = regs[i];
-        }
-    }
-};
-
 // ---------------------------------------------------------------------------------------
 // The forward where its query tiles would leave most of the chip idle (few heads, short sequences): FewForward.
 //
