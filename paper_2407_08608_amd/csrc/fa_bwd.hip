@@ -870,6 +870,11 @@ constexpr int few_lds_bytes(int d) {
 // by two additions, MFMA and staging request share their wait states, and the waits for the score products stand a step
 // later.  A tile's first operands are read under the last products of the one before.  Requests go out two to a step of
 // the first product: one to a step of both, they came late where many workgroups ask for the same lines.
+// Where D is computed here a wave has few tiles, most of them of other heads.  What counts then is the code run once and what
+// its requests wait for: the next tile is aimed at in one place, its rows of O follow its staging requests, and dO comes from
+// the staged tile.  (With rows of both asked for ahead of the requests and the code at three places, 0.1 to 0.6 us more.)
+// bf16, whole backward, us, before the 128-query dQ work beside this / with it / so: d = 64 4 on 1 x 32 4.97 / 5.16 / 4.62, 6 on 1 x 59
+// 7.51 / 8.14 / 6.72, 2 x 128 5.56 / 5.43 / 4.88, 16 x 333 causal 9.65 / 9.51 / 8.58; d = 128 16 on 4 x 20 7.35 / 7.74 / 7.02.
 // bf16, this pass of d = 128, H = 32 on 4, N = 2048 causal 126 -> 109 us, no mask (whole) 8 on 1 x 2368 143 -> 128.  (Not kept: eight
 // waves in pairs that share tiles and trade P and dS through the LDS, which put all of them in step: 177.)
 template <typename Tag, int D, bool CAUSAL, bool D_READY>
@@ -922,18 +927,15 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
     float ldpre = 0.f;
     int ldrow = 0;
     const float* ld_head = lse;  // lanes 0..31 carry L, 32..63 carry D
-    i32x4 opre[KS], dopre[KS];   // without D in the workspace: the lane's half of a row of O and of dO
+    i32x4 opre[KS];              // without D in the workspace: the lane's half of a row of O
     BufferWords q_rsrc, do_rsrc;
-    auto aim_rows = [&]() __attribute__((always_inline)) {
+    auto load_rows = [&]() __attribute__((always_inline)) {
         const int row = min(ldrow, N - 1);
         ldpre = ld_head[row];
         if constexpr (!D_READY) {
             const size_t at = ((size_t)bh * kv_group + gi) * N + row;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                opre[ks] = *reinterpret_cast<const i32x4*>(o + at * D + ks * 16 + half * 8);
-                dopre[ks] = *reinterpret_cast<const i32x4*>(dout + at * D + ks * 16 + half * 8);
-            }
+            for (int ks = 0; ks < KS; ++ks) opre[ks] = *reinterpret_cast<const i32x4*>(o + at * D + ks * 16 + half * 8);
         }
     };
     auto aim_head = [&]() __attribute__((always_inline)) {  // the next requests: tile t, counted on into the next query heads
@@ -952,27 +954,28 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
     };
     auto aim_next = [&](bool any) __attribute__((always_inline)) {
         t += NW;
-        if (__builtin_expect(any & (t < n_t), 1)) {  // the same head, which costs a few instructions only
+        if (D_READY && __builtin_expect(any & (t < n_t), 1)) {  // the same head, which costs a few instructions only
             advance(q_rsrc, NW * Tiles::TILE_B);
             advance(do_rsrc, NW * Tiles::TILE_B);
             ldrow += NW * BQ;
-            aim_rows();
+            load_rows();
         } else if (any) {
             aim_head();
-            aim_rows();
+            if constexpr (D_READY) load_rows();
         } else {  // past the last tile: zeros that nothing reads
             q_rsrc.w[2] = do_rsrc.w[2] = 0;
         }
     };
-    // L and -D of the tile aimed at go where its products find them.  Rows past N get L = +inf so that P = exp2(0 - inf) = 0,
-    // and D = 0.  (Keys past N need nothing: what their lanes compute goes to rows of dK and dV that are not stored.)
+    // L and -D of the tile aimed at, which has landed and which the addresses point at, go where its products find them.  Rows
+    // past N get L = +inf so that P = exp2(0 - inf) = 0, and D = 0.  (Keys past N need nothing: what their lanes compute goes
+    // to rows of dK and dV that are not stored.)
     const float ld_factor = half ? -1.f : kLog2e, ld_none = half ? 0.f : INFINITY;
     auto put_rows = [&]() __attribute__((always_inline)) {
         float x = ldpre;
         if constexpr (!D_READY) {
             float d_row = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) d_row = dot8<Tag>(opre[ks], dopre[ks], d_row);
+            for (int ks = 0; ks < KS; ++ks) d_row = dot8<Tag>(opre[ks], tiles.row_read(Tiles::TILE_B, ks), d_row);
             d_row = sum_both_halves(d_row);
             x = half ? d_row : x;
         }
@@ -991,6 +994,7 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
         f32x16 sacc, pacc;
         const uint32_t ld = lds_address(lds_ld) + 16 * half;
         const uint32_t next = tiles.base + (st ^ 1) * Tiles::STAGE_B;
+        if constexpr (!D_READY) aim_next(left > 0);
         i32x4 tr[KP], pa[2], dsa[2];
         auto probability = [&](int rr) __attribute__((always_inline)) {
             sacc[rr] = fast_exp2(__builtin_fmaf(sacc[rr], sc, -l4[rr >> 2][rr & 3]));
@@ -1013,6 +1017,8 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
             else if constexpr (u < KS) MfmaVgprAcc<Tag>::template run_and_load<u * 1024>(sacc, a, kreg[u], q_rsrc, next, tiles.src[u]);
             else if constexpr (u == KS) MfmaVgprAcc<Tag>::start(pacc, a, vreg[u - KS]);
             else MfmaVgprAcc<Tag>::run(pacc, a, vreg[u - KS]);
+            if constexpr (!D_READY && u == KS)
+                if (left > 0) load_rows();
             if constexpr (u == KS + 1) mfma_result_wait_rest<4>(sacc);
             if constexpr (u > KS) {
                 constexpr int i = u - KS - 1;
@@ -1037,8 +1043,8 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
             if constexpr (u + KP < 4 * DT) tr[u % KP] = tr_read(u + KP);
             if constexpr (u == 4 * DT - 2) {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the next tile has landed
-                if (D_READY || left > 0) put_rows();
                 tiles.move(st ? -Tiles::STAGE_B : Tiles::STAGE_B);
+                if (D_READY || left > 0) put_rows();
             }
             if constexpr (u >= 4 * DT - 2)
 #pragma unroll
@@ -1053,14 +1059,14 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
                     pacc[rr] *= sacc[rr];
                     if (rr & 1) dsa[rr >> 3][(rr >> 1) & 3] = E::pack2(pacc[rr - 1], pacc[rr]);
                 }
-            if constexpr (u == 4 * DT - 1) aim_next(left > 1);
+            if constexpr (D_READY && u == 4 * DT - 1) aim_next(left > 1);
             __builtin_amdgcn_sched_barrier(0);
         });
     };
 
     if (mine > 0) {
         aim_head();
-        aim_rows();
+        load_rows();
 #pragma unroll
         for (int n = 0; n < Tiles::NREQ; ++n) tiles.request(q_rsrc, do_rsrc, 0, n);
 #pragma unroll
@@ -1070,11 +1076,11 @@ static __device__ __forceinline__ void dkdv_few(int block, const uint16_t* __res
 #pragma unroll
         for (int u = 0; u < KP; ++u) ring[u] = row_read(u);
         int q0 = t * BQ;
-        aim_next(mine > 1);
+        if constexpr (D_READY) aim_next(mine > 1);
         for (int n = 0, st = 0; n < mine; ++n, st ^= 1) {
             const int q0_next = t * BQ;
             tile(q0, st, mine - 1 - n);
-            q0 = q0_next;
+            q0 = D_READY ? q0_next : t * BQ;
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the zeros of the last request: the LDS is about to be reused
