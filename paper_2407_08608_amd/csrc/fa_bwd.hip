@@ -1258,7 +1258,7 @@ static __device__ __forceinline__ void dq_few(int block, const uint16_t* __restr
 }
 
 // The dQ pass with 128 queries to a workgroup, 32 to each of its four waves, which walk all the keys together: every tile of
-// K and V is staged once for the four of them, three tiles ahead into a ring of eight, one barrier to a tile.  The last product
+// K and V is staged once for the four of them, three tiles ahead into a ring, one barrier to a tile.  The last product
 // comes one tile late, beside the next tile's dS; without that, 128 queries took 68.3 us where these take 63.5 and 32 queries 96.6
 // (bf16, D and this pass, d = 128, H = 32 on 4, N = 2048 causal).
 template <typename Tag, int D, bool CAUSAL, bool D_READY>
@@ -1268,6 +1268,8 @@ static __device__ __forceinline__ void dq_rows(int block, const uint16_t* __rest
                                                float* __restrict__ dvec, uint16_t* __restrict__ dq, int N,
                                                int n_heads, int kv_group, float scale, char* lds) {
     using Tiles = WaveTiles<D>;
+    // (five stages would do for this lead and a product that comes a tile late; eight are there for the key blocks' tiles anyway, and
+    // the ring's remainder by eight is one instruction)
     constexpr int NW = 4, BR = 32 * NW, BK = Tiles::ROWS, STAGES = 8, LEAD = 3;
     constexpr int KS = D / 16, DT = D / 32;
     constexpr int KP = D == 128 ? 8 : 4;      // steps by which operand reads lead their MFMAs
@@ -1446,10 +1448,10 @@ static __device__ __forceinline__ void dq_rows(int block, const uint16_t* __rest
 }
 
 // One launch for the dK/dV pass or for both: n_dkdv workgroups take 32 keys each, the others 32 or 128 queries each
-// (choose_bwd_forms).  With both in one launch the dQ work fills the CUs that the shorter key blocks of a causal dK/dV pass leave
+// (choose_bwd_form).  With both in one launch the dQ work fills the CUs that the shorter key blocks of a causal dK/dV pass leave
 // idle.  (dQ alone comes here where it has to follow the dK/dV pass.)
 // D_READY: D is in the workspace already; otherwise both kinds compute it for the rows they work on (the dK/dV kind
-// once per tile; own_row_sums says when).
+// once per tile; bwd_own_row_sums says when).
 constexpr int kDqRows = 1, kDqFirst = 2;  // dq_form: 128 queries to a workgroup; dQ work ahead of the key blocks
 template <typename Tag, int D, bool CAUSAL, bool D_READY>
 __global__ void __launch_bounds__(256, D == 64 ? 2 : 1)
@@ -1860,79 +1862,6 @@ size_t bwd_workspace_bytes(int B, int H, int N, int d) {
     return (rows * sizeof(float) + 15) & ~(size_t)15;  // D = rowsum(dO o O)
 }
 
-// Which forms the two passes take at d = 64 and 128.  The 32-query / 32-key forms (fa_bwd_few_kernel) make four times as
-// many workgroups, each with a quarter of the serial chain, at a higher price per MFMA, so what counts is how often they
-// fill the chip (kChip: how many it holds at once) and how long the chain is that they shorten: the limits grow with the
-// chain, in 32-row tiles.  Under a causal mask, where the large forms idle at the short end, they grow further, and with
-// four or more query heads to a key/value head, whose key blocks are long chains, once more.
-// In the one launch the dQ pass has 32 queries to a workgroup, its waves splitting the keys, or 128 (kDqRows): a quarter of the
-// staging, starts and ends, but the whole chain.  128 win from `longest` fillings on, and beside long key blocks always
-// (`uneven`: but where both kinds take equally long and come out as one and a half rounds).  Whichever has the longer
-// chains goes first: key blocks of a group of g have g / 4 of the 128-query workgroups'.
-// Whole backward, bf16, us; large forms, dK/dV alone in its 32-key form, one launch (lost to the large forms: the last two):
-//   d = 128 causal   30 x 512 41.8, 38.1, 27.0;  14 on 7 x 4608 399, 354, 300;  32 on 4 x 2048 472, 226, 142;
-//                    32 on 4 x 3584 877, 387, 442;  24 on 12 x 4096 386, 387, 389
-//           no mask  32 x 512 40.6, 39.9, 30.4;  9 x 3584 243, 270, 229;  8 on 1 x 512 127, 52, 35;  90 on 45 x 1024 208, 309, 312;
-//                    109 x 113 20.8, 23.4, 22.7
-//   d = 64  causal   42 x 1024 52.8, 52.3, 41.2;  10 x 5120 217, 190, 138;  72 on 9 x 512 107, 40, 30;  77 x 1536 113, 168, 163;
-//                    109 x 320 23.5, 29.2, 26.4
-//           no mask  22 x 1536 80.4, 77.5, 65.3;  40 on 5 x 512 99, 37, 27;  57 x 512 28.6, 37.6, 36.1;  15 x 3328 175, 186, 198
-// One launch; 32 queries, 128 behind the key blocks, 128 ahead of them (the last two: 32 stay):
-//   d = 128 causal   32 x 512 30.8, 32.6, 26.1;  64 x 256 28.3, 27.1, 23.7;  16 on 8 x 1024 35.8, 37.5, 31.0;  8 x 1024 21.4, 33.9, 28.9;
-//                    4 on 2 x 1024 21.0, 27.3, 27.4
-//           no mask  8 x 2048 76, 85, 70;  64 on 8 x 256 25.4, 25.0, 25.0;  2 x 4096 73, 119, 86;  8 on 4 x 1024 26.4, 29.7, 29.8
-//   d = 64           32 on 4 x 1024, no mask 58.1, 56.0, 59.8;  64 on 8 x 512, causal 30.4, 28.5, 30.9;  16 x 1024, causal 18.8, 26.8, 22.6
-// Over 7300 drawn shapes (1 to 256 heads, groups of 1 to 8, N from 64 to 8192) 0.3 to 1.4 % off the best of five on average,
-// by head dimension and mask.
-struct BwdForms {
-    bool dkdv_few, one_launch;
-    int dq_form;
-};
-template <int D>
-inline BwdForms choose_bwd_forms(long heads, long kv_heads, int N, int causal) {
-    if constexpr (D > 128) return {false, false, 0};
-    struct Limit {  // workgroups, in fillings of the chip: min(most, base + tiles / step)
-        float base, step, most;
-        float at(long tiles) const { const float x = base + (float)tiles / step; return x < most ? x : most; }
-    };
-    constexpr int kChip = D == 64 ? 512 : 256;
-    const Limit one = D == 64 ? (causal ? Limit{3.6f, 16, 10} : Limit{2.05f, 24, 5.8f}) : (causal ? Limit{5.8f, 22, 12} : Limit{3.6f, 26, 6.5f});
-    const Limit key = D == 64 ? (causal ? Limit{1, 64, 4} : Limit{1, 128, 3}) : (causal ? Limit{1, 32, 4} : Limit{1, 32, 2});
-    const long tiles = (N + 31) / 32, group = heads / kv_heads, chain = tiles * group;
-    const float q = (float)(heads * tiles) / kChip, k = (float)(kv_heads * tiles) / kChip;  // fillings
-    float both = tiles > 4 ? one.at(tiles) : tiles < 3 ? 1.25f : D == 64 ? 2.f : 3.2f;
-    if (D == 128 && causal && tiles > 4) both = both < 2.8f + (float)tiles / 6 ? both : 2.8f + (float)tiles / 6;
-    if (group >= 4 && tiles >= 16) both *= D == 64 ? 1.8f : causal ? 1.35f : 1.f;
-    const float rows = (float)(heads * ((N + 127) / 128)) / kChip;  // fillings by workgroups of 128 queries
-    const Limit longest = causal ? Limit{0.2f, 200, 0.62f} : group == 1 ? Limit{0.18f, 400, 0.5f} : Limit{0.2f, 160, 0.65f};
-    const bool uneven = !causal && group == 4 && tiles > 48 && rows > 0.42f && rows < 0.9f;
-    const bool wide = tiles > 2 && (group >= 4 && tiles > 4 ? !uneven : rows >= longest.at(tiles));
-    return {chain >= 6 && k <= key.at(chain), q + k <= both, wide ? kDqRows | (group <= (causal ? 4 : 2) ? kDqFirst : 0) : 0};
-}
-
-// Whether the one launch that runs both passes computes D for itself: cheaper than a launch for it (2.7 us and the gap
-// behind it) while a wave of a key block has few tiles, each of which then reads its rows of O and dO once more, and all
-// workgroups are on the chip at once, so that nothing waits for them.  Whole backward, bf16, us, with / without a launch
-// for D: d = 64, H = 2: N = 64 10.1 / 7.2 (the host's time), 384 10.2 / 8.3, 512 10.0 / 9.7, 1024 12.0 / 15.6; H = 40,
-// N = 384 17.1 / 20.9;  d = 128, H = 2: N = 128 9.5 / 9.4, 256 10.3 / 12.2, 512 12.3 / 18.0.
-template <int D>
-inline bool own_row_sums(long heads, long kv_heads, int N) {
-    const long tiles = (N + 31) / 32;
-    return tiles * (heads / kv_heads) <= (D == 64 ? 12 : 4) && (heads + kv_heads) * tiles <= (D == 64 ? 512 : 256);
-}
-
-// Up to which length the dQ pass takes 128-query workgroups of four waves with 32-key blocks, two or three to a CU,
-// instead of 256-query ones of eight with 64-key blocks: finer tiles waste less on the diagonal and on ragged ends, and
-// the start and end of one workgroup run under the loop of another; over long sequences staging every block twice as
-// often costs more.  Whole backward, bf16, H = 16, us, 256 / 128 queries:
-//   d = 64   no mask: N = 512 160 / 151, 1300 368 / 347, 2048 485 / 487;  causal: 512 128 / 121, 1300 223 / 200,
-//            2048 282 / 274, 3001 437 / 423, 4096 503 / 501
-//   d = 128  no mask: 512 356 / 340, 1300 710 / 690, 2048 931 / 950;  causal: 512 289 / 267, 1300 455 / 427,
-//            2048 575 / 570, 3001 845 / 863
-// Without a mask the line is drawn lower than it would be for these 16 heads: N = 1536, H = 20 68.5 / 65.9 (d = 64) and
-// 112 / 106 (d = 128), but H = 24 82.6 / 86.9 and 153 / 161.
-constexpr int short_rows(int d, int causal) { return causal ? (d == 64 ? 3072 : 1536) : 1280; }
-
 // Whether two runs of bytes share memory.
 inline bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
     const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
@@ -1962,16 +1891,18 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
                            H / H_kv, scale);
     };
     // workgroups of 32 or 128 queries / of 32 keys, when a pass is to use them
-    const BwdForms forms = choose_bwd_forms<D>((long)B * H, (long)B * H_kv, N, causal);
-    const int few_rows = forms.dq_form & kDqRows ? 128 : 32;
-    const long dq_few = forms.one_launch ? (long)B * H * ((N + few_rows - 1) / few_rows) : 0;
-    const long dkdv_few = forms.dkdv_few || forms.one_launch ? (long)B * H_kv * ((N + 31) / 32) : 0;
+    const BwdForm form = D > 128 ? kBwdLarge : choose_bwd_form((long)B * H, (long)B * H_kv, N, D, causal);
+    const bool one_launch = form == kBwdOne32 || form == kBwdOneRows;
+    const int dq_form = form == kBwdOneRows ? kDqRows | (bwd_rows_first(H / H_kv, causal) ? kDqFirst : 0) : 0;
+    const int few_rows = dq_form & kDqRows ? 128 : 32;
+    const long dq_few = one_launch ? (long)B * H * ((N + few_rows - 1) / few_rows) : 0;
+    const long dkdv_few = form != kBwdLarge ? (long)B * H_kv * ((N + 31) / 32) : 0;
     auto few = [&](long n_dkdv, long n_dq, bool d_ready) {
         if constexpr (D <= 128) {
             auto run = [&](auto kernel) {
                 hipLaunchKernelGGL(kernel, dim3((unsigned)(n_dkdv + n_dq)), dim3(256), 0, stream, u16(q), u16(k), u16(v),
                                    u16(o), u16(dout), lse, dvec, static_cast<uint16_t*>(dq),
-                                   static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv), N, (int)n_dkdv, forms.dq_form, B * H, H / H_kv, scale);
+                                   static_cast<uint16_t*>(dk), static_cast<uint16_t*>(dv), N, (int)n_dkdv, dq_form, B * H, H / H_kv, scale);
             };
             if (d_ready) causal ? run(fa_bwd_few_kernel<Tag, D, true, true>) : run(fa_bwd_few_kernel<Tag, D, false, true>);
             else causal ? run(fa_bwd_few_kernel<Tag, D, true, false>) : run(fa_bwd_few_kernel<Tag, D, false, false>);
@@ -1989,7 +1920,7 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
             causal ? dqp(fa_bwd_dq_d256_kernel<Tag, true>, 128, d_ready) : dqp(fa_bwd_dq_d256_kernel<Tag, false>, 128, d_ready);
         } else if (dq_few) {
             few(0, dq_few, d_ready);
-        } else if (N <= short_rows(D, causal)) {
+        } else if (N <= bwd_short_rows(D, causal)) {
             causal ? dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, true>, 128, d_ready) : dqp(fa_bwd_dq_kernel<Tag, D, 32, 4, false>, 128, d_ready);
         } else {
             causal ? dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, true>, 256, d_ready) : dqp(fa_bwd_dq_kernel<Tag, D, 64, 8, false>, 256, d_ready);
@@ -2016,8 +1947,8 @@ static int launch_bwd_t(const void* q, const void* k, const void* v, const void*
         // dQ written over Q or dO: a workgroup of the dQ pass reads these at its own rows before it writes them, but
         // the dK/dV pass reads all of them and has to come first.  (dK or dV may be over O then: D is not computed again.)
         ok = row_sums() && dkdv_pass() && dq_pass(true);
-    } else if (forms.one_launch) {
-        const bool own = !over_o && own_row_sums<D>((long)B * H, (long)B * H_kv, N);
+    } else if (one_launch) {
+        const bool own = !over_o && bwd_own_row_sums((long)B * H, (long)B * H_kv, N, D);
         ok = own || row_sums();
         if (ok) {
             few(dkdv_few, dq_few, !own);

@@ -159,6 +159,171 @@ inline dim3 forward_grid(long heads, int N, int n_qtiles, long total, int causal
     return causal && !paired ? dim3((unsigned)heads, (unsigned)n_qtiles) : dim3((unsigned)total);
 }
 
+// ---- The backward at d = 64 and 128: which forms its passes take
+//
+// Large: a launch for dQ (128 or 256 queries to a workgroup, D beside it), one for dK and dV (128 keys).  The others are
+// fa_bwd_few_kernel's: 32 keys to a workgroup, by itself behind the large dQ pass, or together with the dQ work in one launch,
+// which then comes in workgroups of 32 queries or of 128.
+enum BwdForm { kBwdLarge, kBwdKeys32, kBwdOne32, kBwdOneRows, kBwdForms };
+
+// Up to which length the large dQ pass takes 128-query workgroups of four waves with 32-key blocks, two or three to a CU,
+// instead of 256-query ones of eight with 64-key blocks: finer tiles waste less on the diagonal and on ragged ends, and
+// the start and end of one workgroup run under the loop of another; over long sequences staging every block twice as
+// often costs more.  Whole backward, bf16, H = 16, us, 256 / 128 queries:
+//   d = 64   no mask: N = 512 160 / 151, 1300 368 / 347, 2048 485 / 487;  causal: 512 128 / 121, 1300 223 / 200,
+//            2048 282 / 274, 3001 437 / 423, 4096 503 / 501
+//   d = 128  no mask: 512 356 / 340, 1300 710 / 690, 2048 931 / 950;  causal: 512 289 / 267, 1300 455 / 427,
+//            2048 575 / 570, 3001 845 / 863
+// Without a mask the line is drawn lower than it would be for these 16 heads: N = 1536, H = 20 68.5 / 65.9 (d = 64) and
+// 112 / 106 (d = 128), but H = 24 82.6 / 86.9 and 153 / 161.
+constexpr int bwd_short_rows(int d, int causal) { return causal ? (d == 64 ? 3072 : 1536) : 1280; }
+
+// What the forms cost, us.  A workgroup takes `start` and `tile` for each 32-row tile that its longest wave walks, next to as
+// many others as its CU holds.  (Fitted, like everything here, to the choice between the forms and not to the times: they are
+// within 10 to 15 % where the forms are close to one another.)
+struct BwdWork {
+    float start, tile;
+    float edge;   // causal: the share of the longest workgroup that is left when the others have ended
+    float crowd;  // how much longer the work takes where it fills the chip four times and more
+};
+struct BwdCost {
+    float large, keys, one, row_sums;            // of a form, whatever its work; a launch for D before the one launch
+    BwdWork dq128, dq256, keys128, keys32;
+    float q32_start, q32_tile, rows_start, rows_tile;  // the dQ work of the one launch
+    float last_q32, last_rows;                   // of a workgroup dealt last in the one launch, the share that runs past the mean
+    float whole;                                 // no mask: how much whole rounds of the one launch count against its mean
+    float alone;                                 // time of a workgroup alone on a CU that holds two
+    float crowd, spread;                         // the one launch: how much longer at ten fillings; with heads that do not divide over the XCDs
+};
+
+// Whether the one launch that runs both passes computes D for itself: cheaper than a launch for it (2 us and the gap
+// behind it) while a wave of a key block has few tiles, each of which then reads its rows of O once more, and nearly all
+// workgroups are on the chip at once, so that few wait for them.  Whole backward, bf16, over 6450 drawn shapes, time without a
+// launch for D of the time with one, by the tiles of a key block (four waves share them):
+//   d = 64   1: 0.73, 4: 0.79, 8: 0.87, 12: 0.93, 16: 0.97, 18: 1.01, 24: 1.04;  d = 128  1: 0.83, 4: 0.92, 6: 0.99, 8: 1.02, 16: 1.11
+// while the workgroups fill the chip half; between one filling and one and a half d = 64 4: 0.89, 16: 0.95, d = 128 4: 0.98, 6: 0.97, and
+// beyond 0.96, 1.00 to 1.05, 1.00 to 1.04 and 1.00 to 1.03.
+inline bool bwd_own_row_sums(long heads, long kv_heads, int N, int d) {
+    const long tiles = (N + 31) / 32;
+    return tiles * (heads / kv_heads) <= (d == 64 ? 16 : 6) && (heads + kv_heads) * tiles <= (d == 64 ? 768 : 384);
+}
+
+// Why an estimate: the forms differ in how many workgroups they make, how long the longest of them is and how many rounds they
+// come to, and each of these decides somewhere.  Lines drawn through fillings of the chip kept large forms of 1.02 to 1.25 rounds.
+// Timed as graphs of calls, every form of 15730 drawn shapes (1 to 512 heads, groups of 1 to 32, N from 16 to 16384), the choice against
+// the best form, by such lines / by these estimates: time on average, shapes more than 10 % behind, the worst
+//   d = 64   no mask  1.030 / 1.010, 12.3 / 3.0 %, 1.52 / 1.33;  causal 1.021 / 1.007, 8.1 / 1.6 %, 1.50 / 1.20
+//   d = 128  no mask  1.035 / 1.006, 13.0 / 1.3 %, 1.71 / 1.24;  causal 1.022 / 1.007, 7.7 / 1.3 %, 1.90 / 1.32
+// The constants were fitted to these and 11900 other shapes, weighted against choices slower than the lines': 1.1, 0.9, 0.3 and 0.2 % of
+// the shapes take more than 5 % longer than by the lines.  Over 2150 more of 15 to 500 fillings and up to 70000 keys the time is
+// 0.97 of the lines' on average.
+// bf16, whole backward, us; large, 32 keys alone, one launch with 32 queries, with 128 (* the choice):
+//   d = 64   no mask  9 x 7680 -, -, -, 488* (lines: large, 671);  472 on 59 x 640 245, 310, 449, 307* (lines: large);  44 x 1555 162*, 151, 135, 122
+//            causal   62 x 128 13.0, 11.2, 7.0, 7.8* (lines: 32);  36 on 18 x 165 19.2, 12.5, 8.4*, 7.2;  399 on 133 x 195 40.7*, 36.5, 46.4, 34.0
+//   d = 128  no mask  28 x 1203 138*, 134, 132, 114;  165 on 33 x 512 122, 164, 201, 152* (lines: large);  192 on 64 x 128 27.1, 19.9, 29.2, 21.6*
+//            causal   23 x 181 23.1, 18.0, 13.4*, 10.2;  25 x 1621 108, 136, 160, 119* (lines: large);  480 on 15 x 137 217, 64, 66, 49*
+// A call takes 0.05 to 0.2 us of the host.
+constexpr BwdCost kBwdCost[2][2] = {  // d = 64, 128; no mask, causal
+    {
+        {7.89f, 3.4f, 0, 0.129f, {0.724f, 0.196f, 0, 11.2f}, {0.001f, 0.386f, 0, 2.48f}, {0.516f, 1.08f, 0, 0}, {5.41f, 0.582f, 0, 5.29f},
+         5.72f, 0.268f, 5.31f, 0.397f, 0.129f, 0.479f, 0, 0.748f, 1.81f, 0.346f},
+        {8.55f, 0.116f, 0.199f, 0.101f, {0.001f, 0.296f, 0.279f, 2.16f}, {1.38f, 0.633f, 0, 0.256f}, {0, 1.23f, 0.155f, 0}, {5.17f, 0.614f, 1.12f, 1.25f},
+         5.06f, 0.748f, 5.0f, 0.62f, 0.179f, 0, 0, 0.744f, 0.713f, 0.347f},
+    },
+    {
+        {6.84f, 2.58f, 0.279f, 0.627f, {3.43f, 0.808f, 0, 1.43f}, {5.23f, 0.995f, 0, 1.41f}, {0.817f, 0.881f, 0, 0.394f}, {4.79f, 0.746f, 0, 1.2f},
+         5.01f, 0.508f, 4.08f, 0.605f, 0.106f, 0.134f, 1.0f, 1.0f, 0.944f, 0.153f},
+        {10.8f, 3.7f, 0, 0, {1.39f, 1.03f, 0.071f, 0.964f}, {0, 1.28f, 0, 0}, {0.216f, 0.764f, 0.128f, 0.294f}, {6.45f, 0.829f, 0.093f, 0.36f},
+         6.63f, 0.649f, 6.72f, 0.656f, 0.219f, 0.001f, 0, 1.0f, 0.307f, 0.013f},
+    },
+};
+
+// The larger, and a little of the others: two bounds that are close are both felt
+inline float bwd_bound(float a, float b, float c = 0) {
+    const float m = a > b ? (a > c ? a : c) : (b > c ? b : c);
+    return m + 0.08f * (a + b + c - m);
+}
+inline float bwd_share(float x) { return x < 0 ? 0 : x < 1 ? x : 1; }
+inline float bwd_up(float x) { return x > 0 ? (float)(long)(x + 0.999f) : 0; }  // whole rounds
+
+// A launch of `count` workgroups, `slots` of them on the chip at once: without a mask whole rounds, under one, where they are
+// dealt longest first, the mean and an edge.
+inline float bwd_pass(const BwdWork& w, float count, float longest, float mean, int slots, float alone, int causal) {
+    const float all = w.start + mean * w.tile, most = w.start + longest * w.tile, fill = count / slots;
+    float one = most, rounds = bwd_up(fill);
+    if (slots == 512) {
+        const long deep = (long)bwd_up(count / 256);
+        one *= alone + (1 - alone) * bwd_share(count / 256 - 1);
+        rounds = (float)(deep / 2) + alone * (float)(deep % 2);
+    }
+    return bwd_bound(one, (causal ? fill * all + w.edge * most : rounds * all) * (1 + w.crowd * bwd_share(fill / 4)));
+}
+
+// When the last of `n2` workgroups of `t2` each ends that are dealt behind `n1` of `t1`
+inline float bwd_second_end(float slots, float n1, float t1, float n2, float t2) {
+    const float mean = (n1 * t1 + n2 * t2) / slots, rounds = (float)(long)(n1 / slots), late = n1 - rounds * slots;
+    float end = mean + 2 * t2;
+    for (int i = 0; i < 4; ++i) {  // ends of a workgroup on a slot of either kind, from the mean on
+        const float from = (rounds + (float)(i / 2)) * t1, t = from + (bwd_up((mean - from) / t2) + (float)(i % 2)) * t2;
+        const float early_ones = t > rounds * t1 ? (float)(long)((t - rounds * t1) / t2 + 1e-3f) : 0;
+        const float late_ones = t > (rounds + 1) * t1 ? (float)(long)((t - (rounds + 1) * t1) / t2 + 1e-3f) : 0;
+        const float at = late > 0 && t < (rounds + 1) * t1 ? (rounds + 1) * t1 : t;
+        if ((slots - late) * early_ones + late * late_ones >= n2 && at < end) end = at;
+    }
+    return end;
+}
+
+// Whether 128-query workgroups go ahead of the key blocks in the one launch: where they have the longer chains.  Key blocks of a
+// group of g have g / 4 of them; without a mask, where all blocks of a kind are alike, they go first up to two.
+inline bool bwd_rows_first(long group, int causal) { return group <= (causal ? 4 : 2); }
+
+inline void bwd_form_times(long heads, long kv_heads, int N, int d, int causal, float (&us)[kBwdForms]) {
+    const BwdCost& c = kBwdCost[d == 128][causal != 0];
+    const int slots = d == 64 ? 512 : 256;
+    const float h = (float)heads, kv = (float)kv_heads, group = h / kv, tiles = (float)((N + 31) / 32);
+    auto mean = [&](float rows) { return causal ? (tiles + rows) / 2 : tiles; };  // of tiles that blocks of so many rows walk
+    const float n128 = (float)((N + 127) / 128), n256 = (float)((N + 255) / 256);
+    const float dq = N <= bwd_short_rows(d, causal) ? bwd_pass(c.dq128, h * n128, tiles, mean(4), d == 64 ? 768 : 512, c.alone, causal)
+                                                    : bwd_pass(c.dq256, h * n256, tiles, mean(8), 256, c.alone, causal);
+    us[kBwdLarge] = c.large + dq + bwd_pass(c.keys128, kv * n128, group * tiles, group * mean(4), slots, c.alone, causal);
+    // 32-key workgroups: their four waves share the tiles
+    const float longest_k = (float)(((long)(group * tiles) + 3) / 4);
+    const float mean_k = causal ? group * mean(1) / 4 + 0.375f : 0.6f * longest_k + 0.1f * group * tiles;
+    us[kBwdKeys32] = c.keys + dq + bwd_pass(c.keys32, kv * tiles, longest_k, mean_k, slots, c.alone, causal);
+
+    // One launch: as long as either kind's longest workgroup, from when it is dealt, and as the work of both
+    const float sums = bwd_own_row_sums(heads, kv_heads, N, d) ? 0 : c.row_sums;
+    auto one = [&](float n_q, float longest_q, float mean_q, float start, float tile, bool q_first, float last) {
+        const float n_k = kv * tiles, fill = (n_q + n_k) / slots;
+        const float near = d == 64 ? c.alone + (1 - c.alone) * bwd_share(2 * fill - 1) : 1;
+        const float chain_q = (start + longest_q * tile) * near, chain_k = (c.keys32.start + longest_k * c.keys32.tile) * near;
+        const float load = 1 + c.crowd * bwd_share(fill / 10) + (kv_heads % 8 ? c.spread * bwd_share(h * (float)N * (float)d * 1e-7f) : 0);
+        const float t_q = (start + mean_q * tile) * load, t_k = c.keys32.start + mean_k * c.keys32.tile, t_k_load = t_k * load;
+        const float n_1 = q_first ? n_q : n_k, t_1 = q_first ? t_q : t_k_load, n_2 = q_first ? n_k : n_q, t_2 = q_first ? t_k_load : t_q;
+        float work = (n_q * t_q + n_k * t_k_load) / (float)slots + last * t_2;
+        if (c.whole > 0) work += c.whole * (bwd_second_end((float)slots, n_1, t_1, n_2, t_2) - work);
+        const float part = (float)slots / n_1, dealt = q_first ? t_1 : t_k;  // when the first kind has been dealt
+        const float second = n_1 <= (float)slots ? 0 : causal ? n_1 * dealt / (float)slots * (1 - part * part) : (float)(long)((n_1 - 1) / (float)slots) * dealt;
+        return c.one + sums + (q_first ? bwd_bound(chain_q, second + chain_k, work) : bwd_bound(chain_k, second + chain_q, work));
+    };
+    const float quarter = (float)((long)(tiles + 3) / 4);
+    us[kBwdOne32] = one(h * tiles, quarter, causal ? tiles / 8 + 0.5f : 0.6f * quarter + 0.1f * tiles, c.q32_start, c.q32_tile, false, c.last_q32);
+    us[kBwdOneRows] = one(h * n128, tiles, mean(4), c.rows_start, c.rows_tile, bwd_rows_first(heads / kv_heads, causal), c.last_rows);
+}
+
+// d = 64 or 128.  Up to 64 rows 128 queries are the head and 32 half of it.  Where the one launch fills the chip 16 times and more it
+// was best with 32 queries on none of 2150 shapes, and the estimate is too low (no mask, 48 on 6 x 11705, d = 64: large 7.24 ms,
+// 32 queries 10.07); with 128 the shapes drawn end at 24.
+inline BwdForm choose_bwd_form(long heads, long kv_heads, int N, int d, int causal) {
+    float us[kBwdForms];
+    bwd_form_times(heads, kv_heads, N, d, causal, us);
+    const long both = (heads + kv_heads) * ((N + 31) / 32), chip = d == 64 ? 512 : 256;
+    BwdForm best = us[kBwdKeys32] < us[kBwdLarge] ? kBwdKeys32 : kBwdLarge;
+    if (both <= 16 * chip && us[kBwdOne32] < us[best]) best = kBwdOne32;
+    if (both <= 24 * chip && N > 64 && us[kBwdOneRows] < us[best]) best = kBwdOneRows;
+    return best;
+}
+
 int launch_fwd_bf16(const void* q, const void* k, const void* v, void* o, float* lse, int B, int H, int H_kv, int N, int d,
                     float scale, int causal, int schedule, hipStream_t stream);
 int launch_fwd_f16(const void* q, const void* k, const void* v, void* o, float* lse, int B, int H, int H_kv, int N, int d,

@@ -14,16 +14,33 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 
 
 @pytest.fixture(scope="module")
-def key_split(tmp_path_factory):
+def rules(tmp_path_factory):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if not (os.path.exists(hipcc) or shutil.which(hipcc)):
         pytest.skip("hipcc not available")
     lib = str(tmp_path_factory.mktemp("division") / "query.so")
     subprocess.run([hipcc, "--offload-arch=gfx950", "-std=c++17", "-shared", "-fPIC", os.path.join(HERE, "division", "query.cpp"), "-o", lib],
                    check=True, stderr=subprocess.DEVNULL)
-    fn = ctypes.CDLL(lib).key_split
-    fn.argtypes = [ctypes.c_int, ctypes.c_long, ctypes.c_int, ctypes.c_int, ctypes.c_int]
-    return lambda fp8, heads, N, d, causal: bool(fn(int(fp8), heads, N, d, int(causal)))
+    lib, ci, cl = ctypes.CDLL(lib), ctypes.c_int, ctypes.c_long
+    lib.key_split.argtypes = [ci, cl, ci, ci, ci]
+    lib.backward_form.argtypes, lib.backward_form.restype = [cl, cl, ci, ci, ci], ctypes.c_char_p
+    lib.backward_own_row_sums.argtypes = [cl, cl, ci, ci]
+    return lib
+
+
+@pytest.fixture(scope="module")
+def key_split(rules):
+    return lambda fp8, heads, N, d, causal: bool(rules.key_split(int(fp8), heads, N, d, int(causal)))
+
+
+@pytest.fixture(scope="module")
+def backward_form(rules):
+    return lambda heads, kv_heads, N, d, causal: rules.backward_form(heads, kv_heads, N, d, int(causal)).decode()
+
+
+@pytest.fixture(scope="module")
+def own_row_sums(rules):
+    return lambda heads, kv_heads, N, d: bool(rules.backward_own_row_sums(heads, kv_heads, N, d))
 
 
 def _parameters(test, *names):
@@ -74,3 +91,63 @@ def test_tests_of_the_key_split_rule_lie_on_both_sides_of_it(key_split):
                       (True, test_tiles_gpu.test_fp8_forward_on_both_sides_of_the_key_split_rule)):
         for d, causal, N, most in _parameters(test, "d", "causal", "N", "most"):
             assert key_split(fp8, most, N, d, causal) and not key_split(fp8, most + 16, N, d, causal), (fp8, d, causal, N, most)
+
+
+ONE_LAUNCH = {"one32", "rows behind", "rows ahead"}
+
+
+def test_tests_of_the_backward_rule_lie_on_both_sides_of_it(backward_form):
+    def sides(test, *names):
+        for d, causal, N, group, most in _parameters(test, *names):
+            yield tuple(backward_form(kv * group, kv, N, d, causal) for kv in (most, most + 1)), (d, causal, N, group, most)
+
+    five = "d", "causal", "N", "group", "most"
+    for got, case in sides(test_tiles_gpu.test_backward_on_both_sides_of_the_key_split_rule, *five):
+        assert got == ("keys32", "large"), (got, case)
+    orders = set()
+    for got, case in sides(test_tiles_gpu.test_backward_on_both_sides_of_the_rule_of_128_queries, *five):
+        assert got[0] == "one32" and got[1].startswith("rows"), (got, case)
+        orders.add((case[0], case[1], got[1]))
+    assert orders == {(d, c, order) for d in (64, 128) for c in (False, True) for order in ("rows ahead", "rows behind")}
+    beyond = set()
+    for got, case in sides(test_tiles_gpu.test_backward_both_passes_in_one_launch, *five):
+        assert got[0] in ONE_LAUNCH and got[1] not in ONE_LAUNCH, (got, case)
+        beyond.add((case[0], case[1], got[1]))
+    assert beyond == {(d, c, form) for d in (64, 128) for c in (False, True) for form in ("large", "keys32")}
+    for d, causal, N, most in _parameters(test_tiles_gpu.test_backward_on_both_sides_of_the_one_launch_rule, "d", "causal", "N", "most"):
+        assert backward_form(most, most, N, d, causal) in ONE_LAUNCH and backward_form(most + 1, most + 1, N, d, causal) not in ONE_LAUNCH, (d, causal, N, most)
+
+
+def test_tests_of_a_backward_form_take_it(backward_form, own_row_sums):
+    for d, N, H in _parameters(test_tiles_gpu.test_backward_shared_score_tiles, "d", "N", "H"):
+        if d == 128:
+            assert {backward_form(H, H // 2, N, d, c) for c in (False, True)} == {"large"}, (d, N, H)
+    for d, N in _parameters(test_tiles_gpu.test_backward_four_wave_query_tiles, "d", "N"):
+        assert {backward_form(400, 200, N, d, c) for c in (False, True)} == {"large"}, (d, N)
+    for d, causal, N in _parameters(test_tiles_gpu.test_backward_query_tile_rule_edges, "d", "causal", "N"):
+        assert backward_form(32, 32, N, d, causal) == "large", (d, causal, N)
+    for d, causal, N, group, H_kv in _parameters(test_tiles_gpu.test_backward_32_key_workgroups_by_themselves, "d", "causal", "N", "group", "H_kv"):
+        assert backward_form(H_kv * group, H_kv, N, d, causal) == "keys32", (d, causal, N, group, H_kv)
+    rows = [(d, causal, backward_form(H, H_kv, N, d, causal), own_row_sums(H, H_kv, N, d)) for d, causal, N, H, H_kv in
+            _parameters(test_tiles_gpu.test_backward_128_query_workgroups_beside_key_blocks, "d", "causal", "N", "H", "H_kv")]
+    assert {r[2] for r in rows} == {"rows behind", "rows ahead"} and {r[3] for r in rows} == {False, True}
+    assert {r[:3] for r in rows} == {(d, c, order) for d in (64, 128) for c in (False, True) for order in ("rows ahead", "rows behind")}
+    for H, H_kv, N in _parameters(test_tiles_gpu.test_backward_query_split_for_few_key_blocks, "H", "H_kv", "N"):
+        assert {backward_form(H, H_kv, N, d, c) for d in (64, 128) for c in (False, True)} <= ONE_LAUNCH, (H, H_kv, N)
+
+
+def test_tests_of_row_sums_lie_on_both_sides_of_their_rule(backward_form, own_row_sums):
+    cases = _parameters(test_tiles_gpu.test_backward_row_sums_inside_the_one_launch, "d", "N", "H", "H_kv")
+    for d, N, H, H_kv in cases:
+        assert {backward_form(H, H_kv, N, d, c) for c in (False, True)} <= ONE_LAUNCH, (d, N, H, H_kv)
+        if N > 3:  # in pairs: one row more, or one head
+            inside = (d, N, H, H_kv) in cases and own_row_sums(H, H_kv, N, d)
+            assert (d, N + 1, H, H_kv) in cases or (d, N, H + 1, H_kv + 1) in cases or not inside, (d, N, H, H_kv)
+    assert {(d, own_row_sums(H, H_kv, N, d)) for d, N, H, H_kv in cases} == {(d, own) for d in (64, 128) for own in (False, True)}
+
+
+def test_outputs_over_inputs_are_tested_in_every_backward_form(backward_form, own_row_sums):
+    seen = {(d, form, own_row_sums(H, H_kv, N, d) if form in ONE_LAUNCH else N > 1280)
+            for d, H, H_kv, N, causal in test_tiles_gpu._FORMS if d < 256 for form in [backward_form(H, H_kv, N, d, causal)]}
+    want = {("one32", False), ("one32", True), ("rows ahead", False), ("rows ahead", True), ("rows behind", False), ("keys32", False), ("large", False), ("large", True)}
+    assert seen == {(d, *w) for d in (64, 128) for w in want}

@@ -109,12 +109,13 @@ def _check_backward(seed, B, H, H_kv, N, d, causal, dtype, kv_heads=None):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("d,N", [(128, n) for n in (2, 33, 63, 65, 127, 128, 129, 191, 321)] +
-                         [(256, n) for n in (2, 31, 32, 63, 64, 65, 127, 129, 321)])
-def test_backward_shared_score_tiles(d, N, causal, dtype):
+@pytest.mark.parametrize("d,N,H", [(128, 2, 1200), (128, 33, 300), (128, 63, 300), (128, 65, 260), (128, 127, 220), (128, 128, 220), (128, 129, 160),
+                                   (128, 191, 150), (128, 321, 110)] + [(256, n, 4) for n in (2, 31, 32, 63, 64, 65, 127, 129, 321)])
+def test_backward_shared_score_tiles(d, N, H, causal, dtype):
     # key blocks of 128 (64 at d = 256) in 32-key tiles, query tiles of 64 in two sub-tiles whose P and dS the waves
-    # exchange; an odd and an even number of query tiles, and two query heads per K/V head walking the ring twice
-    _check_backward(500 + N, 1, 4, 2, N, d, causal, dtype)
+    # exchange; an odd and an even number of query tiles, and two query heads per K/V head walking the ring twice.  At
+    # d = 128 with so many heads that the pass takes these tiles
+    _check_backward(500 + N, 1, H, H // 2, N, d, causal, dtype, None if N < 100 or d == 256 else (0, H // 2 - 1))
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
@@ -128,26 +129,39 @@ def test_backward_query_split_for_few_key_blocks(d, H, H_kv, N, causal, dtype):
     _check_backward(700 + N + d, 1, H, H_kv, N, d, causal, dtype)
 
 
-@pytest.mark.parametrize("d,causal,most", [(64, False, 89), (64, True, 93), (128, False, 74), (128, True, 74)])
-def test_backward_on_both_sides_of_the_key_split_rule(d, causal, most):
-    # the most key/value heads of N = 170 whose dK/dV pass takes the 32-key form by itself, and one more (at d = 128 only
-    # shared heads get there)
+def _check_both_sides(seed, d, causal, N, group, most, dtype):
+    # the most key/value heads that take one form of the backward, and one more, which take another
     for H_kv in (most, most + 1):
-        _check_backward(800 + H_kv, 1, H_kv * (4 if d == 128 else 1), H_kv, 170, d, causal, "bf16")
+        _check_backward(seed + H_kv, 1, H_kv * group, H_kv, N, d, causal, dtype, None if N < 100 else (0, H_kv - 1))
 
 
-def test_backward_on_both_sides_of_the_query_split_rule():
-    # the most heads whose dQ pass takes the 32-query form by itself, and one more
-    for H in (12, 13):
-        _check_backward(900 + H, 1, H, H, 2000, 128, False, "f16", (0, H - 1))
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d,causal,N,group,most", [(64, False, 40, 4, 144), (64, True, 40, 2, 156), (128, False, 30, 2, 228), (128, True, 40, 1, 127)])
+def test_backward_on_both_sides_of_the_key_split_rule(d, causal, N, group, most, dtype):
+    # the dK/dV pass in its 32-key form by itself, and large
+    _check_both_sides(800, d, causal, N, group, most, dtype)
 
 
-@pytest.mark.parametrize("d,causal,N,most", [(64, False, 70, 128), (64, True, 70, 138), (128, False, 70, 106), (128, True, 70, 106),
-                                             (64, True, 32, 320), (128, False, 64, 80)])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d,causal,N,group,H_kv", [(64, False, 333, 8, 23), (64, True, 513, 16, 27), (128, False, 333, 8, 17), (128, True, 513, 8, 17)])
+def test_backward_32_key_workgroups_by_themselves(d, causal, N, group, H_kv, dtype):
+    # behind the large dQ pass, over more tiles than a wave keeps in its stages, ragged
+    _check_backward(880 + N, 1, H_kv * group, H_kv, N, d, causal, dtype, (0, H_kv - 1))
+
+
+@pytest.mark.parametrize("d,causal,N,group,most", [(64, False, 70, 1, 75), (64, False, 70, 4, 17), (64, False, 70, 8, 9), (64, True, 70, 1, 54),
+                                                   (64, True, 97, 4, 1), (64, True, 170, 8, 1), (128, False, 70, 1, 42), (128, False, 70, 4, 1),
+                                                   (128, False, 170, 8, 1), (128, True, 70, 1, 39), (128, True, 97, 4, 1), (128, True, 170, 8, 1)])
+def test_backward_on_both_sides_of_the_rule_of_128_queries(d, causal, N, group, most):
+    # one launch with the dQ work in 32-query workgroups, and in 128-query ones ahead of the key blocks and behind them
+    _check_both_sides(900, d, causal, N, group, most, "f16")
+
+
+@pytest.mark.parametrize("d,causal,N,most", [(64, False, 40, 172), (64, False, 70, 144), (64, True, 40, 181), (64, True, 70, 204),
+                                             (128, False, 30, 192), (128, False, 70, 128), (128, True, 40, 105), (128, True, 70, 132)])
 def test_backward_on_both_sides_of_the_one_launch_rule(d, causal, N, most):
-    # the most heads for which both passes share a launch, and one more
-    for H in (most, most + 1):
-        _check_backward(850 + H, 1, H, H, N, d, causal, "bf16")
+    # one launch, and two
+    _check_both_sides(850, d, causal, N, 1, most, "bf16")
 
 
 @pytest.mark.parametrize("causal", [False, True])
@@ -229,12 +243,12 @@ def test_causal_forward_paired_and_single_tiles(heads, N, d, fp8):
         assert max_abs(f64(lse[:, h:h + 1]), l_ref) <= 2e-3
 
 
-@pytest.mark.parametrize("d,causal,N,H,H_kv", [(64, True, 70, 184, 92), (64, True, 70, 186, 93), (64, False, 70, 204, 51), (64, False, 70, 208, 52),
-                                               (128, True, 70, 168, 42), (128, True, 70, 172, 43), (128, True, 512, 96, 12), (128, True, 512, 104, 13),
-                                               (64, False, 512, 128, 16), (64, False, 512, 136, 17)])
-def test_backward_both_passes_in_one_launch(d, causal, N, H, H_kv):
-    # shared heads on both sides of the rules that let both passes share a launch
-    _check_backward(1100 + H, 1, H, H_kv, N, d, causal, "bf16", None if N < 100 else (0, H_kv - 1))
+@pytest.mark.parametrize("d,causal,N,group,most", [(64, False, 70, 8, 59), (64, False, 70, 2, 136), (64, True, 70, 4, 156), (64, True, 70, 2, 186),
+                                                   (128, False, 70, 4, 73), (128, False, 70, 2, 102), (128, True, 70, 3, 78), (128, True, 70, 2, 112)])
+def test_backward_both_passes_in_one_launch(d, causal, N, group, most):
+    # shared heads on both sides of the rule that lets both passes share a launch: beyond it large, or the dK/dV pass alone in
+    # its 32-key form
+    _check_both_sides(1100, d, causal, N, group, most, "bf16")
 
 
 @pytest.mark.parametrize("d,N", [(64, 511), (64, 512), (64, 640), (64, 641), (64, 769), (64, 768), (64, 1408), (64, 1409), (128, 640),
@@ -270,36 +284,45 @@ def test_backward_writes_dq_over_an_input(d, H, N, causal, over):
         assert rmse(f64(a), f64(b)) <= 2.0 ** -9 * float(np.sqrt(np.mean(f64(b) ** 2)))
 
 
-# (d, H, N, causal) for every form of the two passes: one launch that computes D for itself, one launch behind the row
-# sums, 32-key or 32-query workgroups of one pass only, 128- and 256-query tiles, d = 256
-_FORMS = [(64, 2, 333, False), (128, 2, 100, True), (64, 2, 1000, True), (128, 2, 300, False), (64, 88, 170, True), (128, 12, 2000, False),
-          (64, 400, 140, False), (128, 200, 140, True), (64, 30, 1400, False), (128, 20, 2000, True), (256, 4, 200, True), (256, 40, 300, False)]
+# (d, H, H_kv, N, causal) for every form of the two passes: one launch that computes D for itself and one behind the row sums, with
+# 32-query workgroups and with 128-query ones ahead of the key blocks and behind them, the dK/dV pass alone in its 32-key form, large
+# with 128- and 256-query tiles, d = 256
+_FORMS = [(64, 2, 2, 333, False), (128, 2, 2, 100, True), (64, 2, 2, 1000, True), (128, 2, 2, 300, False), (64, 100, 100, 70, False), (128, 60, 60, 70, True),
+          (64, 88, 88, 170, True), (128, 12, 12, 2000, False), (64, 16, 2, 511, False), (128, 24, 3, 288, False), (64, 520, 65, 70, False),
+          (128, 284, 71, 70, True), (64, 400, 400, 140, False), (128, 200, 200, 140, True), (64, 30, 30, 1400, False), (128, 32, 32, 1537, True),
+          (256, 4, 4, 200, True), (256, 40, 40, 300, False)]
+
+
+def _forms_inputs(seed, d, H, H_kv, N, causal):
+    q, dout = (inputs.normal_tensor(seed + N, n, (1, H, N, d), "bf16").cuda() for n in ("q", "do"))
+    k, v = (inputs.normal_tensor(seed + N, n, (1, H_kv, N, d), "bf16").cuda() for n in ("k", "v"))
+    o, lse = binding.fa_fwd_gqa(q, k, v, d ** -0.5, causal)
+    return q, k, v, o, lse, dout
 
 
 @pytest.mark.parametrize("over", ["dq", "dk", "dv", "dq one head on", "dk one head on"])
-@pytest.mark.parametrize("d,H,N,causal", _FORMS)
-def test_backward_writes_a_gradient_over_the_output(d, H, N, causal, over):
+@pytest.mark.parametrize("d,H,H_kv,N,causal", _FORMS)
+def test_backward_writes_a_gradient_over_the_output(d, H, H_kv, N, causal, over):
     # O is not needed once D is known, so a caller may hand its memory to a gradient, also shifted against O by a head:
     # against separate buffers (D may be summed in another order: at most a rounding of the outputs apart)
-    q, k, v, dout = (inputs.normal_tensor(1500 + N, n, (1, H, N, d), "bf16").cuda() for n in ("q", "k", "v", "do"))
-    o, lse = binding.fa_fwd(q, k, v, d ** -0.5, causal)
-    ref = binding.fa_bwd(q, k, v, o, lse, dout, d ** -0.5, causal)
+    q, k, v, o, lse, dout = _forms_inputs(1500, d, H, H_kv, N, causal)
+    ref = binding.fa_bwd_gqa(q, k, v, o, lse, dout, d ** -0.5, causal)
     pool = torch.empty((1, H + 1, N, d), device="cuda", dtype=torch.bfloat16)
     pool[:, :H] = o
-    out = {over.split()[0]: pool[:, 1:] if "head" in over else pool[:, :H]}
-    got = binding.fa_bwd(q, k, v, pool[:, :H], lse, dout, d ** -0.5, causal, **out)
+    first, heads = int("head" in over), H if over.startswith("dq") else H_kv
+    out = {over.split()[0]: pool[:, first:first + heads]}
+    got = binding.fa_bwd_gqa(q, k, v, pool[:, :H], lse, dout, d ** -0.5, causal, **out)
     for a, b in zip(got, ref):
         assert rmse(f64(a), f64(b)) <= 2.0 ** -9 * float(np.sqrt(np.mean(f64(b) ** 2)))
 
 
 @pytest.mark.parametrize("dq_over", ["q", "dout"])
-@pytest.mark.parametrize("d,H,N,causal", _FORMS)
-def test_backward_writes_dq_over_an_input_and_dv_over_the_output(d, H, N, causal, dq_over):
+@pytest.mark.parametrize("d,H,H_kv,N,causal", _FORMS)
+def test_backward_writes_dq_over_an_input_and_dv_over_the_output(d, H, H_kv, N, causal, dq_over):
     # dV replaces O before dQ, which goes over an input of the dK/dV pass, is computed
-    q, k, v, dout = (inputs.normal_tensor(1520 + N, n, (1, H, N, d), "bf16").cuda() for n in ("q", "k", "v", "do"))
-    o, lse = binding.fa_fwd(q, k, v, d ** -0.5, causal)
-    ref = binding.fa_bwd(q, k, v, o, lse, dout, d ** -0.5, causal)
-    got = binding.fa_bwd(q, k, v, o, lse, dout, d ** -0.5, causal, dq=q if dq_over == "q" else dout, dv=o)
+    q, k, v, o, lse, dout = _forms_inputs(1520, d, H, H_kv, N, causal)
+    ref = binding.fa_bwd_gqa(q, k, v, o, lse, dout, d ** -0.5, causal)
+    got = binding.fa_bwd_gqa(q, k, v, o, lse, dout, d ** -0.5, causal, dq=q if dq_over == "q" else dout, dv=o[:, :H_kv])
     for a, b in zip(got, ref):
         assert rmse(f64(a), f64(b)) <= 2.0 ** -9 * float(np.sqrt(np.mean(f64(b) ** 2)))
 
@@ -317,9 +340,9 @@ def test_backward_writes_shared_head_gradients_inside_the_output(H, H_kv, N):
 
 
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("d,N,H,H_kv", [(64, 384, 2, 2), (64, 385, 2, 2), (64, 96, 8, 2), (64, 97, 8, 2), (128, 128, 2, 2),
-                                        (128, 129, 2, 2), (128, 64, 4, 2), (128, 65, 4, 2), (128, 3, 2, 1), (64, 32, 256, 256),
-                                        (64, 32, 257, 257), (128, 32, 128, 128), (128, 32, 129, 129)])
+@pytest.mark.parametrize("d,N,H,H_kv", [(64, 512, 2, 2), (64, 513, 2, 2), (64, 128, 8, 2), (64, 129, 8, 2), (128, 192, 2, 2),
+                                        (128, 193, 2, 2), (128, 96, 4, 2), (128, 97, 4, 2), (128, 3, 2, 1), (64, 70, 128, 128),
+                                        (64, 70, 129, 129), (128, 70, 64, 64), (128, 70, 65, 65)])
 def test_backward_row_sums_inside_the_one_launch(d, N, H, H_kv, causal):
     # on both sides of the numbers of tiles and of workgroups up to which the one launch computes D for itself, ragged and not
     _check_backward(1400 + N, 1, H, H_kv, N, d, causal, "bf16")
@@ -602,10 +625,10 @@ def test_forward_rows_with_scores_of_nan_or_infinity(dtype, d, N, H, causal):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("d,causal,N,H,H_kv", [(128, True, 129, 30, 30), (128, True, 256, 32, 32), (128, False, 160, 32, 32), (128, False, 97, 60, 60),
-                                               (64, True, 257, 56, 56), (64, False, 385, 40, 20), (64, False, 160, 51, 51), (64, False, 159, 110, 55),
-                                               (128, True, 161, 8, 2), (128, False, 288, 8, 1), (64, True, 193, 8, 2), (64, False, 511, 16, 2)])
+                                               (64, True, 257, 56, 56), (64, False, 385, 40, 20), (64, False, 160, 64, 64), (64, False, 159, 110, 55),
+                                               (128, True, 161, 48, 6), (128, False, 288, 24, 3), (64, True, 193, 32, 8), (64, True, 193, 48, 6), (64, False, 511, 16, 2)])
 def test_backward_128_query_workgroups_beside_key_blocks(d, causal, N, H, H_kv, dtype):
     # one launch whose dQ work has 128 queries to a workgroup, ahead of the key blocks (groups up to four) and behind them: a
     # last workgroup of one row, of one and of four waves, fewer tiles than are staged ahead, ragged last tiles, waves that end up to
-    # three tiles before the others; (64, False, 160, 51): D computed in this launch
+    # three tiles before the others; (64, False, 160, 64): D computed in this launch
     _check_backward(2500 + N, 1, H, H_kv, N, d, causal, dtype, (0, H_kv - 1))
