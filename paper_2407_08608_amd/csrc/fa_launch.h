@@ -313,12 +313,12 @@ inline void bwd_form_times(long heads, long kv_heads, int N, int d, int causal, 
 
 // d = 64 or 128.  Up to 64 rows 128 queries are the head and 32 half of it.  Where the one launch fills the chip 16 times and more it
 // was best with 32 queries on none of 2150 shapes, and the estimate is too low (no mask, 48 on 6 x 11705, d = 64: large 7.24 ms,
-// 32 queries 10.07); with 128 the shapes drawn end at 24.
+// 32 queries 10.07); with 128 the shapes drawn end at 24, and with the 32-key form alone at 500, far from the most workgroups a launch takes.
 inline BwdForm choose_bwd_form(long heads, long kv_heads, int N, int d, int causal) {
     float us[kBwdForms];
     bwd_form_times(heads, kv_heads, N, d, causal, us);
     const long both = (heads + kv_heads) * ((N + 31) / 32), chip = d == 64 ? 512 : 256;
-    BwdForm best = us[kBwdKeys32] < us[kBwdLarge] ? kBwdKeys32 : kBwdLarge;
+    BwdForm best = both <= 500 * chip && us[kBwdKeys32] < us[kBwdLarge] ? kBwdKeys32 : kBwdLarge;
     if (both <= 16 * chip && us[kBwdOne32] < us[best]) best = kBwdOne32;
     if (both <= 24 * chip && N > 64 && us[kBwdOneRows] < us[best]) best = kBwdOneRows;
     return best;

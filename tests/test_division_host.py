@@ -151,3 +151,13 @@ def test_outputs_over_inputs_are_tested_in_every_backward_form(backward_form, ow
             for d, H, H_kv, N, causal in test_tiles_gpu._FORMS if d < 256 for form in [backward_form(H, H_kv, N, d, causal)]}
     want = {("one32", False), ("one32", True), ("rows ahead", False), ("rows ahead", True), ("rows behind", False), ("keys32", False), ("large", False), ("large", True)}
     assert seen == {(d, *w) for d in (64, 128) for w in want}
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_backward_rule_at_the_ends_of_its_range(backward_form, d):
+    # one row, the longest head, the most rows a call may have: large wherever the estimates were not compared with times
+    longest = 0x7ff00000 // (4 * d)
+    for causal in (False, True):
+        assert backward_form(1, 1, 1, d, causal) == "one32"
+        for heads, kv_heads, N in ((1, 1, longest), (256, 1, longest), ((1 << 31) - 1, (1 << 31) - 1, 1), (1 << 26, 1, 31), (1 << 24, 1 << 20, 100)):
+            assert backward_form(heads, kv_heads, N, d, causal) == "large", (heads, kv_heads, N, causal)
