@@ -131,10 +131,10 @@ fa_quant_kernel(const void* __restrict__ x, uint8_t* __restrict__ x8, float* __r
         auto multiply = [&]() __attribute__((always_inline)) {
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
-                const signed char* at = signs + 8 * (p + LPR * c);
+                int at = 8 * (p + LPR * c);
                 if constexpr (IN_DTYPE != FA_F32) asm volatile("" : "+v"(at));  // read again: kept, they would cost the ordinary way registers
                 i32x2 s8;
-                __builtin_memcpy(&s8, at, 8);
+                __builtin_memcpy(&s8, signs + at, 8);
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
                     const float s = (float)(signed char)(s8[t >> 2] >> (8 * (t & 3)));
