@@ -873,8 +873,8 @@ constexpr int few_lds_bytes(int d) {
 // Where D is computed here a wave has few tiles, most of them of other heads.  What counts then is the code run once and what
 // its requests wait for: the next tile is aimed at in one place, its rows of O follow its staging requests, and dO comes from
 // the staged tile.  (With rows of both asked for ahead of the requests and the code at three places, 0.1 to 0.6 us more.)
-// bf16, whole backward, us, before the 128-query dQ work beside this / with it / so: d = 64 4 on 1 x 32 4.97 / 5.16 / 4.62, 6 on 1 x 59
-// 7.51 / 8.14 / 6.72, 2 x 128 5.56 / 5.43 / 4.88, 16 x 333 causal 9.65 / 9.51 / 8.58; d = 128 16 on 4 x 20 7.35 / 7.74 / 7.02.
+// bf16, whole backward, us, before the 128-query dQ work beside this / with it / so: d = 64 4 on 1 x 32 4.99 / 5.18 / 4.65, 6 on 1 x 59
+// 7.53 / 8.18 / 6.82, 2 x 128 5.57 / 5.43 / 4.90, 16 x 333 causal 9.65 / 9.46 / 8.46; d = 128 16 on 4 x 20 7.31 / 7.70 / 7.04.
 // bf16, this pass of d = 128, H = 32 on 4, N = 2048 causal 126 -> 109 us, no mask (whole) 8 on 1 x 2368 143 -> 128.  (Not kept: eight
 // waves in pairs that share tiles and trade P and dS through the LDS, which put all of them in step: 177.)
 template <typename Tag, int D, bool CAUSAL, bool D_READY>
