@@ -218,11 +218,12 @@ inline bool bwd_own_row_sums(long heads, long kv_heads, int N, int d) {
 // the shapes take more than 5 % longer than by the lines.  Over 2150 more of 15 to 500 fillings and up to 70000 keys the time is
 // 0.97 of the lines' on average.
 // bf16, whole backward, us; large, 32 keys alone, one launch with 32 queries, with 128 (* the choice):
-//   d = 64   no mask  9 x 7680 -, -, -, 488* (lines: large, 671);  472 on 59 x 640 245, 310, 449, 307* (lines: large);  44 x 1555 162*, 151, 135, 122
+//   d = 64   no mask  9 x 7680 -, -, -, 488* (lines: large, 671);  472 on 59 x 640 245, 310, 449, 307* (lines: large);  44 x 1555 162*, 151, 135, 122;  79 x 256 17.2*, 22.6, 23.9, 18.8
 //            causal   62 x 128 13.0, 11.2, 7.0, 7.8* (lines: 32);  36 on 18 x 165 19.2, 12.5, 8.4*, 7.2;  399 on 133 x 195 40.7*, 36.5, 46.4, 34.0
 //   d = 128  no mask  28 x 1203 138*, 134, 132, 114;  165 on 33 x 512 122, 164, 201, 152* (lines: large);  192 on 64 x 128 27.1, 19.9, 29.2, 21.6*
-//            causal   23 x 181 23.1, 18.0, 13.4*, 10.2;  25 x 1621 108, 136, 160, 119* (lines: large);  480 on 15 x 137 217, 64, 66, 49*
-// A call takes 0.05 to 0.2 us of the host.
+//            causal   23 x 181 23.1, 18.0, 13.4*, 10.2;  25 x 1621 108, 136, 160, 119* (lines: large);  16 x 512 40, 29.9, 17.1, 18.0* (lines: 32);  480 on 15 x 137 217, 64, 66, 49*
+// (With a number of heads that 8 divides, each on one XCD, few-workgroup forms gain up to 15 %, which `spread` follows for large ones
+// only: 80 x 256, d = 64 16.6*, 19.3, 17.3, 15.6.  Fitted for all, it was right no more often.)  A call takes 0.05 to 0.2 us of the host.
 constexpr BwdCost kBwdCost[2][2] = {  // d = 64, 128; no mask, causal
     {
         {7.89f, 3.4f, 0, 0.129f, {0.724f, 0.196f, 0, 11.2f}, {0.001f, 0.386f, 0, 2.48f}, {0.516f, 1.08f, 0, 0}, {5.41f, 0.582f, 0, 5.29f},
