@@ -223,7 +223,7 @@ inline bool bwd_own_row_sums(long heads, long kv_heads, int N, int d) {
 //   d = 128  no mask  28 x 1203 138*, 134, 132, 114;  165 on 33 x 512 122, 164, 201, 152* (lines: large);  192 on 64 x 128 27.1, 19.9, 29.2, 21.6*
 //            causal   23 x 181 23.1, 18.0, 13.4*, 10.2;  25 x 1621 108, 136, 160, 119* (lines: large);  16 x 512 40, 29.9, 17.1, 18.0* (lines: 32);  480 on 15 x 137 217, 64, 66, 49*
 // (With a number of heads that 8 divides, each on one XCD, few-workgroup forms gain up to 15 %, which `spread` follows for large ones
-// only: 80 x 256, d = 64 16.6*, 19.3, 17.3, 15.6.  Fitted for all, it was right no more often.)  A call takes 0.05 to 0.2 us of the host.
+// only: 80 x 256, d = 64 16.6*, 19.3, 17.3, 15.6.  Fitted for all, it was right hardly more often.)  A call takes 0.05 to 0.2 us of the host.
 constexpr BwdCost kBwdCost[2][2] = {  // d = 64, 128; no mask, causal
     {
         {7.89f, 3.4f, 0, 0.129f, {0.724f, 0.196f, 0, 11.2f}, {0.001f, 0.386f, 0, 2.48f}, {0.516f, 1.08f, 0, 0}, {5.41f, 0.582f, 0, 5.29f},
